@@ -670,7 +670,7 @@ __device__ __forceinline__ void bin_hist(const MapBins& mb, uint32_t chunk, uint
     uint32_t* const rb = mb.rowbase + (size_t)chunk * mb.nb;
     for (int k = threadIdx.x; k < mb.nb; k += BIN_TB)
         if (h[k]) rb[k] = atomicAdd(&mb.bins[k], h[k]);
-    if (threadIdx.x == 0 && hmax) atomicMax(&mb.bins[3 * mb.nb + 1], hmax);
+    if (threadIdx.x == 0 && hmax) atomicMax(mb.bins + 3 * mb.nb + 3, hmax);   // (bin_max)
 }
 // the flush kernels serve two maps at once (their chunks fill the chip together):
 // workgroups [0, ga) map a, the rest map b (none when only a is flushed)
@@ -682,33 +682,47 @@ __global__ void __launch_bounds__(BIN_TB) k_bin_hist(MapBins a, MapBins b, uint3
     else bin_hist<CB, RSB>(b, blockIdx.x - ga, h, hmax);
 }
 
-// tile offsets (exclusive scan of the counts, nb <= 4096); clears the counts
-__device__ __forceinline__ void bin_scan(const MapBins& mb, uint32_t* part) {
-    uint32_t* off = mb.bins + mb.nb;
+// where things sit in MapBins::bins (see kernels.hpp)
+__device__ __forceinline__ uint32_t* bin_offsets(const MapBins& mb) { return mb.bins + mb.nb; }
+__device__ __forceinline__ uint32_t* bin_units(const MapBins& mb) { return mb.bins + 2 * mb.nb + 1; }
+__device__ __forceinline__ uint32_t* bin_exp(const MapBins& mb) { return mb.bins + 3 * mb.nb + 2; }
+__device__ __forceinline__ uint32_t* bin_max(const MapBins& mb) { return mb.bins + 3 * mb.nb + 3; }
+
+// tile offsets and the tiles' units of at most ACC_CHUNK records (exclusive scans of the
+// counts, nb <= 4096), and the tile of every unit; clears the counts
+__device__ __forceinline__ void bin_scan(const MapBins& mb, uint64_t* part) {
+    uint32_t* const off = bin_offsets(mb);
+    uint32_t* const uoff = bin_units(mb);
     const int per = (mb.nb + 1023) / 1024;
     const int b = threadIdx.x * per, e = min(b + per, mb.nb);
-    uint32_t s = 0;
-    for (int i = b; i < e; ++i) s += mb.bins[i];
+    auto both = [](uint32_t n) { return (uint64_t)n | (uint64_t)((n + ACC_CHUNK - 1) / ACC_CHUNK) << 32; };
+    uint64_t s = 0;   // records (low) and units (high)
+    for (int i = b; i < e; ++i) s += both(mb.bins[i]);
     part[threadIdx.x] = s;
     __syncthreads();
     for (int o = 1; o < 1024; o <<= 1) {
-        const uint32_t v = threadIdx.x >= (unsigned)o ? part[threadIdx.x - o] : 0u;
+        const uint64_t v = threadIdx.x >= (unsigned)o ? part[threadIdx.x - o] : 0ull;
         __syncthreads();
         part[threadIdx.x] += v;
         __syncthreads();
     }
-    uint32_t run = threadIdx.x ? part[threadIdx.x - 1] : 0u;
+    uint64_t run = threadIdx.x ? part[threadIdx.x - 1] : 0ull;
     for (int i = b; i < e; ++i) {
-        const uint32_t v = mb.bins[i];
-        off[i] = run;
+        const uint64_t v = both(mb.bins[i]);
+        off[i] = (uint32_t)run;
+        uoff[i] = (uint32_t)(run >> 32);
+        for (uint32_t u = 0; u < (uint32_t)(v >> 32); ++u) mb.unit_tile[uoff[i] + u] = (uint32_t)i;
         run += v;
         mb.bins[i] = 0u;
     }
-    if (threadIdx.x == 1023) off[mb.nb] = part[1023];
+    if (threadIdx.x == 1023) {
+        off[mb.nb] = (uint32_t)part[1023];
+        uoff[mb.nb] = (uint32_t)(part[1023] >> 32);
+    }
 }
 // workgroup 0: map a, workgroup 1: map b
 __global__ void __launch_bounds__(1024) k_bin_scan(MapBins a, MapBins b) {
-    __shared__ uint32_t part[1024];
+    __shared__ uint64_t part[1024];
     bin_scan(blockIdx.x == 0 ? a : b, part);
 }
 
@@ -752,99 +766,93 @@ __global__ void __launch_bounds__(BIN_TB) k_bin_place(MapBins a, MapBins b, uint
     else bin_place<RSB>(b, blockIdx.x - ga, cnt);
 }
 
-// Accumulation over fixed chunks of the tile-sorted records (balanced whatever the
-// tile sizes): a workgroup walks the tiles its chunk covers and, per tile, sums the
-// records in LDS over the tile plus one halo row/column and stores the (T + 1)^2 x C
-// block at pair index chunk + tile (unique: both grow along the sorted records).
+// Accumulation of one unit: at most ACC_CHUNK of the sorted records of one tile, summed in
+// LDS over the tile plus one halo row/column; the (T + 1)^2 x C block goes to the stage at
+// the unit's number.  A workgroup takes one unit at a time (clearing, two barriers and the
+// block's store cost about 3 us however few the records): with fixed chunks of the sorted
+// records instead, a chunk that covered a sparsely hit part of the map walked hundreds of
+// tiles one after the other (317 x 203 x 9 spp, 500^2 principled maps: 651 us for the
+// flush of the first four depths, now 44; 256^2 x 64 spp, 512^2 maps: 97 us, now 90).
 template <int C, int RS>
-__device__ __forceinline__ void bin_accum(const MapBins& mb, uint32_t c, long long* t) {
+__device__ __forceinline__ void bin_accum(const MapBins& mb, uint32_t u, long long* t) {
     // Sums in 64-bit fixed point (integer LDS atomics are exact and much faster than
-    // FP32 ones): values scaled by 2^E with |chunk sum| < 2^62 for every texel, i.e.
-    // 2^-50 of the largest record value as resolution.  The chunk sums are stored as
+    // FP32 ones): values scaled by 2^E with |unit sum| < 2^62 for every texel, i.e.
+    // 2^-50 of the largest record value as resolution.  The unit sums are stored as
     // integers, so the texel totals the gather forms do not depend on how the records
-    // were split into chunks (which varies with the order atomics placed them in).
-    const uint32_t* off = mb.bins + mb.nb;
-    const uint32_t total = off[mb.nb];
-    const uint32_t i0 = c * ACC_CHUNK;
-    if (c == 0 && threadIdx.x == 0) *mb.count = 0u;   // the counting passes are done
-    if (i0 >= total) return;   // uniform per workgroup
-    const uint32_t i1 = min(total, i0 + ACC_CHUNK);
-    const float gmax = __uint_as_float(mb.bins[3 * mb.nb + 1]);
+    // were split into units (which varies with the order atomics placed them in).
+    const uint32_t* off = bin_offsets(mb);
+    const int b = (int)mb.unit_tile[u];
+    const uint32_t s0 = off[b] + (u - bin_units(mb)[b]) * ACC_CHUNK, s1 = min(off[b + 1], s0 + ACC_CHUNK);
     int ge = 0;
-    frexpf(gmax, &ge);                              // gmax < 2^ge
+    frexpf(__uint_as_float(*bin_max(mb)), &ge);     // largest |value| < 2^ge
     const int E = 62 - 12 - ge;                     // ACC_CHUNK = 2^12 contributions at most
     const double up = ldexp(1.0, E);
-    if (c == 0 && threadIdx.x == 0) mb.bins[2 * mb.nb + 1] = (uint32_t)E;   // for the gather
-    int lo = 0, hi = mb.nb;   // the tile holding record i0: last b with off[b] <= i0
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (off[mid] <= i0) lo = mid;
-        else hi = mid;
-    }
-    int b = lo;
+    if (u == 0 && threadIdx.x == 0) *bin_exp(mb) = (uint32_t)E;   // for the gather
     const int S = mb.T + 1, SS = S * S * C;
-    for (;;) {
-        const uint32_t s0 = max(off[b], i0), s1 = min(off[b + 1], i1);
-        for (int k = threadIdx.x; k < SS; k += ACC_TB) t[k] = 0;
-        __syncthreads();
-        const int tx0 = (b % mb.nbx) * mb.T, ty0 = (b / mb.nbx) * mb.T;
-        bool bad = false;
-        float rv[RS];
-        // The samples of one pixel sit together in the sorted records and share texels,
-        // and an LDS atomic instruction whose lanes meet at one address is serialised: the
-        // lanes of a wave take records m = ceil(n / 64) apart (lane l: slot [l m, l m + m)
-        // of the tile's n records), i.e. from different pixels
-        const uint32_t n = s1 - s0, m = (n + 63u) >> 6;
-        for (uint32_t k = threadIdx.x; k < 64u * m; k += ACC_TB) {
-            const uint32_t j = (k & 63u) * m + (k >> 6);
-            if (j >= n) continue;
-            const float* p = load_record<RS>(mb.sorted + (size_t)(s0 + j) * RS, rv);
-            const uint32_t head = __float_as_uint(p[0]);
-            const uint32_t base = head & 0x0fffffffu;
-            const int y0 = (int)(base / (uint32_t)mb.W), x0 = (int)(base - (uint32_t)y0 * (uint32_t)mb.W);
-            const int lx = x0 - tx0, ly = y0 - ty0;
-            const int dx = (int)((head >> 28) & 1u), dy = (int)((head >> 29) & 1u);
-            const double ax = p[1], ay = p[2];
-            const double w[4] = {(1.0 - ax) * (1.0 - ay), ax * (1.0 - ay), (1.0 - ax) * ay, ax * ay};
-            const int idx[4] = {ly * S + lx, ly * S + lx + dx, (ly + dy) * S + lx, (ly + dy) * S + lx + dx};
+    for (int k = threadIdx.x; k < SS; k += ACC_TB) t[k] = 0;
+    __syncthreads();
+    const int tx0 = (b % mb.nbx) * mb.T, ty0 = (b / mb.nbx) * mb.T;
+    bool bad = false;
+    float rv[RS];
+    // The samples of one pixel sit together in the sorted records and share texels,
+    // and an LDS atomic instruction whose lanes meet at one address is serialised: the
+    // lanes of a wave take records m = ceil(n / 64) apart (lane l: slot [l m, l m + m)
+    // of the unit's n records), i.e. from different pixels
+    const uint32_t n = s1 - s0, m = (n + 63u) >> 6;
+    for (uint32_t k = threadIdx.x; k < 64u * m; k += ACC_TB) {
+        const uint32_t j = (k & 63u) * m + (k >> 6);
+        if (j >= n) continue;
+        const float* p = load_record<RS>(mb.sorted + (size_t)(s0 + j) * RS, rv);
+        const uint32_t head = __float_as_uint(p[0]);
+        const uint32_t base = head & 0x0fffffffu;
+        const int y0 = (int)(base / (uint32_t)mb.W), x0 = (int)(base - (uint32_t)y0 * (uint32_t)mb.W);
+        const int lx = x0 - tx0, ly = y0 - ty0;
+        const int dx = (int)((head >> 28) & 1u), dy = (int)((head >> 29) & 1u);
+        const double ax = p[1], ay = p[2];
+        const double w[4] = {(1.0 - ax) * (1.0 - ay), ax * (1.0 - ay), (1.0 - ax) * ay, ax * ay};
+        const int idx[4] = {ly * S + lx, ly * S + lx + dx, (ly + dy) * S + lx, (ly + dy) * S + lx + dx};
 #pragma unroll
-            for (int ch = 0; ch < C; ++ch) {
-                const double g = (double)p[3 + ch] * up;
-                bad = bad || !(fabs(g) <= 0x1p62);       // non-finite cotangent
+        for (int ch = 0; ch < C; ++ch) {
+            const double g = (double)p[3 + ch] * up;
+            bad = bad || !(fabs(g) <= 0x1p62);       // non-finite cotangent
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const long long q = bad ? 0ll : __double2ll_rn(g * w[k]);
-                    if (q != 0ll) atomicAdd((unsigned long long*)&t[idx[k] * C + ch], (unsigned long long)q);
-                }
+            for (int k = 0; k < 4; ++k) {
+                const long long q = bad ? 0ll : __double2ll_rn(g * w[k]);
+                if (q != 0ll) atomicAdd((unsigned long long*)&t[idx[k] * C + ch], (unsigned long long)q);
             }
         }
-        const bool any_bad = __syncthreads_or(bad);
-        long long* st = mb.stage + (size_t)(c + b) * SS;
-        for (int k = threadIdx.x; k < SS; k += ACC_TB) st[k] = any_bad ? STAGE_NAN : t[k];
-        __syncthreads();
-        if (off[b + 1] >= i1) break;
-        ++b;
-        while (off[b + 1] == off[b]) ++b;   // skip empty tiles (a later tile holds record i1 - 1)
+    }
+    const bool any_bad = __syncthreads_or(bad);
+    long long* st = mb.stage + (size_t)u * SS;
+    for (int k = threadIdx.x; k < SS; k += ACC_TB) st[k] = any_bad ? STAGE_NAN : t[k];
+    __syncthreads();   // (t is cleared by the next unit)
+}
+// both maps' units in turn (bs: map b has records of its own)
+template <int CA, int RSA, int CB, int RSB>
+__global__ void __launch_bounds__(ACC_TB) k_bin_accum(MapBins a, MapBins b, int bs) {
+    __shared__ long long t[(MAP_MAX_T + 1) * (MAP_MAX_T + 1) * (CA > CB ? CA : CB)];
+    const uint32_t ua = bin_units(a)[a.nb], ub = bs ? bin_units(b)[b.nb] : 0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {   // the counting passes are done
+        *a.count = 0u;
+        if (bs) *b.count = 0u;
+    }
+    for (uint32_t u = blockIdx.x; u < ua + ub; u += gridDim.x) {
+        if (u < ua) bin_accum<CA, RSA>(a, u, t);
+        else bin_accum<CB, RSB>(b, u - ua, t);
     }
 }
-template <int CA, int RSA, int CB, int RSB>
-__global__ void __launch_bounds__(ACC_TB) k_bin_accum(MapBins a, MapBins b, uint32_t ga) {
-    __shared__ long long t[(MAP_MAX_T + 1) * (MAP_MAX_T + 1) * (CA > CB ? CA : CB)];
-    if (blockIdx.x < ga) bin_accum<CA, RSA>(a, blockIdx.x, t);
-    else bin_accum<CB, RSB>(b, blockIdx.x - ga, t);
-}
 
-// one thread per texel: the blocks of every (chunk, tile) pair of its own tile plus
+// one thread per texel: the blocks of every unit of its own tile plus
 // the halos of the tiles to the left, above and above-left, added into the map (each
 // texel written by one thread)
 template <int C>
 __device__ __forceinline__ void bin_gather(const MapBins& mb, float* __restrict__ out, int stride, int64_t t) {
-    if (t == 0) mb.bins[3 * mb.nb + 1] = 0u;   // largest |value|: read by the accumulation only
+    if (t == 0) *bin_max(mb) = 0u;   // largest |value|: read by the accumulation only
     if (t >= (int64_t)mb.W * mb.H) return;
     const int y = (int)(t / mb.W), x = (int)(t - (int64_t)y * mb.W);
     const int T = mb.T, S = T + 1, SS = S * S * C;
     const int tx = x / T, ty = y / T, lx = x - tx * T, ly = y - ty * T;
-    const uint32_t* off = mb.bins + mb.nb;
+    const uint32_t* uoff = bin_units(mb);
     // exact 128-bit two's-complement totals of the integer block sums (a texel can take
     // more blocks than 64 bits hold), converted to floating point once
     unsigned long long lo[C];
@@ -857,10 +865,9 @@ __device__ __forceinline__ void bin_gather(const MapBins& mb, float* __restrict_
     }
     auto add = [&](int bx, int by, int ix, int iy) {
         const int b = by * mb.nbx + bx;
-        const uint32_t a = off[b], e = off[b + 1];
-        if (a == e) return;
-        for (uint32_t c = a / ACC_CHUNK; c <= (e - 1) / ACC_CHUNK; ++c) {
-            const long long* p = mb.stage + (size_t)(c + b) * SS + ((size_t)iy * S + ix) * C;
+        const uint32_t e = uoff[b + 1];
+        for (uint32_t u = uoff[b]; u < e; ++u) {
+            const long long* p = mb.stage + (size_t)u * SS + ((size_t)iy * S + ix) * C;
 #pragma unroll
             for (int ch = 0; ch < C; ++ch) {
                 const long long q = p[ch];
@@ -875,7 +882,7 @@ __device__ __forceinline__ void bin_gather(const MapBins& mb, float* __restrict_
     if (lx == 0 && tx > 0) add(tx - 1, ty, T, ly);
     if (ly == 0 && ty > 0) add(tx, ty - 1, lx, T);
     if (lx == 0 && ly == 0 && tx > 0 && ty > 0) add(tx - 1, ty - 1, T, T);
-    const double down = ldexp(1.0, -(int)mb.bins[2 * mb.nb + 1]);
+    const double down = ldexp(1.0, -(int)*bin_exp(mb));
     float* o = out + (size_t)t * stride;
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) {
@@ -1524,12 +1531,14 @@ template <int CA, int RSA, int CB, int RSB>
 static void flush_maps(const Launch& l, const MapBins& a, float* oa, int sa, const MapBins* b, float* ob, int sb) {
     const MapBins& bb = b ? *b : a;
     const uint32_t ha = (uint32_t)((a.cap + BIN_CHUNK - 1) / BIN_CHUNK), hb = b ? (uint32_t)((b->cap + BIN_CHUNK - 1) / BIN_CHUNK) : 0u;
-    const uint32_t aa = (uint32_t)((a.cap + ACC_CHUNK - 1) / ACC_CHUNK), ab = b ? (uint32_t)((b->cap + ACC_CHUNK - 1) / ACC_CHUNK) : 0u;
+    // units are taken in turn by two resident rounds of workgroups at most (two per CU fit)
+    const uint32_t units = (uint32_t)(map_units(a.cap, a.nb) + (b ? map_units(b->cap, b->nb) : 0));
+    const uint32_t acc = std::min<uint32_t>(units, 1024u);
     const uint32_t ta = grid_of((int64_t)a.W * a.H, 256), tb = b ? grid_of((int64_t)b->W * b->H, 256) : 0u;
     hipLaunchKernelGGL((k_bin_hist<CA, RSA, CB, RSB>), dim3(ha + hb), dim3(BIN_TB), 0, l.st, a, bb, ha);
     hipLaunchKernelGGL(k_bin_scan, dim3(b ? 2 : 1), dim3(1024), 0, l.st, a, bb);
     hipLaunchKernelGGL((k_bin_place<RSA, RSB>), dim3(ha + hb), dim3(BIN_TB), 0, l.st, a, bb, ha);
-    hipLaunchKernelGGL((k_bin_accum<CA, RSA, CB, RSB>), dim3(aa + ab), dim3(ACC_TB), 0, l.st, a, bb, aa);
+    hipLaunchKernelGGL((k_bin_accum<CA, RSA, CB, RSB>), dim3(acc), dim3(ACC_TB), 0, l.st, a, bb, b ? 1 : 0);
     hipLaunchKernelGGL((k_bin_gather<CA, CB>), dim3(ta + tb), dim3(256), 0, l.st, a, oa, sa, bb, b ? ob : oa,
                        b ? sb : sa, ta);
 }

@@ -149,8 +149,9 @@ inline size_t spill_ints(int grid_cap, int rounds) { return (size_t)trace_grid_c
 constexpr int MAP_MAX_BINS = 4096;
 constexpr int MAP_MAX_T = 16;   // tile side 8 or 16: maps up to 1024 x 1024 are binned
 constexpr int BIN_DEPTHS = 4;   // replay depths between flushes (record capacity follows)
-constexpr int ACC_CHUNK = 4096; // records per workgroup of the accumulation; the stage holds
-                                // ceil(cap / ACC_CHUNK) + nb blocks of (T + 1)^2 x C floats
+constexpr int ACC_CHUNK = 4096; // most records of one tile a workgroup of the accumulation sums
+                                // at once (a unit); the stage holds one block of (T + 1)^2 x C
+                                // sums per unit
 constexpr int ACC_TB = 1024;    // threads per workgroup of the accumulation
 constexpr int BIN_CHUNK = 16384;// records per workgroup of the histogram and the placement
 constexpr int BIN_TB = 1024;    // their threads per workgroup: 16 waves share one LDS
@@ -161,15 +162,20 @@ constexpr long long STAGE_NAN = -0x7fffffffffffffffll - 1;   // INT64_MIN
 struct MapBins {
     float* rec;          // records of rs floats (null: binning off, the replay scatters directly)
     float* sorted;       // the same records grouped by tile
-    long long* stage;    // per (chunk, tile) pair (T + 1)^2 x C exact fixed-point sums (tile plus one
-                         // halo row/column); STAGE_NAN marks a chunk with a non-finite value
+    long long* stage;    // per unit (T + 1)^2 x C exact fixed-point sums (tile plus one halo
+                         // row/column); STAGE_NAN marks a unit with a non-finite value
     uint32_t* count;     // records appended since the last flush (may exceed cap)
-    uint32_t* bins;      // counts[nb], offsets[nb + 1], fixed-point exponent E, (unused)[nb - 1],
-                         // largest |value| (float bits)
+    uint32_t* bins;      // counts[nb], offsets[nb + 1], first units[nb + 1], fixed-point exponent
+                         // E, largest |value| (float bits): map_bin_words(nb)
+    uint32_t* unit_tile; // tile of every unit
     uint32_t* rowbase;   // per (BIN_CHUNK chunk, tile): where the chunk's records start in the tile
     int64_t cap;         // record capacity
     int W, H, T, nbx, nby, nb;
 };
+
+constexpr int64_t map_bin_words(int64_t nb) { return 3 * nb + 4; }
+// most units of cap records in nb tiles
+constexpr int64_t map_units(int64_t cap, int64_t nb) { return (cap + ACC_CHUNK - 1) / ACC_CHUNK + nb; }
 
 // adjoint additions (see adjoint.hip)
 struct alignas(16) PendX {   // per channel c: albedo, roughness, specular, metallic, normal map (xyz)

@@ -155,9 +155,10 @@ void make_map_bins(dpcs_context ctx, ZeroList& zl, MapBins& mb, const char* name
     if (!map_tiling(W, H, T, nbx, nby)) return;
     cap = std::min<int64_t>(cap, int64_t(1) << 31);
     const int nb = nbx * nby;
-    const size_t rec = 4 * (size_t)RS * cap, stage = 8 * (size_t)((cap + ACC_CHUNK - 1) / ACC_CHUNK + nb) * (T + 1) * (T + 1) * C;
+    const size_t rec = 4 * (size_t)RS * cap, units = (size_t)map_units(cap, nb);
+    const size_t stage = 8 * units * (T + 1) * (T + 1) * C;
     const size_t rows = 4 * (size_t)((cap + BIN_CHUNK - 1) / BIN_CHUNK) * nb;
-    const size_t bytes = 2 * rec + stage + rows + 4 * (3 * (size_t)nb + 2) + 8 * 256;
+    const size_t bytes = 2 * rec + stage + rows + 4 * (size_t)map_bin_words(nb) + 4 * units + 8 * 256;
     dpcs_status st = DPCS_OK;
     char* b = (char*)scratch(ctx, name, bytes, &st);
     if (!b) {   // run without binning
@@ -173,7 +174,8 @@ void make_map_bins(dpcs_context ctx, ZeroList& zl, MapBins& mb, const char* name
     mb.sorted = (float*)take(rec);
     mb.stage = (long long*)take(stage);
     mb.count = (uint32_t*)take(4);
-    mb.bins = (uint32_t*)take(4 * (3 * (size_t)nb + 2));
+    mb.bins = (uint32_t*)take(4 * (size_t)map_bin_words(nb));
+    mb.unit_tile = (uint32_t*)take(4 * units);
     mb.rowbase = (uint32_t*)take(rows);
     mb.cap = cap;
     mb.W = W;
@@ -183,7 +185,7 @@ void make_map_bins(dpcs_context ctx, ZeroList& zl, MapBins& mb, const char* name
     mb.nby = nby;
     mb.nb = nb;
     zl.add((float*)mb.count, 1);
-    zl.add((float*)mb.bins, 3 * (int64_t)nb + 2);
+    zl.add((float*)mb.bins, map_bin_words(nb));
 }
 
 static void inv3(const double* m, double* o) {

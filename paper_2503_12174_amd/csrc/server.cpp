@@ -101,14 +101,15 @@ struct Seg {
 // Binning buffers of the loop's compensation waves (map cotangents sorted by tile and
 // summed in fixed point, as a single request's VJP does), carved for the largest binned
 // map (1024 x 1024: 16-texel tiles, 4096 of them); a wave binds them to its request's
-// map size.  Layout: records, sorted records, stage blocks, count, bins, chunk row bases.
+// map size.  Layout: records, sorted records, stage blocks, count, bins, unit tiles, chunk
+// row bases.
 size_t loop_bins_bytes(int64_t cap, int C, int RS) {
     const size_t rec = 4 * (size_t)RS * cap;
-    const size_t stage = 8 * (size_t)((cap + ACC_CHUNK - 1) / ACC_CHUNK + MAP_MAX_BINS) * (MAP_MAX_T + 1) *
-                         (MAP_MAX_T + 1) * C;
+    const size_t units = (size_t)map_units(cap, MAP_MAX_BINS);
+    const size_t stage = 8 * units * (MAP_MAX_T + 1) * (MAP_MAX_T + 1) * C;
     const size_t rows = 4 * (size_t)((cap + BIN_CHUNK - 1) / BIN_CHUNK) * MAP_MAX_BINS;
     auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
-    return 2 * up(rec) + up(stage) + up(4) + up(4 * (3 * (size_t)MAP_MAX_BINS + 2)) + up(rows);
+    return 2 * up(rec) + up(stage) + up(4) + up(4 * (size_t)map_bin_words(MAP_MAX_BINS)) + up(4 * units) + up(rows);
 }
 
 // the buffers at base as bins of a W x H map (false: the map is too large to bin)
@@ -118,8 +119,8 @@ bool loop_bins_view(char* base, int64_t cap, int C, int RS, int W, int H, MapBin
     if (!base || !map_tiling(W, H, T, nbx, nby)) return false;
     auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
     const size_t rec = 4 * (size_t)RS * cap;
-    const size_t stage = 8 * (size_t)((cap + ACC_CHUNK - 1) / ACC_CHUNK + MAP_MAX_BINS) * (MAP_MAX_T + 1) *
-                         (MAP_MAX_T + 1) * C;
+    const size_t units = (size_t)map_units(cap, MAP_MAX_BINS);
+    const size_t stage = 8 * units * (MAP_MAX_T + 1) * (MAP_MAX_T + 1) * C;
     char* b = base;
     mb.rec = (float*)b;
     b += up(rec);
@@ -130,7 +131,9 @@ bool loop_bins_view(char* base, int64_t cap, int C, int RS, int W, int H, MapBin
     mb.count = (uint32_t*)b;
     b += up(4);
     mb.bins = (uint32_t*)b;
-    b += up(4 * (3 * (size_t)MAP_MAX_BINS + 2));
+    b += up(4 * (size_t)map_bin_words(MAP_MAX_BINS));
+    mb.unit_tile = (uint32_t*)b;
+    b += up(4 * units);
     mb.rowbase = (uint32_t*)b;
     mb.cap = cap;
     mb.W = W;
@@ -363,9 +366,9 @@ void dpcs_server_s::wave(Launch& l) {
             } else {   // a fresh histogram for this map size
                 ZeroList zl(l);
                 zl.add((float*)ab.tb.count, 1);
-                zl.add((float*)ab.tb.bins, 3 * (int64_t)MAP_MAX_BINS + 2);
+                zl.add((float*)ab.tb.bins, map_bin_words(MAP_MAX_BINS));
                 zl.add((float*)ab.eb.count, 1);
-                zl.add((float*)ab.eb.bins, 3 * (int64_t)MAP_MAX_BINS + 2);
+                zl.add((float*)ab.eb.bins, map_bin_words(MAP_MAX_BINS));
                 zl.launch();
                 ++st_binned;
             }
