@@ -9,8 +9,8 @@
 // remaining radiance starts at the sample's total and loses each vertex's own
 // contributions as the replay passes them.
 //
-//   adj_pixel   CRF backward (Eq. 5) and the clip backward (Eq. 12) per pixel; seeds
-//               the per-sample cotangent delta and the remaining radiance
+//   adj_pixel   CRF backward (Eq. 5) and the clip backward (Eq. 12) per pixel: the pixel's
+//               cotangent for the record replay, or per sample for the re-tracing one
 //   (raygen, trace: the forward kernels)
 //   adj_shade   settles the previous vertex's bounce derivative, removes emission,
 //               emits next-event shadow rays with their gradient payloads, bounces
@@ -202,32 +202,42 @@ __device__ __forceinline__ bool put_ep_rec(const MapBins& mb, uint32_t slot, dou
 // ---------------------------------------------------------------- per pixel
 // Eq. 5 backward: y = g_c w E_c, I_c = y^gamma_c;  Eq. 12 backward per sample.
 // PIX_LANES lanes per pixel stride over its samples, reductions inside the lane group.
+// per_sample (the re-tracing replay): the samples' cotangents go to delta and their
+// radiance to q.L.  Otherwise (the record replay) the pixel's cotangent alone goes to delta
+// at the pixel's first sample: the replay forms a sample's own from it and the sample's
+// radiance, so this pass reads the radiance once and writes 16 bytes per pixel (256^2 x 64
+// spp: 48 -> 16 us, bound by that read).
 __global__ void __launch_bounds__(BLOCK) k_adj_pixel(Queues q, AdjQueues aq, ReqDesc r, uint32_t p0, uint32_t p1,
-                                                     const float* sample_L, float4* pix_dE) {
+                                                     const float* sample_L, float4* pix_dE, bool per_sample) {
     const uint32_t p = p0 + (blockIdx.x * BLOCK + threadIdx.x) / PIX_LANES;
     const int lane = threadIdx.x & (PIX_LANES - 1);
     float acc[7] = {0, 0, 0, 0, 0, 0, 0};   // d gamma_c[3], d w[3], d threshold
     if (p < p1) {   // uniform per lane group
         const float thr = clip_threshold(r);
+        const uint32_t sid0 = p * (uint32_t)r.spp - r.g_base + r.sid_base;
         float Ls[3] = {0.f, 0.f, 0.f};
+        float over[3] = {0.f, 0.f, 0.f};   // this lane's clipped samples per channel
         for (int s = lane; s < r.spp; s += PIX_LANES) {
-            const uint32_t g = p * (uint32_t)r.spp + (uint32_t)s;
             float4 L;
             if (sample_L) {
-                L = make_float4(sample_L[3 * (size_t)g], sample_L[3 * (size_t)g + 1], sample_L[3 * (size_t)g + 2], 0.f);
-                q.L[g - r.g_base + r.sid_base] = L;
+                const size_t g = (size_t)p * (uint32_t)r.spp + (uint32_t)s;
+                L = make_float4(sample_L[3 * g], sample_L[3 * g + 1], sample_L[3 * g + 2], 0.f);
+                if (per_sample) q.L[sid0 + s] = L;
             } else {
-                L = q.L[g - r.g_base + r.sid_base];
+                L = q.L[sid0 + s];
             }
-            Ls[0] += r.clip ? fminf(L.x, thr) : L.x;
-            Ls[1] += r.clip ? fminf(L.y, thr) : L.y;
-            Ls[2] += r.clip ? fminf(L.z, thr) : L.z;
+            const float l[3] = {L.x, L.y, L.z};
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                Ls[c] += r.clip ? fminf(l[c], thr) : l[c];
+                if (r.clip && l[c] > thr) over[c] += 1.f;
+            }
         }
 #pragma unroll
         for (int c = 0; c < 3; ++c)
 #pragma unroll
             for (int off = PIX_LANES / 2; off > 0; off >>= 1) Ls[c] += __shfl_xor(Ls[c], off);
-        float dE[3];
+        float dE[3], gs[3];
         for (int c = 0; c < 3; ++c) {
             const float Ec = Ls[c] / (float)r.spp;
             const float w = scalar(r, 15 + c), gc = scalar(r, 12 + c);
@@ -248,24 +258,17 @@ __global__ void __launch_bounds__(BLOCK) k_adj_pixel(Queues q, AdjQueues aq, Req
                     acc[3 + c] += dy * r.crf_gain * Ec;
                 }
             }
+            gs[c] = dE[c] / (float)r.spp;
+            if (over[c] > 0.f) acc[6] += gs[c] * over[c];   // clipped: the threshold's gradient
         }
         if (pix_dE && lane == 0) pix_dE[p] = make_float4(dE[0], dE[1], dE[2], 0.f);
-        for (int s = lane; s < r.spp; s += PIX_LANES) {
-            const uint32_t g = p * (uint32_t)r.spp + (uint32_t)s;
-            const uint32_t sid = g - r.g_base + r.sid_base;
-            const float4 L = q.L[sid];
-            const float l[3] = {L.x, L.y, L.z};
-            float dl[3];
-            for (int c = 0; c < 3; ++c) {
-                const float gs = dE[c] / (float)r.spp;
-                if (r.clip && l[c] > thr) {   // clipped: the sample's radiance does not matter
-                    acc[6] += gs;
-                    dl[c] = 0.f;
-                } else {
-                    dl[c] = gs;
-                }
+        if (!per_sample) {
+            if (lane == 0) aq.delta[sid0] = make_float4(gs[0], gs[1], gs[2], 0.f);
+        } else {
+            for (int s = lane; s < r.spp; s += PIX_LANES) {
+                const float4 L = q.L[sid0 + s];
+                aq.delta[sid0 + s] = clip_cotangent(r, make_float4(gs[0], gs[1], gs[2], 0.f), L, thr);
             }
-            aq.delta[sid] = make_float4(dl[0], dl[1], dl[2], 0.f);
         }
     }
     // block reduction of the scalar partials, one atomic per value per workgroup
@@ -922,11 +925,21 @@ __device__ __forceinline__ void replay_count_clear(const Queues& q, int depth) {
 // One bounce of the replay when the forward kept its path records: the vertex's leaf and
 // the visibility of its shadow rays are read instead of traced.  Shading, the
 // next-event terms and the bounce are re-evaluated with the forward's Philox counters.
-// The next-event cotangents on the BRDF maps at this vertex travel with the path and
-// are added to its bounce derivative when that is settled at the next vertex, so each
-// vertex scatters into the maps once (twice where the path ends).
-template <bool UNI>
-__global__ void __launch_bounds__(BLOCK) k_adj_replay(Queues q, AdjQueues aq, int cur, int depth, ReqDesc uni,
+// A path carries its throughput and remaining radiance already multiplied by the sample's
+// cotangent (delta beta and delta L_r: every term is linear in delta), 96 bytes in all.
+// The records say which vertices are lit, so a sample is replayed only up to the last one
+// (replay_start): beyond it the remaining radiance is exactly zero.  A bounce is taken only
+// before that vertex, where what remains after this vertex's own terms is known, so its
+// derivative L_r / f df is settled here and every vertex leaves one map record.
+// Bound by memory traffic and FP64 issue; on the 50k-triangle corner (256^2 x 64 spp, depth
+// 4), where about a third of the vertices lie at or before a sample's last lit one, the four
+// launches take 358 us against 812 us when every vertex was replayed and the bounce
+// derivatives waited, with 60 more bytes of state, for the next vertex.
+// TEX: the maps' cotangents are wanted; without them only projector light counts, no
+// derivative of the reflectance is formed and no remaining radiance carried.
+template <bool UNI, bool TEX>
+__global__ void __launch_bounds__(BLOCK) k_adj_replay(Queues q, AdjQueues aq, int cur, int depth,
+                                                      const float* __restrict__ sample_L, ReqDesc uni,
                                                       const ReqDesc* __restrict__ table) {
     const int nxt = cur ^ 1;
     const uint32_t n = *replay_count(q, depth);
@@ -937,218 +950,176 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay(Queues q, AdjQueues aq, in
         replay_count_clear(q, depth);
         return;
     }
-    {
-        const uint32_t i = base + threadIdx.x;
-        bool cont = false;
-        PathO no{};
-        PathD nd{};
-        float4 nb = {}, nrl = {}, npenda = {}, npn = {};
-        float2 npend = {};
-        double2 npuv = {};
-        float npns = 0.f;
-        // map cotangents of the previous vertex (a) and of this one when the path ends here (b)
-        bool a_on = false, b_on = false, e_on = false;
-        double a_u = 0.0, a_v = 0.0, b_u = 0.0, b_v = 0.0;
-        float ag[5] = {0.f, 0.f, 0.f, 0.f, 0.f}, bg[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-        // E_p cotangent of this vertex's projector term
-        double e_pu = 0.0, e_pv = 0.0;
-        float eg[3] = {0.f, 0.f, 0.f};
-        int lslot = -1;   // request slot of this lane's path (-1: no path)
-        const ReqDesc* rp = &sel<UNI>(uni, table, 0);
-        if (i < n) {
-            PathO o;
-            PathD dd;
-            float4 b, rl, penda;
-            // the previous vertex's pending cotangents (read when penda.w >= 0)
-            float2 pend = {};
-            double2 puv = {};
-            float4 pn = {};
-            float pns = 0.f;
-            if (UNI && depth == 0) {
-                // the dense camera wave (queue index = batch sample index): the ray is
-                // regenerated as the forward's raygen made it instead of read back
-                const uint32_t g = i - uni.sid_base + uni.g_base;
-                const D3 cd = camera_dir(uni, g);
+    const uint32_t i = base + threadIdx.x;
+    bool cont = false;
+    PathO no{};
+    PathD nd{};
+    float4 nb = {}, nrl = {};
+    bool t_on = false, e_on = false;   // map cotangents of this vertex, E_p cotangent of its projector term
+    double t_u = 0.0, t_v = 0.0, e_pu = 0.0, e_pv = 0.0;
+    float tg[5] = {0.f, 0.f, 0.f, 0.f, 0.f}, eg[3] = {0.f, 0.f, 0.f};
+    int lslot = -1;   // request slot of this lane's path (-1: no path)
+    const ReqDesc* rp = &sel<UNI>(uni, table, 0);
+    if (i < n) {
+        PathO o;
+        PathD dd;
+        float4 b, rl = {};
+        int lit;
+        if (depth == 0) {
+            if constexpr (UNI) {   // the dense camera wave: queue index = batch sample index
                 o = PathO{uni.cam_o[0], uni.cam_o[1], uni.cam_o[2], 0, -1};
-                dd = PathD{cd.x, cd.y, cd.z, g, 0u};
-                b = make_float4(1.0f, 1.0f, 1.0f, 0.0f);
-                rl = q.L[i];                                  // remaining radiance = the sample's total
-                penda = make_float4(0.f, 0.f, 0.f, -1.f);     // no pending bounce
+                dd.g = i - uni.sid_base + uni.g_base;
             } else {
                 o = nt_ld(&q.po[cur][i]);
                 dd = nt_ld(&q.pd[cur][i]);
-                b = nt_ld(&q.pb[cur][i]);
-                if (depth == 0) {   // camera wave of several requests: as above, from the queue's rays
-                    rl = q.L[i];
-                    penda = make_float4(0.f, 0.f, 0.f, -1.f);
-                } else {
-                    rl = nt_ld(&aq.rl[cur][i]);
-                    penda = nt_ld(&aq.penda[cur][i]);
-                    // loaded with the path state (every path past depth 0 bounced, so
-                    // they are nearly always used): behind the penda.w test they cost a
-                    // further trip to memory
-                    pend = nt_ld(&aq.pend[cur][i]);
-                    puv = nt_ld(&aq.puv[cur][i]);
-                    pn = nt_ld(&aq.pn[cur][i]);
-                    pns = nt_ld(&aq.pns[cur][i]);
-                }
             }
+            const ReqDesc& r = sel<UNI>(uni, table, o.slot);
+            const ReplayStart t = replay_start<TEX>(r, dd.g, sample_L, q.L, aq.delta);
+            lit = t.lit;
+            b = t.dl;
+            rl = make_float4(t.dl.x * t.L.x, t.dl.y * t.L.y, t.dl.z * t.L.z, 0.f);
+            if constexpr (UNI)
+                if (lit >= 0) {
+                    const D3 cd = camera_dir(uni, dd.g);
+                    dd.x = cd.x, dd.y = cd.y, dd.z = cd.z;
+                }
+        } else {
+            o = nt_ld(&q.po[cur][i]);
+            dd = nt_ld(&q.pd[cur][i]);
+            b = nt_ld(&q.pb[cur][i]);
+            if constexpr (TEX) rl = nt_ld(&aq.rl[cur][i]);
+            lit = (int)dd.pad;
+        }
+        if (lit >= depth) {
             const ReqDesc& r = sel<UNI>(uni, table, o.slot);
             rp = &r;
             lslot = o.slot;
             const uint32_t g = dd.g;
-            const uint32_t sid = g - r.g_base + r.sid_base;
-            const uint32_t rec = __builtin_nontemporal_load(&r.rec[(size_t)(g - r.rec_g0) * r.max_depth + depth]);
-            const int leaf = (int)(rec & REC_LEAF) - 1;
-            const float4 dl = aq.delta[sid];
-            const D3 delta = d3(dl.x, dl.y, dl.z);
-            const D3 beta = d3(b.x, b.y, b.z);
-            if (penda.w >= 0.f) {
-                // previous vertex: its next-event cotangents plus d/df of its bounce,
-                // beta_k f cos/pdf R_{k+1} -> R_{k+1} / f (zero when this ray escaped)
-                a_on = true;
-                a_u = puv.x;
-                a_v = puv.y;
-                double ga0 = pn.x, ga1 = pn.y, ga2 = pn.z, gr = pn.w, gs = pns;
-                if (leaf >= 0) {
-                    const D3 t = delta * d3(rl.x, rl.y, rl.z) * d3(penda.x, penda.y, penda.z);
-                    const double sum = t.x + t.y + t.z;
-                    ga0 += t.x * (1.0 / PI);
-                    ga1 += t.y * (1.0 / PI);
-                    ga2 += t.z * (1.0 / PI);
-                    gr += sum * pend.x;
-                    gs += sum * pend.y;
-                }
-                ag[0] = (float)ga0;
-                ag[1] = (float)ga1;
-                ag[2] = (float)ga2;
-                ag[3] = (float)gr;
-                ag[4] = (float)gs;
+            const uint32_t rec = r.rec[(size_t)(g - r.rec_g0) * r.max_depth + depth];
+            const int leaf = rec_leaf(r, rec);
+            const Surf s = surface(r, leaf, d3(o.x, o.y, o.z), d3(dd.x, dd.y, dd.z));
+            const D3 db = d3(b.x, b.y, b.z);
+            if (TEX && r.emission) {
+                const float4 e = r.emission[leaf];
+                rl.x -= (float)(db.x * e.x);
+                rl.y -= (float)(db.y * e.y);
+                rl.z -= (float)(db.z * e.z);
             }
-            if (leaf >= 0) {
-                const Surf s = surface(r, leaf, d3(o.x, o.y, o.z), d3(dd.x, dd.y, dd.z));
-                if (r.emission) {
-                    const float4 e = r.emission[leaf];
-                    rl.x -= (float)(beta.x * e.x);
-                    rl.y -= (float)(beta.y * e.y);
-                    rl.z -= (float)(beta.z * e.z);
-                }
-                const D3 db = delta * beta;
-                D3 nga = d3(0., 0., 0.);
-                double ngr = 0.0, ngs = 0.0;
-                ProjNee p;
-                if ((rec & REC_PRJ) && projector_nee(r, s, p)) {
+            D3 ga = d3(0., 0., 0.);
+            double gr = 0.0, gs = 0.0;
+            ProjNee p;
+            if ((rec & REC_PRJ) && projector_nee(r, s, p)) {
+                const Brdf f = brdf_eval<TEX>(r.brdf, s.n, s.wo, p.wp, s.alb, s.rough, s.spec);
+                const D3 gE = db * f.f * p.geom;   // d/dE_p before the bilinear weights
+                e_on = r.dEp != nullptr;
+                e_pu = p.pu;
+                e_pv = p.pv;
+                eg[0] = (float)gE.x;
+                eg[1] = (float)gE.y;
+                eg[2] = (float)gE.z;
+                if constexpr (TEX) {
                     const D4 E = fetch4(r.Ep, p.pb);
-                    const Brdf f = brdf_eval<true>(r.brdf, s.n, s.wo, p.wp, s.alb, s.rough, s.spec);
                     const D3 Ex = d3(E.x, E.y, E.z) * p.geom;
-                    const D3 C = beta * f.f * Ex;
-                    const D3 gE = db * f.f * p.geom;   // d/dE_p before the bilinear weights
+                    const D3 C = db * f.f * Ex;
                     const double sx = db.x * Ex.x + db.y * Ex.y + db.z * Ex.z;
-                    e_on = r.dEp != nullptr;
-                    e_pu = p.pu;
-                    e_pv = p.pv;
-                    eg[0] = (float)gE.x;
-                    eg[1] = (float)gE.y;
-                    eg[2] = (float)gE.z;
-                    nga = nga + db * Ex * (1.0 / PI);
-                    ngr += sx * f.ds_dr;
-                    ngs += sx * f.ds_dsp;
+                    ga = ga + db * Ex * (1.0 / PI);
+                    gr += sx * f.ds_dr;
+                    gs += sx * f.ds_dsp;
                     rl.x -= (float)C.x;
                     rl.y -= (float)C.y;
                     rl.z -= (float)C.z;
                 }
+            }
+            if constexpr (TEX) {
                 if (r.env_on && (rec & REC_ENV)) {
                     const U4 x = vertex_rng(r, g, 2u + 2u * depth);
                     const D3 we = sample_cosine(s.n, u24(x.x), u24(x.y));
                     const Brdf f = brdf_eval<true>(r.brdf, s.n, s.wo, we, s.alb, s.rough, s.spec);
                     const D3 Ee = d3(r.env[0], r.env[1], r.env[2]) * PI;
-                    const D3 C = beta * f.f * Ee;
+                    const D3 C = db * f.f * Ee;
                     const double sx = db.x * Ee.x + db.y * Ee.y + db.z * Ee.z;
-                    nga = nga + db * Ee * (1.0 / PI);
-                    ngr += sx * f.ds_dr;
-                    ngs += sx * f.ds_dsp;
+                    ga = ga + db * Ee * (1.0 / PI);
+                    gr += sx * f.ds_dr;
+                    gs += sx * f.ds_dsp;
                     rl.x -= (float)C.x;
                     rl.y -= (float)C.y;
                     rl.z -= (float)C.z;
                 }
-                if (depth < r.max_depth - 1) {
-                    const U4 x = vertex_rng(r, g, 1u + 2u * depth);
-                    const D3 wi = sample_bounce(r.brdf, s.n, s.wo, s.rough, u24(x.x), u24(x.y), u24(x.z));
-                    const double ci = dot(s.n, wi);
-                    const double pdf = bounce_pdf(r.brdf, s.n, s.wo, wi, s.rough);
-                    if (ci > 0.0 && pdf > 0.0) {
-                        const Brdf f = brdf_eval<true>(r.brdf, s.n, s.wo, wi, s.alb, s.rough, s.spec);
-                        const D3 nbeta = beta * (f.f * (ci / pdf));
-                        cont = true;
-                        no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
-                        nd = PathD{wi.x, wi.y, wi.z, g, 0u};
-                        nb = make_float4((float)nbeta.x, (float)nbeta.y, (float)nbeta.z, 0.0f);
-                        nrl = rl;
-                        npuv = make_double2(s.u, s.v);
-                        npend = make_float2((float)f.ds_dr, (float)f.ds_dsp);
-                        npenda = make_float4(f.f.x > 0.0 ? (float)(1.0 / f.f.x) : 0.f,
-                                             f.f.y > 0.0 ? (float)(1.0 / f.f.y) : 0.f,
-                                             f.f.z > 0.0 ? (float)(1.0 / f.f.z) : 0.f, 1.f);
-                        npn = make_float4((float)nga.x, (float)nga.y, (float)nga.z, (float)ngr);
-                        npns = (float)ngs;
+            }
+            if (depth < lit) {
+                const U4 x = vertex_rng(r, g, 1u + 2u * depth);
+                const D3 wi = sample_bounce(r.brdf, s.n, s.wo, s.rough, u24(x.x), u24(x.y), u24(x.z));
+                const double ci = dot(s.n, wi);
+                const double pdf = bounce_pdf(r.brdf, s.n, s.wo, wi, s.rough);
+                if (ci > 0.0 && pdf > 0.0) {
+                    const Brdf f = brdf_eval<TEX>(r.brdf, s.n, s.wo, wi, s.alb, s.rough, s.spec);
+                    const D3 ndb = db * (f.f * (ci / pdf));
+                    cont = true;
+                    no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
+                    nd = PathD{wi.x, wi.y, wi.z, g, (uint32_t)lit};
+                    nb = make_float4((float)ndb.x, (float)ndb.y, (float)ndb.z, 0.0f);
+                    nrl = rl;
+                    if constexpr (TEX) {   // d/df of beta f cos/pdf R_{k+1}: L_r / f
+                        const D3 t = d3(f.f.x > 0.0 ? rl.x / f.f.x : 0.0, f.f.y > 0.0 ? rl.y / f.f.y : 0.0,
+                                        f.f.z > 0.0 ? rl.z / f.f.z : 0.0);
+                        const double sum = t.x + t.y + t.z;
+                        ga = ga + t * (1.0 / PI);
+                        gr += sum * f.ds_dr;
+                        gs += sum * f.ds_dsp;
                     }
                 }
-                if (!cont) {   // the path ends here: its next-event cotangents go out now
-                    b_on = true;
-                    b_u = s.u;
-                    b_v = s.v;
-                    bg[0] = (float)nga.x;
-                    bg[1] = (float)nga.y;
-                    bg[2] = (float)nga.z;
-                    bg[3] = (float)ngr;
-                    bg[4] = (float)ngs;
-                }
+            }
+            if constexpr (TEX) {
+                t_u = s.u;
+                t_v = s.v;
+                tg[0] = (float)ga.x;
+                tg[1] = (float)ga.y;
+                tg[2] = (float)ga.z;
+                tg[3] = (float)gr;
+                tg[4] = (float)gs;
+                t_on = tg[0] != 0.f || tg[1] != 0.f || tg[2] != 0.f || tg[3] != 0.f || tg[4] != 0.f;
             }
         }
-        if (UNI && aq.tb.rec) {   // records for the binned flush (direct atomics if full)
-            const bool to_e = e_on && aq.eb.rec;
-            const bool pred[3] = {a_on, b_on, to_e};
-            uint32_t* const ctr[3] = {aq.tb.count, aq.tb.count, aq.eb.count};
-            uint32_t at[3];
-            block_append<3>(pred, ctr, at);
-            if (a_on && !put_tex_rec(aq.tb, at[0], a_u, a_v, ag)) scatter_tex_lane(*rp, a_u, a_v, ag);
-            if (b_on && !put_tex_rec(aq.tb, at[1], b_u, b_v, bg)) scatter_tex_lane(*rp, b_u, b_v, bg);
-            if (e_on && !(to_e && put_ep_rec(aq.eb, at[2], e_pu, e_pv, eg))) scatter_ep_lane(*rp, e_pu, e_pv, eg);
-        } else if (UNI) {
-            scatter_tex(*rp, a_on, a_u, a_v, ag);
-            scatter_tex(*rp, b_on, b_u, b_v, bg);
-            if (rp->dEp) scatter_ep(*rp, e_on, e_pu, e_pv, eg);
-        } else {
-            // several requests: when every path of this wave belongs to one of them (the
-            // usual case, segments are contiguous) the wave still sums shared texels
-            const unsigned long long vm = __ballot(lslot >= 0);
-            const int s0 = vm ? __shfl(lslot, __ffsll(vm) - 1) : -1;
-            if (s0 >= 0 && __ballot(lslot >= 0 && lslot != s0) == 0ull) {
-                const ReqDesc& rr = table[s0];
-                scatter_tex(rr, a_on, a_u, a_v, ag);
-                scatter_tex(rr, b_on, b_u, b_v, bg);
-                if (rr.dEp) scatter_ep(rr, e_on, e_pu, e_pv, eg);
+    }
+    // records for the binned flush (direct atomics where there is no bin or it is full)
+    const bool to_t = UNI && TEX && t_on && aq.tb.rec, to_e = UNI && e_on && aq.eb.rec;
+    const bool pred[3] = {cont, to_t, to_e};
+    uint32_t* const ctr[3] = {replay_count(q, depth + 1), aq.tb.count, aq.eb.count};
+    uint32_t at[3];
+    block_append<3>(pred, ctr, at);
+    replay_count_clear(q, depth);
+    if (cont) {
+        const uint32_t jn = at[0];
+        nt_st(&q.po[nxt][jn], no);
+        nt_st(&q.pd[nxt][jn], nd);
+        nt_st(&q.pb[nxt][jn], nb);
+        if constexpr (TEX) nt_st(&aq.rl[nxt][jn], nrl);
+    }
+    if constexpr (UNI) {
+        if (TEX) {
+            if (aq.tb.rec) {
+                if (t_on && !put_tex_rec(aq.tb, at[1], t_u, t_v, tg)) scatter_tex_lane(*rp, t_u, t_v, tg);
             } else {
-                if (a_on) scatter_tex_lane(*rp, a_u, a_v, ag);
-                if (b_on) scatter_tex_lane(*rp, b_u, b_v, bg);
-                if (e_on) scatter_ep_lane(*rp, e_pu, e_pv, eg);
+                scatter_tex(*rp, t_on, t_u, t_v, tg);
             }
         }
-        const bool pred[1] = {cont};
-        uint32_t* const ctr[1] = {replay_count(q, depth + 1)};
-        uint32_t jn;
-        block_append<1>(pred, ctr, &jn);
-        replay_count_clear(q, depth);
-        if (cont) {
-            nt_st(&q.po[nxt][jn], no);
-            nt_st(&q.pd[nxt][jn], nd);
-            nt_st(&q.pb[nxt][jn], nb);
-            nt_st(&aq.rl[nxt][jn], nrl);
-            nt_st(&aq.pend[nxt][jn], npend);
-            nt_st(&aq.puv[nxt][jn], npuv);
-            nt_st(&aq.penda[nxt][jn], npenda);
-            nt_st(&aq.pn[nxt][jn], npn);
-            nt_st(&aq.pns[nxt][jn], npns);
+        if (aq.eb.rec) {
+            if (e_on && !put_ep_rec(aq.eb, at[2], e_pu, e_pv, eg)) scatter_ep_lane(*rp, e_pu, e_pv, eg);
+        } else if (rp->dEp) {
+            scatter_ep(*rp, e_on, e_pu, e_pv, eg);
+        }
+    } else {
+        // several requests: when every path of this wave belongs to one of them (the
+        // usual case, segments are contiguous) the wave still sums shared texels
+        const unsigned long long vm = __ballot(lslot >= 0);
+        const int s0 = vm ? __shfl(lslot, __ffsll(vm) - 1) : -1;
+        if (s0 >= 0 && __ballot(lslot >= 0 && lslot != s0) == 0ull) {
+            const ReqDesc& rr = table[s0];
+            scatter_tex(rr, t_on, t_u, t_v, tg);
+            if (rr.dEp) scatter_ep(rr, e_on, e_pu, e_pv, eg);
+        } else {
+            if (t_on) scatter_tex_lane(*rp, t_u, t_v, tg);
+            if (e_on) scatter_ep_lane(*rp, e_pu, e_pv, eg);
         }
     }
 }
@@ -1158,12 +1129,13 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay(Queues q, AdjQueues aq, in
 // Every term of a vertex is beta_c f_c c S_c with c the cosine about the shading normal
 // and S_c its remaining factor: E_c / (cos^3 alpha d^2) for the projector, L_env pi / c
 // for the environment (the sampling pdf c / pi held fixed), R_{k+1} / pdf for the bounce;
-// its derivative w.r.t. a map value is beta_c d(f_c c) S_c.  For the bounce S_c is only
-// known at the next vertex, where beta_c f_c c S_c = its remaining radiance rl_c: the
-// vertex leaves the coefficients d(f_c c)/d theta / (f_c c) (PendX), the next one
-// multiplies them by delta_c rl_c.  Normal cotangents are carried in the stored map
-// values (through the vertex's frame), so the records hold 9 channels.
-__global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq, int cur, int depth, ReqDesc r) {
+// its derivative w.r.t. a map value is beta_c d(f_c c) S_c.  For the bounce beta_c f_c c S_c
+// is what remains of the sample's radiance after the vertex's own terms, rl_c, so its
+// derivative is rl_c d(f_c c) / (f_c c).  Normal cotangents go to the stored map values
+// (through the vertex's frame), so the records hold 9 channels.
+template <bool TEX>
+__global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq, int cur, int depth,
+                                                          const float* __restrict__ sample_L, ReqDesc r) {
     const int nxt = cur ^ 1;
     const uint32_t n = *replay_count(q, depth);
     const uint32_t base = blockIdx.x * BLOCK;
@@ -1175,95 +1147,62 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq
     bool cont = false;
     PathO no{};
     PathD nd{};
-    float4 nb = {}, nrl = {}, npn = {}, npnx = {};
-    PendX npx{};
-    double2 npuv = {};
-    float npns = 0.f;
-    bool a_on = false, b_on = false, e_on = false;
-    double a_u = 0.0, a_v = 0.0, b_u = 0.0, b_v = 0.0;
-    float ag[9] = {}, bg[9] = {};
-    double e_pu = 0.0, e_pv = 0.0;
-    float eg[3] = {0.f, 0.f, 0.f};
+    float4 nb = {}, nrl = {};
+    bool t_on = false, e_on = false;
+    double t_u = 0.0, t_v = 0.0, e_pu = 0.0, e_pv = 0.0;
+    float tg[9] = {}, eg[3] = {0.f, 0.f, 0.f};
     if (i < n) {
         PathO o;
         PathD dd;
-        float4 b, rl, penda;
-        if (depth == 0) {   // the dense camera wave, regenerated as the forward's raygen made it
-            const uint32_t g = i - r.sid_base + r.g_base;
-            const D3 cd = camera_dir(r, g);
+        float4 b, rl = {};
+        int lit;
+        if (depth == 0) {   // the dense camera wave: queue index = batch sample index
             o = PathO{r.cam_o[0], r.cam_o[1], r.cam_o[2], 0, -1};
-            dd = PathD{cd.x, cd.y, cd.z, g, 0u};
-            b = make_float4(1.0f, 1.0f, 1.0f, 0.0f);
-            rl = q.L[i];
-            penda = make_float4(0.f, 0.f, 0.f, -1.f);
+            dd.g = i - r.sid_base + r.g_base;
+            const ReplayStart t = replay_start<TEX>(r, dd.g, sample_L, q.L, aq.delta);
+            lit = t.lit;
+            b = t.dl;
+            rl = make_float4(t.dl.x * t.L.x, t.dl.y * t.L.y, t.dl.z * t.L.z, 0.f);
+            if (lit >= 0) {
+                const D3 cd = camera_dir(r, dd.g);
+                dd.x = cd.x, dd.y = cd.y, dd.z = cd.z;
+            }
         } else {
             o = nt_ld(&q.po[cur][i]);
             dd = nt_ld(&q.pd[cur][i]);
             b = nt_ld(&q.pb[cur][i]);
-            rl = nt_ld(&aq.rl[cur][i]);
-            penda = nt_ld(&aq.penda[cur][i]);
+            if constexpr (TEX) rl = nt_ld(&aq.rl[cur][i]);
+            lit = (int)dd.pad;
         }
-        const uint32_t g = dd.g;
-        const uint32_t sid = g - r.g_base + r.sid_base;
-        const uint32_t rec = __builtin_nontemporal_load(&r.rec[(size_t)(g - r.rec_g0) * r.max_depth + depth]);
-        const int leaf = (int)(rec & REC_LEAF) - 1;
-        const float4 dl = aq.delta[sid];
-        const D3 delta = d3(dl.x, dl.y, dl.z);
-        const D3 beta = d3(b.x, b.y, b.z);
-        if (penda.w >= 0.f) {   // settle the previous vertex: its next-event cotangents and its bounce
-            const double2 puv = nt_ld(&aq.puv[cur][i]);
-            const float4 pn = nt_ld(&aq.pn[cur][i]);
-            const float pns = nt_ld(&aq.pns[cur][i]);
-            const float4 pnx = nt_ld(&aq.pnx[cur][i]);
-            a_on = true;
-            a_u = puv.x;
-            a_v = puv.y;
-            double ga[9] = {pn.x, pn.y, pn.z, pn.w, pns, pnx.x, pnx.y, pnx.z, pnx.w};
-            if (leaf >= 0) {
-                const PendX P = nt_ld(&aq.px[cur][i]);
-                const double w[3] = {delta.x * rl.x, delta.y * rl.y, delta.z * rl.z};
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    ga[c] += w[c] * P.a[c];
-                    ga[3] += w[c] * P.r[c];
-                    ga[4] += w[c] * P.s[c];
-                    ga[5] += w[c] * P.m[c];
-                    ga[6] += w[c] * P.n[3 * c];
-                    ga[7] += w[c] * P.n[3 * c + 1];
-                    ga[8] += w[c] * P.n[3 * c + 2];
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < 9; ++j) ag[j] = (float)ga[j];
-        }
-        if (leaf >= 0) {
+        if (lit >= depth) {
+            const uint32_t g = dd.g;
+            const uint32_t rec = r.rec[(size_t)(g - r.rec_g0) * r.max_depth + depth];
+            const int leaf = rec_leaf(r, rec);
             const Surf s = surface(r, leaf, d3(o.x, o.y, o.z), d3(dd.x, dd.y, dd.z));
             const Shading sh = shading(r, leaf, s);
-            if (r.emission) {
+            const D3 db = d3(b.x, b.y, b.z);
+            if (TEX && r.emission) {
                 const float4 e = r.emission[leaf];
-                rl.x -= (float)(beta.x * e.x);
-                rl.y -= (float)(beta.y * e.y);
-                rl.z -= (float)(beta.z * e.z);
+                rl.x -= (float)(db.x * e.x);
+                rl.y -= (float)(db.y * e.y);
+                rl.z -= (float)(db.z * e.z);
             }
-            const D3 db = delta * beta;
             double ng[6] = {0., 0., 0., 0., 0., 0.};   // albedo rgb, roughness, specular, metallic
             D3 gnv = d3(0., 0., 0.);                   // cotangent of the shading normal
-            auto term = [&](const BrdfX& f, D3 S) {    // cotangents of beta_c f_c c S_c
-                const D3 cs = S * f.c;
-                ng[0] += db.x * f.dfa * cs.x;
-                ng[1] += db.y * f.dfa * cs.y;
-                ng[2] += db.z * f.dfa * cs.z;
-                ng[3] += db.x * f.dfr.x * cs.x + db.y * f.dfr.y * cs.y + db.z * f.dfr.z * cs.z;
-                ng[4] += (db.x * cs.x + db.y * cs.y + db.z * cs.z) * f.dfs;
-                ng[5] += db.x * f.dfm.x * cs.x + db.y * f.dfm.y * cs.y + db.z * f.dfm.z * cs.z;
-                gnv = gnv + f.dn[0] * (db.x * S.x) + f.dn[1] * (db.y * S.y) + f.dn[2] * (db.z * S.z);
+            // cotangents of w_c f_c c, w = db S (next events) or rl / (f c) (the bounce)
+            auto term = [&](const BrdfX& f, D3 w) {
+                const D3 cw = w * f.c;
+                ng[0] += f.dfa * cw.x;
+                ng[1] += f.dfa * cw.y;
+                ng[2] += f.dfa * cw.z;
+                ng[3] += f.dfr.x * cw.x + f.dfr.y * cw.y + f.dfr.z * cw.z;
+                ng[4] += (cw.x + cw.y + cw.z) * f.dfs;
+                ng[5] += f.dfm.x * cw.x + f.dfm.y * cw.y + f.dfm.z * cw.z;
+                gnv = gnv + f.dn[0] * w.x + f.dn[1] * w.y + f.dn[2] * w.z;
             };
             ProjNee p;
             if ((rec & REC_PRJ) && projector_nee(r, s, p)) {
-                const D4 E = fetch4(r.Ep, p.pb);
-                const BrdfX f = brdf_x<true>(r.brdf, s.n, sh.ns, s.wo, p.wp, s.alb, s.rough, s.spec, sh.metal);
-                const D3 S = d3(E.x, E.y, E.z) * p.g0;
-                const D3 C = beta * f.f * S * f.c;
+                const BrdfX f = brdf_x<TEX>(r.brdf, s.n, sh.ns, s.wo, p.wp, s.alb, s.rough, s.spec, sh.metal);
                 const D3 gE = db * f.f * (f.c * p.g0);   // d/dE_p before the bilinear weights
                 e_on = r.dEp != nullptr;
                 e_pu = p.pu;
@@ -1271,98 +1210,86 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq
                 eg[0] = (float)gE.x;
                 eg[1] = (float)gE.y;
                 eg[2] = (float)gE.z;
-                term(f, S);
-                rl.x -= (float)C.x;
-                rl.y -= (float)C.y;
-                rl.z -= (float)C.z;
+                if constexpr (TEX) {
+                    const D4 E = fetch4(r.Ep, p.pb);
+                    const D3 w = db * d3(E.x, E.y, E.z) * p.g0;
+                    const D3 C = f.f * w * f.c;
+                    term(f, w);
+                    rl.x -= (float)C.x;
+                    rl.y -= (float)C.y;
+                    rl.z -= (float)C.z;
+                }
             }
-            if (r.env_on && (rec & REC_ENV)) {
-                const U4 x = vertex_rng(r, g, 2u + 2u * depth);
-                const D3 we = sample_cosine(sh.ns, u24(x.x), u24(x.y));
-                const BrdfX f = brdf_x<true>(r.brdf, s.n, sh.ns, s.wo, we, s.alb, s.rough, s.spec, sh.metal);
-                const D3 Le = d3(r.env[0], r.env[1], r.env[2]);
-                const D3 C = beta * f.f * Le * PI;
-                if (f.c > 0.0) term(f, Le * (PI / f.c));
-                rl.x -= (float)C.x;
-                rl.y -= (float)C.y;
-                rl.z -= (float)C.z;
+            if constexpr (TEX) {
+                if (r.env_on && (rec & REC_ENV)) {
+                    const U4 x = vertex_rng(r, g, 2u + 2u * depth);
+                    const D3 we = sample_cosine(sh.ns, u24(x.x), u24(x.y));
+                    const BrdfX f = brdf_x<true>(r.brdf, s.n, sh.ns, s.wo, we, s.alb, s.rough, s.spec, sh.metal);
+                    const D3 Le = d3(r.env[0], r.env[1], r.env[2]);
+                    const D3 C = db * f.f * Le * PI;
+                    if (f.c > 0.0) term(f, db * Le * (PI / f.c));
+                    rl.x -= (float)C.x;
+                    rl.y -= (float)C.y;
+                    rl.z -= (float)C.z;
+                }
             }
-            const D3 gnm = nmap_cotangent(sh, s.n, gnv);
-            if (depth < r.max_depth - 1) {
+            if (depth < lit) {
                 const U4 x = vertex_rng(r, g, 1u + 2u * depth);
                 const D3 wi = sample_bounce(r.brdf, sh.ns, s.wo, s.rough, u24(x.x), u24(x.y), u24(x.z));
                 const double ci = dot(s.n, wi);
                 const double pdf = bounce_pdf(r.brdf, sh.ns, s.wo, wi, s.rough);
                 if (ci > 0.0 && pdf > 0.0) {
-                    const BrdfX f = brdf_x<true>(r.brdf, s.n, sh.ns, s.wo, wi, s.alb, s.rough, s.spec, sh.metal);
-                    const D3 nbeta = beta * (f.f * (f.c / pdf));
+                    const BrdfX f = brdf_x<TEX>(r.brdf, s.n, sh.ns, s.wo, wi, s.alb, s.rough, s.spec, sh.metal);
+                    const D3 ndb = db * (f.f * (f.c / pdf));
                     cont = true;
                     no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
-                    nd = PathD{wi.x, wi.y, wi.z, g, 0u};
-                    nb = make_float4((float)nbeta.x, (float)nbeta.y, (float)nbeta.z, 0.0f);
+                    nd = PathD{wi.x, wi.y, wi.z, g, (uint32_t)lit};
+                    nb = make_float4((float)ndb.x, (float)ndb.y, (float)ndb.z, 0.0f);
                     nrl = rl;
-                    npuv = make_double2(s.u, s.v);
-                    const double fv[3] = {f.f.x, f.f.y, f.f.z};
-                    const double dfr[3] = {f.dfr.x, f.dfr.y, f.dfr.z}, dfm[3] = {f.dfm.x, f.dfm.y, f.dfm.z};
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        const double inv = fv[c] > 0.0 ? 1.0 / fv[c] : 0.0;
-                        npx.a[c] = (float)(f.dfa * inv);
-                        npx.r[c] = (float)(dfr[c] * inv);
-                        npx.s[c] = (float)(f.dfs * inv);
-                        npx.m[c] = (float)(dfm[c] * inv);
-                        const D3 pn = nmap_cotangent(sh, s.n, f.dn[c]) * (inv / f.c);
-                        npx.n[3 * c] = (float)pn.x;
-                        npx.n[3 * c + 1] = (float)pn.y;
-                        npx.n[3 * c + 2] = (float)pn.z;
-                    }
-                    npn = make_float4((float)ng[0], (float)ng[1], (float)ng[2], (float)ng[3]);
-                    npns = (float)ng[4];
-                    npnx = make_float4((float)ng[5], (float)gnm.x, (float)gnm.y, (float)gnm.z);
+                    if constexpr (TEX)
+                        term(f, d3(f.f.x > 0.0 ? rl.x / (f.f.x * f.c) : 0.0, f.f.y > 0.0 ? rl.y / (f.f.y * f.c) : 0.0,
+                                   f.f.z > 0.0 ? rl.z / (f.f.z * f.c) : 0.0));
                 }
             }
-            if (!cont) {   // the path ends here: its next-event cotangents go out now
-                b_on = true;
-                b_u = s.u;
-                b_v = s.v;
+            if constexpr (TEX) {
+                const D3 gnm = nmap_cotangent(sh, s.n, gnv);
+                t_u = s.u;
+                t_v = s.v;
 #pragma unroll
-                for (int j = 0; j < 6; ++j) bg[j] = (float)ng[j];
-                bg[6] = (float)gnm.x;
-                bg[7] = (float)gnm.y;
-                bg[8] = (float)gnm.z;
+                for (int j = 0; j < 6; ++j) tg[j] = (float)ng[j];
+                tg[6] = (float)gnm.x;
+                tg[7] = (float)gnm.y;
+                tg[8] = (float)gnm.z;
+#pragma unroll
+                for (int j = 0; j < 9; ++j) t_on = t_on || tg[j] != 0.f;
             }
         }
     }
-    if (aq.tb.rec) {   // records for the binned flush (direct atomics if full)
-        const bool to_e = e_on && aq.eb.rec;
-        const bool pred[3] = {a_on, b_on, to_e};
-        uint32_t* const ctr[3] = {aq.tb.count, aq.tb.count, aq.eb.count};
-        uint32_t at[3];
-        block_append<3>(pred, ctr, at);
-        if (a_on && !put_tex9_rec(aq.tb, at[0], a_u, a_v, ag)) scatter_tex9_lane(r, a_u, a_v, ag);
-        if (b_on && !put_tex9_rec(aq.tb, at[1], b_u, b_v, bg)) scatter_tex9_lane(r, b_u, b_v, bg);
-        if (e_on && !(to_e && put_ep_rec(aq.eb, at[2], e_pu, e_pv, eg))) scatter_ep_lane(r, e_pu, e_pv, eg);
-    } else {
-        scatter_tex9(r, a_on, a_u, a_v, ag);
-        scatter_tex9(r, b_on, b_u, b_v, bg);
-        if (r.dEp) scatter_ep(r, e_on, e_pu, e_pv, eg);
-    }
-    const bool pred[1] = {cont};
-    uint32_t* const ctr[1] = {replay_count(q, depth + 1)};
-    uint32_t jn;
-    block_append<1>(pred, ctr, &jn);
+    // records for the binned flush (direct atomics where there is no bin or it is full)
+    const bool to_t = TEX && t_on && aq.tb.rec, to_e = e_on && aq.eb.rec;
+    const bool pred[3] = {cont, to_t, to_e};
+    uint32_t* const ctr[3] = {replay_count(q, depth + 1), aq.tb.count, aq.eb.count};
+    uint32_t at[3];
+    block_append<3>(pred, ctr, at);
     replay_count_clear(q, depth);
     if (cont) {
+        const uint32_t jn = at[0];
         nt_st(&q.po[nxt][jn], no);
         nt_st(&q.pd[nxt][jn], nd);
         nt_st(&q.pb[nxt][jn], nb);
-        nt_st(&aq.rl[nxt][jn], nrl);
-        nt_st(&aq.puv[nxt][jn], npuv);
-        nt_st(&aq.penda[nxt][jn], make_float4(0.f, 0.f, 0.f, 1.f));
-        nt_st(&aq.pn[nxt][jn], npn);
-        nt_st(&aq.pns[nxt][jn], npns);
-        nt_st(&aq.pnx[nxt][jn], npnx);
-        nt_st(&aq.px[nxt][jn], npx);
+        if constexpr (TEX) nt_st(&aq.rl[nxt][jn], nrl);
+    }
+    if (TEX) {
+        if (aq.tb.rec) {
+            if (t_on && !put_tex9_rec(aq.tb, at[1], t_u, t_v, tg)) scatter_tex9_lane(r, t_u, t_v, tg);
+        } else {
+            scatter_tex9(r, t_on, t_u, t_v, tg);
+        }
+    }
+    if (aq.eb.rec) {
+        if (e_on && !put_ep_rec(aq.eb, at[2], e_pu, e_pv, eg)) scatter_ep_lane(r, e_pu, e_pv, eg);
+    } else if (r.dEp) {
+        scatter_ep(r, e_on, e_pu, e_pv, eg);
     }
 }
 
@@ -1477,10 +1404,11 @@ static inline unsigned grid_cap(const Launch& l, int64_t n, int b) {
 }
 
 void launch_adj_pixel(const Launch& l, const Queues& q, const AdjQueues& aq, const ReqDesc& r, uint32_t p0,
-                      uint32_t p1, const float* sample_L, float4* pix_dE) {
+                      uint32_t p1, const float* sample_L, float4* pix_dE, bool per_sample) {
     if (p1 <= p0) return;
     const unsigned g = grid_of((int64_t)(p1 - p0) * PIX_LANES, BLOCK);
-    hipLaunchKernelGGL(k_adj_pixel, dim3(g), dim3(BLOCK), 0, l.st, q, aq, r, p0, p1, sample_L, pix_dE);
+    hipLaunchKernelGGL(k_adj_pixel, dim3(g), dim3(BLOCK), 0, l.st, q, aq, r, p0, p1, sample_L, pix_dE,
+                       per_sample);
     if (r.d_part) hipLaunchKernelGGL(k_sum_partials, dim3(7), dim3(256), 0, l.st, r.d_part, (int)g, 8, 7, r.d_acc);
 }
 size_t partial_floats(int64_t pixels_per_wave, int64_t proj_pixels) {
@@ -1508,14 +1436,17 @@ void launch_adj_shadow(const Launch& l, const Queues& q, const AdjQueues& aq, in
     }
 }
 void launch_adj_replay(const Launch& l, const Queues& q, const AdjQueues& aq, int cur, int depth, const ReqDesc& uni,
-                       const ReqDesc* table, int64_t n_upper) {
+                       const ReqDesc* table, int64_t n_upper, const float* sample_L) {
     const dim3 g(grid_of(n_upper, BLOCK)), b(BLOCK);
-    if (!table && uni.tex4b) {
-        hipLaunchKernelGGL(k_adj_replay_ext, g, b, 0, l.st, q, aq, cur, depth, uni);
-        return;
+    if (table) {
+        hipLaunchKernelGGL((k_adj_replay<false, true>), g, b, 0, l.st, q, aq, cur, depth, sample_L, uni, table);
+    } else if (uni.tex4b) {
+        if (uni.d_tex) hipLaunchKernelGGL((k_adj_replay_ext<true>), g, b, 0, l.st, q, aq, cur, depth, sample_L, uni);
+        else hipLaunchKernelGGL((k_adj_replay_ext<false>), g, b, 0, l.st, q, aq, cur, depth, sample_L, uni);
+    } else {
+        if (uni.d_tex) hipLaunchKernelGGL((k_adj_replay<true, true>), g, b, 0, l.st, q, aq, cur, depth, sample_L, uni, table);
+        else hipLaunchKernelGGL((k_adj_replay<true, false>), g, b, 0, l.st, q, aq, cur, depth, sample_L, uni, table);
     }
-    if (table) hipLaunchKernelGGL((k_adj_replay<false>), g, b, 0, l.st, q, aq, cur, depth, uni, table);
-    else hipLaunchKernelGGL((k_adj_replay<true>), g, b, 0, l.st, q, aq, cur, depth, uni, table);
 }
 bool map_tiling(int W, int H, int& T, int& nbx, int& nby) {
     for (int t = 8; t <= MAP_MAX_T; t *= 2) {
@@ -1554,9 +1485,10 @@ void launch_map_flush(const Launch& l, const AdjQueues& aq, const ReqDesc& r) {
 }
 void launch_adj_finish(const Launch& l, const ReqDesc& r, float* d_proj, float* d_albedo, float* d_rough,
                        float* d_spec, float* d_scalars, float* acc, float* d_metal, float* d_nmap) {
-    const unsigned g = grid_of((int64_t)r.Wp * r.Hp, BLOCK);
+    const unsigned g = r.dEp ? grid_of((int64_t)r.Wp * r.Hp, BLOCK) : 0u;
     const bool maps = d_albedo || d_rough || d_spec || d_metal || d_nmap;
     const unsigned gm = maps ? grid_of((int64_t)r.tw * r.th, BLOCK) : 0u;
+    if (g + gm == 0) return;   // the camera pose alone
     hipLaunchKernelGGL(k_adj_prf, dim3(g + gm), dim3(BLOCK), 0, l.st, r, d_proj, acc, (int)g, d_albedo, d_rough,
                        d_spec, d_metal, d_nmap);
     hipLaunchKernelGGL(k_adj_scalars, dim3(1), dim3(256), 0, l.st, r, acc, d_scalars, (int)g);

@@ -112,7 +112,8 @@ __device__ __forceinline__ double cam_phi(const ReqDesc& r, const CamFrozen& z, 
 }
 
 // one thread per camera sample of the wave [p0, p1) x spp; partials of the 12 entries
-__global__ void __launch_bounds__(CAM_TB) k_cam_grad(Queues q, AdjQueues aq, ReqDesc r, uint32_t p0, uint32_t p1) {
+__global__ void __launch_bounds__(CAM_TB) k_cam_grad(Queues q, AdjQueues aq, ReqDesc r, uint32_t p0, uint32_t p1,
+                                                     const float* sample_L) {
     double acc[12];
 #pragma unroll
     for (int k = 0; k < 12; ++k) acc[k] = 0.0;
@@ -120,11 +121,13 @@ __global__ void __launch_bounds__(CAM_TB) k_cam_grad(Queues q, AdjQueues aq, Req
     const uint32_t k = blockIdx.x * CAM_TB + threadIdx.x;
     if (k < n) {
         const uint32_t g = p0 * (uint32_t)r.spp + k;
-        const uint32_t sid = g - r.g_base + r.sid_base;
-        const float4 dl = aq.delta[sid];
-        const uint32_t rec = r.rec[(size_t)(g - r.rec_g0) * r.max_depth];
-        const int leaf = (int)(rec & REC_LEAF) - 1;
-        if (leaf >= 0 && (dl.x != 0.f || dl.y != 0.f || dl.z != 0.f)) {
+        // (a sample no light reaches has no gradient, and one that only its first vertex
+        // lights has no bounce term)
+        const ReplayStart t0 = replay_start<true>(r, g, sample_L, q.L, aq.delta);
+        const float4 dl = t0.dl;
+        if (t0.lit >= 0) {
+            const uint32_t rec = r.rec[(size_t)(g - r.rec_g0) * r.max_depth];
+            const int leaf = rec_leaf(r, rec);
             const D3 delta = d3(dl.x, dl.y, dl.z);
             // the forward's camera ray (the same jittered pixel position as camera_dir)
             const uint32_t pixel = g / (uint32_t)r.spp, si = g - pixel * (uint32_t)r.spp;
@@ -153,7 +156,7 @@ __global__ void __launch_bounds__(CAM_TB) k_cam_grad(Queues q, AdjQueues aq, Req
             }
             z.bounced = false;
             z.wi = d3(0., 0., 0.);
-            if (r.max_depth > 1) {
+            if (t0.lit > 0) {
                 const U4 x = vertex_rng(r, g, 1u);
                 z.wi = sample_bounce(r.brdf, ns0, s0.wo, s0.rough, u24(x.x), u24(x.y), u24(x.z));
                 z.bounced = dot(s0.n, z.wi) > 0.0 && bounce_pdf(r.brdf, ns0, s0.wo, z.wi, s0.rough) > 0.0;
@@ -164,7 +167,7 @@ __global__ void __launch_bounds__(CAM_TB) k_cam_grad(Queues q, AdjQueues aq, Req
             const CamSurf c0 = cam_surface(r, z, s0.x);
             cam_eval(r, z, c0, s0.wo, nee0, b0);
             if (z.bounced) {
-                const float4 L = q.L[sid];
+                const float4 L = t0.L;
                 D3 rest = d3(L.x, L.y, L.z) - nee0;
                 if (r.emission) {
                     const float4 e = r.emission[leaf];
@@ -233,11 +236,11 @@ size_t cam_partial_floats(int64_t samples_per_wave) {
 }
 
 void launch_cam_grad(const Launch& l, const Queues& q, const AdjQueues& aq, const ReqDesc& r, uint32_t p0,
-                     uint32_t p1) {
+                     uint32_t p1, const float* sample_L) {
     const int64_t n = (int64_t)(p1 - p0) * r.spp;
     if (n <= 0 || !r.d_cam_part) return;
     const unsigned nb = (unsigned)((n + CAM_TB - 1) / CAM_TB);
-    hipLaunchKernelGGL(k_cam_grad, dim3(nb), dim3(CAM_TB), 0, l.st, q, aq, r, p0, p1);
+    hipLaunchKernelGGL(k_cam_grad, dim3(nb), dim3(CAM_TB), 0, l.st, q, aq, r, p0, p1, sample_L);
     launch_sum_partials(l, r.d_cam_part, (int)nb, 12, 12, r.d_acc + 20);   // after the PRF partials
 }
 

@@ -198,11 +198,15 @@ struct ReqDesc {
     // the forward writes them when rec is set, the replay adjoint reads them
     uint32_t* rec;
     uint32_t rec_g0;
+    uint32_t rec_end;          // REC_END, or 0 on a mesh whose leaf numbers need its bit
 };
 
-// path record word: bits 0..29 leaf + 1 of the vertex hit at that depth (0: the ray
-// escaped), bit 30 environment shadow ray unoccluded, bit 31 projector shadow ray unoccluded
+// path record word: leaf + 1 of the vertex hit at that depth (0: the ray escaped) in bits
+// 0..28, or 0..29 on a mesh of 2^29 triangles; bit 29 otherwise: the path ends at this
+// vertex though its depth allows more (the words after it are not written); bit 30
+// environment shadow ray unoccluded, bit 31 projector shadow ray unoccluded
 constexpr uint32_t REC_LEAF = 0x3fffffffu;
+constexpr uint32_t REC_END = 1u << 29;
 constexpr uint32_t REC_ENV = 1u << 30;
 constexpr uint32_t REC_PRJ = 1u << 31;
 

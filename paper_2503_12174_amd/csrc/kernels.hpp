@@ -178,28 +178,20 @@ constexpr int64_t map_bin_words(int64_t nb) { return 3 * nb + 4; }
 constexpr int64_t map_units(int64_t cap, int64_t nb) { return (cap + ACC_CHUNK - 1) / ACC_CHUNK + nb; }
 
 // adjoint additions (see adjoint.hip)
-struct alignas(16) PendX {   // per channel c: albedo, roughness, specular, metallic, normal map (xyz)
-    float a[3], r[3], s[3], m[3], n[9], pad[3];
-};
 struct AdjQueues {
-    float4* rl[2];     // remaining radiance L_r of the path (rgb, -), follows the path queue
-    float4* delta;     // per batch sample cotangent of its radiance (rgb, -)
+    float4* rl[2];     // remaining radiance L_r of the path (rgb, -), follows the path queue; the
+                       // record replay's: times the sample's cotangent
+    float4* delta;     // re-tracing replay: per batch sample cotangent of its radiance (rgb, -);
+                       // record replay: the pixel's, at its first sample
+    // the re-tracing replay's shadow rays and pending bounces (null for the record replay)
     double2* sproj[2]; // shadow: projector pixel position (pu, pv) of the vertex
     double2* suv[2];   // shadow: texture coordinate (u, v) of the vertex (FP64: 1k+ maps)
     float4* sg[2];     // shadow: E_p cotangent weight per channel (w: -)
     float4* sa[2];     // shadow: albedo cotangent rgb (w: roughness cotangent)
     float* ss[2];      // shadow: specular cotangent
-    float4* pn[2];     // replay: pending next-event cotangents of the previous vertex (albedo rgb, roughness)
-    float* pns[2];     // replay: pending next-event specular cotangent
     double2* puv[2];   // pending bounce: texture coordinate (u, v) of the previous vertex
     float2* pend[2];   // pending bounce: (dr, dsp) cotangent scale of the previous vertex
     float4* penda[2];  // pending bounce: albedo cotangent scale rgb
-    // with the metallic and normal maps (replay only): the pending bounce's derivative
-    // coefficients (d(f_c c)/d theta) / (f_c c) for albedo, roughness, specular, metallic
-    // and the normal map's stored values (21 floats, PendX) and the pending next-event
-    // cotangents of metallic and the normal map (float4)
-    struct PendX* px[2];
-    float4* pnx[2];
     MapBins tb;        // BRDF-map cotangent records (C = 5, 8 floats per record; C = 9, 12 floats
                        // with the metallic and normal maps)
     MapBins eb;        // E_p cotangent records (C = 3, 6 floats per record)
@@ -248,9 +240,11 @@ void launch_set_desc(const Launch& l, ReqDesc* table, int slot, const ReqDesc& r
 // floats of the scalar-partials buffer (ReqDesc::d_part) for waves of up to
 // pixels_per_wave pixels and a projector of proj_pixels pixels
 size_t partial_floats(int64_t pixels_per_wave, int64_t proj_pixels);
-// pix_dE (optional): per-pixel cotangent of the clipped pixel mean (rgb, -), whole image
+// pix_dE (optional): per-pixel cotangent of the clipped pixel mean (rgb, -), whole image;
+// per_sample: for the re-tracing replay (the record replay and the camera-pose gradient
+// take the samples' radiance from sample_L, or q.L if null, themselves)
 void launch_adj_pixel(const Launch& l, const Queues& q, const AdjQueues& aq, const ReqDesc& r, uint32_t p0,
-                      uint32_t p1, const float* sample_L, float4* pix_dE = nullptr);
+                      uint32_t p1, const float* sample_L, float4* pix_dE, bool per_sample);
 void launch_adj_raygen(const Launch& l, const Queues& q, const AdjQueues& aq, const ReqDesc& r, int slot, uint32_t g0,
                        uint32_t n);
 void launch_adj_shade(const Launch& l, const Queues& q, const AdjQueues& aq, int cur, int depth, const ReqDesc& uni,
@@ -258,9 +252,10 @@ void launch_adj_shade(const Launch& l, const Queues& q, const AdjQueues& aq, int
 void launch_adj_shadow(const Launch& l, const Queues& q, const AdjQueues& aq, int which, int nxt, const ReqDesc& uni,
                        const ReqDesc* table, int64_t n_upper);
 // replay of one bounce from the path records (no tracing): shade, next-event gradients
-// for the recorded visibilities, bounce
+// for the recorded visibilities, bounce; sample_L (one request): the samples' radiance,
+// null: q.L holds it
 void launch_adj_replay(const Launch& l, const Queues& q, const AdjQueues& aq, int cur, int depth, const ReqDesc& uni,
-                       const ReqDesc* table, int64_t n_upper);
+                       const ReqDesc* table, int64_t n_upper, const float* sample_L = nullptr);
 // adds the binned records of tb / eb into r.d_tex / r.dEp and empties the bins
 void launch_map_flush(const Launch& l, const AdjQueues& aq, const ReqDesc& r);
 // tile side and bin count for a W x H map (false: too many tiles, bin nothing)
@@ -270,7 +265,8 @@ bool map_tiling(int W, int H, int& T, int& nbx, int& nby);
 // records): per-workgroup partials into r.d_cam_part (cam_partial_floats of the wave's
 // samples), summed in a fixed order into r.d_acc[20..32)
 size_t cam_partial_floats(int64_t samples_per_wave);
-void launch_cam_grad(const Launch& l, const Queues& q, const AdjQueues& aq, const ReqDesc& r, uint32_t p0, uint32_t p1);
+void launch_cam_grad(const Launch& l, const Queues& q, const AdjQueues& aq, const ReqDesc& r, uint32_t p0, uint32_t p1,
+                     const float* sample_L);
 // dst[k] += the sum of nb partials part[b * stride + k], k < nv, in a fixed order
 void launch_sum_partials(const Launch& l, const float* part, int nb, int stride, int nv, float* dst);
 void launch_adj_finish(const Launch& l, const ReqDesc& r, float* d_proj, float* d_albedo, float* d_rough,

@@ -186,7 +186,6 @@ __global__ void __launch_bounds__(BLOCK) k_shade(Queues q, int cur, int depth, R
                 if (r.out_hits)
                     for (int k = 1; k < r.max_depth; ++k) r.out_hits[(size_t)g * r.max_depth + k] = -2;
             }
-            if (r.rec) __builtin_nontemporal_store((uint32_t)(leaf + 1), &r.rec[(size_t)(g - r.rec_g0) * r.max_depth + depth]);
             if (leaf < 0) {
                 if (r.out_hits) r.out_hits[(size_t)g * r.max_depth + depth] = -1;
                 if (depth == 0 && r.env_on) {   // a camera ray that escapes sees the environment
@@ -268,6 +267,11 @@ __global__ void __launch_bounds__(BLOCK) k_shade(Queues q, int cur, int depth, R
                         nb = make_float4((float)nbeta.x, (float)nbeta.y, (float)nbeta.z, 0.0f);
                     }
                 }
+            }
+            if (r.rec) {
+                const uint32_t end = leaf >= 0 && !cont && depth < r.max_depth - 1 ? r.rec_end : 0u;
+                __builtin_nontemporal_store((uint32_t)(leaf + 1) | end,
+                                            &r.rec[(size_t)(g - r.rec_g0) * r.max_depth + depth]);
             }
         }
         const bool pred[3] = {cont, shp, she};

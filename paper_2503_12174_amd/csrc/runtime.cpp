@@ -112,11 +112,12 @@ bool make_queues(dpcs_context ctx, const char* name, int64_t cap, Queues& q, dpc
     return true;
 }
 
-bool make_adj_queues(dpcs_context ctx, const char* name, int64_t cap, AdjQueues& aq, dpcs_status* st, bool ext) {
+bool make_adj_queues(dpcs_context ctx, const char* name, int64_t cap, AdjQueues& aq, dpcs_status* st, bool retrace) {
     const size_t c = (size_t)cap;
-    // per path 2 x 144 + 16 bytes (+ 2 x 112 with the metallic / normal maps); + 256 bytes
-    // of alignment slack per part (27 parts)
-    const size_t bytes = c * (2 * 144 + 16 + (ext ? 2 * (sizeof(PendX) + 16) : 0)) + 32 * 256;
+    // per path 2 x 16 + 16 bytes, and 2 x 108 for the re-tracing replay; + 256 bytes of
+    // alignment slack per part (at most 19 parts)
+    const size_t bytes = c * (2 * 16 + 16 + (retrace ? 2 * 108 : 0)) + 32 * 256;
+    aq = AdjQueues{};
     char* b = (char*)scratch(ctx, name, bytes, st);
     if (!b) return false;
     auto take = [&](size_t n) {
@@ -126,6 +127,7 @@ bool make_adj_queues(dpcs_context ctx, const char* name, int64_t cap, AdjQueues&
     };
     for (int k = 0; k < 2; ++k) {
         aq.rl[k] = (float4*)take(16 * c);
+        if (!retrace) continue;
         aq.puv[k] = (double2*)take(16 * c);
         aq.pend[k] = (float2*)take(8 * c);
         aq.penda[k] = (float4*)take(16 * c);
@@ -134,14 +136,8 @@ bool make_adj_queues(dpcs_context ctx, const char* name, int64_t cap, AdjQueues&
         aq.sg[k] = (float4*)take(16 * c);
         aq.sa[k] = (float4*)take(16 * c);
         aq.ss[k] = (float*)take(4 * c);
-        aq.pn[k] = (float4*)take(16 * c);
-        aq.pns[k] = (float*)take(4 * c);
-        aq.px[k] = ext ? (PendX*)take(sizeof(PendX) * c) : nullptr;
-        aq.pnx[k] = ext ? (float4*)take(16 * c) : nullptr;
     }
     aq.delta = (float4*)take(16 * c);
-    aq.tb = MapBins{};
-    aq.eb = MapBins{};
     return true;
 }
 
@@ -307,6 +303,7 @@ bool fill_desc(dpcs_context, ReqDesc& r, const dpcs_render_params* p, dpcs_scene
     r.dscal = p->device_scalars;
     r.proj_image = proj_image;
     r.dtex_c = (p->metallic || p->normal_map) ? 9 : 5;   // tex4b is set where the maps are packed
+    r.rec_end = sc->nt < (1 << 29) ? REC_END : 0u;
     return true;
 }
 
@@ -834,16 +831,17 @@ void adjoint_wave(dpcs_context ctx, Queues& q, const AdjQueues& aq, ReqDesc& r, 
     r.g_base = a * (uint32_t)r.spp;
     r.sid_base = 0;
     int pr = prof_begin(ctx, DPCS_STAGE_ADJ_PIXEL);
-    launch_adj_pixel(l, q, aq, r, a, b, sample_L, pix_dE);
-    launch_cam_grad(l, q, aq, r, a, b);   // (no-op unless the camera-pose gradient is asked for)
+    launch_adj_pixel(l, q, aq, r, a, b, sample_L, pix_dE, r.rec == nullptr);
+    launch_cam_grad(l, q, aq, r, a, b, sample_L);   // (no-op unless the camera-pose gradient is asked for)
     prof_end(ctx, pr, nullptr, b - a);
     int cur = 0;
     if (r.rec) {   // the forward's path records stand in for tracing (camera rays regenerated in depth 0)
+        if (!r.d_tex && !r.dEp) return;   // no map or projector gradient asked for
         // (the replay's queue sizes rotate over their own slots: one reset for all depths)
         launch_set_count(l, q.cnt, REPLAY_CNT, n, REPLAY_CNT + 1, REPLAY_CNT + 2);
         for (int d = 0; d < r.max_depth; ++d) {
             pr = prof_begin(ctx, DPCS_STAGE_ADJ_SHADE);
-            launch_adj_replay(l, q, aq, cur, d, r, nullptr, n);
+            launch_adj_replay(l, q, aq, cur, d, r, nullptr, n, sample_L);
             prof_end(ctx, pr, q.cnt + REPLAY_CNT + d % 3, 0);
             if ((aq.tb.rec || aq.eb.rec) && ((d + 1) % BIN_DEPTHS == 0 || d == r.max_depth - 1)) {
                 pr = prof_begin(ctx, DPCS_STAGE_OTHER);

@@ -374,13 +374,13 @@ void dpcs_server_s::wave(Launch& l) {
             }
         }
         for (const Seg& s : segs)
-            if (s.q->adjoint) launch_adj_pixel(l, q, aq, s.q->r, s.a, s.b, nullptr);
+            if (s.q->adjoint) launch_adj_pixel(l, q, aq, s.q->r, s.a, s.b, nullptr, nullptr, !replay);
         // queue sizes: the replay's rotate over their own slots; re-tracing, the
         // closest-hit launch empties the queues shading appends to
         if (binq || replay) launch_set_count(l, q.cnt, REPLAY_CNT, (uint32_t)n_adj, REPLAY_CNT + 1, REPLAY_CNT + 2);
         else launch_set_count(l, q.cnt, 0, (uint32_t)n_adj, 1, 4);
-        for (const Seg& s : segs)
-            if (s.q->adjoint) launch_adj_raygen(l, q, aq, s.q->r, s.q->slot, s.q->r.g_base, (s.b - s.a) * s.q->r.spp);
+        for (const Seg& s : segs)   // (the one-request replay makes its camera rays itself)
+            if (s.q->adjoint && !binq) launch_adj_raygen(l, q, aq, s.q->r, s.q->slot, s.q->r.g_base, (s.b - s.a) * s.q->r.spp);
         cur = 0;
         for (int d = 0; d < max_depth; ++d) {
             if (binq) {
@@ -522,7 +522,7 @@ extern "C" dpcs_status dpcs_server_create(dpcs_context ctx, size_t memory_budget
     s->budget = memory_budget_bytes;
     s->max_slots = max_slots;
     // shared wave queues take at most a quarter of the budget
-    const size_t per_path = (2 * 80 + 4 + 2 * 52 + 16) + (2 * 144 + 16);
+    const size_t per_path = (2 * 80 + 4 + 2 * 52 + 16) + (2 * 124 + 16);
     const int64_t fit = (int64_t)(memory_budget_bytes / 4 / per_path);
     s->cap = std::max<int64_t>(1024, std::min<int64_t>({ctx->capacity, int64_t(1) << 22, fit}));
     s->lat_cap = std::min<int64_t>(s->cap, int64_t(1) << 21);
@@ -539,10 +539,10 @@ extern "C" dpcs_status dpcs_server_create(dpcs_context ctx, size_t memory_budget
         delete s;
         return fail(ctx, DPCS_E_INVALID, "memory budget smaller than the shared queues of one wave");
     }
-    // binning buffers for one-request compensation waves (records of up to BIN_DEPTHS + 1
-    // texture and BIN_DEPTHS E_p entries per path between flushes), when they take at most
+    // binning buffers for one-request compensation waves (records of up to BIN_DEPTHS
+    // texture and E_p entries per path between flushes), when they take at most
     // a quarter of the budget (~1.2 GB for 2^21-path waves)
-    s->tex_bins_cap = s->lat_cap * (BIN_DEPTHS + 1);
+    s->tex_bins_cap = s->lat_cap * BIN_DEPTHS;
     s->ep_bins_cap = s->lat_cap * BIN_DEPTHS;
     const size_t bins_bytes = loop_bins_bytes(s->tex_bins_cap, 5, 8) + loop_bins_bytes(s->ep_bins_cap, 3, 6);
     const bool binning = bins_bytes <= s->budget / 4 && s->shared_bytes + bins_bytes < s->budget;
@@ -603,8 +603,6 @@ extern "C" dpcs_status dpcs_server_create(dpcs_context ctx, size_t memory_budget
         s->aq.sg[k] = (float4*)take(16 * c);
         s->aq.sa[k] = (float4*)take(16 * c);
         s->aq.ss[k] = (float*)take(4 * c);
-        s->aq.pn[k] = (float4*)take(16 * c);
-        s->aq.pns[k] = (float*)take(4 * c);
     }
     s->q.hit = (int*)take(4 * c);
     s->q.L = (float4*)take(16 * c);

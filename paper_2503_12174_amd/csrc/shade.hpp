@@ -255,4 +255,65 @@ __device__ __forceinline__ U4 vertex_rng(const ReqDesc& r, uint32_t g, uint32_t 
     return philox4x32_10(pixel, s + r.sample_offset, block, 0u, r.seed_lo, r.seed_hi);
 }
 
+// ---------------------------------------------------------------- path records
+__device__ __forceinline__ int rec_leaf(const ReqDesc& r, uint32_t w) {
+    return (int)(w & (REC_LEAF ^ r.rec_end)) - 1;
+}
+// The last vertex of sample g whose own light reaches the camera (-1: none), read from its
+// records: the remaining radiance past it is exactly zero, so a replay has nothing to
+// differentiate beyond.  ENV: environment light counts (it carries no E_p cotangent).
+// all: the last vertex on a surface, whether lit or not.  Records without the end bit
+// (meshes of 2^29 triangles) may name a later vertex than the path has, never an earlier one.
+template <bool ENV>
+__device__ __forceinline__ int last_lit(const ReqDesc& r, uint32_t g, bool all) {
+    const uint32_t* w = r.rec + (size_t)(g - r.rec_g0) * r.max_depth;
+    const uint32_t light = REC_PRJ | (ENV && r.env_on ? REC_ENV : 0u);
+    const bool any = all || (ENV && r.emission != nullptr);
+    int lit = -1;
+    for (int d0 = 0; d0 < r.max_depth; d0 += 4) {
+        uint32_t v[4];   // four words at once: one trip to memory for the usual depths
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = w[min(d0 + k, r.max_depth - 1)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (d0 + k >= r.max_depth || rec_leaf(r, v[k]) < 0) return lit;
+            if (any || (v[k] & light)) lit = d0 + k;
+            if (v[k] & r.rec_end) return lit;
+        }
+    }
+    return lit;
+}
+// cotangent of a sample's radiance L from its pixel's: zero where the clip (Eq. 12) holds
+__device__ __forceinline__ float4 clip_cotangent(const ReqDesc& r, float4 dp, float4 L, float thr) {
+    if (r.clip) {
+        if (L.x > thr) dp.x = 0.f;
+        if (L.y > thr) dp.y = 0.f;
+        if (L.z > thr) dp.z = 0.f;
+    }
+    return dp;
+}
+// A record replay's camera sample: its radiance (the forward's per-sample output, or the
+// wave's) and cotangent, and the last vertex worth replaying.  A sample whose cotangent or
+// radiance is not finite is followed to its path's end, so NaN reaches every map value
+// that its path touched.
+struct ReplayStart {
+    float4 L, dl;
+    int lit;
+};
+template <bool ENV>
+__device__ __forceinline__ ReplayStart replay_start(const ReqDesc& r, uint32_t g, const float* __restrict__ sample_L,
+                                                    const float4* __restrict__ wave_L,
+                                                    const float4* __restrict__ delta) {
+    ReplayStart t;
+    const uint32_t sid = g - r.g_base + r.sid_base, s = g % (uint32_t)r.spp;
+    if (sample_L) t.L = make_float4(sample_L[3 * (size_t)g], sample_L[3 * (size_t)g + 1], sample_L[3 * (size_t)g + 2], 0.f);
+    else t.L = wave_L[sid];
+    t.dl = clip_cotangent(r, delta[sid - s], t.L, clip_threshold(r));
+    const float x = (t.L.x + t.L.y + t.L.z) * 0.f + (t.dl.x + t.dl.y + t.dl.z) * 0.f;   // 0, or NaN if any is not finite
+    t.lit = -1;
+    if (x != 0.f) t.lit = last_lit<true>(r, g, true);
+    else if (t.dl.x != 0.f || t.dl.y != 0.f || t.dl.z != 0.f) t.lit = last_lit<ENV>(r, g, false);
+    return t;
+}
+
 }  // namespace dpcs

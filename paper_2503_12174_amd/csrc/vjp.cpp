@@ -40,11 +40,21 @@ extern "C" dpcs_status dpcs_render_vjp(dpcs_context ctx, dpcs_scene scene, const
     dpcs_status st = DPCS_OK;
     if (!prepare_request(ctx, r, params, "vjp", &st)) return st;
     const size_t nEp = (size_t)r.Wp * r.Hp, nT = (size_t)r.tw * r.th;
-    float* dEp = (float*)scratch(ctx, "vjp.dEp", sizeof(float) * 4 * nEp, &st);
-    if (!dEp) return st;
+    // Path records: the caller's (whole image, from the forward call that produced
+    // sample_radiance), or this call's own per wave when it runs the forward itself.
+    // With sample_radiance alone the replay traces again.
+    const bool own_rec = !sample_radiance, records = own_rec || path_records;
+    // The record replay forms only what is asked for: the maps' cotangents (a compensation
+    // step asks for the projector image's alone: no texture records, sort or bounce
+    // derivatives), and E_p's when the projector image or the scalars want it.
+    const bool want_tex = !records || grads->d_albedo || grads->d_roughness || grads->d_specular || grads->d_metallic ||
+                          grads->d_normal_map;
+    const bool want_ep = !records || grads->d_proj_image || grads->d_scalars;
+    float* dEp = nullptr;
+    float* dtex = nullptr;
     const int C = r.dtex_c;   // cotangent channels per texel: 5, or 9 with the metallic / normal maps
-    float* dtex = (float*)scratch(ctx, "vjp.dtex", sizeof(float) * C * nT, &st);
-    if (!dtex) return st;
+    if (want_ep && !(dEp = (float*)scratch(ctx, "vjp.dEp", sizeof(float) * 4 * nEp, &st))) return st;
+    if (want_tex && !(dtex = (float*)scratch(ctx, "vjp.dtex", sizeof(float) * C * nT, &st))) return st;
     float* acc = (float*)scratch(ctx, "vjp.acc", sizeof(float) * 32, &st);
     if (!acc) return st;
     Launch l{ctx->stream, ctx->grid_cap};
@@ -75,31 +85,26 @@ extern "C" dpcs_status dpcs_render_vjp(dpcs_context ctx, dpcs_scene scene, const
     Queues q{};
     AdjQueues aq{};
     if (!make_queues(ctx, "fwd.queues", ppw * r.spp, q, &st)) return st;
-    if (!make_adj_queues(ctx, "vjp.queues", ppw * r.spp, aq, &st, ext)) return st;
-    // Path records: the caller's (whole image, from the forward call that produced
-    // sample_radiance), or this call's own per wave when it runs the forward itself.
-    // With sample_radiance alone the replay traces again.
+    if (!make_adj_queues(ctx, "vjp.queues", ppw * r.spp, aq, &st, !records)) return st;
     uint32_t* wave_rec = nullptr;
-    const bool own_rec = !sample_radiance;
-    if ((own_rec || path_records) && scene->nt >= (int)REC_LEAF)
+    if (records && scene->nt >= (int)REC_LEAF)
         return fail(ctx, DPCS_E_UNSUPPORTED, "path records need < 2^30 triangles");
     if (own_rec) {
         wave_rec = (uint32_t*)scratch(ctx, "vjp.records", sizeof(uint32_t) * (size_t)(ppw * r.spp) * r.max_depth, &st);
         if (!wave_rec) return st;
     }
-    {   // the replay bins its map cotangents: per group of k depths at most k + 1 texture
-        // records per path (one per vertex, one more where a path ends) -- the re-tracing
-        // replay writes one per vertex and one per unoccluded shadow ray, at most 3 per
-        // vertex -- and one E_p record per vertex
+    {   // the replay bins its map cotangents: per group of k depths at most k texture records
+        // per path (one per vertex) -- the re-tracing replay writes one per vertex and one
+        // per unoccluded shadow ray, at most 3 per vertex -- and one E_p record per vertex
         const int64_t k = std::min(r.max_depth, BIN_DEPTHS);
-        const int64_t per = (own_rec || path_records) ? k + 1 : 3 * k;
-        if (ext) make_map_bins(ctx, zl, aq.tb, "vjp.tex9_bins", r.tw, r.th, 9, 12, ppw * r.spp * per);
-        else make_map_bins(ctx, zl, aq.tb, "vjp.tex_bins", r.tw, r.th, 5, 8, ppw * r.spp * per);
-        make_map_bins(ctx, zl, aq.eb, "vjp.ep_bins", r.Wp, r.Hp, 3, 6, ppw * r.spp * k);
+        const int64_t per = records ? k : 3 * k;
+        if (want_tex && ext) make_map_bins(ctx, zl, aq.tb, "vjp.tex9_bins", r.tw, r.th, 9, 12, ppw * r.spp * per);
+        else if (want_tex) make_map_bins(ctx, zl, aq.tb, "vjp.tex_bins", r.tw, r.th, 5, 8, ppw * r.spp * per);
+        if (want_ep) make_map_bins(ctx, zl, aq.eb, "vjp.ep_bins", r.Wp, r.Hp, 3, 6, ppw * r.spp * k);
     }
     zl.launch();
     // the forward run here and the re-tracing replay put shadow rays on the side stream
-    int* spill2 = (own_rec || !path_records) ? side_spill(ctx, q) : nullptr;
+    int* spill2 = (own_rec || !records) ? side_spill(ctx, q) : nullptr;
     for (int64_t a = 0; a < npix; a += ppw) {
         const uint32_t b = (uint32_t)std::min(npix, a + ppw);
         if (own_rec) {
