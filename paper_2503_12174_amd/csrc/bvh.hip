@@ -323,7 +323,7 @@ hipError_t build_bvh(hipStream_t st, const BvhInputs& in, BvhOutputs& out, BvhBu
     const int n = in.nt;
     if (kind == BvhBuild::SAH && n > 1) {
         const uint32_t* order = nullptr;
-        const hipError_t e = build_sah(st, in, scratch, host_word, out.nodes, &order);
+        const hipError_t e = build_sah(st, in, scratch, out.nodes, &order);
         if (e != hipSuccess) return e;
         out.order = order;
         return build_leaf_records(st, in, order, out);

@@ -16,6 +16,7 @@ struct BvhInputs {
     const float* Le;         // device emission or null
     int nt;
     float lo[3], scale[3];   // centroid box origin and 1023 / extent
+    float clo[3], chi[3];    // centroid box
     uint32_t* keys[2];
     uint32_t* vals[2];
     uint32_t* hist;          // 256 * ntiles
@@ -35,8 +36,8 @@ struct BvhOutputs {
 };
 // The binary hierarchy with its bounds, then the leaf records.  LBVH: the radix tree over
 // the Morton-sorted codes; PLOC: clustering over the Morton order (scratch of
-// ploc_scratch_bytes); SAH: top-down binned SAH (scratch of sah_scratch_bytes).  PLOC and
-// SAH read one count per round into host_word[0..1].  child / parent_int / parent_leaf
+// ploc_scratch_bytes); SAH: top-down binned SAH (scratch of sah_scratch_bytes).  PLOC reads
+// one count per round into host_word[0..1].  child / parent_int / parent_leaf
 // receive the topology (parent_int must hold -1 everywhere beforehand); out.order points
 // into in.vals (LBVH, PLOC) or into the scratch (SAH).  SAH returns hipErrorNotSupported
 // for a tree deeper than 64 levels.
@@ -47,8 +48,7 @@ size_t ploc_scratch_bytes(int nt);
 hipError_t build_ploc(hipStream_t st, const BvhInputs& in, const uint32_t* order, void* scratch, uint64_t* host_word,
                       float4* nodes);
 size_t sah_scratch_bytes(int nt);
-hipError_t build_sah(hipStream_t st, const BvhInputs& in, void* scratch, uint64_t* host_word, float4* nodes,
-                     const uint32_t** order_out);
+hipError_t build_sah(hipStream_t st, const BvhInputs& in, void* scratch, float4* nodes, const uint32_t** order_out);
 // the 4-wide BVH of a binary one (nt >= 2) and the tree's checks, in scratch of
 // wide_scratch_bytes(nt): result nodes4 (8 float4 per node) and map4 (4 ints per node)
 // point into the scratch; the host reads one count per level into host_words (>= 2)

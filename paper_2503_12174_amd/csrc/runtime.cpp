@@ -558,7 +558,8 @@ extern "C" dpcs_status dpcs_scene_create(dpcs_context ctx, const dpcs_mesh_desc*
     in.Le = (const float*)dLe;
     in.nt = nt;
     for (int k = 0; k < 3; ++k) {
-        in.lo[k] = (float)clo[k];
+        in.lo[k] = in.clo[k] = (float)clo[k];
+        in.chi[k] = (float)chi[k];
         const double ext = chi[k] - clo[k];
         in.scale[k] = ext > 0 ? (float)(1023.0 / ext) : 0.0f;
     }
