@@ -268,9 +268,12 @@ __device__ __forceinline__ void cmpx(float& ka, int& ra, float& kb, int& rb) {
 // down by at least the rounding error of o / d for near planes, up for far planes.
 // With that, a slab value can only err by the relative rounding of 1 / d and of the
 // FMA, which the relative widening in the test covers; it needs no absolute term
-// that would grow for near-axis-parallel rays.  Degenerate axes (d = 0) give NaN or
-// infinite slab values, which the min/max below drop or keep in the conservative
-// direction.  The relative widening multiplies (t x (1 -+ 4e-6)) rather than adding
+// that would grow for near-axis-parallel rays.  An axis along which the ray does not move
+// (|d| < 2^-80, or 0) takes the reciprocal 2^80; every offset is widened by 2^-40 in space
+// besides, so such a slab lets pass exactly the boxes that hold the ray's coordinate, faces
+// included.  (With 1 / 0 both slab values came out NaN and the axis let every box
+// pass: a bounce straight along the normal of an axis-aligned face, one sample in 2^24,
+// walked a whole wall of the corner, 12 ms for one ray.)  The relative widening multiplies (t x (1 -+ 4e-6)) rather than adding
 // a multiple of |t|, so infinite slab values stay infinite instead of turning NaN,
 // and an inverted box (lo = +1e30, hi = -1e30: every near plane ahead of every far
 // plane) is always missed.
@@ -286,14 +289,17 @@ constexpr uint32_t FAR_X = 48u, FAR_Y = 80u, FAR_Z = 112u;
 
 __device__ __forceinline__ Box4Ray box4_setup(V3 o, V3 d) {
     Box4Ray r;
-    // hardware reciprocals (within 1 ulp, +-inf for a zero component like 1 / d)
-    r.ix = __builtin_amdgcn_rcpf(d.x);
-    r.iy = __builtin_amdgcn_rcpf(d.y);
-    r.iz = __builtin_amdgcn_rcpf(d.z);
+    // hardware reciprocals (within 1 ulp) of components kept away from 0
+    r.ix = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(d.x), 0x1p-80f), d.x));
+    r.iy = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(d.y), 0x1p-80f), d.y));
+    r.iz = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(d.z), 0x1p-80f), d.z));
     // |fl(o rcp(d)) - o / d| <= (2^-23 + 2^-24) |fl(o rcp(d))| (1 + 2^-23); 2^-21 also
-    // covers the rounding of the two sums below
+    // covers the rounding of the two sums below; 2^-40 / |d|: the faces of an axis along
+    // which the ray does not move
     const float px = o.x * r.ix, py = o.y * r.iy, pz = o.z * r.iz;
-    const float ex = fabsf(px) * 0x1p-21f, ey = fabsf(py) * 0x1p-21f, ez = fabsf(pz) * 0x1p-21f;
+    const float ex = fmaf(fabsf(r.ix), 0x1p-40f, fabsf(px) * 0x1p-21f);
+    const float ey = fmaf(fabsf(r.iy), 0x1p-40f, fabsf(py) * 0x1p-21f);
+    const float ez = fmaf(fabsf(r.iz), 0x1p-40f, fabsf(pz) * 0x1p-21f);
     r.anx = -px - ex;
     r.any = -py - ey;
     r.anz = -pz - ez;
