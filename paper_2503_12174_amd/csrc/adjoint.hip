@@ -436,7 +436,7 @@ __global__ void __launch_bounds__(BLOCK) k_adj_shade(Queues q, AdjQueues aq, int
                     const double pdf = bounce_pdf(r.brdf, s.n, s.wo, wi, s.rough);
                     if (ci > 0.0 && pdf > 0.0) {
                         const Brdf f = brdf_eval<true>(r.brdf, s.n, s.wo, wi, s.alb, s.rough, s.spec);
-                        const D3 nbeta = beta * (f.f * (ci / pdf));
+                        const D3 nbeta = beta * (f.f * (ci * frcp(pdf)));
                         cont = true;
                         no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
                         nd = PathD{wi.x, wi.y, wi.z, g, 0u};
@@ -1053,15 +1053,15 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay(Queues q, AdjQueues aq, in
                 const double pdf = bounce_pdf(r.brdf, s.n, s.wo, wi, s.rough);
                 if (ci > 0.0 && pdf > 0.0) {
                     const Brdf f = brdf_eval<TEX>(r.brdf, s.n, s.wo, wi, s.alb, s.rough, s.spec);
-                    const D3 ndb = db * (f.f * (ci / pdf));
+                    const D3 ndb = db * (f.f * (ci * frcp(pdf)));
                     cont = true;
                     no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
                     nd = PathD{wi.x, wi.y, wi.z, g, (uint32_t)lit};
                     nb = make_float4((float)ndb.x, (float)ndb.y, (float)ndb.z, 0.0f);
                     nrl = rl;
                     if constexpr (TEX) {   // d/df of beta f cos/pdf R_{k+1}: L_r / f
-                        const D3 t = d3(f.f.x > 0.0 ? rl.x / f.f.x : 0.0, f.f.y > 0.0 ? rl.y / f.f.y : 0.0,
-                                        f.f.z > 0.0 ? rl.z / f.f.z : 0.0);
+                        const D3 t = d3(f.f.x > 0.0 ? rl.x * frcp(f.f.x) : 0.0, f.f.y > 0.0 ? rl.y * frcp(f.f.y) : 0.0,
+                                        f.f.z > 0.0 ? rl.z * frcp(f.f.z) : 0.0);
                         const double sum = t.x + t.y + t.z;
                         ga = ga + t * (1.0 / PI);
                         gr += sum * f.ds_dr;
@@ -1227,7 +1227,7 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq
                     const BrdfX f = brdf_x<true>(r.brdf, s.n, sh.ns, s.wo, we, s.alb, s.rough, s.spec, sh.metal);
                     const D3 Le = d3(r.env[0], r.env[1], r.env[2]);
                     const D3 C = db * f.f * Le * PI;
-                    if (f.c > 0.0) term(f, db * Le * (PI / f.c));
+                    if (f.c > 0.0) term(f, db * Le * (PI * frcp(f.c)));
                     rl.x -= (float)C.x;
                     rl.y -= (float)C.y;
                     rl.z -= (float)C.z;
@@ -1240,15 +1240,15 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq
                 const double pdf = bounce_pdf(r.brdf, sh.ns, s.wo, wi, s.rough);
                 if (ci > 0.0 && pdf > 0.0) {
                     const BrdfX f = brdf_x<TEX>(r.brdf, s.n, sh.ns, s.wo, wi, s.alb, s.rough, s.spec, sh.metal);
-                    const D3 ndb = db * (f.f * (f.c / pdf));
+                    const D3 ndb = db * (f.f * (f.c * frcp(pdf)));
                     cont = true;
                     no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
                     nd = PathD{wi.x, wi.y, wi.z, g, (uint32_t)lit};
                     nb = make_float4((float)ndb.x, (float)ndb.y, (float)ndb.z, 0.0f);
                     nrl = rl;
                     if constexpr (TEX)
-                        term(f, d3(f.f.x > 0.0 ? rl.x / (f.f.x * f.c) : 0.0, f.f.y > 0.0 ? rl.y / (f.f.y * f.c) : 0.0,
-                                   f.f.z > 0.0 ? rl.z / (f.f.z * f.c) : 0.0));
+                        term(f, d3(f.f.x > 0.0 ? rl.x * frcp(f.f.x * f.c) : 0.0, f.f.y > 0.0 ? rl.y * frcp(f.f.y * f.c) : 0.0,
+                                   f.f.z > 0.0 ? rl.z * frcp(f.f.z * f.c) : 0.0));
                 }
             }
             if constexpr (TEX) {

@@ -46,14 +46,14 @@ __device__ __forceinline__ CamSurf cam_surface(const ReqDesc& r, const CamFrozen
     const D3 v0 = to_d(f0), e1 = to_d(f1) - v0, e2 = to_d(f2) - v0, p = x - v0;
     // barycentrics of x in the plane: normal equations of p = b1 e1 + b2 e2
     const double a11 = dot(e1, e1), a12 = dot(e1, e2), a22 = dot(e2, e2), r1 = dot(p, e1), r2 = dot(p, e2);
-    const double inv = 1.0 / (a11 * a22 - a12 * a12);
+    const double inv = frcp(fma(a11, a22, -(a12 * a12)));
     const double b1 = (a22 * r1 - a12 * r2) * inv, b2 = (a11 * r2 - a12 * r1) * inv, b0 = 1.0 - b1 - b2;
     s.x = x;
     s.n = z.n;
     const float4 ua = r.tri_uv[2 * z.leaf], ub = r.tri_uv[2 * z.leaf + 1];
-    s.u = b0 * ua.x + b1 * ua.z + b2 * ub.x;
-    s.v = b0 * ua.y + b1 * ua.w + b2 * ub.y;
-    s.tb = bilinear(s.u * r.tw - 0.5, s.v * r.th - 0.5, r.tw, r.th);
+    s.u = fma(b0, (double)ua.x, fma(b1, (double)ua.z, b2 * ub.x));
+    s.v = fma(b0, (double)ua.y, fma(b1, (double)ua.w, b2 * ub.y));
+    s.tb = bilinear(fma(s.u, (double)r.tw, -0.5), fma(s.v, (double)r.th, -0.5), r.tw, r.th);
     const D4 t4 = fetch4(r.tex4, s.tb);
     CamSurf c;
     c.alb = d3(t4.x, t4.y, t4.z);
@@ -70,17 +70,17 @@ __device__ __forceinline__ CamSurf cam_surface(const ReqDesc& r, const CamFrozen
     c.E = d3(0., 0., 0.);
     c.g = 0.0;
     if (z.prj) {   // the projector term in full, the frustum and cosine decisions held
-        const D3 xp = mat3(r.prj_R, x) + d3(r.prj_t[0], r.prj_t[1], r.prj_t[2]);
-        const double iz = 1.0 / xp.z;
+        const D3 xp = fmat3(r.prj_R, x, d3(r.prj_t[0], r.prj_t[1], r.prj_t[2]));
+        const double iz = frcp(xp.z);
         const double pu = (r.prj_K[0] * xp.x + r.prj_K[1] * xp.y + r.prj_K[2] * xp.z) * iz;
         const double pv = (r.prj_K[3] * xp.x + r.prj_K[4] * xp.y + r.prj_K[5] * xp.z) * iz;
         const D3 tow = d3(r.prj_o[0], r.prj_o[1], r.prj_o[2]) - x;
-        const double dist = sqrt(dot(tow, tow));
-        c.wp = tow * (1.0 / dist);
-        const double ca = xp.z / sqrt(dot(xp, xp));
+        const double id = frsqrt(dot(tow, tow));
+        c.wp = tow * id;
+        const double l2 = dot(xp, xp), ica = l2 * frsqrt(l2) * iz;   // 1 / cos alpha
         const D4 E = fetch4(r.Ep, bilinear(pu - 0.5, pv - 0.5, r.Wp, r.Hp));
         c.E = d3(E.x, E.y, E.z);
-        c.g = 1.0 / (ca * ca * ca * dist * dist);
+        c.g = ica * ica * ica * (id * id);
     }
     return c;
 }
@@ -130,15 +130,15 @@ __global__ void __launch_bounds__(CAM_TB) k_cam_grad(Queues q, AdjQueues aq, Req
             const int leaf = rec_leaf(r, rec);
             const D3 delta = d3(dl.x, dl.y, dl.z);
             // the forward's camera ray (the same jittered pixel position as camera_dir)
-            const uint32_t pixel = g / (uint32_t)r.spp, si = g - pixel * (uint32_t)r.spp;
+            const uint32_t pixel = udiv(g, r.inv_spp), si = g - pixel * (uint32_t)r.spp;
+            const uint32_t iy = udiv(pixel, r.inv_wc), ix = pixel - iy * (uint32_t)r.Wc;
             const U4 u = philox4x32_10(pixel, si + r.sample_offset, 0u, 0u, r.seed_lo, r.seed_hi);
-            const D3 m = mat3(r.cam_Ki, d3((double)(pixel % (uint32_t)r.Wc) + u24(u.x),
-                                           (double)(pixel / (uint32_t)r.Wc) + u24(u.y), 1.0));
+            const D3 m = mat3(r.cam_Ki, d3((double)ix + u24(u.x), (double)iy + u24(u.y), 1.0));
             const D3 qv = d3(r.cam_R[0] * m.x + r.cam_R[3] * m.y + r.cam_R[6] * m.z,
                              r.cam_R[1] * m.x + r.cam_R[4] * m.y + r.cam_R[7] * m.z,
                              r.cam_R[2] * m.x + r.cam_R[5] * m.y + r.cam_R[8] * m.z);
-            const double ql = sqrt(dot(qv, qv));
-            const D3 dir = qv * (1.0 / ql);
+            const double iql = rcp_rn(sqrt_rn(dot(qv, qv)));
+            const D3 dir = qv * iql;
             const D3 o = d3(r.cam_o[0], r.cam_o[1], r.cam_o[2]);
             const Surf s0 = surface(r, leaf, o, dir);
             CamFrozen z;
@@ -152,7 +152,7 @@ __global__ void __launch_bounds__(CAM_TB) k_cam_grad(Queues q, AdjQueues aq, Req
             if (r.env_on) {
                 const U4 x = vertex_rng(r, g, 2u);
                 z.we = sample_cosine(ns0, u24(x.x), u24(x.y));
-                z.Se = d3(r.env[0], r.env[1], r.env[2]) * (PI / dot(ns0, z.we));
+                z.Se = d3(r.env[0], r.env[1], r.env[2]) * (PI * frcp(dot(ns0, z.we)));
             }
             z.bounced = false;
             z.wi = d3(0., 0., 0.);
@@ -187,23 +187,24 @@ __global__ void __launch_bounds__(CAM_TB) k_cam_grad(Queues q, AdjQueues aq, Req
             // and far above the FP64 rounding of the terms (~1e-8 relative in the slope)
             const double tau = dot(s0.x - o, dir);
             const double hx = 1e-8 * tau, hw = 1e-7;
+            const double ihx = frcp(hx);
             const double phi0 = cam_phi(r, z, c0, s0.wo, delta);
             D3 gx = d3(0., 0., 0.), gw = d3(0., 0., 0.);
             const D3 ta[2] = {t1, t2};
             for (int j = 0; j < 2; ++j) {
                 const double fp = cam_phi(r, z, cam_surface(r, z, s0.x + ta[j] * hx), s0.wo, delta);
-                gx = gx + ta[j] * ((fp - phi0) / hx);
+                gx = gx + ta[j] * ((fp - phi0) * ihx);
             }
             const D3 w1 = local_to_world(s0.wo, 1.0, 0.0, 0.0), w2 = local_to_world(s0.wo, 0.0, 1.0, 0.0);
             const D3 wa[2] = {w1, w2};
             for (int j = 0; j < 2; ++j) {   // same point: its lookups reused
                 const double fp = cam_phi(r, z, c0, normalize(s0.wo + wa[j] * hw), delta);
-                gw = gw + wa[j] * ((fp - phi0) / hw);
+                gw = gw + wa[j] * ((fp - phi0) * 1e7);
             }
             // chain to (R, t): a = P^T gx, b = tau a - gw, c = (I - d d^T) b / |q|
             const D3 a = gx - s0.n * (dot(dir, gx) / dot(s0.n, dir));
             const D3 b = a * tau - gw;
-            const D3 c = (b - dir * dot(dir, b)) * (1.0 / ql);
+            const D3 c = (b - dir * dot(dir, b)) * iql;
             const double mi[3] = {m.x, m.y, m.z}, ti[3] = {r.cam_t[0], r.cam_t[1], r.cam_t[2]};
             const double cj[3] = {c.x, c.y, c.z}, aj[3] = {a.x, a.y, a.z};
 #pragma unroll

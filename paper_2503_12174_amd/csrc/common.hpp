@@ -47,16 +47,88 @@ template <class T> __device__ __forceinline__ Vec3<T> cross(Vec3<T> a, Vec3<T> b
     return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
 }
 __device__ __forceinline__ V3 normalize(V3 a) { return a * (1.0f / sqrtf(dot(a, a))); }
-__device__ __forceinline__ D3 normalize(D3 a) { return a * (1.0 / sqrt(dot(a, a))); }
 __device__ __forceinline__ V3 xyz(float4 a) { return v3(a.x, a.y, a.z); }
 __device__ __forceinline__ float4 f4(V3 a, float w) { return make_float4(a.x, a.y, a.z, w); }
 __device__ __forceinline__ V3 to_f(D3 a) { return v3((float)a.x, (float)a.y, (float)a.z); }
 __device__ __forceinline__ D3 to_d(V3 a) { return d3(a.x, a.y, a.z); }
 __device__ __forceinline__ float comp(V3 a, int k) { return k == 0 ? a.x : (k == 1 ? a.y : a.z); }
+
 // 3x3 row-major times vector
 __device__ __forceinline__ D3 mat3(const double* m, D3 a) {
     return d3(m[0] * a.x + m[1] * a.y + m[2] * a.z, m[3] * a.x + m[4] * a.y + m[5] * a.z,
               m[6] * a.x + m[7] * a.y + m[8] * a.z);
+}
+
+// ---------------------------------------------------------------------------
+// FP64 arithmetic of the shading, whose kernels are bound by FP64 issue.  Two kinds:
+//
+// What the next vertex of a path depends on -- camera ray, hit point and normal, roughness
+// and normal-map lookup, sampled direction -- is rounded operation by operation, because a
+// path through white-noise roughness or normal maps multiplies any difference by several
+// hundred per bounce: after five bounces the last bit decides where it goes.  Quotients and
+// roots there are the correctly rounded ones, without the scaling and special cases of the
+// general sequences (div_rn, sqrt_rn: arguments of ordinary size).
+//
+// Everything else -- reflectance and its derivatives, densities, throughput, the projector's
+// geometry -- takes one FMA for a product that is added, and reciprocals and roots from the
+// hardware's estimate (~2^-23) with two Newton steps, within 1-2 ulp (f... functions).  The
+// build contracts nothing by itself (the FP32 triangle test relies on that), so every kernel
+// forms the same value.
+// 50k-triangle corner, 256^2 x 64 spp: camera-vertex shading 214 -> 194 us, record replay
+// 358 -> 326 us (the deeper vertices' shading is bound by its memory traffic); camera-pose
+// terms at 16 spp 258 -> 148 us.
+// ---------------------------------------------------------------------------
+// Newton steps r += r (1 - x r) from the estimate
+__device__ __forceinline__ double frcp(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+// the residual of the quotient added once more: correctly rounded
+__device__ __forceinline__ double div_rn(double a, double b) {
+    const double r = frcp(b), q = a * r;
+    return fma(fma(-b, q, a), r, q);
+}
+__device__ __forceinline__ double rcp_rn(double b) {
+    const double r = frcp(b);
+    return fma(fma(-b, r, 1.0), r, r);
+}
+// sqrt(x), x >= 0 (Goldschmidt's iteration, two residual corrections)
+__device__ __forceinline__ double sqrt_rn(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    g = fma(fma(-g, g, x), h, g);
+    g = fma(fma(-g, g, x), h, g);
+    return x > 0.0 ? g : 0.0;
+}
+__device__ __forceinline__ D3 normalize(D3 a) { return a * rcp_rn(sqrt_rn(dot(a, a))); }
+
+// 1 / sqrt(x), x > 0: Newton steps y += y (1 - x y^2) / 2
+__device__ __forceinline__ double frsqrt(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    const double h = 0.5 * x;
+    y = fma(fma(-h * y, y, 0.5), y, y);
+    return fma(fma(-h * y, y, 0.5), y, y);
+}
+// sqrt(x), x >= 0 (sqrt(0) = 1e-140)
+__device__ __forceinline__ double fsqrt(double x) {
+    const double z = fmax(x, 1e-280);
+    const double y = frsqrt(z), g = z * y;
+    return fma(fma(-g, g, z), 0.5 * y, g);
+}
+__device__ __forceinline__ double fdot(D3 a, D3 b) { return fma(a.x, b.x, fma(a.y, b.y, a.z * b.z)); }
+__device__ __forceinline__ D3 fcross(D3 a, D3 b) {
+    return {fma(a.y, b.z, -(a.z * b.y)), fma(a.z, b.x, -(a.x * b.z)), fma(a.x, b.y, -(a.y * b.x))};
+}
+// a s + b
+__device__ __forceinline__ D3 fmadd(D3 a, double s, D3 b) { return {fma(a.x, s, b.x), fma(a.y, s, b.y), fma(a.z, s, b.z)}; }
+// m a + c
+__device__ __forceinline__ D3 fmat3(const double* m, D3 a, D3 c) {
+    return d3(fma(m[0], a.x, fma(m[1], a.y, fma(m[2], a.z, c.x))), fma(m[3], a.x, fma(m[4], a.y, fma(m[5], a.z, c.y))),
+              fma(m[6], a.x, fma(m[7], a.y, fma(m[8], a.z, c.z))));
 }
 
 // ---------------------------------------------------------------------------
@@ -69,8 +141,10 @@ __device__ __forceinline__ U4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c
                                             uint32_t k1) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        const uint32_t lo0 = 0xD2511F53u * c0, hi0 = __umulhi(0xD2511F53u, c0);
-        const uint32_t lo1 = 0xCD9E8D57u * c2, hi1 = __umulhi(0xCD9E8D57u, c2);
+        // (one 32 x 32 -> 64 multiply each: these run at a quarter of the rate)
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
+        const uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
+        const uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
         const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
         c0 = n0;
         c1 = lo1;
@@ -169,6 +243,7 @@ struct ReqDesc {
     int32_t env_on;
     // sampling
     int32_t spp, max_depth;
+    double inv_spp, inv_wc;  // 1 / spp, 1 / Wc (udiv)
     uint32_t seed_lo, seed_hi, sample_offset;
     // responses
     float prf_gain, crf_gain;
@@ -210,6 +285,10 @@ constexpr uint32_t REC_END = 1u << 29;
 constexpr uint32_t REC_ENV = 1u << 30;
 constexpr uint32_t REC_PRJ = 1u << 31;
 
+// floor(x / n), inv = 1 / n: x + 1/2 lies at least 1 / (2 n) from a multiple of n, far more
+// than the rounding of the product for x < 2^32 and n <= 65536
+__device__ __forceinline__ uint32_t udiv(uint32_t x, double inv) { return (uint32_t)(((double)x + 0.5) * inv); }
+
 __device__ __forceinline__ float scalar(const ReqDesc& r, int k) { return r.dscal ? r.dscal[k] : r.scal[k]; }
 __device__ __forceinline__ float clip_threshold(const ReqDesc& r) {
     float w0 = scalar(r, 15), w1 = scalar(r, 16), w2 = scalar(r, 17);
@@ -238,29 +317,31 @@ __device__ __forceinline__ double ggx_alpha(double r) { return fmax(r * r, ALPHA
 template <bool GRAD>
 __device__ __forceinline__ Brdf brdf_eval(int kind, D3 n, D3 wo, D3 wi, D3 alb, double r, double sp) {
     Brdf b{d3(0., 0., 0.), 0., 0.};
-    const double ci = dot(n, wi), co = dot(n, wo);
+    const double ci = fdot(n, wi), co = fdot(n, wo);
     if (ci <= 0.0 || co <= 0.0) return b;
     b.f = alb * (1.0 / PI);
     if (kind == 0) return b;
     const D3 v = wi + wo;
-    const double vv = dot(v, v), nv = dot(n, v);
-    const D3 nxv = cross(n, v);
-    const double c2v = nv * nv, s2v = dot(nxv, nxv);
+    const double vv = fdot(v, v), nv = fdot(n, v);
+    const D3 nxv = fcross(n, v);
+    const double c2v = nv * nv;
     const double a = ggx_alpha(r);
-    const double a2 = a * a;
-    const double kv = a2 * c2v + s2v;
-    const double qi = sqrt(a2 + (1.0 - a2) * ci * ci), qo = sqrt(a2 + (1.0 - a2) * co * co);
+    const double a2 = a * a, b2 = 1.0 - a2;
+    const double kv = fma(a2, c2v, fdot(nxv, nxv));
+    const double qi = fsqrt(fma(b2 * ci, ci, a2)), qo = fsqrt(fma(b2 * co, co, a2));
     const double F0 = 0.08 * sp;
-    const double m = 1.0 - 0.5 * sqrt(vv);
-    const double m5 = m * m * m * m * m;
-    const double F = F0 + (1.0 - F0) * m5;
-    const double DGw = a2 * vv * vv / (PI * kv * kv * (ci + qi) * (co + qo));   // D G / (4 ci co)
+    const double m = fma(-0.5, fsqrt(vv), 1.0), m2 = m * m;
+    const double m5 = m2 * m2 * m;
+    const double F = fma(1.0 - F0, m5, F0);
+    const double gi = ci + qi, go = co + qo;
+    const double DGw = a2 * vv * vv * frcp(PI * kv * kv * gi * go);   // D G / (4 ci co)
     const double s = F * DGw;
     b.f = b.f + d3(s, s, s);
     if (GRAD) {
         // d ln D / da = (2 / a)(1 - 2 a^2 cos^2 / k);  d ln G1 / da = -a (1 - c^2) / (q (c + q))
-        const double dlnD = 2.0 / a * (1.0 - 2.0 * a2 * c2v / kv);
-        const double dlnG = -a * ((1.0 - ci * ci) / (qi * (ci + qi)) + (1.0 - co * co) / (qo * (co + qo)));
+        const double dlnD = 2.0 * frcp(a) * fma(-2.0 * a2 * c2v, frcp(kv), 1.0);
+        const double di = qi * gi, dd = qo * go;
+        const double dlnG = -a * fma(fma(-ci, ci, 1.0), dd, fma(-co, co, 1.0) * di) * frcp(di * dd);
         const double da_dr = (r * r > ALPHA_MIN) ? 2.0 * r : 0.0;
         b.ds_dr = s * (dlnD + dlnG) * da_dr;
         b.ds_dsp = 0.08 * (1.0 - m5) * DGw;
@@ -289,12 +370,12 @@ __device__ __forceinline__ BrdfX brdf_x(int kind, D3 ng, D3 ns, D3 wo, D3 wi, D3
                                         double mu) {
     BrdfX b;
     b.f = d3(0., 0., 0.);
-    b.c = dot(ns, wi);
+    b.c = fdot(ns, wi);
     b.dfa = b.dfs = 0.0;
     b.dfr = b.dfm = d3(0., 0., 0.);
     b.dn[0] = b.dn[1] = b.dn[2] = d3(0., 0., 0.);
-    const double ci = b.c, co = dot(ns, wo);
-    if (ci <= 0.0 || co <= 0.0 || dot(ng, wi) <= 0.0) return b;
+    const double ci = b.c, co = fdot(ns, wo);
+    if (ci <= 0.0 || co <= 0.0 || fdot(ng, wi) <= 0.0) return b;
     if (kind == 0) {
         b.f = alb * (1.0 / PI);
         if (GRAD) {
@@ -306,26 +387,29 @@ __device__ __forceinline__ BrdfX brdf_x(int kind, D3 ng, D3 ns, D3 wo, D3 wi, D3
         return b;
     }
     const D3 v = wi + wo;
-    const double vv = dot(v, v), nv = dot(ns, v);
-    const D3 nxv = cross(ns, v);
-    const double c2v = nv * nv, s2v = dot(nxv, nxv);
+    const double vv = fdot(v, v), nv = fdot(ns, v);
+    const D3 nxv = fcross(ns, v);
+    const double c2v = nv * nv;
     const double a = ggx_alpha(r);
-    const double a2 = a * a;
-    const double kv = a2 * c2v + s2v;
-    const double qi = sqrt(a2 + (1.0 - a2) * ci * ci), qo = sqrt(a2 + (1.0 - a2) * co * co);
-    const double m = 1.0 - 0.5 * sqrt(vv);
-    const double m5 = m * m * m * m * m;
-    const double DGw = a2 * vv * vv / (PI * kv * kv * (ci + qi) * (co + qo));   // D G / (4 ci co)
-    const double kd = 1.0 - mu;
-    const D3 F0 = d3(kd * (0.08 * sp) + mu * alb.x, kd * (0.08 * sp) + mu * alb.y, kd * (0.08 * sp) + mu * alb.z);
-    const D3 F = d3(F0.x + (1.0 - F0.x) * m5, F0.y + (1.0 - F0.y) * m5, F0.z + (1.0 - F0.z) * m5);
-    b.f = alb * (kd / PI) + F * DGw;
+    const double a2 = a * a, b2 = 1.0 - a2;
+    const double kv = fma(a2, c2v, fdot(nxv, nxv));
+    const double qi = fsqrt(fma(b2 * ci, ci, a2)), qo = fsqrt(fma(b2 * co, co, a2));
+    const double m = fma(-0.5, fsqrt(vv), 1.0), m2 = m * m;
+    const double m5 = m2 * m2 * m;
+    const double gi = ci + qi, go = co + qo;
+    const double DGw = a2 * vv * vv * frcp(PI * kv * kv * gi * go);   // D G / (4 ci co)
+    const double kd = 1.0 - mu, f0 = kd * (0.08 * sp);
+    const D3 F0 = d3(fma(mu, alb.x, f0), fma(mu, alb.y, f0), fma(mu, alb.z, f0));
+    const D3 F = d3(fma(1.0 - F0.x, m5, F0.x), fma(1.0 - F0.y, m5, F0.y), fma(1.0 - F0.z, m5, F0.z));
+    b.f = fmadd(F, DGw, alb * (kd * (1.0 / PI)));
     if (GRAD) {
-        const double dlnD = 2.0 / a * (1.0 - 2.0 * a2 * c2v / kv);
-        const double dlnG = -a * ((1.0 - ci * ci) / (qi * (ci + qi)) + (1.0 - co * co) / (qo * (co + qo)));
+        const double ikv = frcp(kv);
+        const double dlnD = 2.0 * frcp(a) * fma(-2.0 * a2 * c2v, ikv, 1.0);
+        const double di = qi * gi, dd = qo * go;
+        const double dlnG = -a * fma(fma(-ci, ci, 1.0), dd, fma(-co, co, 1.0) * di) * frcp(di * dd);
         const double da_dr = (r * r > ALPHA_MIN) ? 2.0 * r : 0.0;
         const double dDGw_dr = DGw * (dlnD + dlnG) * da_dr;
-        b.dfa = kd / PI + mu * (1.0 - m5) * DGw;
+        b.dfa = fma(mu * (1.0 - m5), DGw, kd * (1.0 / PI));
         b.dfr = F * dDGw_dr;
         b.dfs = kd * 0.08 * (1.0 - m5) * DGw;
         b.dfm = alb * (-1.0 / PI) + (alb - d3(0.08 * sp, 0.08 * sp, 0.08 * sp)) * ((1.0 - m5) * DGw);
@@ -333,19 +417,20 @@ __device__ __forceinline__ BrdfX brdf_x(int kind, D3 ng, D3 ns, D3 wo, D3 wi, D3
         // c_h = ns.h (h = v / |v|): dD/dc_h = -4 a^2 c_h (a^2 - 1) / (pi k^3), k = kv / vv,
         // dG1/dc = 2 a^2 / (q (c + q)^2), and dS/dns = (dD/dc_h h G1i G1o + D dG1i wi G1o
         // + D G1i dG1o wo) / (4 co) - S / co wo
-        const double iv = 1.0 / sqrt(vv);
+        const double iv = frsqrt(vv);
         const double ch = nv * iv;
-        const double k = kv / vv;
-        const double D = a2 / (PI * k * k);
-        const double G1i = 2.0 * ci / (ci + qi), G1o = 2.0 * co / (co + qo);
-        const double dD = -4.0 * a2 * ch * (a2 - 1.0) / (PI * k * k * k);
-        const double dG1i = 2.0 * a2 / (qi * (ci + qi) * (ci + qi)), dG1o = 2.0 * a2 / (qo * (co + qo) * (co + qo));
+        const double ik = vv * ikv;                     // 1 / k
+        const double D = a2 * (1.0 / PI) * ik * ik;
+        const double igi = frcp(gi), igo = frcp(go);
+        const double G1i = 2.0 * ci * igi, G1o = 2.0 * co * igo;
+        const double dD = 4.0 * ch * b2 * D * ik;
+        const double dG1i = 2.0 * a2 * igi * igi * frcp(qi), dG1o = 2.0 * a2 * igo * igo * frcp(qo);
         const double S = DGw * ci;
-        const double i4 = 1.0 / (4.0 * co);
-        const D3 dS = v * (dD * G1i * G1o * i4 * iv) + wi * (D * dG1i * G1o * i4) + wo * (D * G1i * dG1o * i4 - S / co);
-        b.dn[0] = wi * (kd * alb.x / PI) + dS * F.x;
-        b.dn[1] = wi * (kd * alb.y / PI) + dS * F.y;
-        b.dn[2] = wi * (kd * alb.z / PI) + dS * F.z;
+        const double ico = frcp(co), i4 = 0.25 * ico;
+        const D3 dS = fmadd(v, dD * G1i * G1o * i4 * iv, fmadd(wi, D * dG1i * G1o * i4, wo * fma(D * G1i * dG1o, i4, -(S * ico))));
+        b.dn[0] = fmadd(dS, F.x, wi * (kd * alb.x * (1.0 / PI)));
+        b.dn[1] = fmadd(dS, F.y, wi * (kd * alb.y * (1.0 / PI)));
+        b.dn[2] = fmadd(dS, F.z, wi * (kd * alb.z * (1.0 / PI)));
     }
     return b;
 }
@@ -353,7 +438,7 @@ __device__ __forceinline__ BrdfX brdf_x(int kind, D3 ng, D3 ns, D3 wo, D3 wi, D3
 // branchless orthonormal basis (Duff et al., JCGT 2017)
 __device__ __forceinline__ D3 local_to_world(D3 n, double x, double y, double z) {
     const double s = copysign(1.0, n.z);
-    const double a = -1.0 / (s + n.z);
+    const double a = -rcp_rn(s + n.z);
     const double b = n.x * n.y * a;
     const D3 t1 = d3(1.0 + s * n.x * n.x * a, s * b, -s * n.x);
     const D3 t2 = d3(b, s + n.y * n.y * a, -n.y);
@@ -361,29 +446,31 @@ __device__ __forceinline__ D3 local_to_world(D3 n, double x, double y, double z)
 }
 
 __device__ __forceinline__ D3 sample_cosine(D3 n, double u1, double u2) {
-    const double rr = sqrt(u1);
+    const double rr = sqrt_rn(u1);
     double sn, cs;
     sincos(2.0 * PI * u2, &sn, &cs);
-    return local_to_world(n, rr * cs, rr * sn, sqrt(1.0 - u1));
+    return local_to_world(n, rr * cs, rr * sn, sqrt_rn(1.0 - u1));
 }
 
-// GGX normal-distribution sampling (Walter et al. 2007): tan^2 theta_h = a^2 u1 / (1 - u1)
-__device__ __forceinline__ D3 sample_ggx_h(D3 n, double r, double u1, double u2) {
-    const double a = ggx_alpha(r);
-    const double t2 = a * a * u1 / (1.0 - u1);
-    const double ct = 1.0 / sqrt(1.0 + t2);
-    const double st = sqrt(t2) * ct;
-    double sn, cs;
-    sincos(2.0 * PI * u2, &sn, &cs);
-    return local_to_world(n, st * cs, st * sn, ct);
-}
-
+// Cosine lobe, or (probability P_SPEC) the GGX normal distribution (Walter et al. 2007):
+// tan^2 theta_h = a^2 u1 / (1 - u1), wo reflected about h.  The lanes of a wave draw
+// different lobes: the azimuth and the turn to world space are shared by both.
 __device__ __forceinline__ D3 sample_bounce(int kind, D3 n, D3 wo, double r, double ulobe, double u1, double u2) {
-    if (kind == 1 && ulobe < P_SPEC) {
-        const D3 h = sample_ggx_h(n, r, u1, u2);
-        return h * (2.0 * dot(wo, h)) - wo;
+    const bool spec = kind == 1 && ulobe < P_SPEC;
+    double st, ct;
+    if (spec) {
+        const double a = ggx_alpha(r);
+        const double t2 = div_rn(a * a * u1, 1.0 - u1);
+        ct = rcp_rn(sqrt_rn(1.0 + t2));
+        st = sqrt_rn(t2) * ct;
+    } else {
+        st = sqrt_rn(u1);
+        ct = sqrt_rn(1.0 - u1);
     }
-    return sample_cosine(n, u1, u2);
+    double sn, cs;
+    sincos(2.0 * PI * u2, &sn, &cs);
+    const D3 h = local_to_world(n, st * cs, st * sn, ct);
+    return spec ? h * (2.0 * dot(wo, h)) - wo : h;
 }
 
 // density of sample_bounce (solid angle); the microfacet normal that produced wi is
@@ -391,19 +478,19 @@ __device__ __forceinline__ D3 sample_bounce(int kind, D3 n, D3 wo, double r, dou
 // (GGX part: D(h) |n.h| / (4 |wo.h|) = a^2 vv^2 |n.v| / (4 pi kv^2 |wo.v|), v = wi + wo as
 // in brdf_eval)
 __device__ __forceinline__ double bounce_pdf(int kind, D3 n, D3 wo, D3 wi, double r) {
-    const double ci = dot(n, wi);
+    const double ci = fdot(n, wi);
     const double pd = ci > 0.0 ? ci * (1.0 / PI) : 0.0;
     if (kind == 0) return pd;
     const D3 v = wi + wo;
-    const double nv = fabs(dot(n, v)), ov = fabs(dot(wo, v));
+    const double nv = fabs(fdot(n, v)), ov = fabs(fdot(wo, v));
     double ps = 0.0;
     if (nv > 0.0 && ov > 0.0) {
-        const D3 nxv = cross(n, v);
-        const double vv = dot(v, v), a = ggx_alpha(r), a2 = a * a;
-        const double kv = a2 * nv * nv + dot(nxv, nxv);
-        ps = a2 * vv * vv * nv / (4.0 * PI * kv * kv * ov);
+        const D3 nxv = fcross(n, v);
+        const double vv = fdot(v, v), a = ggx_alpha(r), a2 = a * a;
+        const double kv = fma(a2, nv * nv, fdot(nxv, nxv));
+        ps = a2 * vv * vv * nv * frcp(4.0 * PI * kv * kv * ov);
     }
-    return (1.0 - P_SPEC) * pd + P_SPEC * ps;
+    return fma(1.0 - P_SPEC, pd, P_SPEC * ps);
 }
 
 // ---------------------------------------------------------------------------
@@ -452,7 +539,17 @@ __device__ __forceinline__ Bilin bilinear(double x, double y, int W, int H) {
 struct D4 {
     double x, y, z, w;
 };
+// rgb of a map with FMAs; w (the roughness, which directs paths) rounded step by step
 __device__ __forceinline__ D4 fetch4(const float4* __restrict__ t, const Bilin& b) {
+    const float4 p = t[b.i00], q = t[b.i10], s = t[b.i01], u = t[b.i11];
+    auto mix = [&](float k00, float k10, float k01, float k11) {
+        return fma(b.w00, (double)k00, fma(b.w10, (double)k10, fma(b.w01, (double)k01, b.w11 * k11)));
+    };
+    return D4{mix(p.x, q.x, s.x, u.x), mix(p.y, q.y, s.y, u.y), mix(p.z, q.z, s.z, u.z),
+              b.w00 * p.w + b.w10 * q.w + b.w01 * s.w + b.w11 * u.w};
+}
+// the normal map and metallic: every channel rounded step by step (the normal directs paths)
+__device__ __forceinline__ D4 fetch4_rn(const float4* __restrict__ t, const Bilin& b) {
     const float4 p = t[b.i00], q = t[b.i10], s = t[b.i01], u = t[b.i11];
     return D4{b.w00 * p.x + b.w10 * q.x + b.w01 * s.x + b.w11 * u.x,
               b.w00 * p.y + b.w10 * q.y + b.w01 * s.y + b.w11 * u.y,
@@ -460,7 +557,7 @@ __device__ __forceinline__ D4 fetch4(const float4* __restrict__ t, const Bilin& 
               b.w00 * p.w + b.w10 * q.w + b.w01 * s.w + b.w11 * u.w};
 }
 __device__ __forceinline__ double fetch1(const float* __restrict__ t, const Bilin& b) {
-    return b.w00 * t[b.i00] + b.w10 * t[b.i10] + b.w01 * t[b.i01] + b.w11 * t[b.i11];
+    return fma(b.w00, (double)t[b.i00], fma(b.w10, (double)t[b.i10], fma(b.w01, (double)t[b.i01], b.w11 * t[b.i11])));
 }
 
 }  // namespace dpcs

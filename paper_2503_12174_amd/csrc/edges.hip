@@ -418,6 +418,7 @@ dpcs_status camera_edge_term(dpcs_context ctx, dpcs_scene sc, const ReqDesc& r, 
             re.seed_hi = a.seed_hi;
             re.sample_offset = 0;
             re.spp = 1;
+            re.inv_spp = 1.0;
             re.g_base = (uint32_t)k0;
             re.sid_base = side ? m : 0u;
             re.rec = nullptr;

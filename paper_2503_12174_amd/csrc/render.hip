@@ -146,7 +146,7 @@ __global__ void __launch_bounds__(TB) TRAVERSAL_OCCUPANCY k_trace(Queues q, int 
 // camera rays generated here as in k_trace (throughput 1, the sample's radiance started
 // at zero here)
 template <bool UNI, bool EXT, bool CAM = false>
-__global__ void __launch_bounds__(BLOCK) k_shade(Queues q, int cur, int depth, ReqDesc uni,
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EXT || !UNI ? 4 : 5))) k_shade(Queues q, int cur, int depth, ReqDesc uni,
                                                  const ReqDesc* __restrict__ table) {
     const int nxt = cur ^ 1;
     const uint32_t n = q.cnt[cur];
@@ -159,7 +159,11 @@ __global__ void __launch_bounds__(BLOCK) k_shade(Queues q, int cur, int depth, R
         bool cont = false, shp = false, she = false;
         PathO no{};
         PathD nd{};
-        float4 nb = {}, po = {}, pd = {}, pc = {}, eo = {}, ed = {}, ec = {};
+        float4 nb = {};
+        // shadow rays: the origin, slot, triangle left and sample are common to both lights
+        V3 so = {}, pw = {}, pc = {}, ew = {}, ec = {};
+        int slot = 0, prim = -1;
+        uint32_t sample = 0u;
         float ptmax = 0.0f;
         if (i < n) {
             PathO o;
@@ -201,10 +205,18 @@ __global__ void __launch_bounds__(BLOCK) k_shade(Queues q, int cur, int depth, R
                 Surf s = surface_geo(r, leaf, d3(o.x, o.y, o.z), d3(dd.x, dd.y, dd.z));
                 ProjNee p;
                 const bool prj = projector_nee(r, s, p);
-                D4 E{};
-                if (prj) E = fetch4(r.Ep, p.pb);
+                D3 Eg = d3(0., 0., 0.);   // E_p times the geometry factor
+                if (prj) {
+                    const D4 E = fetch4(r.Ep, p.pb);
+                    Eg = d3(E.x, E.y, E.z) * (EXT ? p.g0 : p.geom);
+                    ptmax = (float)(p.dist - r.tmin);
+                }
                 surface_maps(r, s);
                 if (r.out_hits) r.out_hits[(size_t)g * r.max_depth + depth] = s.prim;
+                so = to_f(s.x);
+                slot = o.slot;
+                prim = s.prim;
+                sample = sid;
                 if (r.emission) {   // test scenes: surface emission
                     const float4 e = r.emission[leaf];
                     float4 L = q.L[sid];
@@ -220,17 +232,15 @@ __global__ void __launch_bounds__(BLOCK) k_shade(Queues q, int cur, int depth, R
                     D3 C;
                     if constexpr (EXT) {
                         const BrdfX f = brdf_x<false>(r.brdf, s.n, ns, s.wo, p.wp, s.alb, s.rough, s.spec, sh.metal);
-                        C = beta * f.f * d3(E.x, E.y, E.z) * (f.c * p.g0);
+                        C = beta * f.f * Eg * f.c;
                     } else {
                         const Brdf f = brdf_eval<false>(r.brdf, s.n, s.wo, p.wp, s.alb, s.rough, s.spec);
-                        C = beta * f.f * d3(E.x, E.y, E.z) * p.geom;
+                        C = beta * f.f * Eg;
                     }
                     if (r.rec || C.x > 0.0 || C.y > 0.0 || C.z > 0.0) {
                         shp = true;
-                        po = f4(to_f(s.x), __int_as_float(o.slot));
-                        pd = f4(to_f(p.wp), __int_as_float(s.prim));
-                        pc = f4(to_f(C), __uint_as_float(sid));
-                        ptmax = (float)(p.dist - r.tmin);
+                        pw = to_f(p.wp);
+                        pc = to_f(C);
                     }
                 }
                 if (r.env_on) {
@@ -242,9 +252,8 @@ __global__ void __launch_bounds__(BLOCK) k_shade(Queues q, int cur, int depth, R
                     const D3 C = beta * fv * d3(r.env[0], r.env[1], r.env[2]) * PI;
                     if (r.rec || C.x > 0.0 || C.y > 0.0 || C.z > 0.0) {
                         she = true;
-                        eo = f4(to_f(s.x), __int_as_float(o.slot));
-                        ed = f4(to_f(we), __int_as_float(s.prim));
-                        ec = f4(to_f(C), __uint_as_float(sid));
+                        ew = to_f(we);
+                        ec = to_f(C);
                     }
                 }
                 if (depth < r.max_depth - 1) {
@@ -256,10 +265,10 @@ __global__ void __launch_bounds__(BLOCK) k_shade(Queues q, int cur, int depth, R
                         D3 nbeta;
                         if constexpr (EXT) {
                             const BrdfX f = brdf_x<false>(r.brdf, s.n, ns, s.wo, wi, s.alb, s.rough, s.spec, sh.metal);
-                            nbeta = beta * (f.f * (f.c / pdf));
+                            nbeta = beta * (f.f * (f.c * frcp(pdf)));
                         } else {
                             const Brdf f = brdf_eval<false>(r.brdf, s.n, s.wo, wi, s.alb, s.rough, s.spec);
-                            nbeta = beta * (f.f * (ci / pdf));
+                            nbeta = beta * (f.f * (ci * frcp(pdf)));
                         }
                         cont = true;
                         no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
@@ -275,7 +284,7 @@ __global__ void __launch_bounds__(BLOCK) k_shade(Queues q, int cur, int depth, R
             }
         }
         const bool pred[3] = {cont, shp, she};
-        const int key[3] = {octant(nd.x, nd.y, nd.z), 0, octant(ed.x, ed.y, ed.z)};
+        const int key[3] = {octant(nd.x, nd.y, nd.z), 0, octant(ew.x, ew.y, ew.z)};
         uint32_t* const ctr[3] = {&q.cnt[nxt], &q.cnt[shadow_slot(cur, 0)], &q.cnt[shadow_slot(cur, 1)]};
         uint32_t at[3];
         block_append_keyed<3, 8>(pred, key, ctr, at);
@@ -286,15 +295,15 @@ __global__ void __launch_bounds__(BLOCK) k_shade(Queues q, int cur, int depth, R
             nt_st(&q.pb[nxt][jn], nb);
         }
         if (shp) {
-            nt_st(&q.so[0][jp], po);
-            nt_st(&q.sd[0][jp], pd);
-            nt_st(&q.sc[0][jp], pc);
+            nt_st(&q.so[0][jp], f4(so, __int_as_float(slot)));
+            nt_st(&q.sd[0][jp], f4(pw, __int_as_float(prim)));
+            nt_st(&q.sc[0][jp], f4(pc, __uint_as_float(sample)));
             __builtin_nontemporal_store(ptmax, &q.st[0][jp]);
         }
         if (she) {
-            nt_st(&q.so[1][je], eo);
-            nt_st(&q.sd[1][je], ed);
-            nt_st(&q.sc[1][je], ec);
+            nt_st(&q.so[1][je], f4(so, __int_as_float(slot)));
+            nt_st(&q.sd[1][je], f4(ew, __int_as_float(prim)));
+            nt_st(&q.sc[1][je], f4(ec, __uint_as_float(sample)));
             __builtin_nontemporal_store(__builtin_inff(), &q.st[1][je]);
         }
     }

@@ -287,6 +287,8 @@ bool fill_desc(dpcs_context, ReqDesc& r, const dpcs_render_params* p, dpcs_scene
     }
     r.spp = p->spp;
     r.max_depth = p->max_depth;
+    r.inv_spp = 1.0 / r.spp;
+    r.inv_wc = 1.0 / r.Wc;
     r.seed_lo = (uint32_t)p->seed;
     r.seed_hi = (uint32_t)(p->seed >> 32);
     r.sample_offset = p->sample_offset;

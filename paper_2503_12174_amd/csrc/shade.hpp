@@ -106,11 +106,10 @@ __device__ __forceinline__ int octant(double x, double y, double z) {
 
 // camera ray of global sample g (pixel = g / spp, sample = g % spp), Eq. 6 inverted
 __device__ __forceinline__ D3 camera_dir(const ReqDesc& r, uint32_t g) {
-    const uint32_t pixel = g / (uint32_t)r.spp, s = g - pixel * (uint32_t)r.spp;
+    const uint32_t pixel = udiv(g, r.inv_spp), s = g - pixel * (uint32_t)r.spp;
+    const uint32_t iy = udiv(pixel, r.inv_wc), ix = pixel - iy * (uint32_t)r.Wc;
     const U4 x = philox4x32_10(pixel, s + r.sample_offset, 0u, 0u, r.seed_lo, r.seed_hi);
-    const double px = (double)(pixel % (uint32_t)r.Wc) + u24(x.x);
-    const double py = (double)(pixel / (uint32_t)r.Wc) + u24(x.y);
-    return normalize(mat3(r.cam_M, d3(px, py, 1.0)));
+    return normalize(mat3(r.cam_M, d3((double)ix + u24(x.x), (double)iy + u24(x.y), 1.0)));
 }
 
 struct Surf {
@@ -126,10 +125,11 @@ struct Surf {
 // T along dP/du of the triangle's texture parameterisation, orthogonal to the two-sided
 // geometric normal n (the Duff et al. basis when the parameterisation is degenerate),
 // B = n x T; the map value v decodes to t = 2 v - 1 and ns = (t_x T + t_y B + t_z n) / |t|
-// (n itself when t = 0).  th = t / |t|, tlen = |t| for the chain rule back to v.
+// (n itself when t = 0).  th = t / |t|, itlen = 1 / |t| (0 when t = 0) for the chain rule
+// back to v.
 struct Shading {
     D3 ns, T, B, th;
-    double tlen, metal;
+    double itlen, metal;
 };
 __device__ __forceinline__ Shading shading(const ReqDesc& r, int leaf, const Surf& s) {
     Shading h;
@@ -143,24 +143,26 @@ __device__ __forceinline__ Shading shading(const ReqDesc& r, int leaf, const Sur
     const double det = du1 * dv2 - du2 * dv1;
     D3 t = d3(0., 0., 0.);
     if (det != 0.0) {
-        const D3 dpdu = (e1 * dv2 - e2 * dv1) * (1.0 / det);
+        const D3 dpdu = (e1 * dv2 - e2 * dv1) * rcp_rn(det);
         t = dpdu - s.n * dot(s.n, dpdu);
     }
-    const double tl = sqrt(dot(t, t));
+    const double tl = sqrt_rn(dot(t, t));
     if (tl > 0.0) {
-        h.T = t * (1.0 / tl);
+        h.T = t * rcp_rn(tl);
     } else {   // first axis of the Duff et al. basis of n
         const double sg = copysign(1.0, s.n.z);
-        const double a = -1.0 / (sg + s.n.z);
+        const double a = -rcp_rn(sg + s.n.z);
         h.T = d3(1.0 + sg * s.n.x * s.n.x * a, sg * s.n.x * s.n.y * a, -sg * s.n.x);
     }
     h.B = cross(s.n, h.T);
-    const D4 m = fetch4(r.tex4b, s.tb);
+    const D4 m = fetch4_rn(r.tex4b, s.tb);
     h.metal = r.brdf ? m.w : 0.0;
     const D3 tv = d3(2.0 * m.x - 1.0, 2.0 * m.y - 1.0, 2.0 * m.z - 1.0);
-    h.tlen = sqrt(dot(tv, tv));
-    if (h.tlen > 0.0) {
-        h.th = tv * (1.0 / h.tlen);
+    const double tlen = sqrt_rn(dot(tv, tv));
+    h.itlen = 0.0;
+    if (tlen > 0.0) {
+        h.itlen = rcp_rn(tlen);
+        h.th = tv * h.itlen;
         h.ns = h.T * h.th.x + h.B * h.th.y + s.n * h.th.z;
     } else {
         h.th = d3(0., 0., 1.);
@@ -170,9 +172,9 @@ __device__ __forceinline__ Shading shading(const ReqDesc& r, int leaf, const Sur
 }
 // cotangent of the stored map value v from a cotangent g of ns: ns = F t / |t|, t = 2 v - 1
 __device__ __forceinline__ D3 nmap_cotangent(const Shading& h, const D3& n, D3 g) {
-    if (!(h.tlen > 0.0)) return d3(0., 0., 0.);
-    const D3 gl = d3(dot(h.T, g), dot(h.B, g), dot(n, g));
-    const D3 gt = (gl - h.th * dot(h.th, gl)) * (1.0 / h.tlen);
+    if (!(h.itlen > 0.0)) return d3(0., 0., 0.);
+    const D3 gl = d3(fdot(h.T, g), fdot(h.B, g), fdot(n, g));
+    const D3 gt = fmadd(h.th, -fdot(h.th, gl), gl) * h.itlen;
     return gt * 2.0;
 }
 
@@ -194,7 +196,7 @@ __device__ __forceinline__ Surf surface_geo(const ReqDesc& r, int leaf, D3 o, D3
     const double det = dot(e1, p);
     double b1 = 1.0 / 3.0, b2 = 1.0 / 3.0;
     if (det != 0.0) {
-        const double inv = 1.0 / det;
+        const double inv = rcp_rn(det);
         const D3 tv = o - v0;
         b1 = dot(tv, p) * inv;
         b2 = dot(d, cross(tv, e1)) * inv;
@@ -232,26 +234,28 @@ struct ProjNee {
     Bilin pb;
 };
 __device__ __forceinline__ bool projector_nee(const ReqDesc& r, const Surf& s, ProjNee& p) {
-    const D3 xp = mat3(r.prj_R, s.x) + d3(r.prj_t[0], r.prj_t[1], r.prj_t[2]);
+    const D3 xp = fmat3(r.prj_R, s.x, d3(r.prj_t[0], r.prj_t[1], r.prj_t[2]));
     if (!(xp.z > 0.0)) return false;
-    const double iz = 1.0 / xp.z;
-    p.pu = (r.prj_K[0] * xp.x + r.prj_K[1] * xp.y + r.prj_K[2] * xp.z) * iz;
-    p.pv = (r.prj_K[3] * xp.x + r.prj_K[4] * xp.y + r.prj_K[5] * xp.z) * iz;
+    const double iz = frcp(xp.z);
+    p.pu = fma(r.prj_K[0], xp.x, fma(r.prj_K[1], xp.y, r.prj_K[2] * xp.z)) * iz;
+    p.pv = fma(r.prj_K[3], xp.x, fma(r.prj_K[4], xp.y, r.prj_K[5] * xp.z)) * iz;
     if (!(p.pu >= 0.0 && p.pu < (double)r.Wp && p.pv >= 0.0 && p.pv < (double)r.Hp)) return false;
     const D3 tow = d3(r.prj_o[0], r.prj_o[1], r.prj_o[2]) - s.x;
-    p.dist = sqrt(dot(tow, tow));
-    p.wp = tow * (1.0 / p.dist);
-    const double cp = dot(s.n, p.wp);
+    const double d2 = fdot(tow, tow), id = frsqrt(d2);
+    p.dist = d2 * id;
+    p.wp = tow * id;
+    const double cp = fdot(s.n, p.wp);
     if (!(cp > 0.0)) return false;
-    const double ca = xp.z / sqrt(dot(xp, xp));
-    p.geom = cp / (ca * ca * ca * p.dist * p.dist);
-    p.g0 = 1.0 / (ca * ca * ca * p.dist * p.dist);
+    const double l2 = fdot(xp, xp);
+    const double ica = l2 * frsqrt(l2) * iz;   // 1 / cos alpha = |xp| / xp.z
+    p.g0 = ica * ica * ica * (id * id);
+    p.geom = cp * p.g0;
     p.pb = bilinear(p.pu - 0.5, p.pv - 0.5, r.Wp, r.Hp);
     return true;
 }
 
 __device__ __forceinline__ U4 vertex_rng(const ReqDesc& r, uint32_t g, uint32_t block) {
-    const uint32_t pixel = g / (uint32_t)r.spp, s = g - pixel * (uint32_t)r.spp;
+    const uint32_t pixel = udiv(g, r.inv_spp), s = g - pixel * (uint32_t)r.spp;
     return philox4x32_10(pixel, s + r.sample_offset, block, 0u, r.seed_lo, r.seed_hi);
 }
 
@@ -305,7 +309,7 @@ __device__ __forceinline__ ReplayStart replay_start(const ReqDesc& r, uint32_t g
                                                     const float4* __restrict__ wave_L,
                                                     const float4* __restrict__ delta) {
     ReplayStart t;
-    const uint32_t sid = g - r.g_base + r.sid_base, s = g % (uint32_t)r.spp;
+    const uint32_t sid = g - r.g_base + r.sid_base, s = g - udiv(g, r.inv_spp) * (uint32_t)r.spp;
     if (sample_L) t.L = make_float4(sample_L[3 * (size_t)g], sample_L[3 * (size_t)g + 1], sample_L[3 * (size_t)g + 2], 0.f);
     else t.L = wave_L[sid];
     t.dl = clip_cotangent(r, delta[sid - s], t.L, clip_threshold(r));
