@@ -8,7 +8,7 @@
 //     internal node finds its key range and split; equal codes split by index.
 //  4. Bounds bottom-up: a thread per leaf climbs; the second thread to reach a node
 //     (atomic arrival counter) writes the node's two child boxes and continues.
-//  5. Leaf-ordered 48-byte triangle records and UV / emission records.
+//  5. Leaf-ordered 64-byte triangle records (with texture coordinates) and emission records.
 #include <climits>
 
 #include "kernels.hpp"
@@ -228,33 +228,35 @@ __global__ void k_single_node(const float* __restrict__ V, const int* __restrict
 
 __global__ void k_leaf_records(const float* __restrict__ V, const int* __restrict__ F, const float* __restrict__ UV,
                                const float* __restrict__ Le, const uint32_t* __restrict__ order, int n,
-                               float4* __restrict__ tris, float4* __restrict__ tri_uv, float4* __restrict__ em,
+                               float4* __restrict__ tris, float4* __restrict__ em,
                                int* __restrict__ leaf_of_prim) {
     const int l = blockIdx.x * blockDim.x + threadIdx.x;
     if (l >= n) return;
     if (order[l] >= (uint32_t)n) return;
     const int p = (int)order[l];
     const int a = F[3 * p], b = F[3 * p + 1], c = F[3 * p + 2];
-    tris[3 * l] = make_float4(V[3 * a], V[3 * a + 1], V[3 * a + 2], __int_as_float(p));
-    tris[3 * l + 1] = make_float4(V[3 * b], V[3 * b + 1], V[3 * b + 2], 0.0f);
-    tris[3 * l + 2] = make_float4(V[3 * c], V[3 * c + 1], V[3 * c + 2], 0.0f);
     const float* uv = UV + 6 * (size_t)p;
-    tri_uv[2 * l] = make_float4(uv[0], uv[1], uv[2], uv[3]);
-    tri_uv[2 * l + 1] = make_float4(uv[4], uv[5], 0.0f, 0.0f);
+    float4* t = tris + 4 * (size_t)l;
+    t[0] = make_float4(V[3 * a], V[3 * a + 1], V[3 * a + 2], __int_as_float(p));
+    t[1] = make_float4(V[3 * b], V[3 * b + 1], V[3 * b + 2], uv[0]);
+    t[2] = make_float4(V[3 * c], V[3 * c + 1], V[3 * c + 2], uv[1]);
+    t[3] = make_float4(uv[2], uv[3], uv[4], uv[5]);
     if (em) em[l] = make_float4(Le[3 * p], Le[3 * p + 1], Le[3 * p + 2], 0.0f);
     leaf_of_prim[p] = l;
 }
 
-// the leaf records' vertices at new positions (original index bits in v0.w kept)
+// the leaf records' vertices at new positions (texture coordinates kept)
 __global__ void k_refit_tris(const float* __restrict__ V, const int* __restrict__ F, const uint32_t* __restrict__ order,
                              int n, float4* __restrict__ tris) {
     const int l = blockIdx.x * blockDim.x + threadIdx.x;
     if (l >= n || order[l] >= (uint32_t)n) return;
     const int p = (int)order[l];
     const int a = F[3 * p], b = F[3 * p + 1], c = F[3 * p + 2];
-    tris[3 * l] = make_float4(V[3 * a], V[3 * a + 1], V[3 * a + 2], __int_as_float(p));
-    tris[3 * l + 1] = make_float4(V[3 * b], V[3 * b + 1], V[3 * b + 2], 0.0f);
-    tris[3 * l + 2] = make_float4(V[3 * c], V[3 * c + 1], V[3 * c + 2], 0.0f);
+    float4* t = tris + 4 * (size_t)l;
+    const float u = t[1].w, v = t[2].w;
+    t[0] = make_float4(V[3 * a], V[3 * a + 1], V[3 * a + 2], __int_as_float(p));
+    t[1] = make_float4(V[3 * b], V[3 * b + 1], V[3 * b + 2], u);
+    t[2] = make_float4(V[3 * c], V[3 * c + 1], V[3 * c + 2], v);
 }
 
 // one thread per 4-wide child slot: the box of the binary node behind it (the union of
@@ -279,7 +281,8 @@ __global__ void k_refit_wide(const float4* __restrict__ nodes, const float4* __r
     } else {
         const int l = ~ref;
         if (l >= nt) return;
-        const float4 a = tris[3 * l], c = tris[3 * l + 1], e = tris[3 * l + 2];
+        const float4* t = tris + 4 * (size_t)l;
+        const float4 a = t[0], c = t[1], e = t[2];
         const float x[3] = {a.x, c.x, e.x}, y[3] = {a.y, c.y, e.y}, z[3] = {a.z, c.z, e.z};
         b[0] = fminf(x[0], fminf(x[1], x[2]));
         b[1] = fminf(y[0], fminf(y[1], y[2]));
@@ -299,7 +302,7 @@ hipError_t build_leaf_records(hipStream_t st, const BvhInputs& in, const uint32_
     const int n = in.nt;
     out.order = order;
     hipLaunchKernelGGL(k_leaf_records, dim3(grid_of(n, 256)), dim3(256), 0, st, in.V, in.F, in.UV, in.Le, order, n,
-                       out.tris, out.tri_uv, out.emission, out.leaf_of_prim);
+                       out.tris, out.emission, out.leaf_of_prim);
     return hipGetLastError();
 }
 
@@ -355,7 +358,7 @@ hipError_t build_bvh(hipStream_t st, const BvhInputs& in, BvhOutputs& out, BvhBu
                            in.parent_int, in.parent_leaf, in.flags, in.node_box, out.nodes);
     }
     hipLaunchKernelGGL(k_leaf_records, dim3(grid_of(n, 256)), dim3(256), 0, st, in.V, in.F, in.UV, in.Le, order, n,
-                       out.tris, out.tri_uv, out.emission, out.leaf_of_prim);
+                       out.tris, out.emission, out.leaf_of_prim);
     return hipGetLastError();
 }
 

@@ -42,7 +42,9 @@ struct CamSurf {
 __device__ __forceinline__ CamSurf cam_surface(const ReqDesc& r, const CamFrozen& z, D3 x) {
     Surf s;
     V3 f0, f1, f2;
-    load_tri(r.tris, z.leaf, f0, f1, f2, s.prim);
+    float4 ua;
+    float2 ub;
+    load_tri_uv(r.tris, z.leaf, f0, f1, f2, s.prim, ua, ub);
     const D3 v0 = to_d(f0), e1 = to_d(f1) - v0, e2 = to_d(f2) - v0, p = x - v0;
     // barycentrics of x in the plane: normal equations of p = b1 e1 + b2 e2
     const double a11 = dot(e1, e1), a12 = dot(e1, e2), a22 = dot(e2, e2), r1 = dot(p, e1), r2 = dot(p, e2);
@@ -50,7 +52,6 @@ __device__ __forceinline__ CamSurf cam_surface(const ReqDesc& r, const CamFrozen
     const double b1 = (a22 * r1 - a12 * r2) * inv, b2 = (a11 * r2 - a12 * r1) * inv, b0 = 1.0 - b1 - b2;
     s.x = x;
     s.n = z.n;
-    const float4 ua = r.tri_uv[2 * z.leaf], ub = r.tri_uv[2 * z.leaf + 1];
     s.u = fma(b0, (double)ua.x, fma(b1, (double)ua.z, b2 * ub.x));
     s.v = fma(b0, (double)ua.y, fma(b1, (double)ua.w, b2 * ub.y));
     s.tb = bilinear(fma(s.u, (double)r.tw, -0.5), fma(s.v, (double)r.th, -0.5), r.tw, r.th);

@@ -225,9 +225,8 @@ struct ReqDesc {
     // scene (BVH + leaf-ordered triangle records)
     const float4* nodes;     // binary BVH (4 float4 per node)
     const float4* nodes4;    // 4-wide BVH (8 float4 per node), or null: traverse the binary one
-    const float4* tris;      // 3 float4 per leaf: v0 (w = prim id bits), v1, v2
+    const float4* tris;      // 4 float4 per leaf (trace.hpp): vertices, prim id, texture coordinates
     int32_t top_nodes;       // leading 4-wide nodes (breadth-first order) staged in LDS, <= TOP_NODES
-    const float4* tri_uv;    // 2 float4 per leaf: (u0 v0 u1 v1), (u2 v2 - -)
     const float4* emission;  // per leaf (rgb, -) or null
     float tmin;
     // material

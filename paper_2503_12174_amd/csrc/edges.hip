@@ -56,11 +56,15 @@ struct EdgeArgs {
 };
 
 __device__ __forceinline__ D3 corner_pos(const ReqDesc& r, int leaf, int k) {
-    const float4 v = r.tris[3 * leaf + k];
+    const float4 v = r.tris[4 * (size_t)leaf + k];
     return d3(v.x, v.y, v.z);
 }
 __device__ __forceinline__ float2 corner_uv(const ReqDesc& r, int leaf, int k) {
-    const float4 a = r.tri_uv[2 * leaf], b = r.tri_uv[2 * leaf + 1];
+    V3 v0, v1, v2;
+    int prim;
+    float4 a;
+    float2 b;
+    load_tri_uv(r.tris, leaf, v0, v1, v2, prim, a, b);
     return k == 0 ? make_float2(a.x, a.y) : k == 1 ? make_float2(a.z, a.w) : make_float2(b.x, b.y);
 }
 
@@ -261,7 +265,7 @@ namespace {
 bool build_edges(dpcs_context ctx, dpcs_scene sc, dpcs_status* st) {
     const int nt = sc->nt;
     std::vector<int32_t> F(3 * (size_t)nt), leaf(nt);
-    std::vector<float4> tris(3 * (size_t)nt);
+    std::vector<float4> tris(4 * (size_t)nt);
     if (!hip_ok(ctx, hipMemcpyAsync(F.data(), sc->F, sizeof(int32_t) * F.size(), hipMemcpyDeviceToHost, ctx->stream),
                 "edge table: indices") ||
         !hip_ok(ctx, hipMemcpyAsync(leaf.data(), sc->leaf_of_prim, sizeof(int32_t) * nt, hipMemcpyDeviceToHost,
@@ -279,7 +283,7 @@ bool build_edges(dpcs_context ctx, dpcs_scene sc, dpcs_status* st) {
     for (int f = 0; f < nt; ++f)
         for (int k = 0; k < 3; ++k) {
             const int v = F[3 * (size_t)f + k];
-            const float4 p = tris[3 * (size_t)leaf[f] + k];
+            const float4 p = tris[4 * (size_t)leaf[f] + k];
             used[v] = 1;
             pos[3 * (size_t)v] = p.x;
             pos[3 * (size_t)v + 1] = p.y;
@@ -313,7 +317,7 @@ bool build_edges(dpcs_context ctx, dpcs_scene sc, dpcs_status* st) {
     std::vector<Key> key;
     key.reserve(3 * (size_t)nt);
     for (int f = 0; f < nt; ++f) {
-        const float4* t = &tris[3 * (size_t)leaf[f]];
+        const float4* t = &tris[4 * (size_t)leaf[f]];
         const double ax = (double)t[1].x - t[0].x, ay = (double)t[1].y - t[0].y, az = (double)t[1].z - t[0].z;
         const double bx = (double)t[2].x - t[0].x, by = (double)t[2].y - t[0].y, bz = (double)t[2].z - t[0].z;
         if (ay * bz - az * by == 0.0 && az * bx - ax * bz == 0.0 && ax * by - ay * bx == 0.0) continue;

@@ -28,8 +28,7 @@ struct BvhInputs {
 };
 struct BvhOutputs {
     float4* nodes;           // 4 * max(nt - 1, 1)
-    float4* tris;            // 3 * nt
-    float4* tri_uv;          // 2 * nt
+    float4* tris;            // 4 * nt
     float4* emission;        // nt or null
     int* leaf_of_prim;       // nt
     const uint32_t* order;   // leaf -> original triangle (points into keys/vals scratch)
@@ -70,7 +69,7 @@ struct WideResult {
 };
 size_t wide_scratch_bytes(int nt);
 hipError_t build_wide(hipStream_t st, const WideArgs& a, void* scratch, uint64_t* host_words, WideResult& res);
-// leaf-ordered triangle / UV / emission records for a leaf order built elsewhere
+// leaf-ordered triangle / emission records for a leaf order built elsewhere
 hipError_t build_leaf_records(hipStream_t st, const BvhInputs& in, const uint32_t* order, BvhOutputs& out);
 // new vertex positions on a fixed topology: the binary node boxes bottom-up (flags: ni
 // zeroed ints, node_box: 6 ni floats of scratch), the leaf records' vertices, and the

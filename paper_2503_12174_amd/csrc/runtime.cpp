@@ -273,7 +273,6 @@ bool fill_desc(dpcs_context, ReqDesc& r, const dpcs_render_params* p, dpcs_scene
     r.nodes4 = sc->nodes4;
     r.tris = sc->tris;
     r.top_nodes = sc->nodes4 ? std::min(TOP_NODES, sc->nnodes4) : 0;
-    r.tri_uv = sc->tri_uv;
     r.emission = sc->emission;
     r.tmin = sc->tmin;
     r.brdf = p->brdf;
@@ -475,8 +474,7 @@ extern "C" dpcs_status dpcs_scene_create(dpcs_context ctx, const dpcs_mesh_desc*
         }
     };
     dmalloc((void**)&sc->nodes, sizeof(float4) * 4 * ni);
-    dmalloc((void**)&sc->tris, sizeof(float4) * 3 * (nt + 1));   // + the dummy leaf of empty BVH4 slots
-    dmalloc((void**)&sc->tri_uv, sizeof(float4) * 2 * nt);
+    dmalloc((void**)&sc->tris, sizeof(float4) * 4 * (size_t)(nt + 1));   // + the dummy leaf of empty BVH4 slots
     if (m->emission) dmalloc((void**)&sc->emission, sizeof(float4) * nt);
     dmalloc((void**)&sc->leaf_of_prim, sizeof(int) * nt);
     dmalloc((void**)&sc->F, sizeof(int) * 3 * nt);
@@ -486,7 +484,7 @@ extern "C" dpcs_status dpcs_scene_create(dpcs_context ctx, const dpcs_mesh_desc*
     dmalloc((void**)&sc->parent_leaf, sizeof(int) * nt);
     sc->nv = nv;
     sc->nnodes = ni;
-    sc->bytes = (int64_t)sizeof(float4) * (4 * ni + 3 * (nt + 1) + 2 * nt + (m->emission ? nt : 0)) + 4 * nt +
+    sc->bytes = (int64_t)sizeof(float4) * (4 * (int64_t)ni + 4 * ((int64_t)nt + 1) + (m->emission ? nt : 0)) + 4 * nt +
                 4 * (3 * (int64_t)nt + nt + 2 * (int64_t)ni + ni + nt);
     // build temporaries: the uploaded vertices, uvs and emission, the sort and bounds
     // buffers carved from one allocation (each part rounded up to 256 bytes), and the
@@ -522,7 +520,6 @@ extern "C" dpcs_status dpcs_scene_create(dpcs_context ctx, const dpcs_mesh_desc*
         (void)hipFree(sc->nodes);
         if (sc->nodes4) (void)hipFree(sc->nodes4);
         (void)hipFree(sc->tris);
-        (void)hipFree(sc->tri_uv);
         if (sc->emission) (void)hipFree(sc->emission);
         (void)hipFree(sc->leaf_of_prim);
         for (void* q : {(void*)sc->F, (void*)sc->order, (void*)sc->child, (void*)sc->parent_int, (void*)sc->parent_leaf,
@@ -567,7 +564,6 @@ extern "C" dpcs_status dpcs_scene_create(dpcs_context ctx, const dpcs_mesh_desc*
     }
     bo.nodes = sc->nodes;
     bo.tris = sc->tris;
-    bo.tri_uv = sc->tri_uv;
     bo.emission = sc->emission;
     bo.leaf_of_prim = sc->leaf_of_prim;
     hipStream_t st = ctx->stream;
@@ -637,10 +633,10 @@ extern "C" dpcs_status dpcs_scene_create(dpcs_context ctx, const dpcs_mesh_desc*
         int none = -1;
         float none_f;
         std::memcpy(&none_f, &none, 4);
-        const float4 dummy[3] = {make_float4(qn, qn, qn, none_f), make_float4(qn, qn, qn, 0.f),
-                                 make_float4(qn, qn, qn, 0.f)};
+        const float4 dummy[4] = {make_float4(qn, qn, qn, none_f), make_float4(qn, qn, qn, 0.f),
+                                 make_float4(qn, qn, qn, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
         const size_t b4 = sizeof(float4) * 8 * (size_t)wr.nnodes4, bm = sizeof(int) * 4 * (size_t)wr.nnodes4;
-        hipError_t e4 = hipMemcpy(sc->tris + 3 * (size_t)nt, dummy, sizeof(dummy), hipMemcpyHostToDevice);
+        hipError_t e4 = hipMemcpy(sc->tris + 4 * (size_t)nt, dummy, sizeof(dummy), hipMemcpyHostToDevice);
         if (e4 == hipSuccess) e4 = hipMalloc((void**)&sc->nodes4, b4);
         if (e4 == hipSuccess) e4 = hipMalloc((void**)&sc->map4, bm);
         if (e4 == hipSuccess) e4 = hipMemcpyAsync(sc->nodes4, wr.nodes4, b4, hipMemcpyDeviceToDevice, st);
@@ -687,7 +683,6 @@ extern "C" dpcs_status dpcs_scene_destroy(dpcs_scene s) {
     (void)hipFree(s->nodes);
     if (s->nodes4) (void)hipFree(s->nodes4);
     (void)hipFree(s->tris);
-    (void)hipFree(s->tri_uv);
     if (s->emission) (void)hipFree(s->emission);
     (void)hipFree(s->leaf_of_prim);
     for (void* q : {(void*)s->F, (void*)s->order, (void*)s->child, (void*)s->parent_int, (void*)s->parent_leaf,

@@ -51,7 +51,6 @@ struct dpcs_scene_s {
     float4* nodes = nullptr;
     float4* nodes4 = nullptr;              // 4-wide BVH, or null
     float4* tris = nullptr;
-    float4* tri_uv = nullptr;
     float4* emission = nullptr;
     int* leaf_of_prim = nullptr;
     // topology kept for dpcs_scene_refit: triangles, leaf order, binary children and

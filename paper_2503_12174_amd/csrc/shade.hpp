@@ -135,9 +135,10 @@ __device__ __forceinline__ Shading shading(const ReqDesc& r, int leaf, const Sur
     Shading h;
     V3 f0, f1, f2;
     int prim;
-    load_tri(r.tris, leaf, f0, f1, f2, prim);
+    float4 ua;
+    float2 ub;
+    load_tri_uv(r.tris, leaf, f0, f1, f2, prim, ua, ub);
     const D3 e1 = to_d(f1) - to_d(f0), e2 = to_d(f2) - to_d(f0);
-    const float4 ua = r.tri_uv[2 * leaf], ub = r.tri_uv[2 * leaf + 1];
     const double du1 = (double)ua.z - ua.x, dv1 = (double)ua.w - ua.y;
     const double du2 = (double)ub.x - ua.x, dv2 = (double)ub.y - ua.y;
     const double det = du1 * dv2 - du2 * dv1;
@@ -186,10 +187,9 @@ __device__ __forceinline__ D3 nmap_cotangent(const Shading& h, const D3& n, D3 g
 __device__ __forceinline__ Surf surface_geo(const ReqDesc& r, int leaf, D3 o, D3 d) {
     Surf s;
     V3 f0, f1, f2;
-    load_tri(r.tris, leaf, f0, f1, f2, s.prim);
-    // the corner texture coordinates load with the vertices (both need only the leaf): read
-    // after the barycentrics, they cost a second trip to memory
-    const float4 ua = r.tri_uv[2 * leaf], ub = r.tri_uv[2 * leaf + 1];
+    float4 ua;
+    float2 ub;
+    load_tri_uv(r.tris, leaf, f0, f1, f2, s.prim, ua, ub);
     const D3 v0 = to_d(f0), v1 = to_d(f1), v2 = to_d(f2);
     const D3 e1 = v1 - v0, e2 = v2 - v0;
     const D3 p = cross(d, e2);
