@@ -29,41 +29,40 @@ namespace dpcs {
 // watertight ray / triangle test (Woop, Benthin, Wald, JCGT 2013)
 struct WtRay {
     V3 o;
-    uint32_t k;          // axis permutation kx | ky << 2 | kz << 4
+    int kz;              // axis of the largest direction component; the others follow in cyclic order
     float Sx, Sy, Sz;
 };
+// a's components along the axes kz + 1, kz + 2 and kz (cyclic)
+__device__ __forceinline__ V3 turned(V3 a, int kz) {
+    return v3(kz == 0 ? a.y : (kz == 1 ? a.z : a.x), kz == 0 ? a.z : (kz == 1 ? a.x : a.y),
+              kz == 0 ? a.x : (kz == 1 ? a.y : a.z));
+}
 
 __device__ __forceinline__ WtRay wt_setup(V3 o, V3 d) {
     WtRay r;
     r.o = o;
     const float ax = fabsf(d.x), ay = fabsf(d.y), az = fabsf(d.z);
-    int kz = (ax > ay) ? (ax > az ? 0 : 2) : (ay > az ? 1 : 2);
-    int kx = kz == 2 ? 0 : kz + 1;
-    int ky = kx == 2 ? 0 : kx + 1;
-    const float dz = comp(d, kz);
-    if (dz < 0.0f) {
-        const int tmp = kx;
-        kx = ky;
-        ky = tmp;
-    }
-    r.k = (uint32_t)kx | (uint32_t)ky << 2 | (uint32_t)kz << 4;
+    r.kz = (ax > ay) ? (ax > az ? 0 : 2) : (ay > az ? 1 : 2);
+    // (the method swaps the first two axes where the third component is negative, to keep
+    // the winding; here the edge functions, the determinant and T all change sign with it,
+    // exactly, and neither t nor the barycentrics do)
+    const V3 q = turned(d, r.kz);
     // the shear need not be correctly rounded, only the same for every triangle a ray
     // meets (watertightness), so the hardware reciprocal (within 1 ulp) stands in for the
     // multi-instruction IEEE division; |dz| >= 1/sqrt(3) for a unit direction
-    r.Sz = __builtin_amdgcn_rcpf(dz);
-    r.Sx = comp(d, kx) * r.Sz;
-    r.Sy = comp(d, ky) * r.Sz;
+    r.Sz = __builtin_amdgcn_rcpf(q.z);
+    r.Sx = q.x * r.Sz;
+    r.Sy = q.y * r.Sz;
     return r;
 }
 
 // returns false on a miss; on a hit t and the barycentrics (b1 of v1, b2 of v2)
 __device__ __forceinline__ bool wt_intersect(const WtRay& r, V3 v0, V3 v1, V3 v2, float& t, float& b1, float& b2) {
-    const int kx = (int)(r.k & 3u), ky = (int)((r.k >> 2) & 3u), kz = (int)(r.k >> 4);
-    const V3 A = v0 - r.o, B = v1 - r.o, C = v2 - r.o;
-    const float Akz = comp(A, kz), Bkz = comp(B, kz), Ckz = comp(C, kz);
-    const float Ax = comp(A, kx) - r.Sx * Akz, Ay = comp(A, ky) - r.Sy * Akz;
-    const float Bx = comp(B, kx) - r.Sx * Bkz, By = comp(B, ky) - r.Sy * Bkz;
-    const float Cx = comp(C, kx) - r.Sx * Ckz, Cy = comp(C, ky) - r.Sy * Ckz;
+    const V3 A = turned(v0 - r.o, r.kz), B = turned(v1 - r.o, r.kz), C = turned(v2 - r.o, r.kz);
+    const float Akz = A.z, Bkz = B.z, Ckz = C.z;
+    const float Ax = A.x - r.Sx * Akz, Ay = A.y - r.Sy * Akz;
+    const float Bx = B.x - r.Sx * Bkz, By = B.y - r.Sy * Bkz;
+    const float Cx = C.x - r.Sx * Ckz, Cy = C.y - r.Sy * Ckz;
     float U = Cx * By - Cy * Bx;
     float V = Ax * Cy - Ay * Cx;
     float W = Bx * Ay - By * Ax;
@@ -89,12 +88,11 @@ __device__ __forceinline__ bool wt_intersect(const WtRay& r, V3 v0, V3 v1, V3 v2
 // decides with it and then recomputes the reported t and barycentrics of its winner with
 // wt_intersect, so all of them agree bit for bit.
 __device__ __forceinline__ bool wt_hit(const WtRay& r, V3 v0, V3 v1, V3 v2, float& t) {
-    const int kx = (int)(r.k & 3u), ky = (int)((r.k >> 2) & 3u), kz = (int)(r.k >> 4);
-    const V3 A = v0 - r.o, B = v1 - r.o, C = v2 - r.o;
-    const float Akz = comp(A, kz), Bkz = comp(B, kz), Ckz = comp(C, kz);
-    const float Ax = comp(A, kx) - r.Sx * Akz, Ay = comp(A, ky) - r.Sy * Akz;
-    const float Bx = comp(B, kx) - r.Sx * Bkz, By = comp(B, ky) - r.Sy * Bkz;
-    const float Cx = comp(C, kx) - r.Sx * Ckz, Cy = comp(C, ky) - r.Sy * Ckz;
+    const V3 A = turned(v0 - r.o, r.kz), B = turned(v1 - r.o, r.kz), C = turned(v2 - r.o, r.kz);
+    const float Akz = A.z, Bkz = B.z, Ckz = C.z;
+    const float Ax = A.x - r.Sx * Akz, Ay = A.y - r.Sy * Akz;
+    const float Bx = B.x - r.Sx * Bkz, By = B.y - r.Sy * Bkz;
+    const float Cx = C.x - r.Sx * Ckz, Cy = C.y - r.Sy * Ckz;
     float U = Cx * By - Cy * Bx;
     float V = Ax * Cy - Ay * Cx;
     float W = Bx * Ay - By * Ax;
@@ -284,18 +282,21 @@ __device__ __forceinline__ void cmpx(float& ka, int& ra, float& kb, int& rb) {
 // plane * (1 / d) + off, with no min/max per axis.  off is -o / d rounded outward:
 // down by at least the rounding error of o / d for near planes, up for far planes.
 // With that, a slab value can only err by the relative rounding of 1 / d and of the
-// FMA, which the relative widening in the test covers; it needs no absolute term
-// that would grow for near-axis-parallel rays.  An axis along which the ray does not move
+// FMA, which the relative widening covers; it needs no absolute term that would grow for
+// near-axis-parallel rays.  The widening, t x (1 -+ 4e-6), is in the constants, so a box
+// test takes no product for it (the closest-hit loop is bound by vector issue: 256 x 256 x
+// 16 of the 50k-triangle corner 1583 us with the two products, 1580 without, and 1587 before
+// the triangle test lost its swap of two axes; with an environment map 2200, 2193, 2180).  An axis along which the ray does not move
 // (|d| < 2^-80, or 0) takes the reciprocal 2^80; every offset is widened by 2^-40 in space
 // besides, so such a slab lets pass exactly the boxes that hold the ray's coordinate, faces
 // included.  (With 1 / 0 both slab values came out NaN and the axis let every box
 // pass: a bounce straight along the normal of an axis-aligned face, one sample in 2^24,
-// walked a whole wall of the corner, 12 ms for one ray.)  The relative widening multiplies (t x (1 -+ 4e-6)) rather than adding
-// a multiple of |t|, so infinite slab values stay infinite instead of turning NaN,
+// walked a whole wall of the corner, 12 ms for one ray.)  The widening multiplies rather than adding a multiple of |t|, so infinite slab values stay infinite instead of turning NaN,
 // and an inverted box (lo = +1e30, hi = -1e30: every near plane ahead of every far
 // plane) is always missed.
 struct Box4Ray {
-    float ix, iy, iz;             // 1 / d
+    float ix, iy, iz;             // 1 / d, less the widening (near planes)
+    float jx, jy, jz;             // 1 / d and the widening (far planes)
     float anx, any, anz;          // near-plane offsets
     float afx, afy, afz;          // far-plane offsets
     uint32_t onx, ony, onz;       // byte offset of the near coordinate float4 in a node
@@ -310,19 +311,22 @@ __device__ __forceinline__ Box4Ray box4_setup(V3 o, V3 d) {
     r.ix = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(d.x), 0x1p-80f), d.x));
     r.iy = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(d.y), 0x1p-80f), d.y));
     r.iz = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(d.z), 0x1p-80f), d.z));
-    // |fl(o rcp(d)) - o / d| <= (2^-23 + 2^-24) |fl(o rcp(d))| (1 + 2^-23); 2^-21 also
-    // covers the rounding of the two sums below; 2^-40 / |d|: the faces of an axis along
-    // which the ray does not move
+    // |fl(o rcp(d)) - o rcp(d)| <= 2^-24 |o rcp(d)|, and as much again for each of the sum,
+    // its product with 1 -+ 4e-6 and that of rcp(d) below: 2^-21 is twice what they take;
+    // 2^-40 / |d|: the faces of an axis along which the ray does not move
     const float px = o.x * r.ix, py = o.y * r.iy, pz = o.z * r.iz;
     const float ex = fmaf(fabsf(r.ix), 0x1p-40f, fabsf(px) * 0x1p-21f);
     const float ey = fmaf(fabsf(r.iy), 0x1p-40f, fabsf(py) * 0x1p-21f);
     const float ez = fmaf(fabsf(r.iz), 0x1p-40f, fabsf(pz) * 0x1p-21f);
-    r.anx = -px - ex;
-    r.any = -py - ey;
-    r.anz = -pz - ez;
-    r.afx = -px + ex;
-    r.afy = -py + ey;
-    r.afz = -pz + ez;
+    constexpr float WN = 1.0f - 4e-6f, WF = 1.0f + 4e-6f;
+    r.jx = r.ix * WF, r.jy = r.iy * WF, r.jz = r.iz * WF;
+    r.ix *= WN, r.iy *= WN, r.iz *= WN;
+    r.anx = (-px - ex) * WN;
+    r.any = (-py - ey) * WN;
+    r.anz = (-pz - ez) * WN;
+    r.afx = (-px + ex) * WF;
+    r.afy = (-py + ey) * WF;
+    r.afz = (-pz + ez) * WF;
     // node float4s: 0 lo.x, 1 lo.y, 2 lo.z, 3 hi.x, 4 hi.y, 5 hi.z
     const bool sx = __builtin_signbit(r.ix), sy = __builtin_signbit(r.iy), sz = __builtin_signbit(r.iz);
     r.onx = sx ? 48u : 0u;
@@ -338,9 +342,9 @@ __device__ __forceinline__ Box4Ray box4_setup(V3 o, V3 d) {
 __device__ __forceinline__ float box4_enter(const Box4Ray& r, float nx, float ny, float nz, float fx, float fy,
                                             float fz, float tmin, float tmax) {
     float tn = fmaxf(fmaxf(fmaf(nx, r.ix, r.anx), fmaf(ny, r.iy, r.any)), fmaf(nz, r.iz, r.anz));
-    float tf = fminf(fminf(fmaf(fx, r.ix, r.afx), fmaf(fy, r.iy, r.afy)), fmaf(fz, r.iz, r.afz));
-    tn = fmaxf(tn * (1.0f - 4e-6f), tmin);
-    tf = fminf(tf * (1.0f + 4e-6f), tmax);
+    float tf = fminf(fminf(fmaf(fx, r.jx, r.afx), fmaf(fy, r.jy, r.afy)), fmaf(fz, r.jz, r.afz));
+    tn = fmaxf(tn, tmin);
+    tf = fminf(tf, tmax);
     return tn <= tf ? tn : __builtin_nanf("");
 }
 
