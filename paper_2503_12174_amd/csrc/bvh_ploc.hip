@@ -370,7 +370,7 @@ __global__ void __launch_bounds__(TB) k_collapse_write(const float4* __restrict_
     for (int q = 0; q < 6; ++q) o[q] = make_float4(box[q][0], box[q][1], box[q][2], box[q][3]);
     o[6] = make_float4(__int_as_float(refs[0]), __int_as_float(refs[1]), __int_as_float(refs[2]),
                        __int_as_float(refs[3]));
-    o[7] = make_float4(0.f, 0.f, 0.f, 0.f);
+    o[7] = make_float4(__int_as_float(bin[e]), 0.f, 0.f, 0.f);   // (for refits)
 }
 
 size_t wide_scratch_bytes(int nt) {
@@ -418,6 +418,7 @@ hipError_t build_wide(hipStream_t st, const WideArgs& a, void* scratch, uint64_t
         e = hipMemcpyAsync(host_words, total, sizeof(uint64_t), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return e;
+        if (levels <= MAX_LEVELS4) res.level_base[levels - 1] = base;
         base += m;
         m = (int)(uint32_t)host_words[0];
         cur ^= 1;
@@ -428,6 +429,7 @@ hipError_t build_wide(hipStream_t st, const WideArgs& a, void* scratch, uint64_t
     if (e != hipSuccess) return e;
     int hs[4];
     std::memcpy(hs, host_words, sizeof hs);
+    if (levels <= MAX_LEVELS4) res.level_base[levels] = base;
     res.nnodes4 = base;
     res.depth4 = levels;
     res.stack_bound = hs[0];

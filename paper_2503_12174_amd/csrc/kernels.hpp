@@ -58,10 +58,12 @@ struct WideArgs {
     const uint32_t* order;
     int nt;
 };
+constexpr int MAX_LEVELS4 = 64;   // scenes are made of trees no deeper than that
 struct WideResult {
     float4* nodes4;
     int* map4;
     int nnodes4, depth4;   // 4-wide nodes and levels
+    int level_base[MAX_LEVELS4 + 1];   // first node of every level, and nnodes4
     int stack_bound;       // most stack entries a traversal holds
     int depth;             // binary depth (internal nodes on the longest root-to-leaf path)
     bool malformed;        // a leaf reached other than once, a parent chain off the root, or
@@ -71,9 +73,11 @@ size_t wide_scratch_bytes(int nt);
 hipError_t build_wide(hipStream_t st, const WideArgs& a, void* scratch, uint64_t* host_words, WideResult& res);
 // leaf-ordered triangle / emission records for a leaf order built elsewhere
 hipError_t build_leaf_records(hipStream_t st, const BvhInputs& in, const uint32_t* order, BvhOutputs& out);
-// new vertex positions on a fixed topology: the binary node boxes bottom-up (flags: ni
-// zeroed ints, node_box: 6 ni floats of scratch), the leaf records' vertices, and the
-// 4-wide nodes' child boxes from map4 (4 per node: binary node, ~leaf, or INT_MIN empty)
+// new vertex positions on a fixed topology: the leaf records' vertices and the boxes of the
+// binary nodes and of the 4-wide nodes, from map4 (4 per node: binary node, ~leaf, or
+// INT_MIN empty) and the first node of every 4-wide level (level_base, nlevels + 1 entries).
+// Without a 4-wide tree (nodes4 null) the binary boxes are climbed to with flags (ni zeroed
+// ints) and node_box (6 ni floats of scratch), which are not used otherwise.
 struct RefitArgs {
     const float* V;
     const int* F;
@@ -90,7 +94,7 @@ struct RefitArgs {
     const int* map4;
     int nnodes4;
 };
-hipError_t refit_bvh(hipStream_t st, const RefitArgs& a);
+hipError_t refit_bvh(hipStream_t st, const RefitArgs& a, const int* level_base, int nlevels);
 
 // ------------------------------------------------------------------ path queues
 // Structure-of-arrays queues in HBM.  Path state is FP64 position/direction (PathO,

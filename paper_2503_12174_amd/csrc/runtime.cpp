@@ -649,6 +649,8 @@ extern "C" dpcs_status dpcs_scene_create(dpcs_context ctx, const dpcs_mesh_desc*
             return DPCS_E_DEVICE;
         }
         sc->nnodes4 = wr.nnodes4;
+        sc->nlevels4 = wr.depth4;   // <= the binary depth <= MAX_LEVELS4
+        std::copy(wr.level_base, wr.level_base + wr.depth4 + 1, sc->level4);
         sc->bytes += (int64_t)(b4 + bm);
     }
     cleanup_tmp();
@@ -703,15 +705,20 @@ extern "C" dpcs_status dpcs_scene_refit(dpcs_context ctx, dpcs_scene s, const fl
     if (!hip_ok(ctx, hipSetDevice(ctx->device), "hipSetDevice")) return DPCS_E_DEVICE;
     dpcs_status st = DPCS_OK;
     const int ni = s->nnodes;
-    int* flags = (int*)scratch(ctx, "refit.flags", sizeof(int) * ni, &st);
-    if (!flags) return st;
-    float* box = (float*)scratch(ctx, "refit.box", sizeof(float) * 6 * ni, &st);
-    if (!box) return st;
-    Launch l{ctx->stream, ctx->grid_cap};
-    launch_zero(l, (float*)flags, ni);
+    int* flags = nullptr;
+    float* box = nullptr;
+    if (!s->nodes4) {
+        flags = (int*)scratch(ctx, "refit.flags", sizeof(int) * ni, &st);
+        if (!flags) return st;
+        box = (float*)scratch(ctx, "refit.box", sizeof(float) * 6 * ni, &st);
+        if (!box) return st;
+        Launch l{ctx->stream, ctx->grid_cap};
+        launch_zero(l, (float*)flags, ni);
+    }
     RefitArgs a{positions, s->F, s->order, s->child, s->parent_int, s->parent_leaf, flags, box, s->nt,
                 s->nodes, s->tris, s->nodes4, s->map4, s->nodes4 ? s->nnodes4 : 0};
-    if (!hip_ok(ctx, refit_bvh(ctx->stream, a), "scene refit")) return DPCS_E_DEVICE;
+    if (!hip_ok(ctx, refit_bvh(ctx->stream, a, s->level4, s->nlevels4), "scene refit"))
+        return DPCS_E_DEVICE;
     s->edges_valid = false;   // vertices may have met or parted: the edge table is welded again
     ctx->err.clear();
     return DPCS_OK;

@@ -61,6 +61,7 @@ struct dpcs_scene_s {
     int* parent_int = nullptr;
     int* parent_leaf = nullptr;
     int* map4 = nullptr;
+    int level4[dpcs::MAX_LEVELS4 + 1] = {0}, nlevels4 = 0;   // first 4-wide node of every level, and nnodes4
     int nv = 0;
     int nt = 0, nnodes = 0, nnodes4 = 0, depth = 0;
     float tmin = 0.0f;
