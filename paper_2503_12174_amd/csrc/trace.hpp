@@ -14,7 +14,7 @@
 // Triangle record (64 B, half a cache line): v0 (w = original triangle index bits), v1 (w = u0),
 // v2 (w = v0 of the texture coordinates), then (u1, v1, u2, v2): a triangle test and a
 // vertex's shading each touch one aligned 64-byte block.  With 48-byte vertex records and
-// 32-byte coordinate records apart a vertex's shading touched 2.4 lines: 256 x 256 x 16 of the
+// 32-byte coordinate records apart a vertex's shading touched 2.4 lines: 256 x 256 x 64 of the
 // 50k-triangle corner 1596 us, 1587 with this record; a step of its fit 2348 us, 2313.
 //
 // Closest hit: smallest t in (tmin, tmax); equal t -> smaller original triangle
@@ -285,7 +285,7 @@ __device__ __forceinline__ void cmpx(float& ka, int& ra, float& kb, int& rb) {
 // FMA, which the relative widening covers; it needs no absolute term that would grow for
 // near-axis-parallel rays.  The widening, t x (1 -+ 4e-6), is in the constants, so a box
 // test takes no product for it (the closest-hit loop is bound by vector issue: 256 x 256 x
-// 16 of the 50k-triangle corner 1583 us with the two products, 1580 without, and 1587 before
+// 64 of the 50k-triangle corner 1583 us with the two products, 1580 without, and 1587 before
 // the triangle test lost its swap of two axes; with an environment map 2200, 2193, 2180).  An axis along which the ray does not move
 // (|d| < 2^-80, or 0) takes the reciprocal 2^80; every offset is widened by 2^-40 in space
 // besides, so such a slab lets pass exactly the boxes that hold the ray's coordinate, faces
