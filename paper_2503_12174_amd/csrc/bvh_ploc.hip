@@ -14,7 +14,8 @@
 //
 // Collapse: breadth first, one level per launch; each 4-wide node takes a binary node's
 // two children and keeps opening the internal child with the largest surface area (the
-// first such child on a tie) until it holds four.  The next level is numbered by a prefix
+// first such child on a tie) until it holds four; its internal children take its first
+// slots.  The next level is numbered by a prefix
 // sum over this level's nodes in order, so the numbering is breadth first and the top of
 // the tree is the leading block of nodes (what a traversal workgroup stages in LDS).  The
 // pass also records the binary node or leaf behind every slot (for refits), the worst
@@ -279,6 +280,16 @@ __device__ int pick_kids(const float4* __restrict__ nodes, int ni, int b, Kid k[
         k[cnt] = bin_kid(nodes, c, 1);
         ++cnt;
     }
+    // the internal children first, each kind in order: they get consecutive numbers, and a
+    // traversal has a child's number from its slot
+    Kid in[4], lf[4];
+    int ni_ = 0, nl = 0;
+    for (int j = 0; j < cnt; ++j) {
+        if (k[j].ref >= 0) in[ni_++] = k[j];
+        else lf[nl++] = k[j];
+    }
+    for (int j = 0; j < ni_; ++j) k[j] = in[j];
+    for (int j = 0; j < nl; ++j) k[ni_ + j] = lf[j];
     return cnt;
 }
 

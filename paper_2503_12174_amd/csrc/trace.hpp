@@ -264,16 +264,10 @@ __device__ __forceinline__ bool traverse(const float4* __restrict__ nodes, const
     return best_leaf >= 0;
 }
 
-// compare-exchange on (key, ref) pairs, smaller key first
-__device__ __forceinline__ void cmpx(float& ka, int& ra, float& kb, int& rb) {
-    if (kb < ka) {
-        const float k = ka;
-        ka = kb;
-        kb = k;
-        const int r = ra;
-        ra = rb;
-        rb = r;
-    }
+__device__ __forceinline__ void sort2(uint32_t& a, uint32_t& b) {
+    const uint32_t lo = min(a, b);
+    b = max(a, b);
+    a = lo;
 }
 
 // Ray constants of the 4-wide box tests.  Per axis, the sign of the direction says
@@ -335,17 +329,15 @@ __device__ __forceinline__ Box4Ray box4_setup(V3 o, V3 d) {
     return r;
 }
 
-// entry distance of the ray into a child box of a node (near / far planes as loaded),
-// widened by 4e-6 relative like box_enter; NaN where missed, so a single test
-// `t <= bound` both checks the hit and the bound.  (A negative entry or exit is
-// scaled the wrong way, which the clamp to tmin > 0 makes irrelevant.)
-__device__ __forceinline__ float box4_enter(const Box4Ray& r, float nx, float ny, float nz, float fx, float fy,
-                                            float fz, float tmin, float tmax) {
-    float tn = fmaxf(fmaxf(fmaf(nx, r.ix, r.anx), fmaf(ny, r.iy, r.any)), fmaf(nz, r.iz, r.anz));
-    float tf = fminf(fminf(fmaf(fx, r.jx, r.afx), fmaf(fy, r.jy, r.afy)), fmaf(fz, r.jz, r.afz));
+// Whether the ray meets a child box of a node (near / far planes as loaded) before tmax,
+// and the entry distance tn.  (A negative entry or exit is scaled the wrong way, which the
+// clamp to tmin > 0 makes irrelevant.)
+__device__ __forceinline__ bool box4_hit(const Box4Ray& r, float nx, float ny, float nz, float fx, float fy, float fz,
+                                         float tmin, float tmax, float& tn) {
+    tn = fmaxf(fmaxf(fmaf(nx, r.ix, r.anx), fmaf(ny, r.iy, r.any)), fmaf(nz, r.iz, r.anz));
     tn = fmaxf(tn, tmin);
-    tf = fminf(tf, tmax);
-    return tn <= tf ? tn : __builtin_nanf("");
+    const float tf = fminf(fminf(fmaf(fx, r.jx, r.afx), fmaf(fy, r.jy, r.afy)), fmaf(fz, r.jz, r.afz));
+    return tn <= fminf(tf, tmax);
 }
 
 // The top of the 4-wide tree in LDS: the collapse numbers nodes breadth first, so nodes
@@ -366,13 +358,13 @@ __device__ __forceinline__ TopNodes stage_top(float4* lds, const float4* __restr
     return TopNodes{lds, 128u * (uint32_t)n};
 }
 
-// One 4-wide query's state: the ray constants, the best hit so far, the stack depth and
-// the next node (-1: the query has ended).
+// One 4-wide query's state: the ray constants, the best hit so far, the stack depth, the
+// next node (-1: the walk has ended) and a leaf ~pend whose triangle is still to be tested (0: none).
 struct Trav4 {
     Box4Ray br;
     WtRay wr;
     float tmin, best_t;
-    int skip, best_leaf, sp, node;
+    int skip, best_leaf, sp, node, pend;
 };
 
 __device__ __forceinline__ void trav4_start(Trav4& s, V3 o, V3 d, float tmin, float tmax, int skip) {
@@ -384,11 +376,40 @@ __device__ __forceinline__ void trav4_start(Trav4& s, V3 o, V3 d, float tmin, fl
     s.best_leaf = -1;
     s.sp = 0;
     s.node = 0;
+    s.pend = 0;
+}
+
+// this lane's bit of a lane mask
+__device__ __forceinline__ bool lane_of(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// the triangle of leaf ~s.pend
+template <bool ANY, class VIS>
+__device__ __forceinline__ void trav4_leaf(Trav4& s, const float4* __restrict__ tris, VIS& vis) {
+    V3 v0, v1, v2;
+    int prim;
+    vis.tri();
+    load_tri(tris, ~s.pend, v0, v1, v2, prim);
+    float t;
+    // the triangle left is rejected after the test, not before it: checked first, the
+    // prim id was loaded alone and the vertices only after the compare (two dependent
+    // round trips to memory per test)
+    const bool hit = wt_hit(s.wr, v0, v1, v2, t);
+    if (!hit | !(t > s.tmin) | (prim == s.skip)) return;
+    bool take = t < s.best_t;
+    if constexpr (!ANY) {
+        // equal t: the smaller original index wins (the current best's index is read
+        // back from its record, so no register holds it)
+        if (!take && t == s.best_t && s.best_leaf >= 0) take = prim < __float_as_int(tris[4 * (size_t)(uint32_t)s.best_leaf].w);
+    }
+    if (take) {
+        s.best_t = t;
+        s.best_leaf = ~s.pend;
+    }
 }
 
 // One node of the query (s.node >= 0): its four box tests, the leaf children hit tested
-// at once, the internal children still in range visited nearest first (the others
-// pushed, farthest first); s.node becomes the next node, or -1 when the query ends.
+// or held back, the internal children still in range visited nearest first (the others
+// pushed, farthest first); s.node becomes the next node, or -1 when the walk ends.
 template <bool ANY, int SHORT, int TBK, class VIS>
 __device__ __forceinline__ void trav4_visit(Trav4& s, const float4* __restrict__ nodes, const float4* __restrict__ tris,
                                             int* stack, int* spill, int lane, VIS& vis, TopNodes top) {
@@ -422,83 +443,81 @@ __device__ __forceinline__ void trav4_visit(Trav4& s, const float4* __restrict__
         fz = *reinterpret_cast<const float4*>(base + (az ^ FAR_Z));
         cr = *reinterpret_cast<const int4*>(base + (nb + 96u));
     }
-    const int cc[4] = {cr.x, cr.y, cr.z, cr.w};
-    float tc[4];
-    tc[0] = box4_enter(s.br, nx.x, ny.x, nz.x, fx.x, fy.x, fz.x, s.tmin, s.best_t);
-    tc[1] = box4_enter(s.br, nx.y, ny.y, nz.y, fx.y, fy.y, fz.y, s.tmin, s.best_t);
-    tc[2] = box4_enter(s.br, nx.z, ny.z, nz.z, fx.z, fy.z, fz.z, s.tmin, s.best_t);
-    tc[3] = box4_enter(s.br, nx.w, ny.w, nz.w, fx.w, fy.w, fz.w, s.tmin, s.best_t);
-    // Leaf children whose box is hit, tested one per pass; the wave runs as many passes
-    // as its busiest lane needs.
-    uint32_t lm = 0u;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        if (cc[k] < 0 && tc[k] <= s.best_t) lm |= 1u << k;
-    auto test_leaf = [&](int leaf) {
-        V3 v0, v1, v2;
-        int prim;
-        vis.tri();
-        load_tri(tris, leaf, v0, v1, v2, prim);
-        float t;
-        // the triangle left is rejected after the test, not before it: checked first, the
-        // prim id was loaded alone and the vertices only after the compare (two dependent
-        // round trips to memory per test)
-        const bool hit = wt_hit(s.wr, v0, v1, v2, t);
-        if (!hit | !(t > s.tmin) | (prim == s.skip)) return;
-        bool take = t < s.best_t;
-        if constexpr (!ANY) {
-            // equal t: the smaller original index wins (the current best's index is read
-            // back from its record, so no register holds it)
-            if (!take && t == s.best_t && s.best_leaf >= 0) take = prim < __float_as_int(tris[4 * (size_t)(uint32_t)s.best_leaf].w);
+    // The outcomes as lane masks: the choice of leaves and children is scalar work beside the
+    // vector unit, which bounds the loop.  With it, the packed sort keys and one branch for
+    // spilled stack entries, the launch of first bounces (256 x 256 x 64, 50k triangles) issues
+    // 196 M vector instructions instead of 244 M, and the three bounces take 767 us instead of
+    // 812; the loads of whole nodes by 64 lanes apart keep the address unit 75 % busy beside it.
+    float tn[4];
+    uint64_t h0 = __ballot(box4_hit(s.br, nx.x, ny.x, nz.x, fx.x, fy.x, fz.x, s.tmin, s.best_t, tn[0]));
+    uint64_t h1 = __ballot(box4_hit(s.br, nx.y, ny.y, nz.y, fx.y, fy.y, fz.y, s.tmin, s.best_t, tn[1]));
+    uint64_t h2 = __ballot(box4_hit(s.br, nx.z, ny.z, nz.z, fx.z, fy.z, fz.z, s.tmin, s.best_t, tn[2]));
+    uint64_t h3 = __ballot(box4_hit(s.br, nx.w, ny.w, nz.w, fx.w, fy.w, fz.w, s.tmin, s.best_t, tn[3]));
+    // Leaf children whose box is hit.  A lane holds one of them back (pend); all lanes that
+    // hold one test it together once a lane has found a second.  Tested as they came, the
+    // loop ran 0.82 triangle tests per node with 9 of 64 lanes in each (incoherent rays);
+    // held back, the closest hits of 256 x 256 x 64 in the 50k-triangle corner beyond the camera's
+    // take 797 us instead of 839, at a bound on the distance that is a step late.  (Two held
+    // per lane: 908; a list per lane in LDS and leaves on the stack were slower still.)
+    const uint64_t f0 = __ballot(cr.x < 0), f1 = __ballot(cr.y < 0), f2 = __ballot(cr.z < 0), f3 = __ballot(cr.w < 0);
+    uint64_t l0 = h0 & f0, l1 = h1 & f1, l2 = h2 & f2, l3 = h3 & f3;
+    h0 &= ~f0, h1 &= ~f1, h2 &= ~f2, h3 &= ~f3;
+    if ((l0 | l1 | l2 | l3) != 0ull) {
+        // the first leaf of the list, removed from it in the lanes `on`
+        auto next = [&](uint64_t on) {
+            const int leaf = lane_of(l0) ? cr.x : (lane_of(l1) ? cr.y : (lane_of(l2) ? cr.z : cr.w));
+            l3 &= ~(on & ~(l0 | l1 | l2));
+            l2 &= ~(on & ~(l0 | l1));
+            l1 &= ~(on & ~l0);
+            l0 &= ~on;
+            return leaf;
+        };
+        const uint64_t free = __ballot(s.pend >= 0) & (l0 | l1 | l2 | l3);
+        const int leaf = next(free);
+        s.pend = lane_of(free) ? leaf : s.pend;
+        if ((l0 | l1 | l2 | l3) != 0ull) {
+#pragma clang loop unroll(disable)
+            do {
+                if (s.pend < 0) trav4_leaf<ANY>(s, tris, vis);
+                const uint64_t more = l0 | l1 | l2 | l3;
+                const int nl = next(~0ull);
+                s.pend = lane_of(more) ? nl : 0;
+            } while ((l0 | l1 | l2 | l3) != 0ull);
+            h0 &= __ballot(tn[0] <= s.best_t), h1 &= __ballot(tn[1] <= s.best_t);
+            h2 &= __ballot(tn[2] <= s.best_t), h3 &= __ballot(tn[3] <= s.best_t);
         }
-        if (take) {
-            s.best_t = t;
-            s.best_leaf = leaf;
-        }
-    };
-    {
-        // the lane's hit leaves compacted: pass j runs when some lane has more than j of
-        // them (fewer passes than one per slot any lane uses)
-        const int nl = __popc(lm);
-        uint32_t m = lm;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (j < nl) {
-                const int k = __builtin_ctz(m);
-                m &= m - 1u;
-                test_leaf(~(k == 0 ? cc[0] : (k == 1 ? cc[1] : (k == 2 ? cc[2] : cc[3]))));
-            }
     }
-    // internal children still in range (a missed box reports NaN; one entered only at
-    // +inf is dropped like a miss)
-    float key[4];
-    int ref[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const bool in = cc[k] >= 0 && tc[k] <= s.best_t;
-        key[k] = in ? tc[k] : __builtin_inff();
-        ref[k] = cc[k];
-    }
-    cmpx(key[0], ref[0], key[1], ref[1]);
-    cmpx(key[2], ref[2], key[3], ref[3]);
-    cmpx(key[0], ref[0], key[2], ref[2]);
-    cmpx(key[1], ref[1], key[3], ref[3]);
-    cmpx(key[1], ref[1], key[2], ref[2]);
+    // internal children still in range: the slot number in the two lowest bits of the entry
+    // distance (positive, so ordered as an integer), sorted by minima and maxima; a node's
+    // internal children are its first slots, numbered one after the other, so the slot
+    // gives the child
+    uint32_t k0 = lane_of(h0) ? (__float_as_uint(tn[0]) & ~3u) : ~0u, k1 = lane_of(h1) ? (__float_as_uint(tn[1]) & ~3u) | 1u : ~0u;
+    uint32_t k2 = lane_of(h2) ? (__float_as_uint(tn[2]) & ~3u) | 2u : ~0u, k3 = lane_of(h3) ? (__float_as_uint(tn[3]) & ~3u) | 3u : ~0u;
+    sort2(k0, k1);
+    sort2(k2, k3);
+    sort2(k0, k2);
+    sort2(k1, k3);
+    sort2(k1, k2);
     if (ANY && s.best_leaf >= 0) {   // any hit ends the query
         s.node = -1;
-    } else if (key[0] < __builtin_inff()) {
-        s.node = ref[0];
-        // every candidate is written to LDS, at sp, or at the lane's extra entry SHORT
-        // once the LDS part is full (a write that is not kept is overwritten or never
-        // read), so only the rare spill to global memory is a branch
-#pragma unroll
-        for (int k = 3; k >= 1; --k) {
-            const bool v = key[k] < __builtin_inff();
-            stack[min(s.sp, SHORT) * TBK + lane] = ref[k];
-            if constexpr (SHORT < MAX_STACK)
-                if (v && s.sp >= SHORT && s.sp < MAX_STACK) spill[(s.sp - SHORT) * TBK + lane] = ref[k];
-            s.sp = v && s.sp < MAX_STACK ? s.sp + 1 : s.sp;
-        }
+    } else if (k0 != ~0u) {
+        s.node = cr.x + (int)(k0 & 3u);
+        // the others pushed, farthest first: each is written to LDS, at its place, or at the
+        // lane's extra entry SHORT once the LDS part is full (a write that is not kept is
+        // overwritten or never read); one branch for the rare ones that belong in global memory
+        const bool p3 = k3 != ~0u, p2 = k2 != ~0u, p1 = k1 != ~0u;
+        const int r3 = cr.x + (int)(k3 & 3u), r2 = cr.x + (int)(k2 & 3u), r1 = cr.x + (int)(k1 & 3u);
+        const int a3 = s.sp, a2 = a3 + (p3 ? 1 : 0), a1 = a2 + (p2 ? 1 : 0), sp = a1 + (p1 ? 1 : 0);
+        stack[min(a3, SHORT) * TBK + lane] = r3;
+        stack[min(a2, SHORT) * TBK + lane] = r2;
+        stack[min(a1, SHORT) * TBK + lane] = r1;
+        if constexpr (SHORT < MAX_STACK)
+            if (sp > SHORT) {
+                if (p3 && a3 >= SHORT && a3 < MAX_STACK) spill[(a3 - SHORT) * TBK + lane] = r3;
+                if (p2 && a2 >= SHORT && a2 < MAX_STACK) spill[(a2 - SHORT) * TBK + lane] = r2;
+                if (p1 && a1 >= SHORT && a1 < MAX_STACK) spill[(a1 - SHORT) * TBK + lane] = r1;
+            }
+        s.sp = min(sp, MAX_STACK);
     } else if (s.sp > 0) {
         --s.sp;
         // an LDS read always (clamped index) and a global read only for spilled entries:
@@ -527,6 +546,7 @@ __device__ __forceinline__ bool traverse4(const float4* __restrict__ nodes, cons
     // branch of the one loop, instead of a nested loop whose lanes wait until every
     // lane of the wave needs a pop
     while (s.node >= 0) trav4_visit<ANY, SHORT, TBK>(s, nodes, tris, stack, spill, lane, vis, top);
+    if (s.pend < 0 && !(ANY && s.best_leaf >= 0)) trav4_leaf<ANY>(s, tris, vis);
     // the barycentrics of the hit: the same test on its triangle again (same arithmetic,
     // same bits), which keeps them out of the loop's registers
     float bb1 = 0.f, bb2 = 0.f;
