@@ -509,7 +509,7 @@ __global__ void __launch_bounds__(TB) ADJ_SHADOW_OCCUPANCY k_adj_shadow(Queues q
     __shared__ float4 ltop[UNI ? 8 * TOP_NODES : 1];
     int* spill = q.spill + (size_t)blockIdx.x * TB * SPILL;
     const uint32_t n = q.cnt[shadow_slot(nxt ^ 1, which)];
-    TopNodes top{nullptr, 0u};
+    TopNodes top{ltop, 0u};   // (a constant base: its offset is part of the LDS reads)
     if constexpr (UNI)   // one tree for the whole launch: stage its top levels
         if (uni.nodes4) top = stage_top<TB>(ltop, uni.nodes4, uni.top_nodes);
     // the loop bound is uniform per workgroup so every lane reaches the wave-level scatter

@@ -110,7 +110,7 @@ __global__ void __launch_bounds__(TB) TRAVERSAL_OCCUPANCY k_trace(Queues q, int 
         q.cnt[shadow_slot(cur, 0)] = 0u;
         q.cnt[shadow_slot(cur, 1)] = 0u;
     }
-    TopNodes top{nullptr, 0u};
+    TopNodes top{ltop, 0u};   // (a constant base: its offset is part of the LDS reads)
     if constexpr (UNI)   // one tree for the whole launch: stage its top levels
         if (uni.nodes4) top = stage_top<TB>(ltop, uni.nodes4, uni.top_nodes);
     for (uint32_t i = blockIdx.x * TB + threadIdx.x; i < n; i += gridDim.x * TB) {
@@ -321,7 +321,7 @@ __global__ void __launch_bounds__(TB) SHADOW_OCCUPANCY k_shadow(Queues q, int wh
     __shared__ float4 ltop[TREE ? 8 * TOP_NODES : 1];
     int* spill = q.spill + (size_t)blockIdx.x * TB * SPILL;
     const uint32_t n = q.cnt[shadow_slot(depth & 1, which)];
-    TopNodes top{nullptr, 0u};
+    TopNodes top{ltop, 0u};   // (a constant base: its offset is part of the LDS reads)
     if constexpr (TREE)
         if (uni.nodes4) top = stage_top<TB>(ltop, uni.nodes4, uni.top_nodes);
     for (uint32_t i = blockIdx.x * TB + threadIdx.x; i < n; i += gridDim.x * TB) {
