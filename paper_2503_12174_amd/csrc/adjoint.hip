@@ -647,12 +647,12 @@ __device__ __forceinline__ void store_record(float* __restrict__ p, const float*
 template <int C, int RS>
 __device__ __forceinline__ void bin_hist(const MapBins& mb, uint32_t chunk, uint32_t* h, uint32_t& hmax) {
     const uint32_t n = map_records(mb);
-    const uint32_t b0 = chunk * BIN_CHUNK;
+    const uint32_t b0 = chunk * (uint32_t)mb.chunk;
     if (b0 >= n) return;   // uniform per workgroup
     for (int k = threadIdx.x; k < mb.nb; k += BIN_TB) h[k] = 0u;
     if (threadIdx.x == 0) hmax = 0u;
     __syncthreads();
-    const uint32_t e = min(n, b0 + BIN_CHUNK);
+    const uint32_t e = min(n, b0 + (uint32_t)mb.chunk);
     float m = 0.f;
     for (uint32_t base = b0; base < e; base += BIN_TB) {
         const uint32_t i = base + threadIdx.x;
@@ -737,9 +737,9 @@ __global__ void __launch_bounds__(1024) k_bin_scan(MapBins a, MapBins b) {
 template <int RS>
 __device__ __forceinline__ void bin_place(const MapBins& mb, uint32_t chunk, uint32_t* cnt) {
     const uint32_t n = map_records(mb);
-    const uint32_t b0 = chunk * BIN_CHUNK;
+    const uint32_t b0 = chunk * (uint32_t)mb.chunk;
     if (b0 >= n) return;   // uniform per workgroup
-    const uint32_t e = min(n, b0 + BIN_CHUNK);
+    const uint32_t e = min(n, b0 + (uint32_t)mb.chunk);
     const uint32_t* off = mb.bins + mb.nb;
     const uint32_t* rb = mb.rowbase + (size_t)chunk * mb.nb;
     for (int k = threadIdx.x; k < mb.nb; k += BIN_TB) cnt[k] = off[k] + rb[k];
@@ -755,6 +755,7 @@ __device__ __forceinline__ void bin_place(const MapBins& mb, uint32_t chunk, uin
         }
 #pragma unroll
         for (int u = 0; u < BIN_U; ++u) {
+            if (base + u * BIN_TB >= e) break;   // (uniform)
             const uint32_t bin = valid[u] ? (uint32_t)map_bin(mb, __float_as_uint(v[u][0])) : 0u;
             const uint32_t pos = lds_bin_add(cnt, valid[u], bin);
             if (!valid[u] || (int64_t)pos >= mb.cap) continue;   // pos < cap always for consistent counts
@@ -1461,9 +1462,9 @@ bool map_tiling(int W, int H, int& T, int& nbx, int& nby) {
 template <int CA, int RSA, int CB, int RSB>
 static void flush_maps(const Launch& l, const MapBins& a, float* oa, int sa, const MapBins* b, float* ob, int sb) {
     const MapBins& bb = b ? *b : a;
-    const uint32_t ha = (uint32_t)((a.cap + BIN_CHUNK - 1) / BIN_CHUNK), hb = b ? (uint32_t)((b->cap + BIN_CHUNK - 1) / BIN_CHUNK) : 0u;
+    const uint32_t ha = (uint32_t)bin_chunks(a.fill, a.chunk), hb = b ? (uint32_t)bin_chunks(b->fill, b->chunk) : 0u;
     // units are taken in turn by two resident rounds of workgroups at most (two per CU fit)
-    const uint32_t units = (uint32_t)(map_units(a.cap, a.nb) + (b ? map_units(b->cap, b->nb) : 0));
+    const uint32_t units = (uint32_t)(map_units(a.fill, a.nb) + (b ? map_units(b->fill, b->nb) : 0));
     const uint32_t acc = std::min<uint32_t>(units, 1024u);
     const uint32_t ta = grid_of((int64_t)a.W * a.H, 256), tb = b ? grid_of((int64_t)b->W * b->H, 256) : 0u;
     hipLaunchKernelGGL((k_bin_hist<CA, RSA, CB, RSB>), dim3(ha + hb), dim3(BIN_TB), 0, l.st, a, bb, ha);

@@ -156,9 +156,10 @@ constexpr int ACC_CHUNK = 4096; // most records of one tile a workgroup of the a
                                 // at once (a unit); the stage holds one block of (T + 1)^2 x C
                                 // sums per unit
 constexpr int ACC_TB = 1024;    // threads per workgroup of the accumulation
-constexpr int BIN_CHUNK = 16384;// records per workgroup of the histogram and the placement
-constexpr int BIN_TB = 1024;    // their threads per workgroup: 16 waves share one LDS
-                                // histogram, so the few chunks of a flush still fill the chip
+constexpr int BIN_CHUNK = 4096; // records per workgroup of the histogram and the placement, at
+constexpr int BIN_CHUNK_MIN = 1024;   // most and at least (bin_chunk)
+constexpr int BIN_BLOCKS = 2048;      // workgroups they are spread over before chunks grow
+constexpr int BIN_TB = 1024;    // their threads per workgroup: 16 waves share one LDS histogram
 constexpr int BIN_U = 4;        // records a thread of the placement loads at once
 static_assert(BIN_CHUNK % (BIN_TB * BIN_U) == 0, "placement chunking");
 constexpr long long STAGE_NAN = -0x7fffffffffffffffll - 1;   // INT64_MIN
@@ -171,10 +172,24 @@ struct MapBins {
     uint32_t* bins;      // counts[nb], offsets[nb + 1], first units[nb + 1], fixed-point exponent
                          // E, largest |value| (float bits): map_bin_words(nb)
     uint32_t* unit_tile; // tile of every unit
-    uint32_t* rowbase;   // per (BIN_CHUNK chunk, tile): where the chunk's records start in the tile
+    uint32_t* rowbase;   // per (chunk, tile): where the chunk's records start in the tile
     int64_t cap;         // record capacity
+    int64_t fill;        // most records before the next flush (<= cap)
+    int chunk;           // records per workgroup of the histogram and the placement
     int W, H, T, nbx, nby, nb;
 };
+
+// Records per workgroup of a flush of at most `fill` records.  A larger chunk has fewer global
+// atomics and rows per record, a smaller one more workgroups and waves in flight.  Histogram +
+// placement, by chunk: 64 x 64 x 32 (fill 0.4 M) 27 + 24 us at 16384, 11 + 10 at 4096, 6 + 6 at
+// 1024; 256 x 256 x 16 (4.2 M) 19 + 21 at 2048, 28 + 23 at 1024; 256 x 256 x 64 (16.8 M) 51 + 126
+// at 16384, 53 + 83 at 4096, 62 + 82 at 2048, 102 + 106 at 1024.
+constexpr int bin_chunk(int64_t fill) {
+    int c = BIN_CHUNK_MIN;
+    while (c < BIN_CHUNK && fill > (int64_t)c * BIN_BLOCKS) c *= 2;
+    return c;
+}
+constexpr int64_t bin_chunks(int64_t fill, int chunk) { return (fill + chunk - 1) / chunk; }
 
 constexpr int64_t map_bin_words(int64_t nb) { return 3 * nb + 4; }
 // most units of cap records in nb tiles

@@ -153,7 +153,8 @@ void make_map_bins(dpcs_context ctx, ZeroList& zl, MapBins& mb, const char* name
     const int nb = nbx * nby;
     const size_t rec = 4 * (size_t)RS * cap, units = (size_t)map_units(cap, nb);
     const size_t stage = 8 * units * (T + 1) * (T + 1) * C;
-    const size_t rows = 4 * (size_t)((cap + BIN_CHUNK - 1) / BIN_CHUNK) * nb;
+    const int chunk = bin_chunk(cap);
+    const size_t rows = 4 * (size_t)bin_chunks(cap, chunk) * nb;
     const size_t bytes = 2 * rec + stage + rows + 4 * (size_t)map_bin_words(nb) + 4 * units + 8 * 256;
     dpcs_status st = DPCS_OK;
     char* b = (char*)scratch(ctx, name, bytes, &st);
@@ -173,7 +174,8 @@ void make_map_bins(dpcs_context ctx, ZeroList& zl, MapBins& mb, const char* name
     mb.bins = (uint32_t*)take(4 * (size_t)map_bin_words(nb));
     mb.unit_tile = (uint32_t*)take(4 * units);
     mb.rowbase = (uint32_t*)take(rows);
-    mb.cap = cap;
+    mb.cap = mb.fill = cap;
+    mb.chunk = chunk;
     mb.W = W;
     mb.H = H;
     mb.T = T;

@@ -103,17 +103,19 @@ struct Seg {
 // map (1024 x 1024: 16-texel tiles, 4096 of them); a wave binds them to its request's
 // map size.  Layout: records, sorted records, stage blocks, count, bins, unit tiles, chunk
 // row bases.
+constexpr int LOOP_ROW_CHUNK = 16384;
 size_t loop_bins_bytes(int64_t cap, int C, int RS) {
     const size_t rec = 4 * (size_t)RS * cap;
     const size_t units = (size_t)map_units(cap, MAP_MAX_BINS);
     const size_t stage = 8 * units * (MAP_MAX_T + 1) * (MAP_MAX_T + 1) * C;
-    const size_t rows = 4 * (size_t)((cap + BIN_CHUNK - 1) / BIN_CHUNK) * MAP_MAX_BINS;
+    const size_t rows = 4 * (size_t)bin_chunks(cap, LOOP_ROW_CHUNK) * MAP_MAX_BINS;
     auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
     return 2 * up(rec) + up(stage) + up(4) + up(4 * (size_t)map_bin_words(MAP_MAX_BINS)) + up(4 * units) + up(rows);
 }
 
-// the buffers at base as bins of a W x H map (false: the map is too large to bin)
-bool loop_bins_view(char* base, int64_t cap, int C, int RS, int W, int H, MapBins& mb) {
+// the buffers at base as bins of a W x H map for flushes of at most `fill` records (false:
+// the map is too large to bin)
+bool loop_bins_view(char* base, int64_t cap, int64_t fill, int C, int RS, int W, int H, MapBins& mb) {
     mb = MapBins{};
     int T = 0, nbx = 0, nby = 0;
     if (!base || !map_tiling(W, H, T, nbx, nby)) return false;
@@ -136,6 +138,12 @@ bool loop_bins_view(char* base, int64_t cap, int C, int RS, int W, int H, MapBin
     b += up(4 * units);
     mb.rowbase = (uint32_t*)b;
     mb.cap = cap;
+    mb.fill = std::min(fill, cap);
+    // (the rows hold chunks of LOOP_ROW_CHUNK records of the most tiles: smaller chunks while
+    // they fit)
+    mb.chunk = bin_chunk(mb.fill);
+    while (mb.chunk < LOOP_ROW_CHUNK && bin_chunks(mb.fill, mb.chunk) * nbx * nby > bin_chunks(cap, LOOP_ROW_CHUNK) * MAP_MAX_BINS)
+        mb.chunk *= 2;
     mb.W = W;
     mb.H = H;
     mb.T = T;
@@ -360,8 +368,9 @@ void dpcs_server_s::wave(Launch& l) {
         if (replay) {
             for (const Seg& s : segs)
                 if (s.q->adjoint) binq = binq == nullptr || binq == s.q ? s.q : (Req*)-1;
-            if (binq == (Req*)-1 || !loop_bins_view(tex_bins, tex_bins_cap, 5, 8, binq->r.tw, binq->r.th, ab.tb) ||
-                !loop_bins_view(ep_bins, ep_bins_cap, 3, 6, binq->r.Wp, binq->r.Hp, ab.eb)) {
+            const int64_t fill = n_adj * std::min(max_depth, BIN_DEPTHS);   // a record per vertex and map
+            if (binq == (Req*)-1 || !loop_bins_view(tex_bins, tex_bins_cap, fill, 5, 8, binq->r.tw, binq->r.th, ab.tb) ||
+                !loop_bins_view(ep_bins, ep_bins_cap, fill, 3, 6, binq->r.Wp, binq->r.Hp, ab.eb)) {
                 binq = nullptr;
             } else {   // a fresh histogram for this map size
                 ZeroList zl(l);
