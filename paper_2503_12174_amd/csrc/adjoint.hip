@@ -967,9 +967,9 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay(Queues q, AdjQueues aq, in
         float4 b, rl = {};
         int lit;
         if (depth == 0) {
-            if constexpr (UNI) {   // the dense camera wave: queue index = batch sample index
+            if constexpr (UNI) {   // queue index i: sample i of the request in this wave
                 o = PathO{uni.cam_o[0], uni.cam_o[1], uni.cam_o[2], 0, -1};
-                dd.g = i - uni.sid_base + uni.g_base;
+                dd.g = uni.g_base + i;
             } else {
                 o = nt_ld(&q.po[cur][i]);
                 dd = nt_ld(&q.pd[cur][i]);
@@ -1157,9 +1157,9 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq
         PathD dd;
         float4 b, rl = {};
         int lit;
-        if (depth == 0) {   // the dense camera wave: queue index = batch sample index
+        if (depth == 0) {   // queue index i: sample i of this wave
             o = PathO{r.cam_o[0], r.cam_o[1], r.cam_o[2], 0, -1};
-            dd.g = i - r.sid_base + r.g_base;
+            dd.g = r.g_base + i;
             const ReplayStart t = replay_start<TEX>(r, dd.g, sample_L, q.L, aq.delta);
             lit = t.lit;
             b = t.dl;

@@ -104,6 +104,7 @@ struct Seg {
 // map size.  Layout: records, sorted records, stage blocks, count, bins, unit tiles, chunk
 // row bases.
 constexpr int LOOP_ROW_CHUNK = 16384;
+constexpr int64_t LOOP_BIN_PATHS = 1 << 17;   // paths per request (on average) from which several are binned
 size_t loop_bins_bytes(int64_t cap, int C, int RS) {
     const size_t rec = 4 * (size_t)RS * cap;
     const size_t units = (size_t)map_units(cap, MAP_MAX_BINS);
@@ -359,62 +360,81 @@ void dpcs_server_s::wave(Launch& l) {
     for (const Seg& s : segs) launch_finalize(l, q, s.q->r, table, s.q->slot, s.a, s.b);
     // adjoint replay of the compensation-step segments (a dense prefix of the wave)
     if (any_adj) {
-        // compensation paths of one request, replayed from records, with maps the binning
-        // buffers hold: the replay runs in the one-request form and its map cotangents are
-        // binned and flushed into the request's maps like a single VJP's, instead of one
-        // global atomic per texel and channel
-        Req* binq = nullptr;
-        AdjQueues ab = aq;
-        if (replay) {
-            for (const Seg& s : segs)
-                if (s.q->adjoint) binq = binq == nullptr || binq == s.q ? s.q : (Req*)-1;
-            const int64_t fill = n_adj * std::min(max_depth, BIN_DEPTHS);   // a record per vertex and map
-            if (binq == (Req*)-1 || !loop_bins_view(tex_bins, tex_bins_cap, fill, 5, 8, binq->r.tw, binq->r.th, ab.tb) ||
-                !loop_bins_view(ep_bins, ep_bins_cap, fill, 3, 6, binq->r.Wp, binq->r.Hp, ab.eb)) {
-                binq = nullptr;
-            } else {   // a fresh histogram for this map size
-                ZeroList zl(l);
-                zl.add((float*)ab.tb.count, 1);
-                zl.add((float*)ab.tb.bins, map_bin_words(MAP_MAX_BINS));
-                zl.add((float*)ab.eb.count, 1);
-                zl.add((float*)ab.eb.bins, map_bin_words(MAP_MAX_BINS));
-                zl.launch();
-                ++st_binned;
-            }
-        }
+        // Compensation paths replayed from records, with maps the binning buffers hold: each
+        // request's replay runs in the one-request form, one request after the other, and its
+        // map cotangents are binned and flushed into its maps like a single VJP's, instead of
+        // one global atomic per texel and channel.  (Several requests of fewer than 2^17 paths
+        // each stay together: a step of 8 pairs took, together and apart, 1.68 and 1.69 ms at
+        // 2^16 paths, 1.88 and 1.75 at 2^17, 2.57 and 2.10 at 2^18; 16 pairs of 2^17 3.20 and 3.15.)
+        auto binned = [&](const Seg& s, AdjQueues& ab) {
+            const int64_t fill = (int64_t)(s.b - s.a) * s.q->r.spp * std::min(s.q->r.max_depth, BIN_DEPTHS);   // a record per vertex and map
+            ab = aq;
+            return loop_bins_view(tex_bins, tex_bins_cap, fill, 5, 8, s.q->r.tw, s.q->r.th, ab.tb) &&
+                   loop_bins_view(ep_bins, ep_bins_cap, fill, 3, 6, s.q->r.Wp, s.q->r.Hp, ab.eb);
+        };
+        AdjQueues ab;
+        bool all_binned = replay;
+        int64_t n_req = 0;
+        for (const Seg& s : segs)
+            if (s.q->adjoint) ++n_req, all_binned = all_binned && binned(s, ab);
+        all_binned = all_binned && (n_req == 1 || n_adj >= n_req * LOOP_BIN_PATHS);
+        if (all_binned) ++st_binned;
         for (const Seg& s : segs)
             if (s.q->adjoint) launch_adj_pixel(l, q, aq, s.q->r, s.a, s.b, nullptr, nullptr, !replay);
-        // queue sizes: the replay's rotate over their own slots; re-tracing, the
-        // closest-hit launch empties the queues shading appends to
-        if (binq || replay) launch_set_count(l, q.cnt, REPLAY_CNT, (uint32_t)n_adj, REPLAY_CNT + 1, REPLAY_CNT + 2);
-        else launch_set_count(l, q.cnt, 0, (uint32_t)n_adj, 1, 4);
-        for (const Seg& s : segs)   // (the one-request replay makes its camera rays itself)
-            if (s.q->adjoint && !binq) launch_adj_raygen(l, q, aq, s.q->r, s.q->slot, s.q->r.g_base, (s.b - s.a) * s.q->r.spp);
-        cur = 0;
-        for (int d = 0; d < max_depth; ++d) {
-            if (binq) {
-                launch_adj_replay(l, q, ab, cur, d, binq->r, nullptr, n_adj);
-                if ((d + 1) % BIN_DEPTHS == 0 || d == max_depth - 1) launch_map_flush(l, ab, binq->r);
-            } else if (replay) {
-                launch_adj_replay(l, q, aq, cur, d, any, table, n_adj);
-            } else {   // (adjoint shadow rays beside the next closest hit, as in the forward)
-                launch_trace(l, q, cur, any, nullptr, n_adj);
-                if (side_adj && d > 0) (void)hipStreamWaitEvent(st, ev_shadow, 0);
-                launch_adj_shade(l, q, aq, cur, d, any, table, n_adj);
-                if (side_adj) {
-                    (void)hipEventRecord(ev_shade, st);
-                    (void)hipStreamWaitEvent(side, ev_shade, 0);
-                    launch_adj_shadow(ls, qs, aq, 0, cur ^ 1, any, table, n_adj);
-                    if (env) launch_adj_shadow(ls, qs, aq, 1, cur ^ 1, any, table, n_adj);
-                    (void)hipEventRecord(ev_shadow, side);
-                } else {
-                    launch_adj_shadow(l, q, aq, 0, cur ^ 1, any, table, n_adj);
-                    if (env) launch_adj_shadow(l, q, aq, 1, cur ^ 1, any, table, n_adj);
+        if (all_binned) {
+            int tb_nb = -1, eb_nb = -1;   // tiles of the counters as they were last cleared
+            for (const Seg& s : segs) {
+                if (!s.q->adjoint) continue;
+                const uint32_t n = (s.b - s.a) * (uint32_t)s.q->r.spp;
+                (void)binned(s, ab);
+                if (ab.tb.nb != tb_nb || ab.eb.nb != eb_nb) {   // (a flush leaves its counters at 0)
+                    ZeroList zl(l);
+                    zl.add((float*)ab.tb.count, 1);
+                    zl.add((float*)ab.tb.bins, map_bin_words(ab.tb.nb));
+                    zl.add((float*)ab.eb.count, 1);
+                    zl.add((float*)ab.eb.bins, map_bin_words(ab.eb.nb));
+                    zl.launch();
+                    tb_nb = ab.tb.nb;
+                    eb_nb = ab.eb.nb;
+                }
+                launch_set_count(l, q.cnt, REPLAY_CNT, n, REPLAY_CNT + 1, REPLAY_CNT + 2);
+                cur = 0;
+                for (int d = 0; d < s.q->r.max_depth; ++d) {   // (it makes its camera rays itself)
+                    launch_adj_replay(l, q, ab, cur, d, s.q->r, nullptr, n);
+                    if ((d + 1) % BIN_DEPTHS == 0 || d == s.q->r.max_depth - 1) launch_map_flush(l, ab, s.q->r);
+                    cur ^= 1;
                 }
             }
-            cur ^= 1;
+        } else {
+            // queue sizes: the replay's rotate over their own slots; re-tracing, the
+            // closest-hit launch empties the queues shading appends to
+            if (replay) launch_set_count(l, q.cnt, REPLAY_CNT, (uint32_t)n_adj, REPLAY_CNT + 1, REPLAY_CNT + 2);
+            else launch_set_count(l, q.cnt, 0, (uint32_t)n_adj, 1, 4);
+            for (const Seg& s : segs)
+                if (s.q->adjoint) launch_adj_raygen(l, q, aq, s.q->r, s.q->slot, s.q->r.g_base, (s.b - s.a) * s.q->r.spp);
+            cur = 0;
+            for (int d = 0; d < max_depth; ++d) {
+                if (replay) {
+                    launch_adj_replay(l, q, aq, cur, d, any, table, n_adj);
+                } else {   // (adjoint shadow rays beside the next closest hit, as in the forward)
+                    launch_trace(l, q, cur, any, nullptr, n_adj);
+                    if (side_adj && d > 0) (void)hipStreamWaitEvent(st, ev_shadow, 0);
+                    launch_adj_shade(l, q, aq, cur, d, any, table, n_adj);
+                    if (side_adj) {
+                        (void)hipEventRecord(ev_shade, st);
+                        (void)hipStreamWaitEvent(side, ev_shade, 0);
+                        launch_adj_shadow(ls, qs, aq, 0, cur ^ 1, any, table, n_adj);
+                        if (env) launch_adj_shadow(ls, qs, aq, 1, cur ^ 1, any, table, n_adj);
+                        (void)hipEventRecord(ev_shadow, side);
+                    } else {
+                        launch_adj_shadow(l, q, aq, 0, cur ^ 1, any, table, n_adj);
+                        if (env) launch_adj_shadow(l, q, aq, 1, cur ^ 1, any, table, n_adj);
+                    }
+                }
+                cur ^= 1;
+            }
         }
-        if (side_adj && !binq && !replay) (void)hipStreamWaitEvent(st, ev_shadow, 0);
+        if (side_adj && !replay) (void)hipStreamWaitEvent(st, ev_shadow, 0);
     }
     ++st_waves;
     st_samples += used + n_adj;
