@@ -131,6 +131,16 @@ constexpr int TRACE_TB = 128;                  // threads per workgroup of the t
 // spilled ~150 bytes per lane at 64 VGPRs: at 4 waves (105 VGPRs) nothing spills and
 // the re-tracing step is ~1.5 % faster
 #define ADJ_SHADOW_OCCUPANCY __attribute__((amdgpu_waves_per_eu(4, 4)))
+constexpr int PATH_TB = 64;   // threads per workgroup of the whole-path kernel
+// Waves of up to SMALL_PATHS paths run a whole path per thread (k_paths), larger ones queues and
+// three launches per depth: those gather the paths that go on into full waves at 8 waves per
+// SIMD; k_paths has 4 and loses the lanes whose path ended, but no launch waits for the one
+// before.  Renders by queues and by k_paths: quad and cube, depth 3, 64 x 64 x 4 90 and 46 us,
+// 128 x 128 x 16 165 and 71; corner of 50k triangles, depth 4, 256 x 256 spp 4 372 and 248, spp 8
+// 444 and 400, 640 x 360 x 4 (0.92 M) 581 and 589, 256 x 256 x 16 598 and 675; of 200k, depth 6, lit
+// room, 317 x 203 x 9 (0.58 M) 1086 and 829.  A tree of a few nodes (less than TOP_NODES) has
+// little to gather: 256 x 256 x 16 of the quad and cube 312 and 192.
+constexpr int64_t SMALL_PATHS = 5 << 17, SMALL_PATHS_TINY = 1 << 20;
 // Traversal grids are capped at `rounds` x grid_cap x 128 threads (grid_cap x 128 threads
 // is one resident round at 8 waves per SIMD); the spill region holds SPILL ints for every
 // thread of that grid.  Several rounds let workgroups that finish early be replaced
@@ -234,9 +244,10 @@ struct Launch {
 
 // forward kernels; `uni` is the request descriptor when every path of the launch
 // belongs to one request (table == null), else descriptors are read from `table`.
-void launch_prf(const Launch& l, const ReqDesc& r, float4* Ep);
-void launch_pack_tex(const Launch& l, const ReqDesc& r, const float* albedo, const float* rough, float4* tex4);
-void launch_pack_tex_b(const Launch& l, const ReqDesc& r, const float* nmap, const float* metal, float4* tex4b);
+// what a render reads besides the scene, in one launch: E_p (null: none) and the packed maps (tex4b:
+// null without metallic and normal maps)
+void launch_prepare(const Launch& l, const ReqDesc& r, float4* Ep, const float* albedo, const float* rough, float4* tex4,
+                    const float* nmap = nullptr, const float* metal = nullptr, float4* tex4b = nullptr);
 void launch_set_count(const Launch& l, uint32_t* cnt, int idx, uint32_t value, int zero_from, int zero_to);
 void launch_raygen(const Launch& l, const Queues& q, const ReqDesc& r, const ReqDesc* table, int slot,
                    uint32_t g0, uint32_t n, bool adjoint, const AdjQueues* aq);
@@ -250,6 +261,9 @@ void launch_shade(const Launch& l, const Queues& q, int cur, int depth, const Re
 // table): every ray is on the tree of `uni` (several requests of one scene)
 void launch_shadow(const Launch& l, const Queues& q, int which, const ReqDesc& uni, const ReqDesc* table,
                    int64_t n_upper, int depth, bool one_tree = false);
+// the whole forward of the n camera rays of one small wave (sid_base 0; the spill region holds
+// that many threads)
+void launch_paths(const Launch& l, const Queues& q, const ReqDesc& r, uint32_t n);
 void launch_finalize(const Launch& l, const Queues& q, const ReqDesc& r, const ReqDesc* table, int slot,
                      uint32_t p0, uint32_t p1);
 void launch_set_desc(const Launch& l, ReqDesc* table, int slot, const ReqDesc& r);

@@ -20,8 +20,22 @@ constexpr int TB = TRACE_TB;
 
 // ---------------------------------------------------------------- per texel
 // Eq. 1 with colour mixing: E_p = max(0, g_p M max(I_p, 0)^gamma_p)
-__global__ void k_prf(ReqDesc r, float4* __restrict__ Ep) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+// workgroups [0, gp): E_p; the rest: the maps, albedo and roughness per texel, and normal map and
+// metallic where tex4b is asked for (absent ones stand for no change / metallic 0)
+__global__ void __launch_bounds__(256) k_prepare(ReqDesc r, float4* __restrict__ Ep, uint32_t gp,
+                                                 const float* __restrict__ albedo, const float* __restrict__ rough,
+                                                 float4* __restrict__ tex4, const float* __restrict__ nmap,
+                                                 const float* __restrict__ metal, float4* __restrict__ tex4b) {
+    if (blockIdx.x >= gp) {
+        const int t = (int)((blockIdx.x - gp) * 256u + threadIdx.x);
+        if (t >= r.tw * r.th) return;
+        tex4[t] = make_float4(albedo[3 * t], albedo[3 * t + 1], albedo[3 * t + 2], rough ? rough[t] : 0.0f);
+        if (tex4b)
+            tex4b[t] = make_float4(nmap ? nmap[3 * t] : 0.5f, nmap ? nmap[3 * t + 1] : 0.5f, nmap ? nmap[3 * t + 2] : 1.0f,
+                                   metal ? metal[t] : 0.0f);
+        return;
+    }
+    const int t = (int)(blockIdx.x * 256u + threadIdx.x);
     if (t >= r.Wp * r.Hp) return;
     float y[3];
     for (int c = 0; c < 3; ++c) {
@@ -35,22 +49,6 @@ __global__ void k_prf(ReqDesc r, float4* __restrict__ Ep) {
         e[c] = fmaxf(z, 0.0f);
     }
     Ep[t] = make_float4(e[0], e[1], e[2], 0.0f);
-}
-
-__global__ void k_pack_tex(int n, const float* __restrict__ albedo, const float* __restrict__ rough,
-                           float4* __restrict__ tex4) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    tex4[t] = make_float4(albedo[3 * t], albedo[3 * t + 1], albedo[3 * t + 2], rough ? rough[t] : 0.0f);
-}
-
-// (normal map rgb, metallic) per texel; absent maps stand for no change / metallic 0
-__global__ void k_pack_tex_b(int n, const float* __restrict__ nmap, const float* __restrict__ metal,
-                             float4* __restrict__ tex4b) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    tex4b[t] = make_float4(nmap ? nmap[3 * t] : 0.5f, nmap ? nmap[3 * t + 1] : 0.5f, nmap ? nmap[3 * t + 2] : 1.0f,
-                           metal ? metal[t] : 0.0f);
 }
 
 __global__ void k_set_count(uint32_t* cnt, int idx, uint32_t value, int zero_from, int zero_to) {
@@ -141,6 +139,103 @@ __global__ void __launch_bounds__(TB) TRAVERSAL_OCCUPANCY k_trace(Queues q, int 
 }
 
 // ---------------------------------------------------------------- shading
+// what a vertex hands on: the path's next state and the two lights' shadow rays (origin, triangle
+// left and sample are common to both)
+struct Vertex {
+    bool cont, shp, she;
+    PathO no;
+    PathD nd;
+    float4 nb;
+    V3 so, pw, pc, ew, ec;
+    int prim;
+    float ptmax;
+};
+// One vertex of a path: leaf hit (-1: escaped) by the ray (o, dd) of throughput b.  add: radiance
+// seen directly goes to the sample.
+template <bool EXT, class ADD>
+__device__ __forceinline__ void shade_vertex(const ReqDesc& r, int depth, int leaf, const PathO& o, const PathD& dd, float4 b,
+                                             Vertex& v, ADD add) {
+    const uint32_t g = dd.g;
+    const D3 beta = d3(b.x, b.y, b.z);
+    if (leaf < 0) {
+        if (r.out_hits) r.out_hits[(size_t)g * r.max_depth + depth] = -1;
+        if (depth == 0 && r.env_on) {   // a camera ray that escapes sees the environment
+            add(beta.x * r.env[0], beta.y * r.env[1], beta.z * r.env[2]);
+        }
+    } else {
+        // the projector lookup needs only the point and normal: its texels load
+        // together with the maps' instead of after them
+        Surf s = surface_geo(r, leaf, d3(o.x, o.y, o.z), d3(dd.x, dd.y, dd.z));
+        ProjNee p;
+        const bool prj = projector_nee(r, s, p);
+        D3 Eg = d3(0., 0., 0.);   // E_p times the geometry factor
+        if (prj) {
+            const D4 E = fetch4(r.Ep, p.pb);
+            Eg = d3(E.x, E.y, E.z) * (EXT ? p.g0 : p.geom);
+            v.ptmax = (float)(p.dist - r.tmin);
+        }
+        surface_maps(r, s);
+        if (r.out_hits) r.out_hits[(size_t)g * r.max_depth + depth] = s.prim;
+        v.so = to_f(s.x);
+        v.prim = s.prim;
+        if (r.emission) {   // test scenes: surface emission
+            const float4 e = r.emission[leaf];
+            add(beta.x * e.x, beta.y * e.y, beta.z * e.z);
+        }
+        Shading sh{};
+        if constexpr (EXT) sh = shading(r, leaf, s);
+        const D3 ns = EXT ? sh.ns : s.n;
+        if (prj) {
+            D3 C;
+            if constexpr (EXT) {
+                const BrdfX f = brdf_x<false>(r.brdf, s.n, ns, s.wo, p.wp, s.alb, s.rough, s.spec, sh.metal);
+                C = beta * f.f * Eg * f.c;
+            } else {
+                const Brdf f = brdf_eval<false>(r.brdf, s.n, s.wo, p.wp, s.alb, s.rough, s.spec);
+                C = beta * f.f * Eg;
+            }
+            if (r.rec || C.x > 0.0 || C.y > 0.0 || C.z > 0.0) {
+                v.shp = true;
+                v.pw = to_f(p.wp);
+                v.pc = to_f(C);
+            }
+        }
+        if (r.env_on) {
+            const U4 x = vertex_rng(r, g, 2u + 2u * depth);
+            const D3 we = sample_cosine(ns, u24(x.x), u24(x.y));
+            D3 fv;
+            if constexpr (EXT) fv = brdf_x<false>(r.brdf, s.n, ns, s.wo, we, s.alb, s.rough, s.spec, sh.metal).f;
+            else fv = brdf_eval<false>(r.brdf, s.n, s.wo, we, s.alb, s.rough, s.spec).f;
+            const D3 C = beta * fv * d3(r.env[0], r.env[1], r.env[2]) * PI;
+            if (r.rec || C.x > 0.0 || C.y > 0.0 || C.z > 0.0) {
+                v.she = true;
+                v.ew = to_f(we);
+                v.ec = to_f(C);
+            }
+        }
+        if (depth < r.max_depth - 1) {
+            const U4 x = vertex_rng(r, g, 1u + 2u * depth);
+            const D3 wi = sample_bounce(r.brdf, ns, s.wo, s.rough, u24(x.x), u24(x.y), u24(x.z));
+            const double ci = dot(s.n, wi);   // the path goes on above the geometric surface
+            const double pdf = bounce_pdf(r.brdf, ns, s.wo, wi, s.rough);
+            if (ci > 0.0 && pdf > 0.0) {
+                D3 nbeta;
+                if constexpr (EXT) {
+                    const BrdfX f = brdf_x<false>(r.brdf, s.n, ns, s.wo, wi, s.alb, s.rough, s.spec, sh.metal);
+                    nbeta = beta * (f.f * (f.c * frcp(pdf)));
+                } else {
+                    const Brdf f = brdf_eval<false>(r.brdf, s.n, s.wo, wi, s.alb, s.rough, s.spec);
+                    nbeta = beta * (f.f * (ci * frcp(pdf)));
+                }
+                v.cont = true;
+                v.no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
+                v.nd = PathD{wi.x, wi.y, wi.z, g, 0u};
+                v.nb = make_float4((float)nbeta.x, (float)nbeta.y, (float)nbeta.z, 0.0f);
+            }
+        }
+    }
+}
+
 // EXT: the request has the metallic and normal maps (tex4b): BRDF, cosines and sampling
 // about the shading normal (one request per launch).  CAM: depth 0 of one request, its
 // camera rays generated here as in k_trace (throughput 1, the sample's radiance started
@@ -156,15 +251,10 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EXT 
     if (base >= n) return;   // uniform per workgroup
     {
         const uint32_t i = base + threadIdx.x;
-        bool cont = false, shp = false, she = false;
-        PathO no{};
-        PathD nd{};
-        float4 nb = {};
-        // shadow rays: the origin, slot, triangle left and sample are common to both lights
-        V3 so = {}, pw = {}, pc = {}, ew = {}, ec = {};
-        int slot = 0, prim = -1;
+        Vertex v{};
+        v.prim = -1;
+        int slot = 0;
         uint32_t sample = 0u;
-        float ptmax = 0.0f;
         if (i < n) {
             PathO o;
             PathD dd;
@@ -184,126 +274,47 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EXT 
             const ReqDesc& r = sel<UNI>(uni, table, o.slot);
             const uint32_t g = dd.g;
             const uint32_t sid = g - r.g_base + r.sid_base;
-            const D3 beta = d3(b.x, b.y, b.z);
             if constexpr (CAM) {
                 q.L[sid] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                 if (r.out_hits)
                     for (int k = 1; k < r.max_depth; ++k) r.out_hits[(size_t)g * r.max_depth + k] = -2;
             }
-            if (leaf < 0) {
-                if (r.out_hits) r.out_hits[(size_t)g * r.max_depth + depth] = -1;
-                if (depth == 0 && r.env_on) {   // a camera ray that escapes sees the environment
-                    float4 L = q.L[sid];
-                    L.x += (float)(beta.x * r.env[0]);
-                    L.y += (float)(beta.y * r.env[1]);
-                    L.z += (float)(beta.z * r.env[2]);
-                    q.L[sid] = L;
-                }
-            } else {
-                // the projector lookup needs only the point and normal: its texels load
-                // together with the maps' instead of after them
-                Surf s = surface_geo(r, leaf, d3(o.x, o.y, o.z), d3(dd.x, dd.y, dd.z));
-                ProjNee p;
-                const bool prj = projector_nee(r, s, p);
-                D3 Eg = d3(0., 0., 0.);   // E_p times the geometry factor
-                if (prj) {
-                    const D4 E = fetch4(r.Ep, p.pb);
-                    Eg = d3(E.x, E.y, E.z) * (EXT ? p.g0 : p.geom);
-                    ptmax = (float)(p.dist - r.tmin);
-                }
-                surface_maps(r, s);
-                if (r.out_hits) r.out_hits[(size_t)g * r.max_depth + depth] = s.prim;
-                so = to_f(s.x);
-                slot = o.slot;
-                prim = s.prim;
-                sample = sid;
-                if (r.emission) {   // test scenes: surface emission
-                    const float4 e = r.emission[leaf];
-                    float4 L = q.L[sid];
-                    L.x += (float)(beta.x * e.x);
-                    L.y += (float)(beta.y * e.y);
-                    L.z += (float)(beta.z * e.z);
-                    q.L[sid] = L;
-                }
-                Shading sh{};
-                if constexpr (EXT) sh = shading(r, leaf, s);
-                const D3 ns = EXT ? sh.ns : s.n;
-                if (prj) {
-                    D3 C;
-                    if constexpr (EXT) {
-                        const BrdfX f = brdf_x<false>(r.brdf, s.n, ns, s.wo, p.wp, s.alb, s.rough, s.spec, sh.metal);
-                        C = beta * f.f * Eg * f.c;
-                    } else {
-                        const Brdf f = brdf_eval<false>(r.brdf, s.n, s.wo, p.wp, s.alb, s.rough, s.spec);
-                        C = beta * f.f * Eg;
-                    }
-                    if (r.rec || C.x > 0.0 || C.y > 0.0 || C.z > 0.0) {
-                        shp = true;
-                        pw = to_f(p.wp);
-                        pc = to_f(C);
-                    }
-                }
-                if (r.env_on) {
-                    const U4 x = vertex_rng(r, g, 2u + 2u * depth);
-                    const D3 we = sample_cosine(ns, u24(x.x), u24(x.y));
-                    D3 fv;
-                    if constexpr (EXT) fv = brdf_x<false>(r.brdf, s.n, ns, s.wo, we, s.alb, s.rough, s.spec, sh.metal).f;
-                    else fv = brdf_eval<false>(r.brdf, s.n, s.wo, we, s.alb, s.rough, s.spec).f;
-                    const D3 C = beta * fv * d3(r.env[0], r.env[1], r.env[2]) * PI;
-                    if (r.rec || C.x > 0.0 || C.y > 0.0 || C.z > 0.0) {
-                        she = true;
-                        ew = to_f(we);
-                        ec = to_f(C);
-                    }
-                }
-                if (depth < r.max_depth - 1) {
-                    const U4 x = vertex_rng(r, g, 1u + 2u * depth);
-                    const D3 wi = sample_bounce(r.brdf, ns, s.wo, s.rough, u24(x.x), u24(x.y), u24(x.z));
-                    const double ci = dot(s.n, wi);   // the path goes on above the geometric surface
-                    const double pdf = bounce_pdf(r.brdf, ns, s.wo, wi, s.rough);
-                    if (ci > 0.0 && pdf > 0.0) {
-                        D3 nbeta;
-                        if constexpr (EXT) {
-                            const BrdfX f = brdf_x<false>(r.brdf, s.n, ns, s.wo, wi, s.alb, s.rough, s.spec, sh.metal);
-                            nbeta = beta * (f.f * (f.c * frcp(pdf)));
-                        } else {
-                            const Brdf f = brdf_eval<false>(r.brdf, s.n, s.wo, wi, s.alb, s.rough, s.spec);
-                            nbeta = beta * (f.f * (ci * frcp(pdf)));
-                        }
-                        cont = true;
-                        no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
-                        nd = PathD{wi.x, wi.y, wi.z, g, 0u};
-                        nb = make_float4((float)nbeta.x, (float)nbeta.y, (float)nbeta.z, 0.0f);
-                    }
-                }
-            }
+            shade_vertex<EXT>(r, depth, leaf, o, dd, b, v, [&](double x, double y, double z) {
+                float4 L = q.L[sid];
+                L.x += (float)x;
+                L.y += (float)y;
+                L.z += (float)z;
+                q.L[sid] = L;
+            });
+            slot = o.slot;
+            sample = sid;
             if (r.rec) {
-                const uint32_t end = leaf >= 0 && !cont && depth < r.max_depth - 1 ? r.rec_end : 0u;
+                const uint32_t end = leaf >= 0 && !v.cont && depth < r.max_depth - 1 ? r.rec_end : 0u;
                 __builtin_nontemporal_store((uint32_t)(leaf + 1) | end,
                                             &r.rec[(size_t)(g - r.rec_g0) * r.max_depth + depth]);
             }
         }
-        const bool pred[3] = {cont, shp, she};
-        const int key[3] = {octant(nd.x, nd.y, nd.z), 0, octant(ew.x, ew.y, ew.z)};
+        const bool pred[3] = {v.cont, v.shp, v.she};
+        const int key[3] = {octant(v.nd.x, v.nd.y, v.nd.z), 0, octant(v.ew.x, v.ew.y, v.ew.z)};
         uint32_t* const ctr[3] = {&q.cnt[nxt], &q.cnt[shadow_slot(cur, 0)], &q.cnt[shadow_slot(cur, 1)]};
         uint32_t at[3];
         block_append_keyed<3, 8>(pred, key, ctr, at);
         const uint32_t jn = at[0], jp = at[1], je = at[2];
-        if (cont) {
-            nt_st(&q.po[nxt][jn], no);
-            nt_st(&q.pd[nxt][jn], nd);
-            nt_st(&q.pb[nxt][jn], nb);
+        if (v.cont) {
+            nt_st(&q.po[nxt][jn], v.no);
+            nt_st(&q.pd[nxt][jn], v.nd);
+            nt_st(&q.pb[nxt][jn], v.nb);
         }
-        if (shp) {
-            nt_st(&q.so[0][jp], f4(so, __int_as_float(slot)));
-            nt_st(&q.sd[0][jp], f4(pw, __int_as_float(prim)));
-            nt_st(&q.sc[0][jp], f4(pc, __uint_as_float(sample)));
-            __builtin_nontemporal_store(ptmax, &q.st[0][jp]);
+        if (v.shp) {
+            nt_st(&q.so[0][jp], f4(v.so, __int_as_float(slot)));
+            nt_st(&q.sd[0][jp], f4(v.pw, __int_as_float(v.prim)));
+            nt_st(&q.sc[0][jp], f4(v.pc, __uint_as_float(sample)));
+            __builtin_nontemporal_store(v.ptmax, &q.st[0][jp]);
         }
-        if (she) {
-            nt_st(&q.so[1][je], f4(so, __int_as_float(slot)));
-            nt_st(&q.sd[1][je], f4(ew, __int_as_float(prim)));
-            nt_st(&q.sc[1][je], f4(ec, __uint_as_float(sample)));
+        if (v.she) {
+            nt_st(&q.so[1][je], f4(v.so, __int_as_float(slot)));
+            nt_st(&q.sd[1][je], f4(v.ew, __int_as_float(v.prim)));
+            nt_st(&q.sc[1][je], f4(v.ec, __uint_as_float(sample)));
             __builtin_nontemporal_store(__builtin_inff(), &q.st[1][je]);
         }
     }
@@ -352,6 +363,63 @@ __global__ void __launch_bounds__(TB) SHADOW_OCCUPANCY k_shadow(Queues q, int wh
             }
         }
     }
+}
+
+// ---------------------------------------------------------------- whole paths
+// A small wave's paths, one thread each from the camera to the end: closest hit, shading and
+// shadow rays of every depth in one launch instead of three launches per depth, with the path
+// state and the sample's radiance in registers.  The operations and their order per sample are
+// those of the queues, so the results are the same bits.  Bound by the latency of one path's
+// chain of loads while the chip is not full, then by the traversal loops at 4 waves per SIMD (128
+// registers, a few spilled; 158 without the cap, 3 waves: corner of 50k triangles, 256 x 256 x 8
+// 436 us against 400; 5 waves: 434).  Workgroups of one wave: each ends with its own paths
+// (256 threads: 414).
+template <bool EXT>
+__global__ void __launch_bounds__(PATH_TB) __attribute__((amdgpu_waves_per_eu(4, 4))) k_paths(Queues q, ReqDesc r, uint32_t n) {
+    __shared__ int stack[(SHORT_STACK + 1) * PATH_TB];
+    const uint32_t i = blockIdx.x * PATH_TB + threadIdx.x;
+    if (i >= n) return;
+    int* spill = q.spill + (size_t)blockIdx.x * PATH_TB * SPILL;
+    const uint32_t g = r.g_base + i;
+    const D3 cd = camera_dir(r, g);
+    PathO o{r.cam_o[0], r.cam_o[1], r.cam_o[2], 0, -1};
+    PathD d{cd.x, cd.y, cd.z, g, 0u};
+    float4 b = make_float4(1.0f, 1.0f, 1.0f, 0.0f), L = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (r.out_hits)
+        for (int k = 1; k < r.max_depth; ++k) r.out_hits[(size_t)g * r.max_depth + k] = -2;
+    Visits<false> vis;
+    for (int depth = 0; depth < r.max_depth; ++depth) {
+        Hit h;
+        trace_ray<false, SHORT_STACK, PATH_TB>(r.nodes4, r.nodes, r.tris, v3((float)o.x, (float)o.y, (float)o.z),
+                                              v3((float)d.x, (float)d.y, (float)d.z), r.tmin, __builtin_inff(), o.skip, h,
+                                              stack, spill, threadIdx.x, vis);
+        Vertex v{};
+        shade_vertex<EXT>(r, depth, h.leaf, o, d, b, v, [&](double x, double y, double z) {
+            L.x += (float)x;
+            L.y += (float)y;
+            L.z += (float)z;
+        });
+        uint32_t word = (uint32_t)(h.leaf + 1);
+        if (h.leaf >= 0 && !v.cont && depth < r.max_depth - 1) word |= r.rec_end;
+        for (int w = 0; w < 2; ++w) {
+            if (!(w == 0 ? v.shp : v.she)) continue;
+            const V3 sd = w == 0 ? v.pw : v.ew, c = w == 0 ? v.pc : v.ec;
+            const bool occ = trace_ray<true, SHORT_STACK, PATH_TB>(r.nodes4, r.nodes, r.tris, v.so, sd, r.tmin,
+                                                                  w == 0 ? v.ptmax : __builtin_inff(), v.prim, h, stack,
+                                                                  spill, threadIdx.x, vis);
+            if (occ) continue;
+            L.x += c.x;
+            L.y += c.y;
+            L.z += c.z;
+            word |= w == 0 ? REC_PRJ : REC_ENV;
+        }
+        if (r.rec) r.rec[(size_t)(g - r.rec_g0) * r.max_depth + depth] = word;
+        if (!v.cont) break;
+        o = v.no;
+        d = v.nd;
+        b = v.nb;
+    }
+    q.L[i] = L;
 }
 
 // ---------------------------------------------------------------- finalize
@@ -497,16 +565,10 @@ static inline unsigned grid_cap(const Launch& l, int64_t n, int b) {
     return (unsigned)(g < 1 ? 1 : (g > l.grid_cap ? l.grid_cap : g));
 }
 
-void launch_prf(const Launch& l, const ReqDesc& r, float4* Ep) {
-    hipLaunchKernelGGL(k_prf, dim3(grid_of((int64_t)r.Wp * r.Hp, 256)), dim3(256), 0, l.st, r, Ep);
-}
-void launch_pack_tex(const Launch& l, const ReqDesc& r, const float* albedo, const float* rough, float4* tex4) {
-    const int n = r.tw * r.th;
-    hipLaunchKernelGGL(k_pack_tex, dim3(grid_of(n, 256)), dim3(256), 0, l.st, n, albedo, rough, tex4);
-}
-void launch_pack_tex_b(const Launch& l, const ReqDesc& r, const float* nmap, const float* metal, float4* tex4b) {
-    const int n = r.tw * r.th;
-    hipLaunchKernelGGL(k_pack_tex_b, dim3(grid_of(n, 256)), dim3(256), 0, l.st, n, nmap, metal, tex4b);
+void launch_prepare(const Launch& l, const ReqDesc& r, float4* Ep, const float* albedo, const float* rough, float4* tex4,
+                    const float* nmap, const float* metal, float4* tex4b) {
+    const unsigned gp = Ep ? grid_of((int64_t)r.Wp * r.Hp, 256) : 0u, gt = grid_of((int64_t)r.tw * r.th, 256);
+    hipLaunchKernelGGL(k_prepare, dim3(gp + gt), dim3(256), 0, l.st, r, Ep, gp, albedo, rough, tex4, nmap, metal, tex4b);
 }
 void launch_set_count(const Launch& l, uint32_t* cnt, int idx, uint32_t value, int zero_from, int zero_to) {
     hipLaunchKernelGGL(k_set_count, dim3(1), dim3(64), 0, l.st, cnt, idx, value, zero_from, zero_to);
@@ -578,6 +640,11 @@ void launch_shadow(const Launch& l, const Queues& q, int which, const ReqDesc& u
         if (table) hipLaunchKernelGGL((k_shadow<false, false>), g, b, 0, l.st, q, which, depth, uni, table);
         else hipLaunchKernelGGL((k_shadow<true, false>), g, b, 0, l.st, q, which, depth, uni, table);
     }
+}
+void launch_paths(const Launch& l, const Queues& q, const ReqDesc& r, uint32_t n) {
+    const dim3 g(grid_of(n, PATH_TB)), b(PATH_TB);
+    if (r.tex4b) hipLaunchKernelGGL(k_paths<true>, g, b, 0, l.st, q, r, n);
+    else hipLaunchKernelGGL(k_paths<false>, g, b, 0, l.st, q, r, n);
 }
 void launch_finalize(const Launch& l, const Queues& q, const ReqDesc& r, const ReqDesc*, int, uint32_t p0,
                      uint32_t p1) {

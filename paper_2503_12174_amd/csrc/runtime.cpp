@@ -742,9 +742,8 @@ bool prepare_request(dpcs_context ctx, ReqDesc& r, const dpcs_render_params* p, 
         texb = (float4*)scratch(ctx, c.c_str(), sizeof(float4) * (size_t)r.tw * r.th, st);
         if (!texb) return false;
     }
-    launch_prf(l, r, Ep);
-    launch_pack_tex(l, r, p->albedo, p->brdf == DPCS_BRDF_GGX ? p->roughness : nullptr, tex);
-    if (texb) launch_pack_tex_b(l, r, p->normal_map, p->brdf == DPCS_BRDF_GGX ? p->metallic : nullptr, texb);
+    const bool ggx = p->brdf == DPCS_BRDF_GGX;
+    launch_prepare(l, r, Ep, p->albedo, ggx ? p->roughness : nullptr, tex, p->normal_map, ggx ? p->metallic : nullptr, texb);
     r.Ep = Ep;
     r.tex4 = tex;
     r.tex4b = texb;
@@ -783,6 +782,13 @@ void forward_wave(dpcs_context ctx, Queues& q, ReqDesc& r, uint32_t a, uint32_t 
     const uint32_t n = (b - a) * (uint32_t)r.spp;
     r.g_base = a * (uint32_t)r.spp;
     r.sid_base = 0;
+    const bool tiny = r.nodes4 && r.top_nodes < TOP_NODES;
+    if (!ctx->prof_mode && (int64_t)n <= (tiny ? SMALL_PATHS_TINY : SMALL_PATHS) &&
+        (int64_t)n <= (int64_t)q.trace_blocks * TRACE_TB) {   // (profiling times the stages apart)
+        launch_paths(l, q, r, n);
+        if (finalize) launch_finalize(l, q, r, nullptr, 0, a, b);
+        return;
+    }
     launch_set_count(l, q.cnt, 0, n, 1, 4);
     // the camera rays are generated by the depth-0 closest-hit and shading kernels (no
     // raygen launch); the stage record keeps the count of camera samples
@@ -964,11 +970,9 @@ static dpcs_status render_impl(dpcs_context ctx, dpcs_scene scene, const dpcs_re
     const int prof_mode = ctx->prof_mode;
     if (noalloc) {
         Launch l{ctx->stream, ctx->grid_cap};
-        launch_prf(l, r, na_Ep);
-        launch_pack_tex(l, r, params->albedo, params->brdf == DPCS_BRDF_GGX ? params->roughness : nullptr, na_tex);
-        if (na_texb)
-            launch_pack_tex_b(l, r, params->normal_map, params->brdf == DPCS_BRDF_GGX ? params->metallic : nullptr,
-                              na_texb);
+        const bool ggx = params->brdf == DPCS_BRDF_GGX;
+        launch_prepare(l, r, na_Ep, params->albedo, ggx ? params->roughness : nullptr, na_tex, params->normal_map,
+                       ggx ? params->metallic : nullptr, na_texb);
         ctx->prof_mode = 0;   // profiling records events and pinned counts; not on this path
     } else {
         if (!prepare_request(ctx, r, params, "fwd", &st)) return st;
@@ -1011,7 +1015,7 @@ extern "C" dpcs_status dpcs_render_gbuffer(dpcs_context ctx, dpcs_scene scene, c
     float4* tex = (float4*)scratch(ctx, "gbuf.tex", sizeof(float4) * (size_t)r.tw * r.th, &st);
     if (!tex) return st;
     Launch l{ctx->stream, ctx->grid_cap};
-    launch_pack_tex(l, r, params->albedo, nullptr, tex);
+    launch_prepare(l, r, nullptr, params->albedo, nullptr, tex);
     r.tex4 = tex;
     launch_gbuffer(l, r, gbuffer);
     if (!hip_ok(ctx, hipGetLastError(), "render_gbuffer")) return DPCS_E_DEVICE;

@@ -231,8 +231,7 @@ void dpcs_server_s::admit_locked(Launch& l) {
         const size_t nEp = (size_t)r.Wp * r.Hp, nT = (size_t)r.tw * r.th;
         float4* Ep = (float4*)take(16 * nEp);
         float4* tex = (float4*)take(16 * nT);
-        launch_prf(l, r, Ep);
-        launch_pack_tex(l, r, q->params.albedo, q->params.brdf == DPCS_BRDF_GGX ? q->params.roughness : nullptr, tex);
+        launch_prepare(l, r, Ep, q->params.albedo, q->params.brdf == DPCS_BRDF_GGX ? q->params.roughness : nullptr, tex);
         r.Ep = Ep;
         r.tex4 = tex;
         if (q->adjoint) {

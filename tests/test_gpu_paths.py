@@ -1,0 +1,65 @@
+"""Small waves run whole paths per thread, larger ones (and profiled calls) through the queues:
+the same bits in every output."""
+import numpy as np
+import pytest
+
+from paper_2503_12174_amd import synth
+
+from .gpu_util import GpuRun, ctx
+
+pytestmark = pytest.mark.gpu
+
+
+def _one_triangle():
+    V = np.array([[-0.6, -0.6, 0.0], [0.9, -0.5, 0.02], [0.0, 0.8, -0.01]], np.float32)
+    return synth.Mesh(V, np.array([[0, 1, 2]], np.int32), np.random.default_rng(0).uniform(0, 1, (1, 3, 2)).astype(np.float32))
+
+
+def _case(name):
+    if name == "one triangle":   # (no 4-wide tree)
+        w = synth.quad_cube(spp=3, max_depth=2)
+        w.mesh = _one_triangle()
+    elif name == "quad and cube":
+        w = synth.quad_cube(spp=4, max_depth=3)
+    elif name == "one depth":
+        w = synth.quad_cube(spp=1, max_depth=1)
+    elif name == "emission":
+        w = synth.quad_cube(spp=2, max_depth=5)
+        w.mesh = synth.closed_box(0.5)
+    else:
+        w = synth.corner_50k(spp=5, max_depth=6, res=61, n_quads=40)
+        w.env = np.full(3, 0.0 if name == "corner" else 0.04)
+        if name == "principled, lit":
+            rng = np.random.default_rng(5)
+            w.metallic = rng.uniform(0, 1, (512, 512)).astype(np.float32)
+            n = rng.uniform(0.4, 0.6, (512, 512, 3))
+            n[..., 2] = 1.0
+            w.normal_map = n.astype(np.float32)
+    return w
+
+
+@pytest.mark.parametrize("records", [False, True])
+@pytest.mark.parametrize("name", ["one triangle", "quad and cube", "one depth", "emission", "corner", "corner, lit",
+                                  "principled, lit"])
+def test_whole_paths_equal_the_queues(name, records):
+    import torch
+    from paper_2503_12174_amd import dpcs
+    run = GpuRun(_case(name))
+    p = run.params
+    H, W, c = p.camera.height, p.camera.width, ctx()
+    res = []
+    for prof in (0, 1):
+        c.set_profiling(prof)
+        out, lin = (torch.zeros((H, W, 3), device="cuda") for _ in range(2))
+        L = torch.zeros((H, W, p.spp, 3), device="cuda")
+        hits = torch.zeros((H, W, p.spp, p.max_depth), dtype=torch.int32, device="cuda")
+        rec = torch.zeros((H, W, p.spp, p.max_depth), dtype=torch.int32, device="cuda")
+        dpcs.dpcs_render(c, run.scene, p, run.proj, out, linear=lin, sample_radiance=L, hit_prims=hits,
+                         **(dict(path_records=rec) if records else {}))
+        c.synchronize()
+        res.append([t.cpu().numpy() for t in (out, lin, L, hits, rec)])
+    c.set_profiling(0)
+    for a, b in zip(*res):
+        np.testing.assert_array_equal(a, b)
+    assert (res[0][3] >= 0).any() and res[0][2].max() > 0
+    assert not records or (res[0][4] != 0).any()
