@@ -259,38 +259,47 @@ __device__ __forceinline__ double kid_area(const Kid& c) {
     return dx * dy + dy * dz + dz * dx;
 }
 
-// the up to four children of the 4-wide node over binary node b; returns how many
-__device__ int pick_kids(const float4* __restrict__ nodes, int ni, int b, Kid k[4]) {
+// the up to four children of the 4-wide node over binary node b; returns how many (indices known
+// at compile time throughout: the children stay in registers)
+__device__ __forceinline__ int pick_kids(const float4* __restrict__ nodes, int ni, int b, Kid k[4]) {
     if (b < 0 || b >= ni) return 0;
     k[0] = bin_kid(nodes, b, 0);
     k[1] = bin_kid(nodes, b, 1);
     int cnt = 2;
-    while (cnt < 4) {
-        int best = -1;
+#pragma unroll
+    for (int c = 2; c < 4; ++c) {   // c children so far: open one, if there is an internal one
+        if (cnt < c) break;
+        int best = -1, ref = -1;
         double ba = -1.0;
-        for (int j = 0; j < cnt; ++j)
+#pragma unroll
+        for (int j = 0; j < c; ++j)
             if (k[j].ref >= 0 && k[j].ref < ni && kid_area(k[j]) > ba) {
                 ba = kid_area(k[j]);
                 best = j;
+                ref = k[j].ref;
             }
         if (best < 0) break;
-        const int c = k[best].ref;
-        for (int j = best; j + 1 < cnt; ++j) k[j] = k[j + 1];   // remove it, keeping the order
-        k[cnt - 1] = bin_kid(nodes, c, 0);                       // and append its two children
-        k[cnt] = bin_kid(nodes, c, 1);
-        ++cnt;
+#pragma unroll
+        for (int j = 0; j + 1 < c; ++j)
+            if (j >= best) k[j] = k[j + 1];   // remove it, keeping the order
+        k[c - 1] = bin_kid(nodes, ref, 0);    // and append its two children
+        k[c] = bin_kid(nodes, ref, 1);
+        cnt = c + 1;
     }
-    // the internal children first, each kind in order: they get consecutive numbers, and a
-    // traversal has a child's number from its slot
-    Kid in[4], lf[4];
-    int ni_ = 0, nl = 0;
-    for (int j = 0; j < cnt; ++j) {
-        if (k[j].ref >= 0) in[ni_++] = k[j];
-        else lf[nl++] = k[j];
-    }
-    for (int j = 0; j < ni_; ++j) k[j] = in[j];
-    for (int j = 0; j < nl; ++j) k[ni_ + j] = lf[j];
     return cnt;
+}
+// the internal children first, each kind in order: they get consecutive numbers, and a traversal
+// has a child's number from its slot
+__device__ __forceinline__ void order_kids(Kid k[4], int cnt) {
+#pragma unroll
+    for (int pass = 0; pass < 3; ++pass)
+#pragma unroll
+        for (int j = 0; j < 3 - pass; ++j)
+            if (j + 1 < cnt && k[j].ref < 0 && k[j + 1].ref >= 0) {
+                const Kid t = k[j];
+                k[j] = k[j + 1];
+                k[j + 1] = t;
+            }
 }
 
 __device__ __forceinline__ int internal_kids(const Kid k[4], int cnt) {
@@ -333,6 +342,7 @@ __global__ void __launch_bounds__(TB) k_collapse_write(const float4* __restrict_
     int cnt = 0, internal = 0;
     if (e < m) {
         cnt = pick_kids(nodes, ni, bin[e], k);
+        order_kids(k, cnt);
         internal = internal_kids(k, cnt);
     }
     uint64_t tot;
