@@ -431,8 +431,12 @@ dpcs_status camera_edge_term(dpcs_context ctx, dpcs_scene sc, const ReqDesc& r, 
             re.out_image = nullptr;
             re.out_linear = nullptr;
             re.d_cam_part = nullptr;
-            launch_set_count(l, qe.cnt, 0, m, 1, 4);
             hipLaunchKernelGGL(k_edge_raygen, dim3((m + 255) / 256), dim3(256), 0, l.st, qe, re, a, side);
+            if (!ctx->prof_mode && small_wave(qe, re, m)) {
+                launch_paths(l, qe, re, nullptr, m, false);
+                continue;
+            }
+            launch_set_count(l, qe.cnt, 0, m, 1, 4);
             int cur = 0;
             for (int d = 0; d < re.max_depth; ++d) {
                 launch_trace(l, qe, cur, re, nullptr, m);   // (empties the queues shading appends to)

@@ -374,19 +374,12 @@ __global__ void __launch_bounds__(TB) SHADOW_OCCUPANCY k_shadow(Queues q, int wh
 // registers, a few spilled; 158 without the cap, 3 waves: corner of 50k triangles, 256 x 256 x 8
 // 436 us against 400; 5 waves: 434).  Workgroups of one wave: each ends with its own paths
 // (256 threads: 414).
+// (Two launches, the paths that go on at depth 2 gathered in between, gained 5 % at 0.5 M paths
+// and lost up to 30 % below.)
 template <bool EXT>
-__global__ void __launch_bounds__(PATH_TB) __attribute__((amdgpu_waves_per_eu(4, 4))) k_paths(Queues q, ReqDesc r, uint32_t n) {
-    __shared__ int stack[(SHORT_STACK + 1) * PATH_TB];
-    const uint32_t i = blockIdx.x * PATH_TB + threadIdx.x;
-    if (i >= n) return;
-    int* spill = q.spill + (size_t)blockIdx.x * PATH_TB * SPILL;
-    const uint32_t g = r.g_base + i;
-    const D3 cd = camera_dir(r, g);
-    PathO o{r.cam_o[0], r.cam_o[1], r.cam_o[2], 0, -1};
-    PathD d{cd.x, cd.y, cd.z, g, 0u};
+__device__ __forceinline__ float4 run_path(const ReqDesc& r, PathO o, PathD d, int* stack, int* spill) {
+    const uint32_t g = d.g;
     float4 b = make_float4(1.0f, 1.0f, 1.0f, 0.0f), L = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (r.out_hits)
-        for (int k = 1; k < r.max_depth; ++k) r.out_hits[(size_t)g * r.max_depth + k] = -2;
     Visits<false> vis;
     for (int depth = 0; depth < r.max_depth; ++depth) {
         Hit h;
@@ -419,7 +412,42 @@ __global__ void __launch_bounds__(PATH_TB) __attribute__((amdgpu_waves_per_eu(4,
         d = v.nd;
         b = v.nb;
     }
-    q.L[i] = L;
+    return L;
+}
+
+// SRC: where the rays come from: one request's camera, the queue of one request, or the queue of
+// several requests' camera rays (descriptors in table; a wave mostly holds one request's, and
+// takes its requests one after the other).
+enum PathSource { FROM_CAMERA, FROM_QUEUE, FROM_TABLE };
+template <bool EXT, int SRC>
+__global__ void __launch_bounds__(PATH_TB) __attribute__((amdgpu_waves_per_eu(4, 4)))
+k_paths(Queues q, uint32_t n, ReqDesc uni, const ReqDesc* __restrict__ table) {
+    __shared__ int stack[(SHORT_STACK + 1) * PATH_TB];
+    const uint32_t i = blockIdx.x * PATH_TB + threadIdx.x;
+    if (i >= n) return;
+    int* spill = q.spill + (size_t)blockIdx.x * PATH_TB * SPILL;
+    if constexpr (SRC == FROM_CAMERA) {
+        const uint32_t g = uni.g_base + i;
+        if (uni.out_hits)
+            for (int k = 1; k < uni.max_depth; ++k) uni.out_hits[(size_t)g * uni.max_depth + k] = -2;
+        const D3 cd = camera_dir(uni, g);
+        q.L[i + uni.sid_base] = run_path<EXT>(uni, PathO{uni.cam_o[0], uni.cam_o[1], uni.cam_o[2], 0, -1},
+                                              PathD{cd.x, cd.y, cd.z, g, 0u}, stack, spill);
+    } else {
+        const PathO o = nt_ld(&q.po[0][i]);
+        const PathD d = nt_ld(&q.pd[0][i]);
+        if constexpr (SRC == FROM_QUEUE) {
+            q.L[d.g - uni.g_base + uni.sid_base] = run_path<EXT>(uni, o, d, stack, spill);
+        } else {
+            for (bool wait = true; wait;) {
+                const int s = __builtin_amdgcn_readfirstlane(o.slot);
+                if (o.slot == s) {
+                    q.L[i] = run_path<EXT>(table[s], o, d, stack, spill);
+                    wait = false;
+                }
+            }
+        }
+    }
 }
 
 // ---------------------------------------------------------------- finalize
@@ -641,10 +669,17 @@ void launch_shadow(const Launch& l, const Queues& q, int which, const ReqDesc& u
         else hipLaunchKernelGGL((k_shadow<true, false>), g, b, 0, l.st, q, which, depth, uni, table);
     }
 }
-void launch_paths(const Launch& l, const Queues& q, const ReqDesc& r, uint32_t n) {
+void launch_paths(const Launch& l, const Queues& q, const ReqDesc& r, const ReqDesc* table, uint32_t n, bool cam) {
     const dim3 g(grid_of(n, PATH_TB)), b(PATH_TB);
-    if (r.tex4b) hipLaunchKernelGGL(k_paths<true>, g, b, 0, l.st, q, r, n);
-    else hipLaunchKernelGGL(k_paths<false>, g, b, 0, l.st, q, r, n);
+    if (table) hipLaunchKernelGGL((k_paths<false, FROM_TABLE>), g, b, 0, l.st, q, n, r, table);
+    else if (!cam && r.tex4b) hipLaunchKernelGGL((k_paths<true, FROM_QUEUE>), g, b, 0, l.st, q, n, r, table);
+    else if (!cam) hipLaunchKernelGGL((k_paths<false, FROM_QUEUE>), g, b, 0, l.st, q, n, r, table);
+    else if (r.tex4b) hipLaunchKernelGGL((k_paths<true, FROM_CAMERA>), g, b, 0, l.st, q, n, r, table);
+    else hipLaunchKernelGGL((k_paths<false, FROM_CAMERA>), g, b, 0, l.st, q, n, r, table);
+}
+bool small_wave(const Queues& q, const ReqDesc& r, int64_t n) {
+    const bool tiny = r.nodes4 && r.top_nodes < TOP_NODES;
+    return n <= (tiny ? SMALL_PATHS_TINY : SMALL_PATHS) && n <= (int64_t)q.trace_blocks * TRACE_TB;
 }
 void launch_finalize(const Launch& l, const Queues& q, const ReqDesc& r, const ReqDesc*, int, uint32_t p0,
                      uint32_t p1) {

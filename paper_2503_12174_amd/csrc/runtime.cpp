@@ -782,10 +782,8 @@ void forward_wave(dpcs_context ctx, Queues& q, ReqDesc& r, uint32_t a, uint32_t 
     const uint32_t n = (b - a) * (uint32_t)r.spp;
     r.g_base = a * (uint32_t)r.spp;
     r.sid_base = 0;
-    const bool tiny = r.nodes4 && r.top_nodes < TOP_NODES;
-    if (!ctx->prof_mode && (int64_t)n <= (tiny ? SMALL_PATHS_TINY : SMALL_PATHS) &&
-        (int64_t)n <= (int64_t)q.trace_blocks * TRACE_TB) {   // (profiling times the stages apart)
-        launch_paths(l, q, r, n);
+    if (!ctx->prof_mode && small_wave(q, r, n)) {   // (profiling times the stages apart)
+        launch_paths(l, q, r, nullptr, n, true);
         if (finalize) launch_finalize(l, q, r, nullptr, 0, a, b);
         return;
     }

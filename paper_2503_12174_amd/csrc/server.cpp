@@ -327,7 +327,6 @@ void dpcs_server_s::wave(Launch& l) {
     // queries read nothing else of a descriptor, so they run in the one-request form
     const ReqDesc& any = segs[0].q->r;
     // forward over the shared queues
-    launch_set_count(l, q.cnt, 0, (uint32_t)used, 1, 4);
     for (const Seg& s : segs) launch_raygen(l, q, s.q->r, table, s.q->slot, s.q->r.g_base, (s.b - s.a) * s.q->r.spp,
                                             false, nullptr);
     int cur = 0;
@@ -338,8 +337,11 @@ void dpcs_server_s::wave(Launch& l) {
     const Launch ls{side, ctx->grid_cap};
     // (only full-size waves: at 2^20 paths of a small scene, the scene-fit step's waves,
     // the cross-stream waits cost more than the overlap gained: 2.50 -> 2.62 ms)
-    const bool side_fwd = side && used >= LOOP_SIDE_MIN_PATHS, side_adj = side && n_adj >= LOOP_SIDE_MIN_PATHS;
-    for (int d = 0; d < max_depth; ++d) {
+    const bool small = small_wave(q, any, used);
+    const bool side_fwd = !small && side && used >= LOOP_SIDE_MIN_PATHS, side_adj = side && n_adj >= LOOP_SIDE_MIN_PATHS;
+    if (small) launch_paths(l, q, any, table, (uint32_t)used, false);
+    else launch_set_count(l, q.cnt, 0, (uint32_t)used, 1, 4);
+    for (int d = 0; d < max_depth && !small; ++d) {
         launch_trace(l, q, cur, any, nullptr, used);   // (empties the queues shading appends to)
         if (side_fwd && d > 0) (void)hipStreamWaitEvent(st, ev_shadow, 0);
         launch_shade(l, q, cur, d, any, table, used);

@@ -63,3 +63,23 @@ def test_whole_paths_equal_the_queues(name, records):
         np.testing.assert_array_equal(a, b)
     assert (res[0][3] >= 0).any() and res[0][2].max() > 0
     assert not records or (res[0][4] != 0).any()
+
+
+@pytest.mark.parametrize("env,depth", [(0.0, 3), (0.04, 5)])
+def test_edge_paths_equal_the_queues(env, depth):
+    """The silhouette part of the camera-pose gradient traces its rays from a queue."""
+    from .gpu_util import run_vjp
+    w = synth.corner_50k(spp=3, max_depth=depth, res=48, n_quads=20)
+    w.env = np.full(3, env)
+    G = np.random.default_rng(3).normal(size=(48, 48, 3))
+    res = []
+    for prof in (0, 1):
+        run = GpuRun(w)
+        ctx().set_profiling(prof)
+        res.append(run_vjp(run, G, mode="records", camera=True, edge_density=32.0))
+    ctx().set_profiling(0)
+    assert set(res[0]) == set(res[1])
+    for k in res[0]:
+        if "cam" in k:
+            np.testing.assert_array_equal(res[0][k], res[1][k], err_msg=k)
+            assert np.abs(res[0][k]).max() > 0
