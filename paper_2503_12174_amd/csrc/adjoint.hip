@@ -27,6 +27,7 @@
 namespace dpcs {
 
 constexpr int TB = TRACE_TB;
+constexpr int SUM_TB = 1024;
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
@@ -292,26 +293,21 @@ __global__ void __launch_bounds__(BLOCK) k_adj_pixel(Queues q, AdjQueues aq, Req
 // order (FP64), so the scalar gradients are the same on every run
 // one workgroup per value k < nv (grid nv): dst[k] += the sum of the nb partials of k, in
 // a fixed order (per thread a strided run, then a tree)
-// value k of nb per-block partials (stride floats apart) added to dst[k] by thread 0, in
-// a fixed order (strided FP64 sums, then a tree); a 256-thread workgroup calls it whole
-__device__ __forceinline__ void sum_partial(const float* __restrict__ part, int nb, int stride, int k,
-                                            float* __restrict__ dst, double* red) {
+// value blockIdx.x of nb per-block partials (stride floats apart) added to dst, in a fixed order
+// (strided FP64 sums, then trees)
+__global__ void __launch_bounds__(SUM_TB) k_sum_partials(const float* __restrict__ part, int nb, int stride, int nv,
+                                                         float* __restrict__ dst) {
+    __shared__ double red[SUM_TB / 64];
+    const int k = blockIdx.x;
+    if (k >= nv) return;
     double s = 0.0;
-    for (int b = threadIdx.x; b < nb; b += 256) s += part[(size_t)b * stride + k];
-    red[threadIdx.x] = s;
+    for (int b = threadIdx.x; b < nb; b += SUM_TB) s += part[(size_t)b * stride + k];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0 && red[0] != 0.0) dst[k] += (float)red[0];
-    __syncthreads();   // (red is reused by the next call)
-}
-__global__ void __launch_bounds__(256) k_sum_partials(const float* __restrict__ part, int nb, int stride, int nv,
-                                                      float* __restrict__ dst) {
-    __shared__ double red[256];
-    if ((int)blockIdx.x >= nv) return;
-    sum_partial(part, nb, stride, blockIdx.x, dst, red);
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < SUM_TB / 64; ++w) s += red[w];
+    if (s != 0.0) dst[k] += (float)s;
 }
 
 // replay camera rays at queue index = batch sample index (the depth-0 shading takes
@@ -1378,10 +1374,16 @@ __device__ __forceinline__ void adj_maps(const ReqDesc& r, int t, float* d_albed
 
 // one 256-thread workgroup: the PRF backward's partials (nb blocks) into acc[8..20), then
 // the scalar gradients
-__global__ void __launch_bounds__(256) k_adj_scalars(ReqDesc r, float* __restrict__ acc, float* d_scalars, int nb) {
-    __shared__ double red[256];
-    if (r.d_part)
-        for (int k = 0; k < 12; ++k) sum_partial(r.d_part, nb, 12, k, acc + 8, red);
+// (one wave per value: a workgroup that took the twelve in turn spent 12 us in its barriers)
+__global__ void __launch_bounds__(768) k_adj_scalars(ReqDesc r, float* __restrict__ acc, float* d_scalars, int nb) {
+    if (r.d_part) {
+        const int k = threadIdx.x >> 6;
+        double s = 0.0;
+        for (int b = threadIdx.x & 63; b < nb; b += 64) s += r.d_part[(size_t)b * 12 + k];
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        if ((threadIdx.x & 63) == 0 && s != 0.0) acc[8 + k] += (float)s;
+        __syncthreads();
+    }
     if (threadIdx.x != 0 || !d_scalars) return;
     for (int k = 0; k < 12; ++k) d_scalars[k] = acc[8 + k];           // gamma_p, M
     for (int c = 0; c < 3; ++c) {
@@ -1410,7 +1412,7 @@ void launch_adj_pixel(const Launch& l, const Queues& q, const AdjQueues& aq, con
     const unsigned g = grid_of((int64_t)(p1 - p0) * PIX_LANES, BLOCK);
     hipLaunchKernelGGL(k_adj_pixel, dim3(g), dim3(BLOCK), 0, l.st, q, aq, r, p0, p1, sample_L, pix_dE,
                        per_sample);
-    if (r.d_part) hipLaunchKernelGGL(k_sum_partials, dim3(7), dim3(256), 0, l.st, r.d_part, (int)g, 8, 7, r.d_acc);
+    if (r.d_part) hipLaunchKernelGGL(k_sum_partials, dim3(7), dim3(SUM_TB), 0, l.st, r.d_part, (int)g, 8, 7, r.d_acc);
 }
 size_t partial_floats(int64_t pixels_per_wave, int64_t proj_pixels) {
     return std::max<size_t>(8 * (size_t)grid_of(pixels_per_wave * PIX_LANES, BLOCK), 12 * (size_t)grid_of(proj_pixels, BLOCK));
@@ -1475,7 +1477,7 @@ static void flush_maps(const Launch& l, const MapBins& a, float* oa, int sa, con
                        b ? sb : sa, ta);
 }
 void launch_sum_partials(const Launch& l, const float* part, int nb, int stride, int nv, float* dst) {
-    hipLaunchKernelGGL(k_sum_partials, dim3(nv), dim3(256), 0, l.st, part, nb, stride, nv, dst);
+    hipLaunchKernelGGL(k_sum_partials, dim3(nv), dim3(SUM_TB), 0, l.st, part, nb, stride, nv, dst);
 }
 void launch_map_flush(const Launch& l, const AdjQueues& aq, const ReqDesc& r) {
     const bool tex = aq.tb.rec && r.d_tex, ep = aq.eb.rec && r.dEp;
@@ -1492,7 +1494,7 @@ void launch_adj_finish(const Launch& l, const ReqDesc& r, float* d_proj, float* 
     if (g + gm == 0) return;   // the camera pose alone
     hipLaunchKernelGGL(k_adj_prf, dim3(g + gm), dim3(BLOCK), 0, l.st, r, d_proj, acc, (int)g, d_albedo, d_rough,
                        d_spec, d_metal, d_nmap);
-    hipLaunchKernelGGL(k_adj_scalars, dim3(1), dim3(256), 0, l.st, r, acc, d_scalars, (int)g);
+    hipLaunchKernelGGL(k_adj_scalars, dim3(1), dim3(768), 0, l.st, r, acc, d_scalars, (int)g);
 }
 
 }  // namespace dpcs

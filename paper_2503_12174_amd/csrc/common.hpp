@@ -547,6 +547,14 @@ __device__ __forceinline__ D4 fetch4(const float4* __restrict__ t, const Bilin& 
     return D4{mix(p.x, q.x, s.x, u.x), mix(p.y, q.y, s.y, u.y), mix(p.z, q.z, s.z, u.z),
               b.w00 * p.w + b.w10 * q.w + b.w01 * s.w + b.w11 * u.w};
 }
+// the rgb of fetch4 from the caller's own map, three floats per texel
+__device__ __forceinline__ D3 fetch3(const float* __restrict__ t, const Bilin& b) {
+    const float *p = t + 3 * b.i00, *q = t + 3 * b.i10, *s = t + 3 * b.i01, *u = t + 3 * b.i11;
+    auto mix = [&](float k00, float k10, float k01, float k11) {
+        return fma(b.w00, (double)k00, fma(b.w10, (double)k10, fma(b.w01, (double)k01, b.w11 * k11)));
+    };
+    return d3(mix(p[0], q[0], s[0], u[0]), mix(p[1], q[1], s[1], u[1]), mix(p[2], q[2], s[2], u[2]));
+}
 // the normal map and metallic: every channel rounded step by step (the normal directs paths)
 __device__ __forceinline__ D4 fetch4_rn(const float4* __restrict__ t, const Bilin& b) {
     const float4 p = t[b.i00], q = t[b.i10], s = t[b.i01], u = t[b.i11];

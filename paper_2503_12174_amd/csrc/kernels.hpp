@@ -244,7 +244,7 @@ struct Launch {
 
 // forward kernels; `uni` is the request descriptor when every path of the launch
 // belongs to one request (table == null), else descriptors are read from `table`.
-// what a render reads besides the scene, in one launch: E_p (null: none) and the packed maps (tex4b:
+// what a render reads besides the scene, in one launch: E_p and the packed maps (tex4b:
 // null without metallic and normal maps)
 void launch_prepare(const Launch& l, const ReqDesc& r, float4* Ep, const float* albedo, const float* rough, float4* tex4,
                     const float* nmap = nullptr, const float* metal = nullptr, float4* tex4b = nullptr);
@@ -329,7 +329,7 @@ void launch_debug_intersect(const Launch& l, const float4* nodes4, const float4*
                             int32_t* prim, float* t, float* b1, float* b2);
 void launch_debug_brdf(const Launch& l, int kind, const double* in, int64_t n, double* out);
 // guide features through the pixel centres (out: Wc x Hc x 8 floats, 16-byte aligned)
-void launch_gbuffer(const Launch& l, const ReqDesc& r, float* out);
+void launch_gbuffer(const Launch& l, const ReqDesc& r, const float* albedo, float* out);
 void launch_debug_philox(const Launch& l, uint64_t seed, const uint32_t* ctr, int64_t n, uint32_t* out);
 
 }  // namespace dpcs

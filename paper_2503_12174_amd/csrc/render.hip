@@ -490,7 +490,7 @@ __global__ void __launch_bounds__(256) k_finalize(Queues q, ReqDesc r, uint32_t 
 // One camera ray through each pixel centre; closest hit through the renderer's BVH with
 // a full LDS stack (no spill region), hit attributes in FP64 as the shading uses them.
 // Per pixel two float4: (albedo rgb, n.x), (n.y, n.z, t, 1); zeros on a miss.
-__global__ void __launch_bounds__(TB) k_gbuffer(ReqDesc r, float4* __restrict__ out) {
+__global__ void __launch_bounds__(TB) k_gbuffer(ReqDesc r, const float* __restrict__ albedo, float4* __restrict__ out) {
     __shared__ int stack[(MAX_STACK + 1) * TB];
     const int64_t npix = (int64_t)r.Wc * r.Hc;
     for (int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x; i < npix; i += (int64_t)gridDim.x * TB) {
@@ -504,9 +504,10 @@ __global__ void __launch_bounds__(TB) k_gbuffer(ReqDesc r, float4* __restrict__ 
                                         stack, nullptr, threadIdx.x, vis);
         float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f), b = a;
         if (h.leaf >= 0) {
-            const Surf s = surface(r, h.leaf, o, d);
+            const Surf s = surface_geo(r, h.leaf, o, d);
+            const D3 alb = fetch3(albedo, s.tb);   // (one lookup per pixel: not worth packing the map for)
             const double t = dot(s.x - o, d);
-            a = make_float4((float)s.alb.x, (float)s.alb.y, (float)s.alb.z, (float)s.n.x);
+            a = make_float4((float)alb.x, (float)alb.y, (float)alb.z, (float)s.n.x);
             b = make_float4((float)s.n.y, (float)s.n.z, (float)t, 1.0f);
         }
         out[2 * i] = a;
@@ -595,7 +596,7 @@ static inline unsigned grid_cap(const Launch& l, int64_t n, int b) {
 
 void launch_prepare(const Launch& l, const ReqDesc& r, float4* Ep, const float* albedo, const float* rough, float4* tex4,
                     const float* nmap, const float* metal, float4* tex4b) {
-    const unsigned gp = Ep ? grid_of((int64_t)r.Wp * r.Hp, 256) : 0u, gt = grid_of((int64_t)r.tw * r.th, 256);
+    const unsigned gp = grid_of((int64_t)r.Wp * r.Hp, 256), gt = grid_of((int64_t)r.tw * r.th, 256);
     hipLaunchKernelGGL(k_prepare, dim3(gp + gt), dim3(256), 0, l.st, r, Ep, gp, albedo, rough, tex4, nmap, metal, tex4b);
 }
 void launch_set_count(const Launch& l, uint32_t* cnt, int idx, uint32_t value, int zero_from, int zero_to) {
@@ -693,9 +694,9 @@ void launch_debug_intersect(const Launch& l, const float4* nodes4, const float4*
     hipLaunchKernelGGL(k_debug_intersect, dim3(grid_of(n, TB)), dim3(TB), 0, l.st, nodes4, nodes, tris, leaf_of_prim,
                        nt, tmin, rays, n, mode, prim, t, b1, b2);
 }
-void launch_gbuffer(const Launch& l, const ReqDesc& r, float* out) {
+void launch_gbuffer(const Launch& l, const ReqDesc& r, const float* albedo, float* out) {
     const int64_t n = (int64_t)r.Wc * r.Hc;
-    hipLaunchKernelGGL(k_gbuffer, dim3(grid_cap(l, n, TB)), dim3(TB), 0, l.st, r, reinterpret_cast<float4*>(out));
+    hipLaunchKernelGGL(k_gbuffer, dim3(grid_cap(l, n, TB)), dim3(TB), 0, l.st, r, albedo, reinterpret_cast<float4*>(out));
 }
 void launch_debug_brdf(const Launch& l, int kind, const double* in, int64_t n, double* out) {
     if (n > 0) hipLaunchKernelGGL(k_debug_brdf, dim3(grid_of(n, 256)), dim3(256), 0, l.st, kind, in, n, out);

@@ -400,6 +400,7 @@ extern "C" void dpcs_context_destroy(dpcs_context ctx) {
     if (ctx->ev_shadow) (void)hipEventDestroy(ctx->ev_shadow);
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     if (ctx->dstats) (void)hipFree(ctx->dstats);
+    if (ctx->loss_count) (void)hipFree(ctx->loss_count);
     delete ctx;
 }
 
@@ -1009,13 +1010,8 @@ extern "C" dpcs_status dpcs_render_gbuffer(dpcs_context ctx, dpcs_scene scene, c
     std::string why;
     if (!fill_desc(ctx, r, params, scene, nullptr, &why, false)) return fail(ctx, DPCS_E_INVALID, why);
     if (!hip_ok(ctx, hipSetDevice(ctx->device), "hipSetDevice")) return DPCS_E_DEVICE;
-    dpcs_status st = DPCS_OK;
-    float4* tex = (float4*)scratch(ctx, "gbuf.tex", sizeof(float4) * (size_t)r.tw * r.th, &st);
-    if (!tex) return st;
     Launch l{ctx->stream, ctx->grid_cap};
-    launch_prepare(l, r, nullptr, params->albedo, nullptr, tex);
-    r.tex4 = tex;
-    launch_gbuffer(l, r, gbuffer);
+    launch_gbuffer(l, r, params->albedo, gbuffer);
     if (!hip_ok(ctx, hipGetLastError(), "render_gbuffer")) return DPCS_E_DEVICE;
     ctx->err.clear();
     return DPCS_OK;
