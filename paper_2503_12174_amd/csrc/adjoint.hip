@@ -919,6 +919,106 @@ __device__ __forceinline__ uint32_t* replay_count(const Queues& q, int depth) {
 __device__ __forceinline__ void replay_count_clear(const Queues& q, int depth) {
     if (blockIdx.x == 0 && threadIdx.x == 0) atomicExch(replay_count(q, depth + 2), 0u);
 }
+// what a replayed vertex hands on: the path's next state and the cotangents of its map records
+struct Replayed {
+    bool cont;
+    PathO no;
+    PathD nd;
+    float4 nb, nrl;
+    bool t_on, e_on;   // map cotangents of this vertex, E_p cotangent of its projector term
+    double t_u, t_v, e_pu, e_pv;
+};
+// the vertex at `depth` <= lit of the path (o, dd), throughput b and remaining radiance rl (both
+// times the sample's cotangent)
+template <bool TEX>
+__device__ __forceinline__ void replay_vertex(const ReqDesc& r, int depth, int lit, const PathO& o, const PathD& dd, float4 b,
+                                              float4 rl, Replayed& v, float (&tg)[5], float (&eg)[3]) {
+    const uint32_t g = dd.g;
+    const uint32_t rec = r.rec[(size_t)(g - r.rec_g0) * r.max_depth + depth];
+    const int leaf = rec_leaf(r, rec);
+    const Surf s = surface(r, leaf, d3(o.x, o.y, o.z), d3(dd.x, dd.y, dd.z));
+    const D3 db = d3(b.x, b.y, b.z);
+    if (TEX && r.emission) {
+        const float4 e = r.emission[leaf];
+        rl.x -= (float)(db.x * e.x);
+        rl.y -= (float)(db.y * e.y);
+        rl.z -= (float)(db.z * e.z);
+    }
+    D3 ga = d3(0., 0., 0.);
+    double gr = 0.0, gs = 0.0;
+    ProjNee p;
+    if ((rec & REC_PRJ) && projector_nee(r, s, p)) {
+        const Brdf f = brdf_eval<TEX>(r.brdf, s.n, s.wo, p.wp, s.alb, s.rough, s.spec);
+        const D3 gE = db * f.f * p.geom;   // d/dE_p before the bilinear weights
+        v.e_on = r.dEp != nullptr;
+        v.e_pu = p.pu;
+        v.e_pv = p.pv;
+        eg[0] = (float)gE.x;
+        eg[1] = (float)gE.y;
+        eg[2] = (float)gE.z;
+        if constexpr (TEX) {
+            const D4 E = fetch4(r.Ep, p.pb);
+            const D3 Ex = d3(E.x, E.y, E.z) * p.geom;
+            const D3 C = db * f.f * Ex;
+            const double sx = db.x * Ex.x + db.y * Ex.y + db.z * Ex.z;
+            ga = ga + db * Ex * (1.0 / PI);
+            gr += sx * f.ds_dr;
+            gs += sx * f.ds_dsp;
+            rl.x -= (float)C.x;
+            rl.y -= (float)C.y;
+            rl.z -= (float)C.z;
+        }
+    }
+    if constexpr (TEX) {
+        if (r.env_on && (rec & REC_ENV)) {
+            const U4 x = vertex_rng(r, g, 2u + 2u * depth);
+            const D3 we = sample_cosine(s.n, u24(x.x), u24(x.y));
+            const Brdf f = brdf_eval<true>(r.brdf, s.n, s.wo, we, s.alb, s.rough, s.spec);
+            const D3 Ee = d3(r.env[0], r.env[1], r.env[2]) * PI;
+            const D3 C = db * f.f * Ee;
+            const double sx = db.x * Ee.x + db.y * Ee.y + db.z * Ee.z;
+            ga = ga + db * Ee * (1.0 / PI);
+            gr += sx * f.ds_dr;
+            gs += sx * f.ds_dsp;
+            rl.x -= (float)C.x;
+            rl.y -= (float)C.y;
+            rl.z -= (float)C.z;
+        }
+    }
+    if (depth < lit) {
+        const U4 x = vertex_rng(r, g, 1u + 2u * depth);
+        const D3 wi = sample_bounce(r.brdf, s.n, s.wo, s.rough, u24(x.x), u24(x.y), u24(x.z));
+        const double ci = dot(s.n, wi);
+        const double pdf = bounce_pdf(r.brdf, s.n, s.wo, wi, s.rough);
+        if (ci > 0.0 && pdf > 0.0) {
+            const Brdf f = brdf_eval<TEX>(r.brdf, s.n, s.wo, wi, s.alb, s.rough, s.spec);
+            const D3 ndb = db * (f.f * (ci * frcp(pdf)));
+            v.cont = true;
+            v.no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
+            v.nd = PathD{wi.x, wi.y, wi.z, g, (uint32_t)lit};
+            v.nb = make_float4((float)ndb.x, (float)ndb.y, (float)ndb.z, 0.0f);
+            v.nrl = rl;
+            if constexpr (TEX) {   // d/df of beta f cos/pdf R_{k+1}: L_r / f
+                const D3 t = d3(f.f.x > 0.0 ? rl.x * frcp(f.f.x) : 0.0, f.f.y > 0.0 ? rl.y * frcp(f.f.y) : 0.0,
+                                f.f.z > 0.0 ? rl.z * frcp(f.f.z) : 0.0);
+                const double sum = t.x + t.y + t.z;
+                ga = ga + t * (1.0 / PI);
+                gr += sum * f.ds_dr;
+                gs += sum * f.ds_dsp;
+            }
+        }
+    }
+    if constexpr (TEX) {
+        v.t_u = s.u;
+        v.t_v = s.v;
+        tg[0] = (float)ga.x;
+        tg[1] = (float)ga.y;
+        tg[2] = (float)ga.z;
+        tg[3] = (float)gr;
+        tg[4] = (float)gs;
+        v.t_on = tg[0] != 0.f || tg[1] != 0.f || tg[2] != 0.f || tg[3] != 0.f || tg[4] != 0.f;
+    }
+}
 // One bounce of the replay when the forward kept its path records: the vertex's leaf and
 // the visibility of its shadow rays are read instead of traced.  Shading, the
 // next-event terms and the bounce are re-evaluated with the forward's Philox counters.
@@ -948,12 +1048,7 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay(Queues q, AdjQueues aq, in
         return;
     }
     const uint32_t i = base + threadIdx.x;
-    bool cont = false;
-    PathO no{};
-    PathD nd{};
-    float4 nb = {}, nrl = {};
-    bool t_on = false, e_on = false;   // map cotangents of this vertex, E_p cotangent of its projector term
-    double t_u = 0.0, t_v = 0.0, e_pu = 0.0, e_pv = 0.0;
+    Replayed v{};
     float tg[5] = {0.f, 0.f, 0.f, 0.f, 0.f}, eg[3] = {0.f, 0.f, 0.f};
     int lslot = -1;   // request slot of this lane's path (-1: no path)
     const ReqDesc* rp = &sel<UNI>(uni, table, 0);
@@ -991,119 +1086,35 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay(Queues q, AdjQueues aq, in
             const ReqDesc& r = sel<UNI>(uni, table, o.slot);
             rp = &r;
             lslot = o.slot;
-            const uint32_t g = dd.g;
-            const uint32_t rec = r.rec[(size_t)(g - r.rec_g0) * r.max_depth + depth];
-            const int leaf = rec_leaf(r, rec);
-            const Surf s = surface(r, leaf, d3(o.x, o.y, o.z), d3(dd.x, dd.y, dd.z));
-            const D3 db = d3(b.x, b.y, b.z);
-            if (TEX && r.emission) {
-                const float4 e = r.emission[leaf];
-                rl.x -= (float)(db.x * e.x);
-                rl.y -= (float)(db.y * e.y);
-                rl.z -= (float)(db.z * e.z);
-            }
-            D3 ga = d3(0., 0., 0.);
-            double gr = 0.0, gs = 0.0;
-            ProjNee p;
-            if ((rec & REC_PRJ) && projector_nee(r, s, p)) {
-                const Brdf f = brdf_eval<TEX>(r.brdf, s.n, s.wo, p.wp, s.alb, s.rough, s.spec);
-                const D3 gE = db * f.f * p.geom;   // d/dE_p before the bilinear weights
-                e_on = r.dEp != nullptr;
-                e_pu = p.pu;
-                e_pv = p.pv;
-                eg[0] = (float)gE.x;
-                eg[1] = (float)gE.y;
-                eg[2] = (float)gE.z;
-                if constexpr (TEX) {
-                    const D4 E = fetch4(r.Ep, p.pb);
-                    const D3 Ex = d3(E.x, E.y, E.z) * p.geom;
-                    const D3 C = db * f.f * Ex;
-                    const double sx = db.x * Ex.x + db.y * Ex.y + db.z * Ex.z;
-                    ga = ga + db * Ex * (1.0 / PI);
-                    gr += sx * f.ds_dr;
-                    gs += sx * f.ds_dsp;
-                    rl.x -= (float)C.x;
-                    rl.y -= (float)C.y;
-                    rl.z -= (float)C.z;
-                }
-            }
-            if constexpr (TEX) {
-                if (r.env_on && (rec & REC_ENV)) {
-                    const U4 x = vertex_rng(r, g, 2u + 2u * depth);
-                    const D3 we = sample_cosine(s.n, u24(x.x), u24(x.y));
-                    const Brdf f = brdf_eval<true>(r.brdf, s.n, s.wo, we, s.alb, s.rough, s.spec);
-                    const D3 Ee = d3(r.env[0], r.env[1], r.env[2]) * PI;
-                    const D3 C = db * f.f * Ee;
-                    const double sx = db.x * Ee.x + db.y * Ee.y + db.z * Ee.z;
-                    ga = ga + db * Ee * (1.0 / PI);
-                    gr += sx * f.ds_dr;
-                    gs += sx * f.ds_dsp;
-                    rl.x -= (float)C.x;
-                    rl.y -= (float)C.y;
-                    rl.z -= (float)C.z;
-                }
-            }
-            if (depth < lit) {
-                const U4 x = vertex_rng(r, g, 1u + 2u * depth);
-                const D3 wi = sample_bounce(r.brdf, s.n, s.wo, s.rough, u24(x.x), u24(x.y), u24(x.z));
-                const double ci = dot(s.n, wi);
-                const double pdf = bounce_pdf(r.brdf, s.n, s.wo, wi, s.rough);
-                if (ci > 0.0 && pdf > 0.0) {
-                    const Brdf f = brdf_eval<TEX>(r.brdf, s.n, s.wo, wi, s.alb, s.rough, s.spec);
-                    const D3 ndb = db * (f.f * (ci * frcp(pdf)));
-                    cont = true;
-                    no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
-                    nd = PathD{wi.x, wi.y, wi.z, g, (uint32_t)lit};
-                    nb = make_float4((float)ndb.x, (float)ndb.y, (float)ndb.z, 0.0f);
-                    nrl = rl;
-                    if constexpr (TEX) {   // d/df of beta f cos/pdf R_{k+1}: L_r / f
-                        const D3 t = d3(f.f.x > 0.0 ? rl.x * frcp(f.f.x) : 0.0, f.f.y > 0.0 ? rl.y * frcp(f.f.y) : 0.0,
-                                        f.f.z > 0.0 ? rl.z * frcp(f.f.z) : 0.0);
-                        const double sum = t.x + t.y + t.z;
-                        ga = ga + t * (1.0 / PI);
-                        gr += sum * f.ds_dr;
-                        gs += sum * f.ds_dsp;
-                    }
-                }
-            }
-            if constexpr (TEX) {
-                t_u = s.u;
-                t_v = s.v;
-                tg[0] = (float)ga.x;
-                tg[1] = (float)ga.y;
-                tg[2] = (float)ga.z;
-                tg[3] = (float)gr;
-                tg[4] = (float)gs;
-                t_on = tg[0] != 0.f || tg[1] != 0.f || tg[2] != 0.f || tg[3] != 0.f || tg[4] != 0.f;
-            }
+            replay_vertex<TEX>(r, depth, lit, o, dd, b, rl, v, tg, eg);
         }
     }
-    // records for the binned flush (direct atomics where there is no bin or it is full)
-    const bool to_t = UNI && TEX && t_on && aq.tb.rec, to_e = UNI && e_on && aq.eb.rec;
-    const bool pred[3] = {cont, to_t, to_e};
+    // records for the binned flush (direct atomics where there is v.no bin or it is full)
+    const bool to_t = UNI && TEX && v.t_on && aq.tb.rec, to_e = UNI && v.e_on && aq.eb.rec;
+    const bool pred[3] = {v.cont, to_t, to_e};
     uint32_t* const ctr[3] = {replay_count(q, depth + 1), aq.tb.count, aq.eb.count};
     uint32_t at[3];
     block_append<3>(pred, ctr, at);
     replay_count_clear(q, depth);
-    if (cont) {
+    if (v.cont) {
         const uint32_t jn = at[0];
-        nt_st(&q.po[nxt][jn], no);
-        nt_st(&q.pd[nxt][jn], nd);
-        nt_st(&q.pb[nxt][jn], nb);
-        if constexpr (TEX) nt_st(&aq.rl[nxt][jn], nrl);
+        nt_st(&q.po[nxt][jn], v.no);
+        nt_st(&q.pd[nxt][jn], v.nd);
+        nt_st(&q.pb[nxt][jn], v.nb);
+        if constexpr (TEX) nt_st(&aq.rl[nxt][jn], v.nrl);
     }
     if constexpr (UNI) {
         if (TEX) {
             if (aq.tb.rec) {
-                if (t_on && !put_tex_rec(aq.tb, at[1], t_u, t_v, tg)) scatter_tex_lane(*rp, t_u, t_v, tg);
+                if (v.t_on && !put_tex_rec(aq.tb, at[1], v.t_u, v.t_v, tg)) scatter_tex_lane(*rp, v.t_u, v.t_v, tg);
             } else {
-                scatter_tex(*rp, t_on, t_u, t_v, tg);
+                scatter_tex(*rp, v.t_on, v.t_u, v.t_v, tg);
             }
         }
         if (aq.eb.rec) {
-            if (e_on && !put_ep_rec(aq.eb, at[2], e_pu, e_pv, eg)) scatter_ep_lane(*rp, e_pu, e_pv, eg);
+            if (v.e_on && !put_ep_rec(aq.eb, at[2], v.e_pu, v.e_pv, eg)) scatter_ep_lane(*rp, v.e_pu, v.e_pv, eg);
         } else if (rp->dEp) {
-            scatter_ep(*rp, e_on, e_pu, e_pv, eg);
+            scatter_ep(*rp, v.e_on, v.e_pu, v.e_pv, eg);
         }
     } else {
         // several requests: when every path of this wave belongs to one of them (the
@@ -1112,11 +1123,56 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay(Queues q, AdjQueues aq, in
         const int s0 = vm ? __shfl(lslot, __ffsll(vm) - 1) : -1;
         if (s0 >= 0 && __ballot(lslot >= 0 && lslot != s0) == 0ull) {
             const ReqDesc& rr = table[s0];
-            scatter_tex(rr, t_on, t_u, t_v, tg);
-            if (rr.dEp) scatter_ep(rr, e_on, e_pu, e_pv, eg);
+            scatter_tex(rr, v.t_on, v.t_u, v.t_v, tg);
+            if (rr.dEp) scatter_ep(rr, v.e_on, v.e_pu, v.e_pv, eg);
         } else {
-            if (t_on) scatter_tex_lane(*rp, t_u, t_v, tg);
-            if (e_on) scatter_ep_lane(*rp, e_pu, e_pv, eg);
+            if (v.t_on) scatter_tex_lane(*rp, v.t_u, v.t_v, tg);
+            if (v.e_on) scatter_ep_lane(*rp, v.e_pu, v.e_pv, eg);
+        }
+    }
+}
+
+// A small wave's replay, one thread per sample over all its depths: the map records of every depth go
+// to the bins before one flush (so max_depth <= BIN_DEPTHS), and the path state stays in registers.
+// Bound by the latency of a sample's chain of loads and FP64 operations; once the chip is full, the
+// queues' launches win, which gather the samples that go on (186 registers here: 2 waves per SIMD).
+template <bool TEX>
+__global__ void __launch_bounds__(BLOCK) k_replay_paths(Queues q, AdjQueues aq, uint32_t n, const float* __restrict__ sample_L,
+                                                        ReqDesc r) {
+    const uint32_t i = blockIdx.x * BLOCK + threadIdx.x;
+    PathO o{r.cam_o[0], r.cam_o[1], r.cam_o[2], 0, -1};
+    PathD d{};
+    float4 b = {}, rl = {};
+    int lit = -1;
+    if (i < n) {
+        const uint32_t g = r.g_base + i;
+        const ReplayStart t = replay_start<TEX>(r, g, sample_L, q.L, aq.delta);
+        lit = t.lit;
+        b = t.dl;
+        rl = make_float4(t.dl.x * t.L.x, t.dl.y * t.L.y, t.dl.z * t.L.z, 0.f);
+        if (lit >= 0) {
+            const D3 cd = camera_dir(r, g);
+            d = PathD{cd.x, cd.y, cd.z, g, 0u};
+        }
+    }
+    for (int depth = 0; __syncthreads_or(lit >= depth); ++depth) {   // uniform per workgroup; lit < max_depth
+        Replayed v{};
+        float tg[5] = {0.f, 0.f, 0.f, 0.f, 0.f}, eg[3] = {0.f, 0.f, 0.f};
+        if (lit >= depth) replay_vertex<TEX>(r, depth, lit, o, d, b, rl, v, tg, eg);
+        const bool to_t = TEX && v.t_on;
+        const bool pred[2] = {to_t, v.e_on};
+        uint32_t* const ctr[2] = {aq.tb.count, aq.eb.count};
+        uint32_t at[2];
+        block_append<2>(pred, ctr, at);
+        if (to_t && !put_tex_rec(aq.tb, at[0], v.t_u, v.t_v, tg)) scatter_tex_lane(r, v.t_u, v.t_v, tg);
+        if (v.e_on && !put_ep_rec(aq.eb, at[1], v.e_pu, v.e_pv, eg)) scatter_ep_lane(r, v.e_pu, v.e_pv, eg);
+        if (v.cont) {
+            o = v.no;
+            d = v.nd;
+            b = v.nb;
+            rl = v.nrl;
+        } else {
+            lit = -1;
         }
     }
 }
@@ -1450,6 +1506,15 @@ void launch_adj_replay(const Launch& l, const Queues& q, const AdjQueues& aq, in
         if (uni.d_tex) hipLaunchKernelGGL((k_adj_replay<true, true>), g, b, 0, l.st, q, aq, cur, depth, sample_L, uni, table);
         else hipLaunchKernelGGL((k_adj_replay<true, false>), g, b, 0, l.st, q, aq, cur, depth, sample_L, uni, table);
     }
+}
+bool small_replay(const AdjQueues& aq, const ReqDesc& r, int64_t n) {
+    return n <= SMALL_REPLAY && r.max_depth <= BIN_DEPTHS && !r.tex4b && (!r.d_tex || aq.tb.rec) && (!r.dEp || aq.eb.rec);
+}
+void launch_replay_paths(const Launch& l, const Queues& q, const AdjQueues& aq, const ReqDesc& r, uint32_t n,
+                         const float* sample_L) {
+    const dim3 g(grid_of(n, BLOCK)), b(BLOCK);
+    if (r.d_tex) hipLaunchKernelGGL(k_replay_paths<true>, g, b, 0, l.st, q, aq, n, sample_L, r);
+    else hipLaunchKernelGGL(k_replay_paths<false>, g, b, 0, l.st, q, aq, n, sample_L, r);
 }
 bool map_tiling(int W, int H, int& T, int& nbx, int& nby) {
     for (int t = 8; t <= MAP_MAX_T; t *= 2) {

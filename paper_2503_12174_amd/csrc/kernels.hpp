@@ -291,6 +291,14 @@ void launch_adj_shadow(const Launch& l, const Queues& q, const AdjQueues& aq, in
 void launch_adj_replay(const Launch& l, const Queues& q, const AdjQueues& aq, int cur, int depth, const ReqDesc& uni,
                        const ReqDesc* table, int64_t n_upper, const float* sample_L = nullptr);
 // adds the binned records of tb / eb into r.d_tex / r.dEp and empties the bins
+// The whole replay of a small wave from its records (small_replay: where that pays, and the bins
+// hold every depth's records).  Forward and VJP by depth and whole: quad and cube, 64 x 64 x 32 150
+// and 143 us, 128 x 128 x 16 177 and 182, 256 x 256 x 16 390 and 473; corner of 50k triangles, 128 x
+// 128 x 8 482 and 476, 256 x 256 x 4 375 and 389.
+constexpr int64_t SMALL_REPLAY = 1 << 17;
+bool small_replay(const AdjQueues& aq, const ReqDesc& r, int64_t n);
+void launch_replay_paths(const Launch& l, const Queues& q, const AdjQueues& aq, const ReqDesc& r, uint32_t n,
+                         const float* sample_L = nullptr);
 void launch_map_flush(const Launch& l, const AdjQueues& aq, const ReqDesc& r);
 // tile side and bin count for a W x H map (false: too many tiles, bin nothing)
 bool map_tiling(int W, int H, int& T, int& nbx, int& nby);

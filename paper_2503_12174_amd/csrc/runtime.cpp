@@ -849,6 +849,11 @@ void adjoint_wave(dpcs_context ctx, Queues& q, const AdjQueues& aq, ReqDesc& r, 
     int cur = 0;
     if (r.rec) {   // the forward's path records stand in for tracing (camera rays regenerated in depth 0)
         if (!r.d_tex && !r.dEp) return;   // no map or projector gradient asked for
+        if (!ctx->prof_mode && small_replay(aq, r, n)) {
+            launch_replay_paths(l, q, aq, r, n, sample_L);
+            launch_map_flush(l, aq, r);
+            return;
+        }
         // (the replay's queue sizes rotate over their own slots: one reset for all depths)
         launch_set_count(l, q.cnt, REPLAY_CNT, n, REPLAY_CNT + 1, REPLAY_CNT + 2);
         for (int d = 0; d < r.max_depth; ++d) {

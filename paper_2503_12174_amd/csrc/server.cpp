@@ -398,6 +398,11 @@ void dpcs_server_s::wave(Launch& l) {
                     tb_nb = ab.tb.nb;
                     eb_nb = ab.eb.nb;
                 }
+                if (small_replay(ab, s.q->r, n)) {
+                    launch_replay_paths(l, q, ab, s.q->r, n);
+                    launch_map_flush(l, ab, s.q->r);
+                    continue;
+                }
                 launch_set_count(l, q.cnt, REPLAY_CNT, n, REPLAY_CNT + 1, REPLAY_CNT + 2);
                 cur = 0;
                 for (int d = 0; d < s.q->r.max_depth; ++d) {   // (it makes its camera rays itself)

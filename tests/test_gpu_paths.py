@@ -83,3 +83,37 @@ def test_edge_paths_equal_the_queues(env, depth):
         if "cam" in k:
             np.testing.assert_array_equal(res[0][k], res[1][k], err_msg=k)
             assert np.abs(res[0][k]).max() > 0
+
+
+@pytest.mark.parametrize("maps", [True, False])
+@pytest.mark.parametrize("name,depth", [("quad and cube", 3), ("corner", 1), ("corner, lit", 4), ("corner, lit", 5)])
+def test_whole_replays_equal_the_queues(name, depth, maps):
+    """Small waves of up to four depths are replayed whole, others depth by depth: the map sums
+    are exact, so every gradient has the same bits."""
+    import torch
+    from paper_2503_12174_amd import dpcs
+    from .gpu_util import dev
+    w = _case(name)
+    w.max_depth = depth
+    run = GpuRun(w)
+    p, c = run.params, ctx()
+    H, W = p.camera.height, p.camera.width
+    G = dev(np.random.default_rng(4).normal(size=(H, W, 3)), torch.float32)
+    res = []
+    for prof in (0, 1):
+        c.set_profiling(prof)
+        L = torch.zeros((H, W, p.spp, 3), device="cuda")
+        rec = torch.zeros((H, W, p.spp, p.max_depth), dtype=torch.int32, device="cuda")
+        img = torch.zeros((H, W, 3), device="cuda")
+        dpcs.dpcs_render(c, run.scene, p, run.proj, img, sample_radiance=L, path_records=rec)
+        g = dict(d_proj_image=torch.zeros_like(run.proj), d_scalars=torch.zeros(18, device="cuda"))
+        if maps:
+            g.update(d_albedo=torch.zeros_like(run.albedo), d_roughness=torch.zeros_like(run.rough),
+                     d_specular=torch.zeros_like(run.spec))
+        dpcs.dpcs_render_vjp(c, run.scene, p, run.proj, G, sample_radiance=L, path_records=rec, **g)
+        c.synchronize()
+        res.append({k: v.cpu().numpy() for k, v in g.items()})
+    c.set_profiling(0)
+    for k in res[0]:
+        np.testing.assert_array_equal(res[0][k], res[1][k], err_msg=k)
+    assert np.abs(res[0]["d_proj_image"]).max() > 0
