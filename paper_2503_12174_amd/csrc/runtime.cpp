@@ -796,8 +796,11 @@ void forward_wave(dpcs_context ctx, Queues& q, ReqDesc& r, uint32_t a, uint32_t 
     int cur = 0;
     // A depth's shadow rays run on the side stream (with their own spill region) while the
     // next depth's closest hit runs here, so each fills the other's tail; shading waits
-    // for the previous depth's shadow rays (both add to the samples' radiance), and so
-    // does the finalize.  Profiling keeps every launch on this stream.
+    // for the previous depth's shadow rays (both add to the samples' radiance).  The last
+    // depth's have nothing beside them and stay on this stream (each hand-over between the
+    // streams leaves it idle for 6 to 12 us: 256 x 256 x 64 of the 50k-triangle corner 1520 us so,
+    // 1503 now).
+    // Profiling keeps every launch on this stream.
     const bool side = spill2 && !ctx->prof_mode && (int64_t)n >= SIDE_MIN_PATHS && side_stream(ctx);
     Queues qs = q;
     qs.spill = spill2;
@@ -813,7 +816,7 @@ void forward_wave(dpcs_context ctx, Queues& q, ReqDesc& r, uint32_t a, uint32_t 
         launch_shade(l, q, cur, d, r, nullptr, n, d == 0);
         prof_end(ctx, pr, q.cnt + cur, 0);
         q.stats = prof_stats(ctx, DPCS_STAGE_SHADOW);
-        if (side) {
+        if (side && d + 1 < r.max_depth) {
             (void)hipEventRecord(ctx->ev_shade, ctx->stream);
             (void)hipStreamWaitEvent(ctx->side, ctx->ev_shade, 0);
             for (int w = 0; w < (r.env_on ? 2 : 1); ++w) launch_shadow(ls, qs, w, r, nullptr, n, d);
@@ -828,7 +831,6 @@ void forward_wave(dpcs_context ctx, Queues& q, ReqDesc& r, uint32_t a, uint32_t 
         q.stats = nullptr;
         cur ^= 1;
     }
-    if (side) (void)hipStreamWaitEvent(ctx->stream, ctx->ev_shadow, 0);
     if (finalize) {
         pr = prof_begin(ctx, DPCS_STAGE_FINALIZE);
         launch_finalize(l, q, r, nullptr, 0, a, b);
