@@ -50,27 +50,30 @@ def kernel_hash() -> str:
 
 # algorithmic bytes of one closest-hit query in this layout: path origin and
 # direction read (PathO + PathD = 64 B), each visited BVH node (64 B binary, 128 B
-# 4-wide), each tested triangle record (48 B), the hit index written (4 B)
+# 4-wide), each tested triangle's corners (48 B of its 64 B record), the hit index
+# written (4 B)
 RAY_IO_BYTES = 64 + 4
 NODE_BYTES = 64       # binary BVH node: two child boxes + two child references
 NODE4_BYTES = 128     # 4-wide BVH node: four child boxes (SoA) + four references + pad
 TRI_BYTES = 48
-UV_BYTES = 32          # corner UVs of a triangle
+TRI_RECORD = 64        # the whole record: corners, index, texture coordinates
 SHADE_STATE_IN = 84    # PathO + PathD + throughput + hit index
 PATH_STATE = 80        # PathO + PathD + throughput written for a continuing path
 SHADOW_RECORD = 52     # shadow origin, direction, contribution float4s + t_max
 
 # algorithmic FP32 operations of one closest-hit query (each add, mul, FMA, min, max,
 # compare or select is one operation; a component permutation is a register choice):
-#   per ray      box setup (3 reciprocals, 3 products, 3 error bounds, 6 offsets), the
-#                watertight setup (axis choice 4, 3 quotients), the exact test of the
-#                winner for t and the barycentrics (33 + 3) = 15 + 7 + 36
-#   per node     4 children x (6 slab FMAs, 4 ops of the two 3-way max / min, 2 widenings,
-#                2 clamps, 1 compare) + 5 compare-exchanges ordering the children (3 each)
+#   per ray      box setup (3 reciprocals, 3 products, 3 error bounds, 6 offsets, the
+#                widening of 6 reciprocals and 6 offsets), the watertight setup (axis
+#                choice 4, 3 quotients), the exact test of the winner for t and the
+#                barycentrics (33 + 3) = 27 + 7 + 36
+#   per node     4 children x (6 slab FMAs, 4 ops of the two 3-way max / min, 2 clamps,
+#                1 compare) + 5 compare-exchanges ordering the children (2 each)
+#                (a binary node still widens per box)
 #   per triangle 9 subtractions, 6 FMAs of the shear, 6 of the edge functions, 2 of the
 #                sign test, 2 for the determinant, 3 for T, 3 for t = T Sz / det, 2 range
 #                compares
-OPS_RAY, OPS_NODE4, OPS_NODE2, OPS_TRI = 58, 75, 31, 33
+OPS_RAY, OPS_NODE4, OPS_NODE2, OPS_TRI = 70, 62, 31, 33
 
 
 def parse():
@@ -565,12 +568,12 @@ def main():
             stages["shadow"]["tris_per_ray"] = round(sh["tris"] / sh["items"], 2)
         roof["rays_per_s"] = round(rays_per_launch / (avg_ms * 1e-3), 1)
         # shading's model bytes over the profiled steps (layout above): every vertex reads its
-        # path state, triangle and UV records, 4 packed albedo/roughness texels, 4 specular
+        # path state, triangle record, 4 packed albedo/roughness texels, 4 specular
         # texels and writes a path record; each projector shadow record adds 4 projector
         # texels read and the record written; each continuing path writes its next state
         sd = prof["shade"]
         cont = tr["items"] - prof["raygen"]["items"]
-        shade_bytes = (sd["items"] * (SHADE_STATE_IN + TRI_BYTES + UV_BYTES + 4 * 16 + 4 * 4 + 4)
+        shade_bytes = (sd["items"] * (SHADE_STATE_IN + TRI_RECORD + 4 * 16 + 4 * 4 + 4)
                        + prof["shadow"]["items"] * (4 * 16 + SHADOW_RECORD) + cont * PATH_STATE)
         roof["shade_model_GBps"] = round(shade_bytes / (sd["ms"] * 1e-3) / 1e9, 1)
         # measured device-copy bandwidth (1 GiB read + 1 GiB written), beside the spec peak

@@ -280,12 +280,14 @@ __device__ __forceinline__ void sort2(uint32_t& a, uint32_t& b) {
 // near-axis-parallel rays.  The widening, t x (1 -+ 4e-6), is in the constants, so a box
 // test takes no product for it (the closest-hit loop is bound by vector issue: 256 x 256 x
 // 64 of the 50k-triangle corner 1583 us with the two products, 1580 without, and 1587 before
-// the triangle test lost its swap of two axes; with an environment map 2200, 2193, 2180).  An axis along which the ray does not move
-// (|d| < 2^-80, or 0) takes the reciprocal 2^80; every offset is widened by 2^-40 in space
-// besides, so such a slab lets pass exactly the boxes that hold the ray's coordinate, faces
-// included.  (With 1 / 0 both slab values came out NaN and the axis let every box
-// pass: a bounce straight along the normal of an axis-aligned face, one sample in 2^24,
-// walked a whole wall of the corner, 12 ms for one ray.)  The widening multiplies rather than adding a multiple of |t|, so infinite slab values stay infinite instead of turning NaN,
+// the triangle test lost its swap of two axes; with an environment map 2200, 2193, 2180).
+// An axis along which the ray does not move (|d| < 2^-80, or 0) takes the reciprocal 2^80;
+// every offset is widened by 2^-40 in space besides, so such a slab lets pass exactly the
+// boxes that hold the ray's coordinate, faces included.  (With 1 / 0 both slab values came
+// out NaN and the axis let every box pass: a bounce straight along the normal of an
+// axis-aligned face, one sample in 2^24, walked a whole wall of the corner, 12 ms for one
+// ray.)  The widening multiplies rather than adding a multiple of |t|, so infinite slab
+// values stay infinite instead of turning NaN,
 // and an inverted box (lo = +1e30, hi = -1e30: every near plane ahead of every far
 // plane) is always missed.
 struct Box4Ray {
