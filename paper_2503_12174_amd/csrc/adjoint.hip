@@ -208,9 +208,10 @@ __device__ __forceinline__ bool put_ep_rec(const MapBins& mb, uint32_t slot, dou
 // at the pixel's first sample: the replay forms a sample's own from it and the sample's
 // radiance, so this pass reads the radiance once and writes 16 bytes per pixel (256^2 x 64
 // spp: 48 -> 16 us, bound by that read).
-__global__ void __launch_bounds__(BLOCK) k_adj_pixel(Queues q, AdjQueues aq, ReqDesc r, uint32_t p0, uint32_t p1,
-                                                     const float* sample_L, float4* pix_dE, bool per_sample) {
-    const uint32_t p = p0 + (blockIdx.x * BLOCK + threadIdx.x) / PIX_LANES;
+__device__ __forceinline__ void adj_pixel_block(const Queues& q, const AdjQueues& aq, const ReqDesc& r, uint32_t block,
+                                                uint32_t p0, uint32_t p1, const float* sample_L, float4* pix_dE,
+                                                bool per_sample) {
+    const uint32_t p = p0 + (block * BLOCK + threadIdx.x) / PIX_LANES;
     const int lane = threadIdx.x & (PIX_LANES - 1);
     float acc[7] = {0, 0, 0, 0, 0, 0, 0};   // d gamma_c[3], d w[3], d threshold
     if (p < p1) {   // uniform per lane group
@@ -284,9 +285,19 @@ __global__ void __launch_bounds__(BLOCK) k_adj_pixel(Queues q, AdjQueues aq, Req
     if (threadIdx.x < 7) {
         float v = 0.f;
         for (int k = 0; k < BLOCK / 64; ++k) v += red[threadIdx.x][k];
-        if (r.d_part) r.d_part[8 * (size_t)blockIdx.x + threadIdx.x] = v;
+        if (r.d_part) r.d_part[8 * (size_t)block + threadIdx.x] = v;
         else if (v != 0.f) atomicAdd(&r.d_acc[threadIdx.x], v);
     }
+}
+__global__ void __launch_bounds__(BLOCK) k_adj_pixel(Queues q, AdjQueues aq, ReqDesc r, uint32_t p0, uint32_t p1,
+                                                     const float* sample_L, float4* pix_dE, bool per_sample) {
+    adj_pixel_block(q, aq, r, blockIdx.x, p0, p1, sample_L, pix_dE, per_sample);
+}
+__global__ void __launch_bounds__(BLOCK) k_adj_pixel_segs(Queues q, AdjQueues aq, SegList segs,
+                                                          const ReqDesc* __restrict__ table, bool per_sample) {
+    const int k = seg_of(segs, blockIdx.x);
+    adj_pixel_block(q, aq, table[segs.slot[k]], blockIdx.x - segs.first[k], segs.p0[k], segs.p1[k], nullptr, nullptr,
+                    per_sample);
 }
 
 // dst[k] += the sum over nb workgroup partials part[b * stride + k], k < nv, in a fixed
@@ -1352,14 +1363,14 @@ __device__ __forceinline__ void adj_maps(const ReqDesc& r, int t, float* d_albed
                                          float* d_metal, float* d_nmap);
 // workgroups [0, gp): the PRF backward per projector texel (per-block partials of the
 // 12 scalars); the rest: the map cotangents copied out per texel (adj_maps)
-__global__ void __launch_bounds__(BLOCK) k_adj_prf(ReqDesc r, float* __restrict__ d_proj, float* __restrict__ acc,
-                                                   int gp, float* d_albedo, float* d_rough, float* d_spec,
-                                                   float* d_metal, float* d_nmap) {
-    if ((int)blockIdx.x >= gp) {   // uniform per workgroup
-        adj_maps(r, (blockIdx.x - gp) * BLOCK + threadIdx.x, d_albedo, d_rough, d_spec, d_metal, d_nmap);
+__device__ __forceinline__ void adj_prf_block(const ReqDesc& r, int block, float* __restrict__ d_proj,
+                                              float* __restrict__ acc, int gp, float* d_albedo, float* d_rough,
+                                              float* d_spec, float* d_metal, float* d_nmap) {
+    if (block >= gp) {   // uniform per workgroup
+        adj_maps(r, (block - gp) * BLOCK + threadIdx.x, d_albedo, d_rough, d_spec, d_metal, d_nmap);
         return;
     }
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    const int t = block * BLOCK + threadIdx.x;
     float part[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};   // d gamma_p[3], d M[9]
     if (t < r.Wp * r.Hp) {
         float x[3], y[3], z[3], dz[3];
@@ -1394,9 +1405,28 @@ __global__ void __launch_bounds__(BLOCK) k_adj_prf(ReqDesc r, float* __restrict_
     if (threadIdx.x < 12) {
         float v = 0.f;
         for (int k = 0; k < BLOCK / 64; ++k) v += red[threadIdx.x][k];
-        if (r.d_part) r.d_part[12 * (size_t)blockIdx.x + threadIdx.x] = v;
+        if (r.d_part) r.d_part[12 * (size_t)block + threadIdx.x] = v;
         else if (v != 0.f) atomicAdd(&acc[8 + threadIdx.x], v);
     }
+}
+__global__ void __launch_bounds__(BLOCK) k_adj_prf(ReqDesc r, float* __restrict__ d_proj, float* __restrict__ acc,
+                                                   int gp, float* d_albedo, float* d_rough, float* d_spec,
+                                                   float* d_metal, float* d_nmap) {
+    adj_prf_block(r, (int)blockIdx.x, d_proj, acc, gp, d_albedo, d_rough, d_spec, d_metal, d_nmap);
+}
+// several requests of the loop: where each goes (workgroups first[k], the first gp[k] of them
+// on projector texels)
+struct FinishList {
+    int32_t n;
+    int32_t slot[WAVE_SEGS], gp[WAVE_SEGS];
+    uint32_t first[WAVE_SEGS];
+    float *d_proj[WAVE_SEGS], *d_albedo[WAVE_SEGS], *d_rough[WAVE_SEGS], *d_spec[WAVE_SEGS], *d_scalars[WAVE_SEGS];
+};
+__global__ void __launch_bounds__(BLOCK) k_adj_prf_segs(FinishList f, const ReqDesc* __restrict__ table) {
+    const int k = seg_of(f, blockIdx.x);
+    const ReqDesc& r = table[f.slot[k]];
+    adj_prf_block(r, (int)(blockIdx.x - f.first[k]), f.d_proj[k], r.d_acc, f.gp[k], f.d_albedo[k], f.d_rough[k], f.d_spec[k],
+                  nullptr, nullptr);
 }
 
 // scalar gradients and the de-interleaving of the map cotangents
@@ -1428,19 +1458,7 @@ __device__ __forceinline__ void adj_maps(const ReqDesc& r, int t, float* d_albed
     if (d_spec) d_spec[t] = r.brdf ? s[4] : 0.f;
 }
 
-// one 256-thread workgroup: the PRF backward's partials (nb blocks) into acc[8..20), then
-// the scalar gradients
-// (one wave per value: a workgroup that took the twelve in turn spent 12 us in its barriers)
-__global__ void __launch_bounds__(768) k_adj_scalars(ReqDesc r, float* __restrict__ acc, float* d_scalars, int nb) {
-    if (r.d_part) {
-        const int k = threadIdx.x >> 6;
-        double s = 0.0;
-        for (int b = threadIdx.x & 63; b < nb; b += 64) s += r.d_part[(size_t)b * 12 + k];
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-        if ((threadIdx.x & 63) == 0 && s != 0.0) acc[8 + k] += (float)s;
-        __syncthreads();
-    }
-    if (threadIdx.x != 0 || !d_scalars) return;
+__device__ __forceinline__ void write_scalars(const ReqDesc& r, const float* acc, float* d_scalars) {
     for (int k = 0; k < 12; ++k) d_scalars[k] = acc[8 + k];           // gamma_p, M
     for (int c = 0; c < 3; ++c) {
         d_scalars[12 + c] = acc[c];                                    // gamma_c
@@ -1453,6 +1471,25 @@ __global__ void __launch_bounds__(768) k_adj_scalars(ReqDesc r, float* __restric
         const float wa = scalar(r, 15 + a);
         d_scalars[15 + a] += -acc[6] * r.clip_k / (wa * wa);
     }
+}
+// one 256-thread workgroup: the PRF backward's partials (nb blocks) into acc[8..20), then
+// the scalar gradients
+// (one wave per value: a workgroup that took the twelve in turn spent 12 us in its barriers)
+__global__ void __launch_bounds__(768) k_adj_scalars(ReqDesc r, float* __restrict__ acc, float* d_scalars, int nb) {
+    if (r.d_part) {
+        const int k = threadIdx.x >> 6;
+        double s = 0.0;
+        for (int b = threadIdx.x & 63; b < nb; b += 64) s += r.d_part[(size_t)b * 12 + k];
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        if ((threadIdx.x & 63) == 0 && s != 0.0) acc[8 + k] += (float)s;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0 && d_scalars) write_scalars(r, acc, d_scalars);
+}
+__global__ void k_adj_scalars_segs(FinishList f, const ReqDesc* __restrict__ table) {   // (the atomics have summed them)
+    const ReqDesc& r = table[f.slot[blockIdx.x]];
+    float* const d_scalars = f.d_scalars[blockIdx.x];
+    if (threadIdx.x == 0 && d_scalars) write_scalars(r, r.d_acc, d_scalars);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -1469,6 +1506,13 @@ void launch_adj_pixel(const Launch& l, const Queues& q, const AdjQueues& aq, con
     hipLaunchKernelGGL(k_adj_pixel, dim3(g), dim3(BLOCK), 0, l.st, q, aq, r, p0, p1, sample_L, pix_dE,
                        per_sample);
     if (r.d_part) hipLaunchKernelGGL(k_sum_partials, dim3(7), dim3(SUM_TB), 0, l.st, r.d_part, (int)g, 8, 7, r.d_acc);
+}
+void launch_adj_pixel(const Launch& l, const Queues& q, const AdjQueues& aq, const ReqDesc* table, const WaveSeg* segs,
+                      int n, bool per_sample) {
+    for_seg_lists(segs, n, [](const WaveSeg& s) { return grid_of((int64_t)(s.p1 - s.p0) * PIX_LANES, BLOCK); },
+                  [&](const SegList& a, uint32_t g) {
+                      hipLaunchKernelGGL(k_adj_pixel_segs, dim3(g), dim3(BLOCK), 0, l.st, q, aq, a, table, per_sample);
+                  });
 }
 size_t partial_floats(int64_t pixels_per_wave, int64_t proj_pixels) {
     return std::max<size_t>(8 * (size_t)grid_of(pixels_per_wave * PIX_LANES, BLOCK), 12 * (size_t)grid_of(proj_pixels, BLOCK));
@@ -1560,6 +1604,28 @@ void launch_adj_finish(const Launch& l, const ReqDesc& r, float* d_proj, float* 
     hipLaunchKernelGGL(k_adj_prf, dim3(g + gm), dim3(BLOCK), 0, l.st, r, d_proj, acc, (int)g, d_albedo, d_rough,
                        d_spec, d_metal, d_nmap);
     hipLaunchKernelGGL(k_adj_scalars, dim3(1), dim3(768), 0, l.st, r, acc, d_scalars, (int)g);
+}
+void launch_adj_finish(const Launch& l, const ReqDesc* table, const FinishSeg* segs, int n) {
+    for (int k = 0; k < n; k += WAVE_SEGS) {
+        FinishList f{};
+        uint32_t g = 0;
+        for (int j = k; j < n && j < k + WAVE_SEGS; ++j) {
+            const FinishSeg& s = segs[j];
+            const bool maps = s.d_albedo || s.d_rough || s.d_spec;
+            f.slot[f.n] = s.slot;
+            f.gp[f.n] = (int32_t)grid_of(s.ep_pixels, BLOCK);
+            f.first[f.n] = g;
+            f.d_proj[f.n] = s.d_proj;
+            f.d_albedo[f.n] = s.d_albedo;
+            f.d_rough[f.n] = s.d_rough;
+            f.d_spec[f.n] = s.d_spec;
+            f.d_scalars[f.n] = s.d_scalars;
+            g += (uint32_t)f.gp[f.n] + (maps ? grid_of(s.map_texels, BLOCK) : 0u);
+            ++f.n;
+        }
+        hipLaunchKernelGGL(k_adj_prf_segs, dim3(g), dim3(BLOCK), 0, l.st, f, table);
+        hipLaunchKernelGGL(k_adj_scalars_segs, dim3(f.n), dim3(64), 0, l.st, f, table);
+    }
 }
 
 }  // namespace dpcs

@@ -249,8 +249,54 @@ struct Launch {
 void launch_prepare(const Launch& l, const ReqDesc& r, float4* Ep, const float* albedo, const float* rough, float4* tex4,
                     const float* nmap = nullptr, const float* metal = nullptr, float4* tex4b = nullptr);
 void launch_set_count(const Launch& l, uint32_t* cnt, int idx, uint32_t value, int zero_from, int zero_to);
-void launch_raygen(const Launch& l, const Queues& q, const ReqDesc& r, const ReqDesc* table, int slot,
-                   uint32_t g0, uint32_t n, bool adjoint, const AdjQueues* aq);
+// The request loop's per-request launches, for all segments of a wave at once: a segment is
+// pixels [p0, p1) of the request in descriptor slot `slot` (table[slot], at spp samples a
+// pixel).  Each is a few microseconds on a few hundred workgroups, most of it the launch itself
+// (4,096 pixels of 32 samples: camera rays 6 us, finalize 8, pixel backward 11, finish 8 + 3), so a
+// list of up to WAVE_SEGS segments shares one: workgroup b belongs to the last segment
+// whose first[] is not beyond it.  A step of 8 such pairs, in three waves: 1492 us a request at a
+// time, 1305 us so.
+constexpr int WAVE_SEGS = 16;
+struct WaveSeg {
+    int32_t slot;
+    uint32_t p0, p1;
+    int32_t spp;
+};
+struct SegList {
+    int32_t n;
+    int32_t slot[WAVE_SEGS];
+    uint32_t p0[WAVE_SEGS], p1[WAVE_SEGS], first[WAVE_SEGS];
+};
+// Runs go(list, workgroups) for the segments in lists of at most WAVE_SEGS; blocks(segment) is
+// the number of workgroups a segment takes (0: none, left out).
+template <class BLOCKS, class GO>
+void for_seg_lists(const WaveSeg* segs, int n, BLOCKS blocks, GO go) {
+    SegList a{};
+    uint32_t g = 0;
+    for (int k = 0; k < n; ++k) {
+        const uint32_t b = blocks(segs[k]);
+        if (b == 0) continue;
+        if (a.n == WAVE_SEGS) {
+            go(a, g);
+            a.n = 0;
+            g = 0;
+        }
+        a.slot[a.n] = segs[k].slot;
+        a.p0[a.n] = segs[k].p0;
+        a.p1[a.n] = segs[k].p1;
+        a.first[a.n++] = g;
+        g += b;
+    }
+    if (a.n > 0) go(a, g);
+}
+// the segment of a workgroup
+template <class LIST>
+__host__ __device__ inline int seg_of(const LIST& a, uint32_t block) {
+    int k = 0;
+    for (int j = 1; j < a.n; ++j) k += block >= a.first[j] ? 1 : 0;
+    return k;
+}
+void launch_raygen(const Launch& l, const Queues& q, const ReqDesc* table, const WaveSeg* segs, int n);
 // cam (one request, no table): the queue is the request's camera rays, generated by the
 // closest-hit and shading kernels themselves (no raygen launch, no path state read)
 void launch_trace(const Launch& l, const Queues& q, int cur, const ReqDesc& uni, const ReqDesc* table,
@@ -266,9 +312,11 @@ void launch_shadow(const Launch& l, const Queues& q, int which, const ReqDesc& u
 // spill region holds that many threads).
 void launch_paths(const Launch& l, const Queues& q, const ReqDesc& r, const ReqDesc* table, uint32_t n, bool cam);
 bool small_wave(const Queues& q, const ReqDesc& r, int64_t n);
-void launch_finalize(const Launch& l, const Queues& q, const ReqDesc& r, const ReqDesc* table, int slot,
-                     uint32_t p0, uint32_t p1);
-void launch_set_desc(const Launch& l, ReqDesc* table, int slot, const ReqDesc& r);
+void launch_finalize(const Launch& l, const Queues& q, const ReqDesc& r, uint32_t p0, uint32_t p1);
+void launch_finalize(const Launch& l, const Queues& q, const ReqDesc* table, const WaveSeg* segs, int n);
+// table[slot[k]] = *r[k], k < n: up to DESC_BATCH descriptors as the arguments of one launch
+constexpr int DESC_BATCH = 4;
+void launch_set_desc(const Launch& l, ReqDesc* table, const int* slot, const ReqDesc* const* r, int n);
 
 // adjoint kernels
 // floats of the scalar-partials buffer (ReqDesc::d_part) for waves of up to
@@ -279,6 +327,9 @@ size_t partial_floats(int64_t pixels_per_wave, int64_t proj_pixels);
 // take the samples' radiance from sample_L, or q.L if null, themselves)
 void launch_adj_pixel(const Launch& l, const Queues& q, const AdjQueues& aq, const ReqDesc& r, uint32_t p0,
                       uint32_t p1, const float* sample_L, float4* pix_dE, bool per_sample);
+// (several requests: their scalar cotangents go to d_acc by atomics, so d_part has to be null)
+void launch_adj_pixel(const Launch& l, const Queues& q, const AdjQueues& aq, const ReqDesc* table, const WaveSeg* segs,
+                      int n, bool per_sample);
 void launch_adj_raygen(const Launch& l, const Queues& q, const AdjQueues& aq, const ReqDesc& r, int slot, uint32_t g0,
                        uint32_t n);
 void launch_adj_shade(const Launch& l, const Queues& q, const AdjQueues& aq, int cur, int depth, const ReqDesc& uni,
@@ -314,6 +365,13 @@ void launch_sum_partials(const Launch& l, const float* part, int nb, int stride,
 void launch_adj_finish(const Launch& l, const ReqDesc& r, float* d_proj, float* d_albedo, float* d_rough,
                        float* d_spec, float* d_scalars, float* acc, float* d_metal = nullptr,
                        float* d_nmap = nullptr);
+// the same for several requests of the loop (5-channel maps, d_part null)
+struct FinishSeg {
+    int32_t slot;
+    int64_t ep_pixels, map_texels;
+    float *d_proj, *d_albedo, *d_rough, *d_spec, *d_scalars;
+};
+void launch_adj_finish(const Launch& l, const ReqDesc* table, const FinishSeg* segs, int n);
 void launch_zero(const Launch& l, float* p, int64_t n);
 // Float buffers cleared together by one launch on l's stream: add() collects them (a
 // full list is cleared at once and started again), launch() clears what is held.

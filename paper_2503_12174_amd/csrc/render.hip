@@ -71,15 +71,22 @@ __global__ void k_zero_list(ZeroArgs z) {
         p[i] = 0.0f;
 }
 
-__global__ void k_set_desc(ReqDesc r, ReqDesc* table, int slot) {
-    if (threadIdx.x == 0) table[slot] = r;
+struct DescArgs {
+    ReqDesc r[DESC_BATCH];
+    int32_t slot[DESC_BATCH];
+};
+static_assert(sizeof(DescArgs) <= 3900, "kernel arguments");
+__global__ void k_set_desc(DescArgs a, ReqDesc* table) {
+    if (threadIdx.x == 0) table[a.slot[blockIdx.x]] = a.r[blockIdx.x];
 }
 
 // ---------------------------------------------------------------- raygen
-__global__ void k_raygen(Queues q, ReqDesc r, int slot, uint32_t g0, uint32_t n) {
-    const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const uint32_t g = g0 + k;
+__global__ void k_raygen(Queues q, SegList segs, const ReqDesc* __restrict__ table) {
+    const int seg = seg_of(segs, blockIdx.x), slot = segs.slot[seg];
+    const ReqDesc& r = table[slot];
+    const uint32_t k = (blockIdx.x - segs.first[seg]) * blockDim.x + threadIdx.x;
+    if (k >= (segs.p1[seg] - segs.p0[seg]) * (uint32_t)r.spp) return;
+    const uint32_t g = segs.p0[seg] * (uint32_t)r.spp + k;
     const uint32_t sid = g - r.g_base + r.sid_base;
     const D3 d = camera_dir(r, g);
     q.po[0][sid] = PathO{r.cam_o[0], r.cam_o[1], r.cam_o[2], slot, -1};
@@ -459,8 +466,8 @@ __device__ __forceinline__ float crf(const ReqDesc& r, int c, float Ec) {
 // PIX_LANES lanes per pixel stride over its samples (neighbouring lanes read neighbouring
 // samples), then a reduction inside the lane group; the per-pixel math stays spread
 // over 64 / PIX_LANES pixels per wave.
-__global__ void __launch_bounds__(256) k_finalize(Queues q, ReqDesc r, uint32_t p0, uint32_t p1) {
-    const uint32_t p = p0 + (blockIdx.x * 256u + threadIdx.x) / PIX_LANES;
+__device__ __forceinline__ void finalize_block(const Queues& q, const ReqDesc& r, uint32_t block, uint32_t p0, uint32_t p1) {
+    const uint32_t p = p0 + (block * 256u + threadIdx.x) / PIX_LANES;
     if (p >= p1) return;   // uniform per lane group
     const int lane = threadIdx.x & (PIX_LANES - 1);
     const float thr = clip_threshold(r);
@@ -484,6 +491,13 @@ __global__ void __launch_bounds__(256) k_finalize(Queues q, ReqDesc r, uint32_t 
             if (r.out_linear) r.out_linear[3 * (size_t)p + c] = Ec;
             if (r.out_image) r.out_image[3 * (size_t)p + c] = crf(r, c, Ec);
         }
+}
+__global__ void __launch_bounds__(256) k_finalize(Queues q, ReqDesc r, uint32_t p0, uint32_t p1) {
+    finalize_block(q, r, blockIdx.x, p0, p1);
+}
+__global__ void __launch_bounds__(256) k_finalize_segs(Queues q, SegList segs, const ReqDesc* __restrict__ table) {
+    const int k = seg_of(segs, blockIdx.x);
+    finalize_block(q, table[segs.slot[k]], blockIdx.x - segs.first[k], segs.p0[k], segs.p1[k]);
 }
 
 // ---------------------------------------------------------------- guide features
@@ -620,12 +634,22 @@ void ZeroList::launch() {
     hipLaunchKernelGGL(k_zero_list, dim3(gx, (unsigned)k), dim3(256), 0, l.st, a);
     k = 0;
 }
-void launch_set_desc(const Launch& l, ReqDesc* table, int slot, const ReqDesc& r) {
-    hipLaunchKernelGGL(k_set_desc, dim3(1), dim3(64), 0, l.st, r, table, slot);
+void launch_set_desc(const Launch& l, ReqDesc* table, const int* slot, const ReqDesc* const* r, int n) {
+    for (int k = 0; k < n; k += DESC_BATCH) {
+        DescArgs a{};
+        const int m = std::min(DESC_BATCH, n - k);
+        for (int j = 0; j < m; ++j) {
+            a.r[j] = *r[k + j];
+            a.slot[j] = slot[k + j];
+        }
+        hipLaunchKernelGGL(k_set_desc, dim3(m), dim3(64), 0, l.st, a, table);
+    }
 }
-void launch_raygen(const Launch& l, const Queues& q, const ReqDesc& r, const ReqDesc*, int slot, uint32_t g0,
-                   uint32_t n, bool, const AdjQueues*) {
-    if (n) hipLaunchKernelGGL(k_raygen, dim3(grid_of(n, 256)), dim3(256), 0, l.st, q, r, slot, g0, n);
+void launch_raygen(const Launch& l, const Queues& q, const ReqDesc* table, const WaveSeg* segs, int n) {
+    for_seg_lists(segs, n, [](const WaveSeg& s) { return grid_of((int64_t)(s.p1 - s.p0) * s.spp, 256); },
+                  [&](const SegList& a, uint32_t g) {
+                      hipLaunchKernelGGL(k_raygen, dim3(g), dim3(256), 0, l.st, q, a, table);
+                  });
 }
 void launch_trace(const Launch& l, const Queues& q, int cur, const ReqDesc& uni, const ReqDesc* table,
                   int64_t n_upper, bool cam) {
@@ -682,10 +706,15 @@ bool small_wave(const Queues& q, const ReqDesc& r, int64_t n) {
     const bool tiny = r.nodes4 && r.top_nodes < TOP_NODES;
     return n <= (tiny ? SMALL_PATHS_TINY : SMALL_PATHS) && n <= (int64_t)q.trace_blocks * TRACE_TB;
 }
-void launch_finalize(const Launch& l, const Queues& q, const ReqDesc& r, const ReqDesc*, int, uint32_t p0,
-                     uint32_t p1) {
+void launch_finalize(const Launch& l, const Queues& q, const ReqDesc& r, uint32_t p0, uint32_t p1) {
     if (p1 > p0)
         hipLaunchKernelGGL(k_finalize, dim3(grid_of((int64_t)(p1 - p0) * PIX_LANES, 256)), dim3(256), 0, l.st, q, r, p0, p1);
+}
+void launch_finalize(const Launch& l, const Queues& q, const ReqDesc* table, const WaveSeg* segs, int n) {
+    for_seg_lists(segs, n, [](const WaveSeg& s) { return grid_of((int64_t)(s.p1 - s.p0) * PIX_LANES, 256); },
+                  [&](const SegList& a, uint32_t g) {
+                      hipLaunchKernelGGL(k_finalize_segs, dim3(g), dim3(256), 0, l.st, q, a, table);
+                  });
 }
 void launch_debug_intersect(const Launch& l, const float4* nodes4, const float4* nodes, const float4* tris,
                             const int* leaf_of_prim, int nt, float tmin, const float* rays, int64_t n, int mode,

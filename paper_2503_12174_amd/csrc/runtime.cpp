@@ -785,7 +785,7 @@ void forward_wave(dpcs_context ctx, Queues& q, ReqDesc& r, uint32_t a, uint32_t 
     r.sid_base = 0;
     if (!ctx->prof_mode && small_wave(q, r, n)) {   // (profiling times the stages apart)
         launch_paths(l, q, r, nullptr, n, true);
-        if (finalize) launch_finalize(l, q, r, nullptr, 0, a, b);
+        if (finalize) launch_finalize(l, q, r, a, b);
         return;
     }
     launch_set_count(l, q.cnt, 0, n, 1, 4);
@@ -833,7 +833,7 @@ void forward_wave(dpcs_context ctx, Queues& q, ReqDesc& r, uint32_t a, uint32_t 
     }
     if (finalize) {
         pr = prof_begin(ctx, DPCS_STAGE_FINALIZE);
-        launch_finalize(l, q, r, nullptr, 0, a, b);
+        launch_finalize(l, q, r, a, b);
         prof_end(ctx, pr, nullptr, b - a);
     }
 }

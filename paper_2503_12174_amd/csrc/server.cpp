@@ -205,6 +205,7 @@ struct dpcs_server_s {
 };
 
 void dpcs_server_s::admit_locked(Launch& l) {
+    ZeroList zl(l);   // the admitted requests' accumulators
     while (!queued.empty() && !free_slots.empty()) {
         Req* q = queued.front();
         if (admitted_bytes + q->bytes + shared_bytes > budget) break;   // FIFO: wait for memory
@@ -238,14 +239,13 @@ void dpcs_server_s::admit_locked(Launch& l) {
             r.dEp = (float*)take(16 * nEp);
             r.d_tex = (float*)take(20 * nT);
             r.d_acc = (float*)take(128);
-            ZeroList zl(l);
             zl.add(r.dEp, 4 * (int64_t)nEp);
             zl.add(r.d_tex, 5 * (int64_t)nT);
             zl.add(r.d_acc, 32);
-            zl.launch();
         }
         active.push_back(q);
     }
+    zl.launch();
 }
 
 void dpcs_server_s::wave(Launch& l) {
@@ -321,14 +321,23 @@ void dpcs_server_s::wave(Launch& l) {
         } else {
             q->r.rec = nullptr;
         }
-        launch_set_desc(l, table, q->slot, q->r);
     }
+    std::vector<WaveSeg> wsegs;   // (compensation segments first)
+    std::vector<int> slots;
+    std::vector<const ReqDesc*> descs;
+    int n_adj_segs = 0;
+    for (const Seg& s : segs) {
+        wsegs.push_back({s.q->slot, s.a, s.b, s.q->r.spp});
+        slots.push_back(s.q->slot);
+        descs.push_back(&s.q->r);
+        n_adj_segs += s.q->adjoint ? 1 : 0;
+    }
+    launch_set_desc(l, table, slots.data(), descs.data(), (int)slots.size());
     // the tree of the wave's scene (every segment's descriptor holds it): closest-hit
     // queries read nothing else of a descriptor, so they run in the one-request form
     const ReqDesc& any = segs[0].q->r;
     // forward over the shared queues
-    for (const Seg& s : segs) launch_raygen(l, q, s.q->r, table, s.q->slot, s.q->r.g_base, (s.b - s.a) * s.q->r.spp,
-                                            false, nullptr);
+    launch_raygen(l, q, table, wsegs.data(), (int)wsegs.size());
     int cur = 0;
     // a depth's shadow rays on the side stream beside the next depth's closest hit;
     // shading (both add to the samples' radiance) and the finalize wait for them
@@ -358,7 +367,7 @@ void dpcs_server_s::wave(Launch& l) {
         cur ^= 1;
     }
     if (side_fwd) (void)hipStreamWaitEvent(st, ev_shadow, 0);
-    for (const Seg& s : segs) launch_finalize(l, q, s.q->r, table, s.q->slot, s.a, s.b);
+    launch_finalize(l, q, table, wsegs.data(), (int)wsegs.size());
     // adjoint replay of the compensation-step segments (a dense prefix of the wave)
     if (any_adj) {
         // Compensation paths replayed from records, with maps the binning buffers hold: each
@@ -380,8 +389,7 @@ void dpcs_server_s::wave(Launch& l) {
             if (s.q->adjoint) ++n_req, all_binned = all_binned && binned(s, ab);
         all_binned = all_binned && (n_req == 1 || n_adj >= n_req * LOOP_BIN_PATHS);
         if (all_binned) ++st_binned;
-        for (const Seg& s : segs)
-            if (s.q->adjoint) launch_adj_pixel(l, q, aq, s.q->r, s.a, s.b, nullptr, nullptr, !replay);
+        launch_adj_pixel(l, q, aq, table, wsegs.data(), n_adj_segs, !replay);
         if (all_binned) {
             int tb_nb = -1, eb_nb = -1;   // tiles of the counters as they were last cleared
             for (const Seg& s : segs) {
@@ -445,13 +453,16 @@ void dpcs_server_s::wave(Launch& l) {
     ++st_waves;
     st_samples += used + n_adj;
     if (any_adj) ++(replay ? st_replayed : st_retraced);
+    std::vector<FinishSeg> fin;
+    for (const Seg& s : segs)
+        if (s.q->adjoint && s.q->next_pixel >= s.q->npix)
+            fin.push_back({s.q->slot, (int64_t)s.q->r.Wp * s.q->r.Hp, (int64_t)s.q->r.tw * s.q->r.th, s.q->grads.d_proj_image,
+                           s.q->grads.d_albedo, s.q->grads.d_roughness, s.q->grads.d_specular, s.q->grads.d_scalars});
+    launch_adj_finish(l, table, fin.data(), (int)fin.size());
     for (const Seg& s : segs) {
         Req* q = s.q;
         if (q->next_pixel >= q->npix) {
             q->scheduled_all = true;
-            if (q->adjoint)
-                launch_adj_finish(l, q->r, q->grads.d_proj_image, q->grads.d_albedo, q->grads.d_roughness,
-                                  q->grads.d_specular, q->grads.d_scalars, q->r.d_acc);
             (void)hipEventRecord(q->done, st);
         }
     }
