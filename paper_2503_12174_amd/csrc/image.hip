@@ -160,10 +160,10 @@ bool denoise_args(dpcs_context ctx, const dpcs_denoise_params* p, const float* v
 
 // ---------------------------------------------------------------- losses
 // Sums over a map or an image: each workgroup of a capped grid folds a grid-stride
-// share into two FP64 partial sums; the workgroup that finishes last (a counter says which,
-// and is 0 again afterwards) adds the partials in a fixed order, so the loss is the same on
-// every run.  One launch: the loss of a training step is bound by what its calls cost the
-// host, and a second launch for the last sum cost as much as the first.
+// share into two FP64 partial sums; one workgroup then adds the partials in a fixed
+// order.  No atomics: the loss is the same on every run.
+// (One launch whose last workgroup adds the partials takes longer than two: the fences that
+// order them across the dies' caches cost 19-26 us where both launches take 5-7.)
 constexpr int RED_TB = 256;
 constexpr int RED_MAX_BLOCKS = 1024;
 
@@ -190,36 +190,9 @@ __device__ __forceinline__ void block_sum2(double& a, double& b, double* part) {
     }
 }
 
-// every workgroup's end: its sums to part; the last one forms
-// loss = s0 / n0 + s1 / n1 (a term with n = 0 adds 0)
-__device__ __forceinline__ void finish_loss(double a, double b, double* part, uint32_t* count, double n0, double n1,
-                                            float* __restrict__ loss) {
-    __shared__ bool last;
-    __shared__ double tot[2];
-    block_sum2(a, b, part + 2 * blockIdx.x);
-    if (threadIdx.x == 0) {
-        __threadfence();   // the sums before the count
-        last = atomicAdd(count, 1u) == gridDim.x - 1u;
-    }
-    __syncthreads();
-    if (!last) return;
-    __threadfence();   // the count before the others' sums
-    a = b = 0.0;
-    for (unsigned k = threadIdx.x; k < gridDim.x; k += RED_TB) {
-        a += __hip_atomic_load(&part[2 * k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        b += __hip_atomic_load(&part[2 * k + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    block_sum2(a, b, tot);
-    if (threadIdx.x == 0) {
-        const double l = (n0 > 0.0 ? tot[0] / n0 : 0.0) + (n1 > 0.0 ? tot[1] / n1 : 0.0);
-        loss[0] = (float)l;
-        *count = 0u;
-    }
-}
-
 // sums of |vertical| and |horizontal| neighbour differences of an h x w x c map
-__global__ void __launch_bounds__(RED_TB) k_tv_loss(const float* __restrict__ m, int h, int w, int c, double* part,
-                                                    uint32_t* count, double nv, double nh, float* __restrict__ loss) {
+__global__ void __launch_bounds__(RED_TB) k_tv_partial(const float* __restrict__ m, int h, int w, int c,
+                                                       double* __restrict__ part) {
     const int64_t n = (int64_t)h * w * c, wc = (int64_t)w * c;
     double sv = 0.0, sh = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * RED_TB + threadIdx.x; i < n; i += (int64_t)gridDim.x * RED_TB) {
@@ -228,15 +201,31 @@ __global__ void __launch_bounds__(RED_TB) k_tv_loss(const float* __restrict__ m,
         if (y + 1 < h) sv += fabs((double)m[i + wc] - v);
         if (x + 1 < w) sh += fabs((double)m[i + c] - v);
     }
-    finish_loss(sv, sh, part, count, nv, nh, loss);
+    block_sum2(sv, sh, part + 2 * blockIdx.x);
 }
 
-__global__ void __launch_bounds__(RED_TB) k_l1_loss(const float* __restrict__ a, const float* __restrict__ b, int64_t n,
-                                                    double* part, uint32_t* count, float* __restrict__ loss) {
-    double s = 0.0;
+__global__ void __launch_bounds__(RED_TB) k_l1_partial(const float* __restrict__ a, const float* __restrict__ b,
+                                                       int64_t n, double* __restrict__ part) {
+    double s = 0.0, z = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * RED_TB + threadIdx.x; i < n; i += (int64_t)gridDim.x * RED_TB)
         s += fabs((double)a[i] - (double)b[i]);
-    finish_loss(s, 0.0, part, count, (double)n, 0.0, loss);
+    block_sum2(s, z, part + 2 * blockIdx.x);
+}
+
+// loss = s0 / n0 + s1 / n1 (a term with n = 0 adds 0)
+__global__ void __launch_bounds__(RED_TB) k_loss_final(const double* __restrict__ part, int nb, double n0, double n1,
+                                                       float* __restrict__ loss) {
+    __shared__ double tot[2];
+    double a = 0.0, b = 0.0;
+    for (int k = threadIdx.x; k < nb; k += RED_TB) {
+        a += part[2 * k];
+        b += part[2 * k + 1];
+    }
+    block_sum2(a, b, tot);
+    if (threadIdx.x == 0) {
+        const double l = (n0 > 0.0 ? tot[0] / n0 : 0.0) + (n1 > 0.0 ? tot[1] / n1 : 0.0);
+        loss[0] = (float)l;
+    }
 }
 
 __device__ __forceinline__ double sgn(double x) { return x > 0.0 ? 1.0 : (x < 0.0 ? -1.0 : 0.0); }
@@ -282,20 +271,6 @@ dpcs_status end(dpcs_context ctx, const char* what) {
     if (!hip_ok(ctx, hipGetLastError(), what)) return DPCS_E_DEVICE;
     ctx->err.clear();
     return DPCS_OK;
-}
-
-// the partial sums of a loss and (made on first use, as the scratch is) the context's counter
-double* loss_scratch(dpcs_context ctx, dpcs_status* st) {
-    double* part = (double*)scratch(ctx, "loss.part", sizeof(double) * 2 * RED_MAX_BLOCKS, st);
-    if (!part || ctx->loss_count) return part;
-    if (hipMalloc((void**)&ctx->loss_count, sizeof(uint32_t)) != hipSuccess) {
-        (void)hipGetLastError();
-        ctx->loss_count = nullptr;
-        *st = fail(ctx, DPCS_E_OOM, "hipMalloc failed for the loss counter");
-        return nullptr;
-    }
-    launch_zero(Launch{ctx->stream, ctx->grid_cap}, (float*)ctx->loss_count, 1);
-    return part;
 }
 
 bool map_ok(dpcs_context ctx, const float* m, int32_t h, int32_t w, int32_t c, dpcs_status* st) {
@@ -350,11 +325,12 @@ extern "C" dpcs_status dpcs_tv_loss(dpcs_context ctx, const float* map, int32_t 
     if (st != DPCS_OK) return st;
     if (!map_ok(ctx, map, h, w, c, &st)) return st;
     if (!loss) return fail(ctx, DPCS_E_INVALID, "tv_loss: loss is NULL");
-    double* part = loss_scratch(ctx, &st);
+    double* part = (double*)scratch(ctx, "loss.part", sizeof(double) * 2 * RED_MAX_BLOCKS, &st);
     if (!part) return st;
     const int64_t n = (int64_t)h * w * c;
     const unsigned nb = red_grid(n);
-    hipLaunchKernelGGL(k_tv_loss, dim3(nb), dim3(RED_TB), 0, ctx->stream, map, h, w, c, part, ctx->loss_count,
+    hipLaunchKernelGGL(k_tv_partial, dim3(nb), dim3(RED_TB), 0, ctx->stream, map, h, w, c, part);
+    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(RED_TB), 0, ctx->stream, part, (int)nb,
                        (double)c * (h - 1) * w, (double)c * h * (w - 1), loss);
     return end(ctx, "tv_loss");
 }
@@ -381,10 +357,11 @@ extern "C" dpcs_status dpcs_l1_loss(dpcs_context ctx, const float* a, const floa
     if (st != DPCS_OK) return st;
     if (!a || !b || !loss || n < 1 || n >= (int64_t(1) << 31))
         return fail(ctx, DPCS_E_INVALID, "l1_loss: a, b, loss must not be NULL and 1 <= n < 2^31");
-    double* part = loss_scratch(ctx, &st);
+    double* part = (double*)scratch(ctx, "loss.part", sizeof(double) * 2 * RED_MAX_BLOCKS, &st);
     if (!part) return st;
     const unsigned nb = red_grid(n);
-    hipLaunchKernelGGL(k_l1_loss, dim3(nb), dim3(RED_TB), 0, ctx->stream, a, b, n, part, ctx->loss_count, loss);
+    hipLaunchKernelGGL(k_l1_partial, dim3(nb), dim3(RED_TB), 0, ctx->stream, a, b, n, part);
+    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(RED_TB), 0, ctx->stream, part, (int)nb, (double)n, 0.0, loss);
     return end(ctx, "l1_loss");
 }
 

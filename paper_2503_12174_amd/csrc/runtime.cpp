@@ -400,7 +400,6 @@ extern "C" void dpcs_context_destroy(dpcs_context ctx) {
     if (ctx->ev_shadow) (void)hipEventDestroy(ctx->ev_shadow);
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     if (ctx->dstats) (void)hipFree(ctx->dstats);
-    if (ctx->loss_count) (void)hipFree(ctx->loss_count);
     delete ctx;
 }
 

@@ -39,7 +39,6 @@ struct dpcs_context_s {
     unsigned long long* dstats = nullptr;  // device [DPCS_NUM_STAGES][2]
     void* noalloc = nullptr;               // this device's copy of the no-alloc scratch array
     int noalloc_err = 0;                   // hipError_t of its address lookup
-    uint32_t* loss_count = nullptr;        // workgroups of a loss that have finished (0 between launches)
     // second stream (default priority) for a depth's shadow rays beside the next depth's
     // closest hit, and the two events that order them (made on first use)
     hipStream_t side = nullptr;
