@@ -916,6 +916,48 @@ __global__ void __launch_bounds__(256) k_bin_gather(MapBins a, float* __restrict
     else bin_gather<CB>(b, ob, sb, (int64_t)(blockIdx.x - ga) * 256 + threadIdx.x);
 }
 
+// the same over several requests (JointList)
+__global__ void __launch_bounds__(BIN_TB) k_bin_hist_joint(JointList f) {
+    __shared__ uint32_t h[MAP_MAX_BINS];
+    __shared__ uint32_t hmax;
+    const int k = seg_of(f, blockIdx.x);
+    const uint32_t c = blockIdx.x - f.first[k];
+    if (c < f.na[k]) bin_hist<5, TEX_RS>(f.tb[k], c, h, hmax);
+    else bin_hist<3, EP_RS>(f.eb[k], c - f.na[k], h, hmax);
+}
+__global__ void __launch_bounds__(1024) k_bin_scan_joint(JointList f) {
+    __shared__ uint64_t part[1024];
+    bin_scan(blockIdx.x & 1 ? f.eb[blockIdx.x >> 1] : f.tb[blockIdx.x >> 1], part);
+}
+__global__ void __launch_bounds__(BIN_TB) k_bin_place_joint(JointList f) {
+    __shared__ uint32_t cnt[MAP_MAX_BINS];
+    const int k = seg_of(f, blockIdx.x);
+    const uint32_t c = blockIdx.x - f.first[k];
+    if (c < f.na[k]) bin_place<TEX_RS>(f.tb[k], c, cnt);
+    else bin_place<EP_RS>(f.eb[k], c - f.na[k], cnt);
+}
+__global__ void __launch_bounds__(ACC_TB) k_bin_accum_joint(JointList f) {
+    __shared__ long long t[(MAP_MAX_T + 1) * (MAP_MAX_T + 1) * 5];
+    const int k = seg_of(f, blockIdx.x);
+    const MapBins &a = f.tb[k], &b = f.eb[k];
+    const uint32_t ua = bin_units(a)[a.nb], ub = bin_units(b)[b.nb];
+    const uint32_t u0 = blockIdx.x - f.first[k];
+    if (u0 == 0 && threadIdx.x == 0) {   // the counting passes are done
+        *a.count = 0u;
+        *b.count = 0u;
+    }
+    for (uint32_t u = u0; u < ua + ub; u += f.na[k]) {
+        if (u < ua) bin_accum<5, TEX_RS>(a, u, t);
+        else bin_accum<3, EP_RS>(b, u - ua, t);
+    }
+}
+__global__ void __launch_bounds__(256) k_bin_gather_joint(JointList f) {
+    const int k = seg_of(f, blockIdx.x);
+    const uint32_t c = blockIdx.x - f.first[k];
+    if (c < f.na[k]) bin_gather<5>(f.tb[k], f.d_tex[k], 5, (int64_t)c * 256 + threadIdx.x);
+    else bin_gather<3>(f.eb[k], f.d_ep[k], 4, (int64_t)(c - f.na[k]) * 256 + threadIdx.x);
+}
+
 // ---------------------------------------------------------------- replay from records
 // The replay's queue sizes rotate over three slots, q.cnt[REPLAY_CNT + (depth mod 3)]:
 // a launch reads its own, appends to the next and empties the one after (read by the
@@ -1148,16 +1190,17 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay(Queues q, AdjQueues aq, in
 // Bound by the latency of a sample's chain of loads and FP64 operations; once the chip is full, the
 // queues' launches win, which gather the samples that go on (186 registers here: 2 waves per SIMD).
 template <bool TEX>
-__global__ void __launch_bounds__(BLOCK) k_replay_paths(Queues q, AdjQueues aq, uint32_t n, const float* __restrict__ sample_L,
-                                                        ReqDesc r) {
-    const uint32_t i = blockIdx.x * BLOCK + threadIdx.x;
+__device__ __forceinline__ void replay_paths_block(const Queues& q, float4* delta, const MapBins& tb, const MapBins& eb,
+                                                   uint32_t n, const float* __restrict__ sample_L, const ReqDesc& r,
+                                                   uint32_t block) {
+    const uint32_t i = block * BLOCK + threadIdx.x;
     PathO o{r.cam_o[0], r.cam_o[1], r.cam_o[2], 0, -1};
     PathD d{};
     float4 b = {}, rl = {};
     int lit = -1;
     if (i < n) {
         const uint32_t g = r.g_base + i;
-        const ReplayStart t = replay_start<TEX>(r, g, sample_L, q.L, aq.delta);
+        const ReplayStart t = replay_start<TEX>(r, g, sample_L, q.L, delta);
         lit = t.lit;
         b = t.dl;
         rl = make_float4(t.dl.x * t.L.x, t.dl.y * t.L.y, t.dl.z * t.L.z, 0.f);
@@ -1172,11 +1215,11 @@ __global__ void __launch_bounds__(BLOCK) k_replay_paths(Queues q, AdjQueues aq, 
         if (lit >= depth) replay_vertex<TEX>(r, depth, lit, o, d, b, rl, v, tg, eg);
         const bool to_t = TEX && v.t_on;
         const bool pred[2] = {to_t, v.e_on};
-        uint32_t* const ctr[2] = {aq.tb.count, aq.eb.count};
+        uint32_t* const ctr[2] = {tb.count, eb.count};
         uint32_t at[2];
         block_append<2>(pred, ctr, at);
-        if (to_t && !put_tex_rec(aq.tb, at[0], v.t_u, v.t_v, tg)) scatter_tex_lane(r, v.t_u, v.t_v, tg);
-        if (v.e_on && !put_ep_rec(aq.eb, at[1], v.e_pu, v.e_pv, eg)) scatter_ep_lane(r, v.e_pu, v.e_pv, eg);
+        if (to_t && !put_tex_rec(tb, at[0], v.t_u, v.t_v, tg)) scatter_tex_lane(r, v.t_u, v.t_v, tg);
+        if (v.e_on && !put_ep_rec(eb, at[1], v.e_pu, v.e_pv, eg)) scatter_ep_lane(r, v.e_pu, v.e_pv, eg);
         if (v.cont) {
             o = v.no;
             d = v.nd;
@@ -1186,6 +1229,16 @@ __global__ void __launch_bounds__(BLOCK) k_replay_paths(Queues q, AdjQueues aq, 
             lit = -1;
         }
     }
+}
+template <bool TEX>
+__global__ void __launch_bounds__(BLOCK) k_replay_paths(Queues q, AdjQueues aq, uint32_t n, const float* __restrict__ sample_L,
+                                                        ReqDesc r) {
+    replay_paths_block<TEX>(q, aq.delta, aq.tb, aq.eb, n, sample_L, r, blockIdx.x);
+}
+__global__ void __launch_bounds__(BLOCK) k_replay_paths_joint(Queues q, float4* delta, JointList f,
+                                                              const ReqDesc* __restrict__ table) {
+    const int k = seg_of(f, blockIdx.x);
+    replay_paths_block<true>(q, delta, f.tb[k], f.eb[k], f.paths[k], nullptr, table[f.slot[k]], blockIdx.x - f.first[k]);
 }
 
 // ---------------------------------------------------------------- replay, metallic and normal maps
@@ -1584,6 +1637,33 @@ static void flush_maps(const Launch& l, const MapBins& a, float* oa, int sa, con
     hipLaunchKernelGGL((k_bin_accum<CA, RSA, CB, RSB>), dim3(acc), dim3(ACC_TB), 0, l.st, a, bb, b ? 1 : 0);
     hipLaunchKernelGGL((k_bin_gather<CA, CB>), dim3(ta + tb), dim3(256), 0, l.st, a, oa, sa, bb, b ? ob : oa,
                        b ? sb : sa, ta);
+}
+void launch_replay_joint(const Launch& l, const Queues& q, float4* delta, const ReqDesc* table, JointList& f) {
+    // workgroups of the next launch: na(k) and the rest of request k's
+    auto grid = [&](auto na, auto rest) {
+        uint32_t g = 0;
+        for (int k = 0; k < f.n; ++k) {
+            f.first[k] = g;
+            f.na[k] = (uint32_t)na(k);
+            g += f.na[k] + (uint32_t)rest(k);
+        }
+        return dim3(g);
+    };
+    auto none = [](int) { return 0; };
+    dim3 g = grid([&](int k) { return grid_of(f.paths[k], BLOCK); }, none);
+    hipLaunchKernelGGL(k_replay_paths_joint, g, dim3(BLOCK), 0, l.st, q, delta, f, table);
+    g = grid([&](int k) { return bin_chunks(f.tb[k].fill, f.tb[k].chunk); },
+             [&](int k) { return bin_chunks(f.eb[k].fill, f.eb[k].chunk); });
+    hipLaunchKernelGGL(k_bin_hist_joint, g, dim3(BIN_TB), 0, l.st, f);
+    hipLaunchKernelGGL(k_bin_scan_joint, dim3(2 * f.n), dim3(1024), 0, l.st, f);
+    hipLaunchKernelGGL(k_bin_place_joint, g, dim3(BIN_TB), 0, l.st, f);
+    const int64_t share = 1024 / f.n;   // (two resident rounds in all, as in flush_maps)
+    g = grid([&](int k) { return std::min(share, map_units(f.tb[k].fill, f.tb[k].nb) + map_units(f.eb[k].fill, f.eb[k].nb)); },
+             none);
+    hipLaunchKernelGGL(k_bin_accum_joint, g, dim3(ACC_TB), 0, l.st, f);
+    g = grid([&](int k) { return grid_of((int64_t)f.tb[k].W * f.tb[k].H, 256); },
+             [&](int k) { return grid_of((int64_t)f.eb[k].W * f.eb[k].H, 256); });
+    hipLaunchKernelGGL(k_bin_gather_joint, g, dim3(256), 0, l.st, f);
 }
 void launch_sum_partials(const Launch& l, const float* part, int nb, int stride, int nv, float* dst) {
     hipLaunchKernelGGL(k_sum_partials, dim3(nv), dim3(SUM_TB), 0, l.st, part, nb, stride, nv, dst);

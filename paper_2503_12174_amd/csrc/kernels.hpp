@@ -348,6 +348,20 @@ void launch_adj_replay(const Launch& l, const Queues& q, const AdjQueues& aq, in
 // 128 x 8 482 and 476, 256 x 256 x 4 375 and 389.
 constexpr int64_t SMALL_REPLAY = 1 << 17;
 bool small_replay(const AdjQueues& aq, const ReqDesc& r, int64_t n);
+// The same for up to JOINT_SEGS requests of the loop at once, each with bins of its own, and the
+// flush of all their maps (5-channel maps): six launches for the list instead of six per
+// request, which fill the chip together (a request of 2^17 paths alone: replay 27 us on 512
+// workgroups, flush 32; a step of 8 of them 1360 -> 1176 us).  Per launch, workgroups first[k] on belong to request k;
+// na[k] of them to its texture map (accumulation: the number that takes its units in turn).
+constexpr int JOINT_SEGS = 8;
+struct JointList {
+    int32_t n;
+    int32_t slot[JOINT_SEGS];
+    uint32_t paths[JOINT_SEGS], first[JOINT_SEGS], na[JOINT_SEGS];
+    MapBins tb[JOINT_SEGS], eb[JOINT_SEGS];
+    float *d_tex[JOINT_SEGS], *d_ep[JOINT_SEGS];
+};
+void launch_replay_joint(const Launch& l, const Queues& q, float4* delta, const ReqDesc* table, JointList& f);
 void launch_replay_paths(const Launch& l, const Queues& q, const AdjQueues& aq, const ReqDesc& r, uint32_t n,
                          const float* sample_L = nullptr);
 void launch_map_flush(const Launch& l, const AdjQueues& aq, const ReqDesc& r);

@@ -104,6 +104,10 @@ struct Seg {
 // map size.  Layout: records, sorted records, stage blocks, count, bins, unit tiles, chunk
 // row bases.
 constexpr int LOOP_ROW_CHUNK = 16384;
+// ... and from which several small ones replay and flush together (a step of 8 pairs, by atomics
+// or, at 2^17, one by one, and together: 2^13 paths each 1001 and 993 us, 2^14 1131 and 921, 2^15
+// 1189 and 988, 2^16 1393 and 1195, 2^17 1405 and 1193)
+constexpr int64_t LOOP_JOINT_PATHS = 1 << 13;
 constexpr int64_t LOOP_BIN_PATHS = 1 << 17;   // paths per request (on average) from which several are binned
 size_t loop_bins_bytes(int64_t cap, int C, int RS) {
     const size_t rec = 4 * (size_t)RS * cap;
@@ -154,6 +158,60 @@ bool loop_bins_view(char* base, int64_t cap, int64_t fill, int C, int RS, int W,
     return true;
 }
 
+// Bins of several requests side by side in the buffers [base, base + bytes): for each, records
+// for all its vertices and tiles of its own maps; every request's counters first, in one run
+// (counters: their number of words).  False: a map is too large to bin, or they don't fit.
+bool loop_bins_joint(char* base, size_t bytes, const Seg* const* segs, int n, JointList& f, int64_t& counters) {
+    f = JointList{};
+    if (!base) return false;
+    int64_t total = 0;
+    for (int k = 0; k < n; ++k) {
+        const ReqDesc& r = segs[k]->q->r;
+        f.slot[k] = segs[k]->q->slot;
+        f.paths[k] = (segs[k]->b - segs[k]->a) * (uint32_t)r.spp;
+        f.d_tex[k] = r.d_tex;
+        f.d_ep[k] = r.dEp;
+        const int64_t fill = (int64_t)f.paths[k] * r.max_depth;   // a record per vertex and map
+        total += fill;
+        const int dims[2][2] = {{r.tw, r.th}, {r.Wp, r.Hp}};
+        for (int j = 0; j < 2; ++j) {
+            MapBins& mb = j ? f.eb[k] : f.tb[k];
+            mb.W = dims[j][0];
+            mb.H = dims[j][1];
+            if (!map_tiling(mb.W, mb.H, mb.T, mb.nbx, mb.nby)) return false;
+            mb.nb = mb.nbx * mb.nby;
+            mb.cap = mb.fill = fill;
+        }
+    }
+    f.n = n;
+    size_t at = 0;
+    auto take = [&](size_t size, size_t align) {
+        at = (at + align - 1) & ~(align - 1);
+        char* p = base + at;
+        at += size;
+        return p;
+    };
+    for (int k = 0; k < n; ++k)
+        for (MapBins* mb : {&f.tb[k], &f.eb[k]}) {
+            mb->count = (uint32_t*)take(4, 4);
+            mb->bins = (uint32_t*)take(4 * (size_t)map_bin_words(mb->nb), 4);
+        }
+    counters = (int64_t)(at / 4);
+    for (int k = 0; k < n; ++k)
+        for (int j = 0; j < 2; ++j) {
+            MapBins& mb = j ? f.eb[k] : f.tb[k];
+            const int C = j ? 3 : 5, RS = j ? 6 : 8;
+            const size_t rec = 4 * (size_t)RS * mb.cap, units = (size_t)map_units(mb.cap, mb.nb);
+            mb.chunk = bin_chunk(total);
+            mb.rec = (float*)take(rec, 256);
+            mb.sorted = (float*)take(rec, 256);
+            mb.stage = (long long*)take(8 * units * (mb.T + 1) * (mb.T + 1) * C, 256);
+            mb.unit_tile = (uint32_t*)take(4 * units, 256);
+            mb.rowbase = (uint32_t*)take(4 * (size_t)bin_chunks(mb.cap, mb.chunk) * mb.nb, 256);
+        }
+    return at <= bytes;
+}
+
 size_t request_bytes(const ReqDesc& r, bool adjoint) {
     const size_t nEp = (size_t)r.Wp * r.Hp, nT = (size_t)r.tw * r.th;
     size_t b = 16 * nEp + 256 + 16 * nT + 256;          // E_p, packed maps
@@ -185,6 +243,7 @@ struct dpcs_server_s {
     char* tex_bins = nullptr;    // binning buffers (texture maps, E_p) of one-request
     char* ep_bins = nullptr;     // compensation waves, or null: every wave scatters directly
     int64_t tex_bins_cap = 0, ep_bins_cap = 0;
+    size_t bins_bytes = 0;       // both together, from tex_bins on
     int64_t st_binned = 0;       // waves whose compensation gradients were binned
     std::vector<int> free_slots;
     std::mutex mu;
@@ -374,7 +433,7 @@ void dpcs_server_s::wave(Launch& l) {
         // request's replay runs in the one-request form, one request after the other, and its
         // map cotangents are binned and flushed into its maps like a single VJP's, instead of
         // one global atomic per texel and channel.  (Several requests of fewer than 2^17 paths
-        // each stay together: a step of 8 pairs took, together and apart, 1.68 and 1.69 ms at
+        // each stay in one replay, by atomics, unless they go together below: a step of 8 pairs took, together and apart, 1.68 and 1.69 ms at
         // 2^16 paths, 1.88 and 1.75 at 2^17, 2.57 and 2.10 at 2^18; 16 pairs of 2^17 3.20 and 3.15.)
         auto binned = [&](const Seg& s, AdjQueues& ab) {
             const int64_t fill = (int64_t)(s.b - s.a) * s.q->r.spp * std::min(s.q->r.max_depth, BIN_DEPTHS);   // a record per vertex and map
@@ -387,10 +446,34 @@ void dpcs_server_s::wave(Launch& l) {
         int64_t n_req = 0;
         for (const Seg& s : segs)
             if (s.q->adjoint) ++n_req, all_binned = all_binned && binned(s, ab);
-        all_binned = all_binned && (n_req == 1 || n_adj >= n_req * LOOP_BIN_PATHS);
+        // Several small requests: their replays and flushes in common launches
+        std::vector<JointList> joint;
+        std::vector<int64_t> joint_words;
+        if (all_binned && n_req > 1 && n_adj >= n_req * LOOP_JOINT_PATHS) {
+            std::vector<const Seg*> adj;
+            for (const Seg& s : segs)
+                if (s.q->adjoint) adj.push_back(&s);
+            bool fit = std::all_of(adj.begin(), adj.end(), [&](const Seg* s) {
+                return small_replay(ab, s->q->r, (int64_t)(s->b - s->a) * s->q->r.spp);
+            });
+            for (size_t k = 0; fit && k < adj.size(); k += JOINT_SEGS) {
+                JointList f;
+                int64_t words = 0;
+                fit = loop_bins_joint(tex_bins, bins_bytes, &adj[k], (int)std::min<size_t>(JOINT_SEGS, adj.size() - k), f, words);
+                joint.push_back(f);
+                joint_words.push_back(words);
+            }
+            if (!fit) joint.clear();
+        }
+        all_binned = all_binned && (n_req == 1 || !joint.empty() || n_adj >= n_req * LOOP_BIN_PATHS);
         if (all_binned) ++st_binned;
         launch_adj_pixel(l, q, aq, table, wsegs.data(), n_adj_segs, !replay);
-        if (all_binned) {
+        if (!joint.empty()) {
+            for (size_t k = 0; k < joint.size(); ++k) {   // (the lists share the buffers, one after the other)
+                launch_zero(l, (float*)tex_bins, joint_words[k]);
+                launch_replay_joint(l, q, aq.delta, table, joint[k]);
+            }
+        } else if (all_binned) {
             int tb_nb = -1, eb_nb = -1;   // tiles of the counters as they were last cleared
             for (const Seg& s : segs) {
                 if (!s.q->adjoint) continue;
@@ -610,6 +693,7 @@ extern "C" dpcs_status dpcs_server_create(dpcs_context ctx, size_t memory_budget
     ok = ok && hipMalloc((void**)&s->arena_base, arena_bytes) == hipSuccess;
     if (ok && binning) {
         ok = hipMalloc((void**)&s->tex_bins, bins_bytes) == hipSuccess;
+        s->bins_bytes = bins_bytes;
         s->ep_bins = ok ? s->tex_bins + loop_bins_bytes(s->tex_bins_cap, 5, 8) : nullptr;
     }
     if (!ok) {
