@@ -430,8 +430,8 @@ DPCS_API int32_t dpcs_server_poll(dpcs_server srv, uint64_t* done_ids, int32_t* 
  * latency of the completed requests summed in microseconds, in three parts: [10] submit
  * to admission (queued for memory or a slot), [11] admission to the launch of the
  * request's first wave, [12] from there to completion on the device; [13] waves whose
- * compensation paths binned their map cotangents, request by request (sorted by tile,
- * summed in fixed point), instead of scattering them with atomics. */
+ * compensation paths binned their map cotangents, each request's by itself (sorted by
+ * tile, summed in fixed point), instead of scattering them with atomics. */
 DPCS_API dpcs_status dpcs_server_stats(dpcs_server srv, int64_t* out14);
 /* Waits for every admitted request, then stops the loop. */
 DPCS_API dpcs_status dpcs_server_destroy(dpcs_server srv);

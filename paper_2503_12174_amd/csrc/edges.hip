@@ -433,7 +433,7 @@ dpcs_status camera_edge_term(dpcs_context ctx, dpcs_scene sc, const ReqDesc& r, 
             re.d_cam_part = nullptr;
             hipLaunchKernelGGL(k_edge_raygen, dim3((m + 255) / 256), dim3(256), 0, l.st, qe, re, a, side);
             if (!ctx->prof_mode && small_wave(qe, re, m)) {
-                launch_paths(l, qe, re, nullptr, m, false);
+                launch_paths(l, qe, re, m, false);
                 continue;
             }
             launch_set_count(l, qe.cnt, 0, m, 1, 4);

@@ -307,10 +307,12 @@ void launch_shade(const Launch& l, const Queues& q, int cur, int depth, const Re
 // table): every ray is on the tree of `uni` (several requests of one scene)
 void launch_shadow(const Launch& l, const Queues& q, int which, const ReqDesc& uni, const ReqDesc* table,
                    int64_t n_upper, int depth, bool one_tree = false);
-// the whole forward of n rays of a small wave: one request's camera rays (cam), or the n rays in the
-// path queue, one request's or (with a table) several's.  small_wave: where that pays (and the
-// spill region holds that many threads).
-void launch_paths(const Launch& l, const Queues& q, const ReqDesc& r, const ReqDesc* table, uint32_t n, bool cam);
+// the whole forward of a small wave: n rays of one request, its camera's (cam) or those in the
+// path queue; or the camera rays of several requests' segments (no metallic and normal maps).
+// small_wave: where that pays, and the spill region holds n threads (segments: a workgroup's
+// threads more for each).
+void launch_paths(const Launch& l, const Queues& q, const ReqDesc& r, uint32_t n, bool cam);
+void launch_paths(const Launch& l, const Queues& q, const ReqDesc* table, const WaveSeg* segs, int n);
 bool small_wave(const Queues& q, const ReqDesc& r, int64_t n);
 void launch_finalize(const Launch& l, const Queues& q, const ReqDesc& r, uint32_t p0, uint32_t p1);
 void launch_finalize(const Launch& l, const Queues& q, const ReqDesc* table, const WaveSeg* segs, int n);

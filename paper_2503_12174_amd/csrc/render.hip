@@ -422,39 +422,41 @@ __device__ __forceinline__ float4 run_path(const ReqDesc& r, PathO o, PathD d, i
     return L;
 }
 
-// SRC: where the rays come from: one request's camera, the queue of one request, or the queue of
-// several requests' camera rays (descriptors in table; a wave mostly holds one request's, and
-// takes its requests one after the other).
-enum PathSource { FROM_CAMERA, FROM_QUEUE, FROM_TABLE };
-template <bool EXT, int SRC>
+// the path of sample g of a request, its index in the wave's samples being sid
+template <bool EXT>
+__device__ __forceinline__ void camera_path(const Queues& q, const ReqDesc& r, uint32_t g, int* stack, int* spill) {
+    if (r.out_hits)
+        for (int k = 1; k < r.max_depth; ++k) r.out_hits[(size_t)g * r.max_depth + k] = -2;
+    const D3 cd = camera_dir(r, g);
+    q.L[g - r.g_base + r.sid_base] = run_path<EXT>(r, PathO{r.cam_o[0], r.cam_o[1], r.cam_o[2], 0, -1},
+                                                   PathD{cd.x, cd.y, cd.z, g, 0u}, stack, spill);
+}
+// rays of one request: its camera's (CAM), or those in the path queue
+template <bool EXT, bool CAM>
 __global__ void __launch_bounds__(PATH_TB) __attribute__((amdgpu_waves_per_eu(4, 4)))
-k_paths(Queues q, uint32_t n, ReqDesc uni, const ReqDesc* __restrict__ table) {
+k_paths(Queues q, uint32_t n, ReqDesc uni) {
     __shared__ int stack[(SHORT_STACK + 1) * PATH_TB];
     const uint32_t i = blockIdx.x * PATH_TB + threadIdx.x;
     if (i >= n) return;
     int* spill = q.spill + (size_t)blockIdx.x * PATH_TB * SPILL;
-    if constexpr (SRC == FROM_CAMERA) {
-        const uint32_t g = uni.g_base + i;
-        if (uni.out_hits)
-            for (int k = 1; k < uni.max_depth; ++k) uni.out_hits[(size_t)g * uni.max_depth + k] = -2;
-        const D3 cd = camera_dir(uni, g);
-        q.L[i + uni.sid_base] = run_path<EXT>(uni, PathO{uni.cam_o[0], uni.cam_o[1], uni.cam_o[2], 0, -1},
-                                              PathD{cd.x, cd.y, cd.z, g, 0u}, stack, spill);
+    if constexpr (CAM) {
+        camera_path<EXT>(q, uni, uni.g_base + i, stack, spill);
     } else {
         const PathO o = nt_ld(&q.po[0][i]);
         const PathD d = nt_ld(&q.pd[0][i]);
-        if constexpr (SRC == FROM_QUEUE) {
-            q.L[d.g - uni.g_base + uni.sid_base] = run_path<EXT>(uni, o, d, stack, spill);
-        } else {
-            for (bool wait = true; wait;) {
-                const int s = __builtin_amdgcn_readfirstlane(o.slot);
-                if (o.slot == s) {
-                    q.L[i] = run_path<EXT>(table[s], o, d, stack, spill);
-                    wait = false;
-                }
-            }
-        }
+        q.L[d.g - uni.g_base + uni.sid_base] = run_path<EXT>(uni, o, d, stack, spill);
     }
+}
+// the camera rays of several requests' segments (with the rays made by a launch of their own and
+// read from the queue, a step of 8 pairs of 64 x 64 x 32 took 1173 us, now 1039)
+__global__ void __launch_bounds__(PATH_TB) __attribute__((amdgpu_waves_per_eu(4, 4)))
+k_paths_segs(Queues q, SegList segs, const ReqDesc* __restrict__ table) {
+    __shared__ int stack[(SHORT_STACK + 1) * PATH_TB];
+    const int k = seg_of(segs, blockIdx.x);
+    const ReqDesc& r = table[segs.slot[k]];
+    const uint32_t i = (blockIdx.x - segs.first[k]) * PATH_TB + threadIdx.x;
+    if (i >= (segs.p1[k] - segs.p0[k]) * (uint32_t)r.spp) return;
+    camera_path<false>(q, r, segs.p0[k] * (uint32_t)r.spp + i, stack, q.spill + (size_t)blockIdx.x * PATH_TB * SPILL);
 }
 
 // ---------------------------------------------------------------- finalize
@@ -694,13 +696,18 @@ void launch_shadow(const Launch& l, const Queues& q, int which, const ReqDesc& u
         else hipLaunchKernelGGL((k_shadow<true, false>), g, b, 0, l.st, q, which, depth, uni, table);
     }
 }
-void launch_paths(const Launch& l, const Queues& q, const ReqDesc& r, const ReqDesc* table, uint32_t n, bool cam) {
+void launch_paths(const Launch& l, const Queues& q, const ReqDesc& r, uint32_t n, bool cam) {
     const dim3 g(grid_of(n, PATH_TB)), b(PATH_TB);
-    if (table) hipLaunchKernelGGL((k_paths<false, FROM_TABLE>), g, b, 0, l.st, q, n, r, table);
-    else if (!cam && r.tex4b) hipLaunchKernelGGL((k_paths<true, FROM_QUEUE>), g, b, 0, l.st, q, n, r, table);
-    else if (!cam) hipLaunchKernelGGL((k_paths<false, FROM_QUEUE>), g, b, 0, l.st, q, n, r, table);
-    else if (r.tex4b) hipLaunchKernelGGL((k_paths<true, FROM_CAMERA>), g, b, 0, l.st, q, n, r, table);
-    else hipLaunchKernelGGL((k_paths<false, FROM_CAMERA>), g, b, 0, l.st, q, n, r, table);
+    if (!cam && r.tex4b) hipLaunchKernelGGL((k_paths<true, false>), g, b, 0, l.st, q, n, r);
+    else if (!cam) hipLaunchKernelGGL((k_paths<false, false>), g, b, 0, l.st, q, n, r);
+    else if (r.tex4b) hipLaunchKernelGGL((k_paths<true, true>), g, b, 0, l.st, q, n, r);
+    else hipLaunchKernelGGL((k_paths<false, true>), g, b, 0, l.st, q, n, r);
+}
+void launch_paths(const Launch& l, const Queues& q, const ReqDesc* table, const WaveSeg* segs, int n) {
+    for_seg_lists(segs, n, [](const WaveSeg& s) { return grid_of((int64_t)(s.p1 - s.p0) * s.spp, PATH_TB); },
+                  [&](const SegList& a, uint32_t g) {
+                      hipLaunchKernelGGL(k_paths_segs, dim3(g), dim3(PATH_TB), 0, l.st, q, a, table);
+                  });
 }
 bool small_wave(const Queues& q, const ReqDesc& r, int64_t n) {
     const bool tiny = r.nodes4 && r.top_nodes < TOP_NODES;

@@ -783,7 +783,7 @@ void forward_wave(dpcs_context ctx, Queues& q, ReqDesc& r, uint32_t a, uint32_t 
     r.g_base = a * (uint32_t)r.spp;
     r.sid_base = 0;
     if (!ctx->prof_mode && small_wave(q, r, n)) {   // (profiling times the stages apart)
-        launch_paths(l, q, r, nullptr, n, true);
+        launch_paths(l, q, r, n, true);
         if (finalize) launch_finalize(l, q, r, a, b);
         return;
     }

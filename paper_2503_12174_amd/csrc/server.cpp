@@ -104,11 +104,12 @@ struct Seg {
 // map size.  Layout: records, sorted records, stage blocks, count, bins, unit tiles, chunk
 // row bases.
 constexpr int LOOP_ROW_CHUNK = 16384;
-// ... and from which several small ones replay and flush together (a step of 8 pairs, by atomics
-// or, at 2^17, one by one, and together: 2^13 paths each 1001 and 993 us, 2^14 1131 and 921, 2^15
-// 1189 and 988, 2^16 1393 and 1195, 2^17 1405 and 1193)
+// Paths per request (on average) from which several are binned one by one, and from which
+// several small ones replay and flush together (a step of 8 pairs, by atomics -- at 2^17, one by
+// one -- and together: 2^13 paths each 1001 and 993 us, 2^14 1131 and 921, 2^15 1189 and 988,
+// 2^16 1393 and 1195, 2^17 1405 and 1193)
+constexpr int64_t LOOP_BIN_PATHS = 1 << 17;
 constexpr int64_t LOOP_JOINT_PATHS = 1 << 13;
-constexpr int64_t LOOP_BIN_PATHS = 1 << 17;   // paths per request (on average) from which several are binned
 size_t loop_bins_bytes(int64_t cap, int C, int RS) {
     const size_t rec = 4 * (size_t)RS * cap;
     const size_t units = (size_t)map_units(cap, MAP_MAX_BINS);
@@ -396,7 +397,6 @@ void dpcs_server_s::wave(Launch& l) {
     // queries read nothing else of a descriptor, so they run in the one-request form
     const ReqDesc& any = segs[0].q->r;
     // forward over the shared queues
-    launch_raygen(l, q, table, wsegs.data(), (int)wsegs.size());
     int cur = 0;
     // a depth's shadow rays on the side stream beside the next depth's closest hit;
     // shading (both add to the samples' radiance) and the finalize wait for them
@@ -405,10 +405,14 @@ void dpcs_server_s::wave(Launch& l) {
     const Launch ls{side, ctx->grid_cap};
     // (only full-size waves: at 2^20 paths of a small scene, the scene-fit step's waves,
     // the cross-stream waits cost more than the overlap gained: 2.50 -> 2.62 ms)
-    const bool small = small_wave(q, any, used);
+    const bool small = small_wave(q, any, used + PATH_TB * (int64_t)segs.size());
     const bool side_fwd = !small && side && used >= LOOP_SIDE_MIN_PATHS, side_adj = side && n_adj >= LOOP_SIDE_MIN_PATHS;
-    if (small) launch_paths(l, q, any, table, (uint32_t)used, false);
-    else launch_set_count(l, q.cnt, 0, (uint32_t)used, 1, 4);
+    if (small) {
+        launch_paths(l, q, table, wsegs.data(), (int)wsegs.size());
+    } else {
+        launch_raygen(l, q, table, wsegs.data(), (int)wsegs.size());
+        launch_set_count(l, q.cnt, 0, (uint32_t)used, 1, 4);
+    }
     for (int d = 0; d < max_depth && !small; ++d) {
         launch_trace(l, q, cur, any, nullptr, used);   // (empties the queues shading appends to)
         if (side_fwd && d > 0) (void)hipStreamWaitEvent(st, ev_shadow, 0);
@@ -430,11 +434,12 @@ void dpcs_server_s::wave(Launch& l) {
     // adjoint replay of the compensation-step segments (a dense prefix of the wave)
     if (any_adj) {
         // Compensation paths replayed from records, with maps the binning buffers hold: each
-        // request's replay runs in the one-request form, one request after the other, and its
-        // map cotangents are binned and flushed into its maps like a single VJP's, instead of
-        // one global atomic per texel and channel.  (Several requests of fewer than 2^17 paths
-        // each stay in one replay, by atomics, unless they go together below: a step of 8 pairs took, together and apart, 1.68 and 1.69 ms at
-        // 2^16 paths, 1.88 and 1.75 at 2^17, 2.57 and 2.10 at 2^18; 16 pairs of 2^17 3.20 and 3.15.)
+        // request's map cotangents are binned and flushed into its maps like a single VJP's,
+        // instead of one global atomic per texel and channel.  Small requests do so in common
+        // launches (joint), others in the one-request form, one after the other.  (Where they
+        // are not joint, several requests of fewer than 2^17 paths each stay in one replay, by
+        // atomics: a step of 8 pairs took, by atomics and apart, 1.68 and 1.69 ms at 2^16 paths,
+        // 1.88 and 1.75 at 2^17, 2.57 and 2.10 at 2^18; 16 pairs of 2^17 3.20 and 3.15.)
         auto binned = [&](const Seg& s, AdjQueues& ab) {
             const int64_t fill = (int64_t)(s.b - s.a) * s.q->r.spp * std::min(s.q->r.max_depth, BIN_DEPTHS);   // a record per vertex and map
             ab = aq;
