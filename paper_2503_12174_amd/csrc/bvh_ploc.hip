@@ -328,34 +328,18 @@ __global__ void __launch_bounds__(TB) k_collapse_count(const float4* __restrict_
     if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
-// 4-wide node base + e over binary node bin[e]; its internal children become the next
-// level's entries base + m + prefix, carrying the stack depth reached at this node
-__global__ void __launch_bounds__(TB) k_collapse_write(const float4* __restrict__ nodes, int ni, const int* __restrict__ bin,
-                                                       const int* __restrict__ acc, int m, const uint64_t* __restrict__ sums,
-                                                       int base, int cap4, int nt, float4* __restrict__ nodes4,
-                                                       int* __restrict__ map4, int* __restrict__ nbin,
-                                                       int* __restrict__ nacc, int* __restrict__ stats,
-                                                       int* __restrict__ leaf_seen) {
-    __shared__ uint64_t ws[TB / 64];
-    const int e = blockIdx.x * TB + threadIdx.x;
-    Kid k[4];
-    int cnt = 0, internal = 0;
-    if (e < m) {
-        cnt = pick_kids(nodes, ni, bin[e], k);
-        order_kids(k, cnt);
-        internal = internal_kids(k, cnt);
-    }
-    uint64_t tot;
-    int slot = (int)(sums[blockIdx.x] + block_exclusive((uint64_t)internal, ws, &tot));
-    if (e >= m) return;
-    const int w = base + e;
+// 4-wide node w over binary node b with children k (cnt of them, `internal` internal); its
+// internal children become the next level's entries `slot` on, numbered from next_base, carrying
+// the stack depth reached at this node (a0: above it)
+__device__ __forceinline__ void collapse_node(const Kid k[4], int cnt, int internal, int b, int a0, int w, int next_base,
+                                              int slot, int ni, int cap4, int nt, float4* nodes4, int* map4, int* nbin,
+                                              int* nacc, int* stats, int* leaf_seen) {
     if (cnt < 2 || w >= cap4) {   // never for a well-formed tree
         atomicExch(&stats[1], 1);
         return;
     }
-    const int a = acc[e] + max(internal - 1, 0);   // stack entries held below this node
+    const int a = a0 + max(internal - 1, 0);   // stack entries held below this node
     atomicMax(&stats[0], a);
-    const int next_base = base + m;
     float box[6][4];
     int refs[4];
     for (int j = 0; j < 4; ++j) {
@@ -391,7 +375,85 @@ __global__ void __launch_bounds__(TB) k_collapse_write(const float4* __restrict_
     for (int q = 0; q < 6; ++q) o[q] = make_float4(box[q][0], box[q][1], box[q][2], box[q][3]);
     o[6] = make_float4(__int_as_float(refs[0]), __int_as_float(refs[1]), __int_as_float(refs[2]),
                        __int_as_float(refs[3]));
-    o[7] = make_float4(__int_as_float(bin[e]), 0.f, 0.f, 0.f);   // (for refits)
+    o[7] = make_float4(__int_as_float(b), 0.f, 0.f, 0.f);   // (for refits)
+}
+
+// 4-wide nodes base + e over the binary nodes bin[e] of one level
+__global__ void __launch_bounds__(TB) k_collapse_write(const float4* __restrict__ nodes, int ni, const int* __restrict__ bin,
+                                                       const int* __restrict__ acc, int m, const uint64_t* __restrict__ sums,
+                                                       int base, int cap4, int nt, float4* __restrict__ nodes4,
+                                                       int* __restrict__ map4, int* __restrict__ nbin,
+                                                       int* __restrict__ nacc, int* __restrict__ stats,
+                                                       int* __restrict__ leaf_seen) {
+    __shared__ uint64_t ws[TB / 64];
+    const int e = blockIdx.x * TB + threadIdx.x;
+    Kid k[4];
+    int cnt = 0, internal = 0;
+    if (e < m) {
+        cnt = pick_kids(nodes, ni, bin[e], k);
+        order_kids(k, cnt);
+        internal = internal_kids(k, cnt);
+    }
+    uint64_t tot;
+    int slot = (int)(sums[blockIdx.x] + block_exclusive((uint64_t)internal, ws, &tot));
+    if (e >= m) return;
+    collapse_node(k, cnt, internal, bin[e], acc[e], base + e, base + m, slot, ni, cap4, nt, nodes4, map4, nbin, nacc, stats,
+                  leaf_seen);
+}
+
+// Levels of few nodes, one after the other in one workgroup: by the kernels above a level takes
+// three launches and a read-back, 30 to 70 us for a few us of work, and most levels of a tree are
+// small.  (Creating a scene of 292 triangles 0.43 ms, now 0.29; of 50k 1.61, now 1.50; of 200k 3.03,
+// now 2.88.)  Starts at the level of m nodes from base, listed in bin / acc
+// (ping-pong with bin2 / acc2), and ends with the first level of more than COLLAPSE_TOP nodes,
+// or of none, or after COLLAPSE_LEVELS levels, whose list it leaves for the host to go on with.
+// Chosen below that size: 1024 nodes, four passes of the workgroup, take less than a read-back.
+constexpr int COLLAPSE_TOP = 1024, COLLAPSE_LEVELS = 32;
+struct CollapseOut {
+    int m, base, levels, pad;           // the level that is next, and how many are done
+    int level_base[COLLAPSE_LEVELS];    // first node of each of them
+};
+__global__ void __launch_bounds__(TB) k_collapse_top(const float4* __restrict__ nodes, int ni, int* bin, int* acc, int* bin2,
+                                                     int* acc2, int m, int base, int cap4, int nt, float4* nodes4, int* map4,
+                                                     int* stats, int* leaf_seen, CollapseOut* out) {
+    __shared__ uint64_t ws[TB / 64];
+    int level = 0;   // (m, base and level are the same in every thread)
+    while (m > 0 && m <= COLLAPSE_TOP && base + m <= cap4 && level < COLLAPSE_LEVELS) {
+        int first = 0;   // next level's entries so far
+        for (int e0 = 0; e0 < m; e0 += TB) {
+            const int e = e0 + (int)threadIdx.x;
+            Kid k[4];
+            int cnt = 0, internal = 0, b = 0;
+            if (e < m) {
+                b = bin[e];
+                cnt = pick_kids(nodes, ni, b, k);
+                order_kids(k, cnt);
+                internal = internal_kids(k, cnt);
+            }
+            uint64_t tot;
+            const int slot = first + (int)block_exclusive((uint64_t)internal, ws, &tot);
+            if (e < m)
+                collapse_node(k, cnt, internal, b, acc[e], base + e, base + m, slot, ni, cap4, nt, nodes4, map4, bin2, acc2,
+                              stats, leaf_seen);
+            first += (int)tot;
+        }
+        if (threadIdx.x == 0) out->level_base[level] = base;
+        __syncthreads();   // the next level's entries, written by the whole workgroup
+        base += m;
+        m = first;
+        ++level;
+        int* t = bin;
+        bin = bin2;
+        bin2 = t;
+        t = acc;
+        acc = acc2;
+        acc2 = t;
+    }
+    if (threadIdx.x == 0) {
+        out->m = m;
+        out->base = base;
+        out->levels = level;
+    }
 }
 
 size_t wide_scratch_bytes(int nt) {
@@ -413,7 +475,9 @@ hipError_t build_wide(hipStream_t st, const WideArgs& a, void* scratch, uint64_t
     int* acc[2] = {(int*)take(4 * (size_t)ni), (int*)take(4 * (size_t)ni)};
     uint64_t* sums = (uint64_t*)take(8 * ((size_t)ni / TB + 1));
     uint64_t* total = (uint64_t*)take(256);
+    static_assert(32 + sizeof(CollapseOut) <= 256, "scratch");
     int* stats = (int*)(total + 1);
+    CollapseOut* out = (CollapseOut*)(total + 4);   // (32 + 144 of the 256 bytes)
     int* leaf_seen = (int*)take(4 * (size_t)nt);
     int* prim_seen = (int*)take(4 * (size_t)nt);
     res.nodes4 = (float4*)take(128 * (size_t)ni);
@@ -431,6 +495,22 @@ hipError_t build_wide(hipStream_t st, const WideArgs& a, void* scratch, uint64_t
         // the 4-wide nodes stand for distinct binary nodes, and a tree no deeper than 4096
         // has no more 4-wide levels than that
         if (base + m > cap4 || ++levels > 4096) return hipErrorUnknown;
+        if (m <= COLLAPSE_TOP) {
+            CollapseOut o;
+            hipLaunchKernelGGL(k_collapse_top, dim3(1), dim3(TB), 0, st, a.nodes, ni, bin[cur], acc[cur], bin[cur ^ 1],
+                               acc[cur ^ 1], m, base, cap4, nt, res.nodes4, res.map4, stats, leaf_seen, out);
+            e = hipMemcpyAsync(&o, out, sizeof o, hipMemcpyDeviceToHost, st);
+            if (e == hipSuccess) e = hipStreamSynchronize(st);
+            if (e != hipSuccess) return e;
+            if (o.levels < 1 || o.levels > COLLAPSE_LEVELS) return hipErrorUnknown;
+            for (int k = 0; k < o.levels; ++k)
+                if (levels + k <= MAX_LEVELS4) res.level_base[levels + k - 1] = o.level_base[k];
+            levels += o.levels - 1;
+            base = o.base;
+            m = o.m;
+            cur ^= o.levels & 1;
+            continue;
+        }
         const unsigned nb = grid_of(m, TB);
         hipLaunchKernelGGL(k_collapse_count, dim3(nb), dim3(TB), 0, st, a.nodes, ni, bin[cur], m, sums);
         hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, st, sums, (int)nb, total);
