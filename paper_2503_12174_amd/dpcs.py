@@ -333,11 +333,32 @@ def dpcs_render_vjp(ctx: Context, scene: Scene, params: RenderParams, proj_image
                                            _ptr(sample_radiance), _ptr(path_records), C.byref(g)))
 
 
+def ray_rows(rays):
+    """Rays as the library reads them: rows of 8 floats, o.xyz, d.xyz, tmax, the triangle left
+    (-1: none).  Rows of 6 get tmax = inf and no triangle left; any other shape is refused,
+    since the kernel reads 8 floats for each of the rays.shape[0] rays."""
+    import torch
+    if len(rays.shape) != 2 or rays.shape[1] not in (6, 8):
+        raise ValueError(f"rays must be (n, 8) or (n, 6), not {tuple(rays.shape)}")
+    if rays.shape[1] == 8:
+        return rays
+    rows = torch.as_tensor(rays).new_empty((int(rays.shape[0]), 8))
+    rows[:, :6], rows[:, 6], rows[:, 7] = torch.as_tensor(rays), float("inf"), -1.0
+    return rows
+
+
 def dpcs_debug_intersect(ctx: Context, scene: Scene, rays, use_bvh, prim, t=None, b1=None, b2=None):
     """use_bvh: 0 / False brute force, 1 / True the renderer's BVH, 2 the binary BVH,
-    3 any hit through the renderer's BVH, 4 any hit by brute force."""
-    return ctx.check(lib().dpcs_debug_intersect(ctx.h, scene.h, _ptr(rays), int(rays.shape[0]), int(use_bvh),
-                                                _ptr(prim), _ptr(t), _ptr(b1), _ptr(b2)))
+    3 any hit through the renderer's BVH, 4 any hit by brute force.  rays: see ray_rows."""
+    rows = ray_rows(rays)
+    if rows is not rays and rows.is_cuda:   # made on torch's current stream, read on the context's
+        import torch
+        torch.cuda.current_stream(rows.device).synchronize()
+    st = ctx.check(lib().dpcs_debug_intersect(ctx.h, scene.h, _ptr(rows), int(rows.shape[0]), int(use_bvh),
+                                              _ptr(prim), _ptr(t), _ptr(b1), _ptr(b2)))
+    if rows is not rays:   # they live until the launch has read them
+        ctx.synchronize()
+    return st
 
 
 def dpcs_debug_philox(ctx: Context, seed: int, ctr, out):
