@@ -269,7 +269,7 @@ __device__ __forceinline__ void adj_pixel_block(const Queues& q, const AdjQueues
         } else {
             for (int s = lane; s < r.spp; s += PIX_LANES) {
                 const float4 L = q.L[sid0 + s];
-                aq.delta[sid0 + s] = clip_cotangent(r, make_float4(gs[0], gs[1], gs[2], 0.f), L, thr);
+                aq.delta[sid0 + s] = clip_cotangent(make_float4(gs[0], gs[1], gs[2], 0.f), clipped(r, L, thr));
             }
         }
     }
@@ -981,21 +981,22 @@ struct Replayed {
     bool t_on, e_on;   // map cotangents of this vertex, E_p cotangent of its projector term
     double t_u, t_v, e_pu, e_pv;
 };
-// the vertex at `depth` <= lit of the path (o, dd), throughput b and remaining radiance rl (both
-// times the sample's cotangent)
+// the vertex at `depth` <= lit of the path (o, dd): throughput b, remaining radiance rl, the
+// sample's cotangent dl and tag
 template <bool TEX>
-__device__ __forceinline__ void replay_vertex(const ReqDesc& r, int depth, int lit, const PathO& o, const PathD& dd, float4 b,
-                                              float4 rl, Replayed& v, float (&tg)[5], float (&eg)[3]) {
+__device__ __forceinline__ void replay_vertex(const ReqDesc& r, int depth, uint32_t tag, const PathO& o, const PathD& dd,
+                                              float4 b, float4 dl, float4 rl, Replayed& v, float (&tg)[5], float (&eg)[3]) {
+    const int lit = replay_lit(tag);
     const uint32_t g = dd.g;
     const uint32_t rec = r.rec[(size_t)(g - r.rec_g0) * r.max_depth + depth];
     const int leaf = rec_leaf(r, rec);
     const Surf s = surface(r, leaf, d3(o.x, o.y, o.z), d3(dd.x, dd.y, dd.z));
-    const D3 db = d3(b.x, b.y, b.z);
+    const D3 beta = d3(b.x, b.y, b.z), delta = d3(dl.x, dl.y, dl.z), db = delta * beta;
     if (TEX && r.emission) {
         const float4 e = r.emission[leaf];
-        rl.x -= (float)(db.x * e.x);
-        rl.y -= (float)(db.y * e.y);
-        rl.z -= (float)(db.z * e.z);
+        rl.x -= (float)(beta.x * e.x);
+        rl.y -= (float)(beta.y * e.y);
+        rl.z -= (float)(beta.z * e.z);
     }
     D3 ga = d3(0., 0., 0.);
     double gr = 0.0, gs = 0.0;
@@ -1012,7 +1013,7 @@ __device__ __forceinline__ void replay_vertex(const ReqDesc& r, int depth, int l
         if constexpr (TEX) {
             const D4 E = fetch4(r.Ep, p.pb);
             const D3 Ex = d3(E.x, E.y, E.z) * p.geom;
-            const D3 C = db * f.f * Ex;
+            const D3 C = beta * f.f * Ex;   // (as the forward forms it, here and below)
             const double sx = db.x * Ex.x + db.y * Ex.y + db.z * Ex.z;
             ga = ga + db * Ex * (1.0 / PI);
             gr += sx * f.ds_dr;
@@ -1027,8 +1028,8 @@ __device__ __forceinline__ void replay_vertex(const ReqDesc& r, int depth, int l
             const U4 x = vertex_rng(r, g, 2u + 2u * depth);
             const D3 we = sample_cosine(s.n, u24(x.x), u24(x.y));
             const Brdf f = brdf_eval<true>(r.brdf, s.n, s.wo, we, s.alb, s.rough, s.spec);
-            const D3 Ee = d3(r.env[0], r.env[1], r.env[2]) * PI;
-            const D3 C = db * f.f * Ee;
+            const D3 Le = d3(r.env[0], r.env[1], r.env[2]), Ee = Le * PI;
+            const D3 C = beta * f.f * Le * PI;
             const double sx = db.x * Ee.x + db.y * Ee.y + db.z * Ee.z;
             ga = ga + db * Ee * (1.0 / PI);
             gr += sx * f.ds_dr;
@@ -1045,15 +1046,15 @@ __device__ __forceinline__ void replay_vertex(const ReqDesc& r, int depth, int l
         const double pdf = bounce_pdf(r.brdf, s.n, s.wo, wi, s.rough);
         if (ci > 0.0 && pdf > 0.0) {
             const Brdf f = brdf_eval<TEX>(r.brdf, s.n, s.wo, wi, s.alb, s.rough, s.spec);
-            const D3 ndb = db * (f.f * (ci * frcp(pdf)));
+            const D3 nbeta = beta * (f.f * (ci * frcp(pdf)));
             v.cont = true;
             v.no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
-            v.nd = PathD{wi.x, wi.y, wi.z, g, (uint32_t)lit};
-            v.nb = make_float4((float)ndb.x, (float)ndb.y, (float)ndb.z, 0.0f);
+            v.nd = PathD{wi.x, wi.y, wi.z, g, tag};
+            v.nb = make_float4((float)nbeta.x, (float)nbeta.y, (float)nbeta.z, 0.0f);
             v.nrl = rl;
             if constexpr (TEX) {   // d/df of beta f cos/pdf R_{k+1}: L_r / f
-                const D3 t = d3(f.f.x > 0.0 ? rl.x * frcp(f.f.x) : 0.0, f.f.y > 0.0 ? rl.y * frcp(f.f.y) : 0.0,
-                                f.f.z > 0.0 ? rl.z * frcp(f.f.z) : 0.0);
+                const D3 t = delta * d3(f.f.x > 0.0 ? rl.x * frcp(f.f.x) : 0.0, f.f.y > 0.0 ? rl.y * frcp(f.f.y) : 0.0,
+                                        f.f.z > 0.0 ? rl.z * frcp(f.f.z) : 0.0);
                 const double sum = t.x + t.y + t.z;
                 ga = ga + t * (1.0 / PI);
                 gr += sum * f.ds_dr;
@@ -1075,8 +1076,10 @@ __device__ __forceinline__ void replay_vertex(const ReqDesc& r, int depth, int l
 // One bounce of the replay when the forward kept its path records: the vertex's leaf and
 // the visibility of its shadow rays are read instead of traced.  Shading, the
 // next-event terms and the bounce are re-evaluated with the forward's Philox counters.
-// A path carries its throughput and remaining radiance already multiplied by the sample's
-// cotangent (delta beta and delta L_r: every term is linear in delta), 96 bytes in all.
+// A path carries its throughput and remaining radiance, 96 bytes in all; the sample's cotangent
+// is its pixel's, read again at every vertex, without the channels the path's tag names.
+// The remaining radiance is the sample's minus the very FP32 contributions the forward added.
+// (Carried times the cotangent, every term is rounded once more before the subtraction.)
 // The records say which vertices are lit, so a sample is replayed only up to the last one
 // (replay_start): beyond it the remaining radiance is exactly zero.  A bounce is taken only
 // before that vertex, where what remains after this vertex's own terms is known, so its
@@ -1088,7 +1091,7 @@ __device__ __forceinline__ void replay_vertex(const ReqDesc& r, int depth, int l
 // TEX: the maps' cotangents are wanted; without them only projector light counts, no
 // derivative of the reflectance is formed and no remaining radiance carried.
 template <bool UNI, bool TEX>
-__global__ void __launch_bounds__(BLOCK) k_adj_replay(Queues q, AdjQueues aq, int cur, int depth,
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) k_adj_replay(Queues q, AdjQueues aq, int cur, int depth,
                                                       const float* __restrict__ sample_L, ReqDesc uni,
                                                       const ReqDesc* __restrict__ table) {
     const int nxt = cur ^ 1;
@@ -1108,7 +1111,8 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay(Queues q, AdjQueues aq, in
     if (i < n) {
         PathO o;
         PathD dd;
-        float4 b, rl = {};
+        float4 b, dl = {}, rl = {};
+        uint32_t tag;
         int lit;
         if (depth == 0) {
             if constexpr (UNI) {   // queue index i: sample i of the request in this wave
@@ -1121,8 +1125,10 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay(Queues q, AdjQueues aq, in
             const ReqDesc& r = sel<UNI>(uni, table, o.slot);
             const ReplayStart t = replay_start<TEX>(r, dd.g, sample_L, q.L, aq.delta);
             lit = t.lit;
-            b = t.dl;
-            rl = make_float4(t.dl.x * t.L.x, t.dl.y * t.L.y, t.dl.z * t.L.z, 0.f);
+            tag = t.tag;
+            b = make_float4(1.0f, 1.0f, 1.0f, 0.0f);
+            dl = t.dl;
+            rl = t.L;
             if constexpr (UNI)
                 if (lit >= 0) {
                     const D3 cd = camera_dir(uni, dd.g);
@@ -1133,16 +1139,18 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay(Queues q, AdjQueues aq, in
             dd = nt_ld(&q.pd[cur][i]);
             b = nt_ld(&q.pb[cur][i]);
             if constexpr (TEX) rl = nt_ld(&aq.rl[cur][i]);
-            lit = (int)dd.pad;
+            tag = dd.pad;
+            lit = replay_lit(tag);
+            dl = replay_delta(sel<UNI>(uni, table, o.slot), dd.g, tag, aq.delta);
         }
         if (lit >= depth) {
             const ReqDesc& r = sel<UNI>(uni, table, o.slot);
             rp = &r;
             lslot = o.slot;
-            replay_vertex<TEX>(r, depth, lit, o, dd, b, rl, v, tg, eg);
+            replay_vertex<TEX>(r, depth, tag, o, dd, b, dl, rl, v, tg, eg);
         }
     }
-    // records for the binned flush (direct atomics where there is v.no bin or it is full)
+    // records for the binned flush (direct atomics where there is no bin or it is full)
     const bool to_t = UNI && TEX && v.t_on && aq.tb.rec, to_e = UNI && v.e_on && aq.eb.rec;
     const bool pred[3] = {v.cont, to_t, to_e};
     uint32_t* const ctr[3] = {replay_count(q, depth + 1), aq.tb.count, aq.eb.count};
@@ -1196,14 +1204,16 @@ __device__ __forceinline__ void replay_paths_block(const Queues& q, float4* delt
     const uint32_t i = block * BLOCK + threadIdx.x;
     PathO o{r.cam_o[0], r.cam_o[1], r.cam_o[2], 0, -1};
     PathD d{};
-    float4 b = {}, rl = {};
+    float4 b = make_float4(1.0f, 1.0f, 1.0f, 0.0f), dl = {}, rl = {};
+    uint32_t tag = 0u;
     int lit = -1;
     if (i < n) {
         const uint32_t g = r.g_base + i;
         const ReplayStart t = replay_start<TEX>(r, g, sample_L, q.L, delta);
         lit = t.lit;
-        b = t.dl;
-        rl = make_float4(t.dl.x * t.L.x, t.dl.y * t.L.y, t.dl.z * t.L.z, 0.f);
+        tag = t.tag;
+        dl = t.dl;
+        rl = t.L;
         if (lit >= 0) {
             const D3 cd = camera_dir(r, g);
             d = PathD{cd.x, cd.y, cd.z, g, 0u};
@@ -1212,7 +1222,7 @@ __device__ __forceinline__ void replay_paths_block(const Queues& q, float4* delt
     for (int depth = 0; __syncthreads_or(lit >= depth); ++depth) {   // uniform per workgroup; lit < max_depth
         Replayed v{};
         float tg[5] = {0.f, 0.f, 0.f, 0.f, 0.f}, eg[3] = {0.f, 0.f, 0.f};
-        if (lit >= depth) replay_vertex<TEX>(r, depth, lit, o, d, b, rl, v, tg, eg);
+        if (lit >= depth) replay_vertex<TEX>(r, depth, tag, o, d, b, dl, rl, v, tg, eg);
         const bool to_t = TEX && v.t_on;
         const bool pred[2] = {to_t, v.e_on};
         uint32_t* const ctr[2] = {tb.count, eb.count};
@@ -1248,7 +1258,7 @@ __global__ void __launch_bounds__(BLOCK) k_replay_paths_joint(Queues q, float4* 
 // for the environment (the sampling pdf c / pi held fixed), R_{k+1} / pdf for the bounce;
 // its derivative w.r.t. a map value is beta_c d(f_c c) S_c.  For the bounce beta_c f_c c S_c
 // is what remains of the sample's radiance after the vertex's own terms, rl_c, so its
-// derivative is rl_c d(f_c c) / (f_c c).  Normal cotangents go to the stored map values
+// derivative is delta_c rl_c d(f_c c) / (f_c c).  Normal cotangents go to the stored map values
 // (through the vertex's frame), so the records hold 9 channels.
 template <bool TEX>
 __global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq, int cur, int depth,
@@ -1271,15 +1281,18 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq
     if (i < n) {
         PathO o;
         PathD dd;
-        float4 b, rl = {};
+        float4 b, dl, rl = {};
+        uint32_t tag;
         int lit;
         if (depth == 0) {   // queue index i: sample i of this wave
             o = PathO{r.cam_o[0], r.cam_o[1], r.cam_o[2], 0, -1};
             dd.g = r.g_base + i;
             const ReplayStart t = replay_start<TEX>(r, dd.g, sample_L, q.L, aq.delta);
             lit = t.lit;
-            b = t.dl;
-            rl = make_float4(t.dl.x * t.L.x, t.dl.y * t.L.y, t.dl.z * t.L.z, 0.f);
+            tag = t.tag;
+            b = make_float4(1.0f, 1.0f, 1.0f, 0.0f);
+            dl = t.dl;
+            rl = t.L;
             if (lit >= 0) {
                 const D3 cd = camera_dir(r, dd.g);
                 dd.x = cd.x, dd.y = cd.y, dd.z = cd.z;
@@ -1289,7 +1302,9 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq
             dd = nt_ld(&q.pd[cur][i]);
             b = nt_ld(&q.pb[cur][i]);
             if constexpr (TEX) rl = nt_ld(&aq.rl[cur][i]);
-            lit = (int)dd.pad;
+            tag = dd.pad;
+            lit = replay_lit(tag);
+            dl = replay_delta(r, dd.g, tag, aq.delta);
         }
         if (lit >= depth) {
             const uint32_t g = dd.g;
@@ -1297,16 +1312,16 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq
             const int leaf = rec_leaf(r, rec);
             const Surf s = surface(r, leaf, d3(o.x, o.y, o.z), d3(dd.x, dd.y, dd.z));
             const Shading sh = shading(r, leaf, s);
-            const D3 db = d3(b.x, b.y, b.z);
+            const D3 beta = d3(b.x, b.y, b.z), delta = d3(dl.x, dl.y, dl.z), db = delta * beta;
             if (TEX && r.emission) {
                 const float4 e = r.emission[leaf];
-                rl.x -= (float)(db.x * e.x);
-                rl.y -= (float)(db.y * e.y);
-                rl.z -= (float)(db.z * e.z);
+                rl.x -= (float)(beta.x * e.x);
+                rl.y -= (float)(beta.y * e.y);
+                rl.z -= (float)(beta.z * e.z);
             }
             double ng[6] = {0., 0., 0., 0., 0., 0.};   // albedo rgb, roughness, specular, metallic
             D3 gnv = d3(0., 0., 0.);                   // cotangent of the shading normal
-            // cotangents of w_c f_c c, w = db S (next events) or rl / (f c) (the bounce)
+            // cotangents of w_c f_c c, w = db S (next events) or delta rl / (f c) (the bounce)
             auto term = [&](const BrdfX& f, D3 w) {
                 const D3 cw = w * f.c;
                 ng[0] += f.dfa * cw.x;
@@ -1329,9 +1344,9 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq
                 eg[2] = (float)gE.z;
                 if constexpr (TEX) {
                     const D4 E = fetch4(r.Ep, p.pb);
-                    const D3 w = db * d3(E.x, E.y, E.z) * p.g0;
-                    const D3 C = f.f * w * f.c;
-                    term(f, w);
+                    const D3 Eg = d3(E.x, E.y, E.z) * p.g0;
+                    const D3 C = beta * f.f * Eg * f.c;   // (as the forward forms it, here and below)
+                    term(f, db * Eg);
                     rl.x -= (float)C.x;
                     rl.y -= (float)C.y;
                     rl.z -= (float)C.z;
@@ -1343,7 +1358,7 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq
                     const D3 we = sample_cosine(sh.ns, u24(x.x), u24(x.y));
                     const BrdfX f = brdf_x<true>(r.brdf, s.n, sh.ns, s.wo, we, s.alb, s.rough, s.spec, sh.metal);
                     const D3 Le = d3(r.env[0], r.env[1], r.env[2]);
-                    const D3 C = db * f.f * Le * PI;
+                    const D3 C = beta * f.f * Le * PI;
                     if (f.c > 0.0) term(f, db * Le * (PI * frcp(f.c)));
                     rl.x -= (float)C.x;
                     rl.y -= (float)C.y;
@@ -1357,15 +1372,16 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq
                 const double pdf = bounce_pdf(r.brdf, sh.ns, s.wo, wi, s.rough);
                 if (ci > 0.0 && pdf > 0.0) {
                     const BrdfX f = brdf_x<TEX>(r.brdf, s.n, sh.ns, s.wo, wi, s.alb, s.rough, s.spec, sh.metal);
-                    const D3 ndb = db * (f.f * (f.c * frcp(pdf)));
+                    const D3 nbeta = beta * (f.f * (f.c * frcp(pdf)));
                     cont = true;
                     no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
-                    nd = PathD{wi.x, wi.y, wi.z, g, (uint32_t)lit};
-                    nb = make_float4((float)ndb.x, (float)ndb.y, (float)ndb.z, 0.0f);
+                    nd = PathD{wi.x, wi.y, wi.z, g, tag};
+                    nb = make_float4((float)nbeta.x, (float)nbeta.y, (float)nbeta.z, 0.0f);
                     nrl = rl;
                     if constexpr (TEX)
-                        term(f, d3(f.f.x > 0.0 ? rl.x * frcp(f.f.x * f.c) : 0.0, f.f.y > 0.0 ? rl.y * frcp(f.f.y * f.c) : 0.0,
-                                   f.f.z > 0.0 ? rl.z * frcp(f.f.z * f.c) : 0.0));
+                        term(f, delta * d3(f.f.x > 0.0 ? rl.x * frcp(f.f.x * f.c) : 0.0,
+                                           f.f.y > 0.0 ? rl.y * frcp(f.f.y * f.c) : 0.0,
+                                           f.f.z > 0.0 ? rl.z * frcp(f.f.z * f.c) : 0.0));
                 }
             }
             if constexpr (TEX) {

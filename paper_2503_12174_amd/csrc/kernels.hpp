@@ -207,8 +207,7 @@ constexpr int64_t map_units(int64_t cap, int64_t nb) { return (cap + ACC_CHUNK -
 
 // adjoint additions (see adjoint.hip)
 struct AdjQueues {
-    float4* rl[2];     // remaining radiance L_r of the path (rgb, -), follows the path queue; the
-                       // record replay's: times the sample's cotangent
+    float4* rl[2];     // remaining radiance L_r of the path (rgb, -), follows the path queue
     float4* delta;     // re-tracing replay: per batch sample cotangent of its radiance (rgb, -);
                        // record replay: the pixel's, at its first sample
     // the re-tracing replay's shadow rays and pending bounces (null for the record replay)

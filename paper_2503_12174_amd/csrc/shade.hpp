@@ -287,13 +287,15 @@ __device__ __forceinline__ int last_lit(const ReqDesc& r, uint32_t g, bool all) 
     }
     return lit;
 }
-// cotangent of a sample's radiance L from its pixel's: zero where the clip (Eq. 12) holds
-__device__ __forceinline__ float4 clip_cotangent(const ReqDesc& r, float4 dp, float4 L, float thr) {
-    if (r.clip) {
-        if (L.x > thr) dp.x = 0.f;
-        if (L.y > thr) dp.y = 0.f;
-        if (L.z > thr) dp.z = 0.f;
-    }
+// A sample's cotangent is its pixel's, zero in the channels where the clip (Eq. 12) holds;
+// bit c: channel c of radiance L is clipped
+__device__ __forceinline__ uint32_t clipped(const ReqDesc& r, float4 L, float thr) {
+    return r.clip ? (L.x > thr ? 1u : 0u) | (L.y > thr ? 2u : 0u) | (L.z > thr ? 4u : 0u) : 0u;
+}
+__device__ __forceinline__ float4 clip_cotangent(float4 dp, uint32_t over) {
+    if (over & 1u) dp.x = 0.f;
+    if (over & 2u) dp.y = 0.f;
+    if (over & 4u) dp.z = 0.f;
     return dp;
 }
 // A record replay's camera sample: its radiance (the forward's per-sample output, or the
@@ -303,21 +305,32 @@ __device__ __forceinline__ float4 clip_cotangent(const ReqDesc& r, float4 dp, fl
 struct ReplayStart {
     float4 L, dl;
     int lit;
+    uint32_t tag;   // what the path carries on: lit and the clipped channels (replay_lit, replay_delta)
 };
+__device__ __forceinline__ float4 pixel_delta(const ReqDesc& r, uint32_t g, const float4* __restrict__ delta) {
+    const uint32_t s = g - udiv(g, r.inv_spp) * (uint32_t)r.spp;
+    return delta[g - r.g_base + r.sid_base - s];
+}
 template <bool ENV>
 __device__ __forceinline__ ReplayStart replay_start(const ReqDesc& r, uint32_t g, const float* __restrict__ sample_L,
                                                     const float4* __restrict__ wave_L,
                                                     const float4* __restrict__ delta) {
     ReplayStart t;
-    const uint32_t sid = g - r.g_base + r.sid_base, s = g - udiv(g, r.inv_spp) * (uint32_t)r.spp;
     if (sample_L) t.L = make_float4(sample_L[3 * (size_t)g], sample_L[3 * (size_t)g + 1], sample_L[3 * (size_t)g + 2], 0.f);
-    else t.L = wave_L[sid];
-    t.dl = clip_cotangent(r, delta[sid - s], t.L, clip_threshold(r));
+    else t.L = wave_L[g - r.g_base + r.sid_base];
+    const uint32_t over = clipped(r, t.L, clip_threshold(r));
+    t.dl = clip_cotangent(pixel_delta(r, g, delta), over);
     const float x = (t.L.x + t.L.y + t.L.z) * 0.f + (t.dl.x + t.dl.y + t.dl.z) * 0.f;   // 0, or NaN if any is not finite
     t.lit = -1;
     if (x != 0.f) t.lit = last_lit<true>(r, g, true);
     else if (t.dl.x != 0.f || t.dl.y != 0.f || t.dl.z != 0.f) t.lit = last_lit<ENV>(r, g, false);
+    t.tag = (uint32_t)t.lit | over << 8;   // (lit < 64 where a path goes on)
     return t;
+}
+// the same at a later vertex, from the tag
+__device__ __forceinline__ int replay_lit(uint32_t tag) { return (int)(tag & 255u); }
+__device__ __forceinline__ float4 replay_delta(const ReqDesc& r, uint32_t g, uint32_t tag, const float4* __restrict__ delta) {
+    return clip_cotangent(pixel_delta(r, g, delta), tag >> 8);
 }
 
 }  // namespace dpcs
