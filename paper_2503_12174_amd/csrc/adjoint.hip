@@ -443,7 +443,7 @@ __global__ void __launch_bounds__(BLOCK) k_adj_shade(Queues q, AdjQueues aq, int
                     const double pdf = bounce_pdf(r.brdf, s.n, s.wo, wi, s.rough);
                     if (ci > 0.0 && pdf > 0.0) {
                         const Brdf f = brdf_eval<true>(r.brdf, s.n, s.wo, wi, s.alb, s.rough, s.spec);
-                        const D3 nbeta = beta * (f.f * (ci * frcp(pdf)));
+                        const D3 nbeta = beta * bounce_weight(f.f, ci, pdf);
                         cont = true;
                         no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
                         nd = PathD{wi.x, wi.y, wi.z, g, 0u};
@@ -1046,7 +1046,7 @@ __device__ __forceinline__ void replay_vertex(const ReqDesc& r, int depth, uint3
         const double pdf = bounce_pdf(r.brdf, s.n, s.wo, wi, s.rough);
         if (ci > 0.0 && pdf > 0.0) {
             const Brdf f = brdf_eval<TEX>(r.brdf, s.n, s.wo, wi, s.alb, s.rough, s.spec);
-            const D3 nbeta = beta * (f.f * (ci * frcp(pdf)));
+            const D3 nbeta = beta * bounce_weight(f.f, ci, pdf);
             v.cont = true;
             v.no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
             v.nd = PathD{wi.x, wi.y, wi.z, g, tag};
@@ -1359,7 +1359,7 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq
                     const BrdfX f = brdf_x<true>(r.brdf, s.n, sh.ns, s.wo, we, s.alb, s.rough, s.spec, sh.metal);
                     const D3 Le = d3(r.env[0], r.env[1], r.env[2]);
                     const D3 C = beta * f.f * Le * PI;
-                    if (f.c > 0.0) term(f, db * Le * (PI * frcp(f.c)));
+                    if (f.c > 0.0) term(f, db * Le * div_rn(PI, f.c));
                     rl.x -= (float)C.x;
                     rl.y -= (float)C.y;
                     rl.z -= (float)C.z;
@@ -1372,7 +1372,7 @@ __global__ void __launch_bounds__(BLOCK) k_adj_replay_ext(Queues q, AdjQueues aq
                 const double pdf = bounce_pdf(r.brdf, sh.ns, s.wo, wi, s.rough);
                 if (ci > 0.0 && pdf > 0.0) {
                     const BrdfX f = brdf_x<TEX>(r.brdf, s.n, sh.ns, s.wo, wi, s.alb, s.rough, s.spec, sh.metal);
-                    const D3 nbeta = beta * (f.f * (f.c * frcp(pdf)));
+                    const D3 nbeta = beta * bounce_weight(f.f, f.c, pdf);
                     cont = true;
                     no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};
                     nd = PathD{wi.x, wi.y, wi.z, g, tag};

@@ -71,9 +71,12 @@ __device__ __forceinline__ D3 mat3(const double* m, D3 a) {
 //
 // Everything else -- reflectance and its derivatives, densities, throughput, the projector's
 // geometry -- takes one FMA for a product that is added, and reciprocals and roots from the
-// hardware's estimate (~2^-23) with two Newton steps, within 1-2 ulp (f... functions).  The
-// build contracts nothing by itself (the FP32 triangle test relies on that), so every kernel
-// forms the same value.
+// hardware's estimate (~2^-23) with Newton steps (f... functions); a quotient whose second
+// rounding its result would show is rounded once (div_rn).  The bar is the error of the plain
+// sequence of rounded operations against 128 bits, which none exceeds (tests/test_fp64_forms.py;
+// rms in units of 2^-53, plain and these forms: reflectance 6.3 and 5.5, density 6.3 and 5.4,
+// normal derivatives 5.8 and 5.1, projector falloff 2.3 and 1.4).  The build contracts
+// nothing by itself (the FP32 triangle test relies on that), so every kernel forms the same value.
 // 50k-triangle corner, 256^2 x 64 spp: camera-vertex shading 214 -> 194 us, record replay
 // 358 -> 326 us (the deeper vertices' shading is bound by its memory traffic); camera-pose
 // terms at 16 spp 258 -> 148 us.
@@ -125,6 +128,19 @@ __device__ __forceinline__ D3 fcross(D3 a, D3 b) {
 }
 // a s + b
 __device__ __forceinline__ D3 fmadd(D3 a, double s, D3 b) { return {fma(a.x, s, b.x), fma(a.y, s, b.y), fma(a.z, s, b.z)}; }
+// What the projector's light does on its way to a point: unit direction wp towards it,
+// distance, and falloff 1 / (cos^3 alpha d^2) = |xp|^3 / (xp.z^3 d^2), from the point's place xp
+// in the projector's frame (xp.z > 0) and the vector tow to the projector.  One quotient: by
+// way of 1 / cos alpha its rounding counts three times.
+__device__ __forceinline__ double projector_falloff(D3 xp, D3 tow, D3& wp, double& dist) {
+    const double d2 = fdot(tow, tow), id = frsqrt(d2), d = d2 * id;
+    dist = fma(fma(-d, d, d2), 0.5 * id, d);
+    wp = tow * id;
+    const double l2 = fdot(xp, xp);
+    return div_rn(l2 * fsqrt(l2), xp.z * xp.z * xp.z * d2);
+}
+// the throughput factor of a bounce: reflectance f, cosine c, density pdf > 0
+__device__ __forceinline__ D3 bounce_weight(D3 f, double c, double pdf) { return f * div_rn(c, pdf); }
 // m a + c
 __device__ __forceinline__ D3 fmat3(const double* m, D3 a, D3 c) {
     return d3(fma(m[0], a.x, fma(m[1], a.y, fma(m[2], a.z, c.x))), fma(m[3], a.x, fma(m[4], a.y, fma(m[5], a.z, c.y))),
@@ -316,7 +332,7 @@ __device__ __forceinline__ double ggx_alpha(double r) { return fmax(r * r, ALPHA
 template <bool GRAD>
 __device__ __forceinline__ Brdf brdf_eval(int kind, D3 n, D3 wo, D3 wi, D3 alb, double r, double sp) {
     Brdf b{d3(0., 0., 0.), 0., 0.};
-    const double ci = fdot(n, wi), co = fdot(n, wo);
+    const double ci = dot(n, wi), co = fdot(n, wo);   // (ci: as in the density and the callers, which divide by it)
     if (ci <= 0.0 || co <= 0.0) return b;
     b.f = alb * (1.0 / PI);
     if (kind == 0) return b;
@@ -369,7 +385,7 @@ __device__ __forceinline__ BrdfX brdf_x(int kind, D3 ng, D3 ns, D3 wo, D3 wi, D3
                                         double mu) {
     BrdfX b;
     b.f = d3(0., 0., 0.);
-    b.c = fdot(ns, wi);
+    b.c = dot(ns, wi);
     b.dfa = b.dfs = 0.0;
     b.dfr = b.dfm = d3(0., 0., 0.);
     b.dn[0] = b.dn[1] = b.dn[2] = d3(0., 0., 0.);
@@ -402,8 +418,7 @@ __device__ __forceinline__ BrdfX brdf_x(int kind, D3 ng, D3 ns, D3 wo, D3 wi, D3
     const D3 F = d3(fma(1.0 - F0.x, m5, F0.x), fma(1.0 - F0.y, m5, F0.y), fma(1.0 - F0.z, m5, F0.z));
     b.f = fmadd(F, DGw, alb * (kd * (1.0 / PI)));
     if (GRAD) {
-        const double ikv = frcp(kv);
-        const double dlnD = 2.0 * frcp(a) * fma(-2.0 * a2 * c2v, ikv, 1.0);
+        const double dlnD = 2.0 * frcp(a) * fma(-2.0 * a2 * c2v, frcp(kv), 1.0);
         const double di = qi * gi, dd = qo * go;
         const double dlnG = -a * fma(fma(-ci, ci, 1.0), dd, fma(-co, co, 1.0) * di) * frcp(di * dd);
         const double da_dr = (r * r > ALPHA_MIN) ? 2.0 * r : 0.0;
@@ -418,15 +433,15 @@ __device__ __forceinline__ BrdfX brdf_x(int kind, D3 ng, D3 ns, D3 wo, D3 wi, D3
         // + D G1i dG1o wo) / (4 co) - S / co wo
         const double iv = frsqrt(vv);
         const double ch = nv * iv;
-        const double ik = vv * ikv;                     // 1 / k
+        const double ik = div_rn(vv, kv);               // 1 / k
         const double D = a2 * (1.0 / PI) * ik * ik;
-        const double igi = frcp(gi), igo = frcp(go);
-        const double G1i = 2.0 * ci * igi, G1o = 2.0 * co * igo;
+        const double G1i = div_rn(2.0 * ci, gi), G1o = div_rn(2.0 * co, go);
         const double dD = 4.0 * ch * b2 * D * ik;
-        const double dG1i = 2.0 * a2 * igi * igi * frcp(qi), dG1o = 2.0 * a2 * igo * igo * frcp(qo);
+        const double dG1i = div_rn(2.0 * a2, di * gi), dG1o = div_rn(2.0 * a2, dd * go);
         const double S = DGw * ci;
-        const double ico = frcp(co), i4 = 0.25 * ico;
-        const D3 dS = fmadd(v, dD * G1i * G1o * i4 * iv, fmadd(wi, D * dG1i * G1o * i4, wo * fma(D * G1i * dG1o, i4, -(S * ico))));
+        const double i4 = 0.25 * frcp(co);
+        const D3 dS = fmadd(v, dD * G1i * G1o * i4 * iv,
+                            fmadd(wi, D * dG1i * G1o * i4, wo * fma(D * G1i * dG1o, i4, -div_rn(S, co))));
         b.dn[0] = fmadd(dS, F.x, wi * (kd * alb.x * (1.0 / PI)));
         b.dn[1] = fmadd(dS, F.y, wi * (kd * alb.y * (1.0 / PI)));
         b.dn[2] = fmadd(dS, F.z, wi * (kd * alb.z * (1.0 / PI)));
@@ -477,7 +492,7 @@ __device__ __forceinline__ D3 sample_bounce(int kind, D3 n, D3 wo, double r, dou
 // (GGX part: D(h) |n.h| / (4 |wo.h|) = a^2 vv^2 |n.v| / (4 pi kv^2 |wo.v|), v = wi + wo as
 // in brdf_eval)
 __device__ __forceinline__ double bounce_pdf(int kind, D3 n, D3 wo, D3 wi, double r) {
-    const double ci = fdot(n, wi);
+    const double ci = dot(n, wi);
     const double pd = ci > 0.0 ? ci * (1.0 / PI) : 0.0;
     if (kind == 0) return pd;
     const D3 v = wi + wo;

@@ -229,10 +229,10 @@ __device__ __forceinline__ void shade_vertex(const ReqDesc& r, int depth, int le
                 D3 nbeta;
                 if constexpr (EXT) {
                     const BrdfX f = brdf_x<false>(r.brdf, s.n, ns, s.wo, wi, s.alb, s.rough, s.spec, sh.metal);
-                    nbeta = beta * (f.f * (f.c * frcp(pdf)));
+                    nbeta = beta * bounce_weight(f.f, f.c, pdf);
                 } else {
                     const Brdf f = brdf_eval<false>(r.brdf, s.n, s.wo, wi, s.alb, s.rough, s.spec);
-                    nbeta = beta * (f.f * (ci * frcp(pdf)));
+                    nbeta = beta * bounce_weight(f.f, ci, pdf);
                 }
                 v.cont = true;
                 v.no = PathO{s.x.x, s.x.y, s.x.z, o.slot, s.prim};

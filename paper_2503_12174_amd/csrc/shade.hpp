@@ -241,14 +241,9 @@ __device__ __forceinline__ bool projector_nee(const ReqDesc& r, const Surf& s, P
     p.pv = fma(r.prj_K[3], xp.x, fma(r.prj_K[4], xp.y, r.prj_K[5] * xp.z)) * iz;
     if (!(p.pu >= 0.0 && p.pu < (double)r.Wp && p.pv >= 0.0 && p.pv < (double)r.Hp)) return false;
     const D3 tow = d3(r.prj_o[0], r.prj_o[1], r.prj_o[2]) - s.x;
-    const double d2 = fdot(tow, tow), id = frsqrt(d2);
-    p.dist = d2 * id;
-    p.wp = tow * id;
-    const double cp = fdot(s.n, p.wp);
+    p.g0 = projector_falloff(xp, tow, p.wp, p.dist);
+    const double cp = dot(s.n, p.wp);
     if (!(cp > 0.0)) return false;
-    const double l2 = fdot(xp, xp);
-    const double ica = l2 * frsqrt(l2) * iz;   // 1 / cos alpha = |xp| / xp.z
-    p.g0 = ica * ica * ica * (id * id);
     p.geom = cp * p.g0;
     p.pb = bilinear(p.pu - 0.5, p.pv - 0.5, r.Wp, r.Hp);
     return true;
