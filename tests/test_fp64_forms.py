@@ -141,7 +141,7 @@ static D3 any() {
     }
 }
 int main() {
-    double s[2][USED] = {};
+    double s[2][USED] = {}, d[2][3] = {};
     int cnt = 0;
     for (int it = 0; cnt < 400000; ++it) {
         const D3 n = any(), wo = any(), al = d3(0.05 + 0.9 * uni(), 0.05 + 0.9 * uni(), 0.05 + 0.9 * uni());
@@ -154,9 +154,9 @@ int main() {
         }
         if (co < 0.02 || dot(n, wi) < 0.02) continue;
         // a point 0.3 to 1.5 in front of the projector, and the same vector as the world has it
-        const double z = 0.3 + 1.2 * uni(), d = sqrt(1.0 + 0.16 * uni());
+        const double z = 0.3 + 1.2 * uni(), dd = sqrt(1.0 + 0.16 * uni());
         const D3 xp = d3(0.8 * (uni() - 0.5) * z, 0.8 * (uni() - 0.5) * z, z);
-        const D3 tow = any() * (z * d);
+        const D3 tow = any() * (z * dd);
         __float128 e[NV];
         double p[NV], q[NV];
         plain<__float128>(n, wo, wi, al, r, sp, mt, xp, tow, e);
@@ -174,10 +174,36 @@ int main() {
             s[0][j] += err(p[j]) * err(p[j]);
             s[1][j] += err(q[j]) * err(q[j]);
         }
+        {   // the camera-pose gradient's differences: of the falloff over a step of the point, of
+            // the reflectances over a turn of the outgoing direction
+            const double h = 1e-8 * z, w = 1e-7;
+            const D3 e1 = any(), e2 = any();
+            const D3 X[2] = {xp, d3(xp.x + e1.x * h, xp.y + e1.y * h, xp.z + e1.z * h)};
+            const D3 Y[2] = {tow, d3(tow.x + e2.x * h, tow.y + e2.y * h, tow.z + e2.z * h)};
+            const D3 O[2] = {wo, unit(wo.x + e1.x * w, wo.y + e1.y * w, wo.z + e1.z * w)};
+            __float128 E[2][NV];
+            double P[2][NV], R[2][NV];
+            for (int k = 0; k < 2; ++k) {
+                plain<__float128>(n, O[k], wi, al, r, sp, mt, X[k], Y[k], E[k]);
+                plain<double>(n, O[k], wi, al, r, sp, mt, X[k], Y[k], P[k]);
+                ours(n, O[k], wi, al, r, sp, mt, X[k], Y[k], R[k]);
+            }
+            const int id[3] = {22, 0, 4};
+            for (int v = 0; v < 3; ++v) {
+                const int j = id[v];
+                const double st = v == 0 ? h : w, scale = fabs((double)E[0][j]) / (v == 0 ? z : 1.0);
+                const __float128 x = (E[1][j] - E[0][j]) / (__float128)st;
+                auto err = [&](double f0, double f1) { return fmin(fabs((double)((f1 - f0) / st - x)) / scale, 1e-6); };
+                const double a = err(P[0][j], P[1][j]), b = err(R[0][j], R[1][j]);
+                d[0][v] += a * a, d[1][v] += b * b;
+            }
+        }
         ++cnt;
     }
     for (int j = 0; j < USED; ++j)
         printf("%s %.4f %.4f\n", NAME[j], sqrt(s[0][j] / cnt) * 0x1p53, sqrt(s[1][j] / cnt) * 0x1p53);
+    const char* nd[3] = {"slope_falloff", "slope_f", "slope_pf"};
+    for (int v = 0; v < 3; ++v) printf("%s %.4f %.4f\n", nd[v], sqrt(d[0][v] / cnt) * 1e8, sqrt(d[1][v] / cnt) * 1e8);
     return 0;
 }
 '''
@@ -198,7 +224,7 @@ def errors(tmp_path_factory):
 
 @pytest.mark.parametrize("value", ["f", "d_rough", "d_spec", "density", "pf", "pf_albedo", "pf_rough", "pf_spec", "pf_metal",
                                    "dn0", "dn1", "dn2", "dn3", "dn4", "dn5", "dn6", "dn7", "dn8", "throughput", "lambert",
-                                   "distance", "direction", "falloff"])
+                                   "distance", "direction", "falloff", "slope_falloff", "slope_f", "slope_pf"])
 def test_error_is_no_larger_than_the_plain_sequences(errors, value):
     plain, ours = errors[value]
     assert ours <= 1.02 * plain
