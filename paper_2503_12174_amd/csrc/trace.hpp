@@ -281,8 +281,10 @@ __device__ __forceinline__ void sort2(uint32_t& a, uint32_t& b) {
 // test takes no product for it (the closest-hit loop is bound by vector issue: 256 x 256 x
 // 64 of the 50k-triangle corner 1583 us with the two products, 1580 without, and 1587 before
 // the triangle test lost its swap of two axes; with an environment map 2200, 2193, 2180).
-// An axis along which the ray does not move (|d| < 2^-80, or 0) takes the reciprocal 2^80;
-// every offset is widened by 2^-40 in space besides, so such a slab lets pass exactly the
+// An axis along which the ray does not move (less than 2^-80 of its largest component, so for
+// directions of any length, or 0) takes the reciprocal of that least movement -- infinite for
+// directions shorter than 2^-46, whose slab values on the axis come out NaN or infinite and let
+// every box pass; every offset is widened by 2^-40 in space besides, so such a slab lets pass exactly the
 // boxes that hold the ray's coordinate, faces included.  (With 1 / 0 both slab values came
 // out NaN and the axis let every box pass: a bounce straight along the normal of an
 // axis-aligned face, one sample in 2^24, walked a whole wall of the corner, 12 ms for one
@@ -304,9 +306,10 @@ constexpr uint32_t FAR_X = 48u, FAR_Y = 80u, FAR_Z = 112u;
 __device__ __forceinline__ Box4Ray box4_setup(V3 o, V3 d) {
     Box4Ray r;
     // hardware reciprocals (within 1 ulp) of components kept away from 0
-    r.ix = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(d.x), 0x1p-80f), d.x));
-    r.iy = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(d.y), 0x1p-80f), d.y));
-    r.iz = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(d.z), 0x1p-80f), d.z));
+    const float least = fmaxf(fmaxf(fabsf(d.x), fabsf(d.y)), fabsf(d.z)) * 0x1p-80f;
+    r.ix = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(d.x), least), d.x));
+    r.iy = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(d.y), least), d.y));
+    r.iz = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(d.z), least), d.z));
     // |fl(o rcp(d)) - o rcp(d)| <= 2^-24 |o rcp(d)|, and as much again for each of the sum,
     // its product with 1 -+ 4e-6 and that of rcp(d) below: 2^-21 is twice what they take;
     // 2^-40 / |d|: the faces of an axis along which the ray does not move
