@@ -433,6 +433,11 @@ DPCS_API int32_t dpcs_server_poll(dpcs_server srv, uint64_t* done_ids, int32_t* 
  * compensation paths binned their map cotangents, each request's by itself (sorted by
  * tile, summed in fixed point), instead of scattering them with atomics. */
 DPCS_API dpcs_status dpcs_server_stats(dpcs_server srv, int64_t* out14);
+/* What the loop's waves were made of, out[4]: [0] lists of small compensation requests that
+ * replayed and flushed their map cotangents in common launches (at most 8 requests each);
+ * [1] the most such lists in one wave; [2] requests of several in a wave that were binned one
+ * after the other instead; [3] the most requests in one wave. */
+DPCS_API dpcs_status dpcs_server_wave_stats(dpcs_server srv, int64_t* out4);
 /* Waits for every admitted request, then stops the loop. */
 DPCS_API dpcs_status dpcs_server_destroy(dpcs_server srv);
 

@@ -254,6 +254,8 @@ struct dpcs_server_s {
     std::deque<std::tuple<uint64_t, int32_t, double>> completed;
     bool stop = false;
     int64_t st_submitted = 0, st_completed = 0, st_rejected = 0, st_waves = 0, st_samples = 0, st_peak = 0;
+    int64_t st_joint = 0, st_most_joint = 0;      // joint lists, and the most of them in a wave
+    int64_t st_apart = 0, st_most_segs = 0;       // requests of several binned apart; most requests in a wave
     int64_t st_replayed = 0, st_retraced = 0;   // waves whose compensation segments replayed / re-traced
     int64_t st_wait_us = 0, st_admit_us = 0, st_run_us = 0;   // summed latency parts of completed requests
     int64_t lat_cap = 0;         // most paths per wave
@@ -474,11 +476,14 @@ void dpcs_server_s::wave(Launch& l) {
         if (all_binned) ++st_binned;
         launch_adj_pixel(l, q, aq, table, wsegs.data(), n_adj_segs, !replay);
         if (!joint.empty()) {
+            st_joint += (int64_t)joint.size();
+            st_most_joint = std::max<int64_t>(st_most_joint, (int64_t)joint.size());
             for (size_t k = 0; k < joint.size(); ++k) {   // (the lists share the buffers, one after the other)
                 launch_zero(l, (float*)tex_bins, joint_words[k]);
                 launch_replay_joint(l, q, aq.delta, table, joint[k]);
             }
         } else if (all_binned) {
+            if (n_req > 1) st_apart += n_req;
             int tb_nb = -1, eb_nb = -1;   // tiles of the counters as they were last cleared
             for (const Seg& s : segs) {
                 if (!s.q->adjoint) continue;
@@ -539,6 +544,7 @@ void dpcs_server_s::wave(Launch& l) {
         if (side_adj && !replay) (void)hipStreamWaitEvent(st, ev_shadow, 0);
     }
     ++st_waves;
+    st_most_segs = std::max<int64_t>(st_most_segs, (int64_t)segs.size());
     st_samples += used + n_adj;
     if (any_adj) ++(replay ? st_replayed : st_retraced);
     std::vector<FinishSeg> fin;
@@ -853,6 +859,16 @@ extern "C" dpcs_status dpcs_server_stats(dpcs_server s, int64_t* o) {   // o: 14
     o[11] = s->st_admit_us;
     o[12] = s->st_run_us;
     o[13] = s->st_binned;
+    return DPCS_OK;
+}
+
+extern "C" dpcs_status dpcs_server_wave_stats(dpcs_server s, int64_t* o) {   // o: 4 counters
+    if (!s || !o) return DPCS_E_INVALID;
+    std::lock_guard<std::mutex> lk(s->mu);
+    o[0] = s->st_joint;
+    o[1] = s->st_most_joint;
+    o[2] = s->st_apart;
+    o[3] = s->st_most_segs;
     return DPCS_OK;
 }
 

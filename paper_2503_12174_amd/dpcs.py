@@ -113,7 +113,7 @@ SYMBOLS = ["dpcs_context_create", "dpcs_context_destroy", "dpcs_last_error", "dp
            "dpcs_context_set_capacity", "dpcs_scene_create", "dpcs_scene_get_info", "dpcs_scene_destroy",
            "dpcs_render", "dpcs_render_vjp", "dpcs_debug_intersect", "dpcs_debug_philox", "dpcs_debug_brdf",
            "dpcs_context_set_profiling", "dpcs_context_get_profile", "dpcs_server_create",
-           "dpcs_server_submit", "dpcs_server_poll", "dpcs_server_stats", "dpcs_server_destroy",
+           "dpcs_server_submit", "dpcs_server_poll", "dpcs_server_stats", "dpcs_server_wave_stats", "dpcs_server_destroy",
            "dpcs_denoise", "dpcs_denoise_vjp", "dpcs_render_gbuffer", "dpcs_tv_loss", "dpcs_tv_vjp",
            "dpcs_l1_loss", "dpcs_l1_vjp", "dpcs_render_noalloc", "dpcs_scene_refit"]
 
@@ -150,6 +150,7 @@ def lib():
             "dpcs_server_submit": ([P, C.POINTER(Request)], S),
             "dpcs_server_poll": ([P, P, P, P, I32], I32),
             "dpcs_server_stats": ([P, P], S),
+            "dpcs_server_wave_stats": ([P, P], S),
             "dpcs_server_destroy": ([P], S),
             "dpcs_denoise": ([P, C.POINTER(DenoiseParams), P, P, P], S),
             "dpcs_denoise_vjp": ([P, C.POINTER(DenoiseParams), P, P, P], S),
@@ -450,6 +451,11 @@ class Server:
         keys = ["submitted", "completed", "rejected", "active", "queued", "waves", "samples", "peak_bytes",
                 "replayed_waves", "retraced_waves", "wait_us", "admit_us", "run_us", "binned_waves"]
         return dict(zip(keys, [int(x) for x in v]))
+
+    def wave_stats(self) -> dict:
+        v = (C.c_int64 * 4)()
+        self.ctx.check(lib().dpcs_server_wave_stats(self.h, v))
+        return dict(zip(["joint_lists", "most_lists", "binned_apart", "most_requests"], [int(x) for x in v]))
 
     def close(self):
         if getattr(self, "h", None):
