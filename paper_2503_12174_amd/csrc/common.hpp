@@ -34,7 +34,6 @@ struct Vec3 {
 using V3 = Vec3<float>;
 using D3 = Vec3<double>;
 
-template <class T> __device__ __forceinline__ Vec3<T> mk3(T x, T y, T z) { return Vec3<T>{x, y, z}; }
 __device__ __forceinline__ V3 v3(float x, float y, float z) { return V3{x, y, z}; }
 __device__ __forceinline__ D3 d3(double x, double y, double z) { return D3{x, y, z}; }
 template <class T> __device__ __forceinline__ Vec3<T> operator+(Vec3<T> a, Vec3<T> b) { return {a.x + b.x, a.y + b.y, a.z + b.z}; }
@@ -51,7 +50,6 @@ __device__ __forceinline__ V3 xyz(float4 a) { return v3(a.x, a.y, a.z); }
 __device__ __forceinline__ float4 f4(V3 a, float w) { return make_float4(a.x, a.y, a.z, w); }
 __device__ __forceinline__ V3 to_f(D3 a) { return v3((float)a.x, (float)a.y, (float)a.z); }
 __device__ __forceinline__ D3 to_d(V3 a) { return d3(a.x, a.y, a.z); }
-__device__ __forceinline__ float comp(V3 a, int k) { return k == 0 ? a.x : (k == 1 ? a.y : a.z); }
 
 // 3x3 row-major times vector
 __device__ __forceinline__ D3 mat3(const double* m, D3 a) {

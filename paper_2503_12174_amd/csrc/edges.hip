@@ -439,7 +439,7 @@ dpcs_status camera_edge_term(dpcs_context ctx, dpcs_scene sc, const ReqDesc& r, 
             launch_set_count(l, qe.cnt, 0, m, 1, 4);
             int cur = 0;
             for (int d = 0; d < re.max_depth; ++d) {
-                launch_trace(l, qe, cur, re, nullptr, m);   // (empties the queues shading appends to)
+                launch_trace(l, qe, cur, re, m);   // (empties the queues shading appends to)
                 if (sidestream && d > 0) (void)hipStreamWaitEvent(l.st, ctx->ev_shadow, 0);
                 launch_shade(l, qe, cur, d, re, nullptr, m);
                 if (sidestream) {

@@ -296,16 +296,15 @@ __host__ __device__ inline int seg_of(const LIST& a, uint32_t block) {
     return k;
 }
 void launch_raygen(const Launch& l, const Queues& q, const ReqDesc* table, const WaveSeg* segs, int n);
+// The rays of one launch are on one tree: r's (uni's; requests that share a wave are of one scene).
 // cam (one request, no table): the queue is the request's camera rays, generated by the
 // closest-hit and shading kernels themselves (no raygen launch, no path state read)
-void launch_trace(const Launch& l, const Queues& q, int cur, const ReqDesc& uni, const ReqDesc* table,
-                  int64_t n_upper, bool cam = false);
+void launch_trace(const Launch& l, const Queues& q, int cur, const ReqDesc& r, int64_t n_upper, bool cam = false);
 void launch_shade(const Launch& l, const Queues& q, int cur, int depth, const ReqDesc& uni, const ReqDesc* table,
                   int64_t n_upper, bool cam = false);
-// depth: the bounce the shadow rays leave from (for the path records); one_tree (with a
-// table): every ray is on the tree of `uni` (several requests of one scene)
+// depth: the bounce the shadow rays leave from (for the path records)
 void launch_shadow(const Launch& l, const Queues& q, int which, const ReqDesc& uni, const ReqDesc* table,
-                   int64_t n_upper, int depth, bool one_tree = false);
+                   int64_t n_upper, int depth);
 // the whole forward of a small wave: n rays of one request, its camera's (cam) or those in the
 // path queue; or the camera rays of several requests' segments (no metallic and normal maps).
 // small_wave: where that pays, and the spill region holds n threads (segments: a workgroup's

@@ -102,10 +102,11 @@ __global__ void k_raygen(Queues q, SegList segs, const ReqDesc* __restrict__ tab
 // into q.stats), which a profiler reports apart from the timed launches.
 // CAM: the queue is one request's camera rays, entry i being sample g_base + i: each is
 // generated here (Eq. 6 inverted) instead of being read back from the path queue.
-template <bool UNI, bool PROF, bool CAM = false>
-__global__ void __launch_bounds__(TB) TRAVERSAL_OCCUPANCY k_trace(Queues q, int cur, ReqDesc uni, const ReqDesc* __restrict__ table) {
+// Every ray of the launch is on the tree of r, whose top is staged in LDS.
+template <bool PROF, bool CAM>
+__global__ void __launch_bounds__(TB) TRAVERSAL_OCCUPANCY k_trace(Queues q, int cur, ReqDesc r) {
     __shared__ int stack[(SHORT_STACK + 1) * TB];
-    __shared__ float4 ltop[UNI ? 8 * TOP_NODES : 1];
+    __shared__ float4 ltop[8 * TOP_NODES];
     int* spill = q.spill + (size_t)blockIdx.x * TB * SPILL;
     const uint32_t n = q.cnt[cur];
     // the queues the shading after this launch appends to start empty (this kernel reads
@@ -116,21 +117,19 @@ __global__ void __launch_bounds__(TB) TRAVERSAL_OCCUPANCY k_trace(Queues q, int 
         q.cnt[shadow_slot(cur, 1)] = 0u;
     }
     TopNodes top{ltop, 0u};   // (a constant base: its offset is part of the LDS reads)
-    if constexpr (UNI)   // one tree for the whole launch: stage its top levels
-        if (uni.nodes4) top = stage_top<TB>(ltop, uni.nodes4, uni.top_nodes);
+    if (r.nodes4) top = stage_top<TB>(ltop, r.nodes4, r.top_nodes);
     for (uint32_t i = blockIdx.x * TB + threadIdx.x; i < n; i += gridDim.x * TB) {
         PathO o;
         PathD d;
         if constexpr (CAM) {
-            const uint32_t g = uni.g_base + i;
-            const D3 cd = camera_dir(uni, g);
-            o = PathO{uni.cam_o[0], uni.cam_o[1], uni.cam_o[2], 0, -1};
+            const uint32_t g = r.g_base + i;
+            const D3 cd = camera_dir(r, g);
+            o = PathO{r.cam_o[0], r.cam_o[1], r.cam_o[2], 0, -1};
             d = PathD{cd.x, cd.y, cd.z, g, 0u};
         } else {
             o = nt_ld(&q.po[cur][i]);
             d = nt_ld(&q.pd[cur][i]);
         }
-        const ReqDesc& r = sel<UNI>(uni, table, o.slot);
         Hit h;
         Visits<PROF> vis;
         trace_ray<false, SHORT_STACK, TB>(r.nodes4, r.nodes, r.tris, v3((float)o.x, (float)o.y, (float)o.z),
@@ -330,25 +329,23 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EXT 
 // ---------------------------------------------------------------- shadows
 // PROF: the counting pass's instantiation (node and triangle visit counters, summed
 // into q.stats), which a profiler reports apart from the timed launches
-// TREE: every ray of the launch is on the tree of `uni` (several requests of one scene):
-// the tree's top is staged and its pointers come from `uni`, the rest from the table
-template <bool UNI, bool PROF, bool TREE = UNI>
+// Every ray of the launch is on the tree of `uni` (several requests are of one scene): the
+// tree's top is staged and its pointers come from `uni`, the rest from the table (UNI false)
+template <bool UNI, bool PROF>
 __global__ void __launch_bounds__(TB) SHADOW_OCCUPANCY k_shadow(Queues q, int which, int depth, ReqDesc uni,
                                                const ReqDesc* __restrict__ table) {
     __shared__ int stack[(SHORT_STACK + 1) * TB];
-    __shared__ float4 ltop[TREE ? 8 * TOP_NODES : 1];
+    __shared__ float4 ltop[8 * TOP_NODES];
     int* spill = q.spill + (size_t)blockIdx.x * TB * SPILL;
     const uint32_t n = q.cnt[shadow_slot(depth & 1, which)];
     TopNodes top{ltop, 0u};   // (a constant base: its offset is part of the LDS reads)
-    if constexpr (TREE)
-        if (uni.nodes4) top = stage_top<TB>(ltop, uni.nodes4, uni.top_nodes);
+    if (uni.nodes4) top = stage_top<TB>(ltop, uni.nodes4, uni.top_nodes);
     for (uint32_t i = blockIdx.x * TB + threadIdx.x; i < n; i += gridDim.x * TB) {
         const float4 o = nt_ld(&q.so[which][i]), d = nt_ld(&q.sd[which][i]);
         const ReqDesc& r = sel<UNI>(uni, table, __float_as_int(o.w));
-        const ReqDesc& tr = TREE ? uni : r;
         Hit h;
         Visits<PROF> vis;
-        const bool occ = trace_ray<true, SHORT_STACK, TB>(tr.nodes4, tr.nodes, tr.tris, xyz(o), xyz(d), tr.tmin,
+        const bool occ = trace_ray<true, SHORT_STACK, TB>(uni.nodes4, uni.nodes, uni.tris, xyz(o), xyz(d), uni.tmin,
                                                          nt_ld(&q.st[which][i]), __float_as_int(d.w), h, stack,
                                                          spill, threadIdx.x, vis, top);
         if constexpr (PROF)
@@ -653,21 +650,12 @@ void launch_raygen(const Launch& l, const Queues& q, const ReqDesc* table, const
                       hipLaunchKernelGGL(k_raygen, dim3(g), dim3(256), 0, l.st, q, a, table);
                   });
 }
-void launch_trace(const Launch& l, const Queues& q, int cur, const ReqDesc& uni, const ReqDesc* table,
-                  int64_t n_upper, bool cam) {
+void launch_trace(const Launch& l, const Queues& q, int cur, const ReqDesc& r, int64_t n_upper, bool cam) {
     const dim3 g(grid_cap(Launch{l.st, q.trace_blocks}, n_upper, TB)), b(TB);
-    if (cam && !table) {
-        if (q.stats) hipLaunchKernelGGL((k_trace<true, true, true>), g, b, 0, l.st, q, cur, uni, table);
-        else hipLaunchKernelGGL((k_trace<true, false, true>), g, b, 0, l.st, q, cur, uni, table);
-        return;
-    }
-    if (q.stats) {
-        if (table) hipLaunchKernelGGL((k_trace<false, true>), g, b, 0, l.st, q, cur, uni, table);
-        else hipLaunchKernelGGL((k_trace<true, true>), g, b, 0, l.st, q, cur, uni, table);
-    } else {
-        if (table) hipLaunchKernelGGL((k_trace<false, false>), g, b, 0, l.st, q, cur, uni, table);
-        else hipLaunchKernelGGL((k_trace<true, false>), g, b, 0, l.st, q, cur, uni, table);
-    }
+    if (cam && q.stats) hipLaunchKernelGGL((k_trace<true, true>), g, b, 0, l.st, q, cur, r);
+    else if (cam) hipLaunchKernelGGL((k_trace<false, true>), g, b, 0, l.st, q, cur, r);
+    else if (q.stats) hipLaunchKernelGGL((k_trace<true, false>), g, b, 0, l.st, q, cur, r);
+    else hipLaunchKernelGGL((k_trace<false, false>), g, b, 0, l.st, q, cur, r);
 }
 void launch_shade(const Launch& l, const Queues& q, int cur, int depth, const ReqDesc& uni, const ReqDesc* table,
                   int64_t n_upper, bool cam) {
@@ -682,19 +670,11 @@ void launch_shade(const Launch& l, const Queues& q, int cur, int depth, const Re
     else hipLaunchKernelGGL((k_shade<true, false>), g, b, 0, l.st, q, cur, depth, uni, table);
 }
 void launch_shadow(const Launch& l, const Queues& q, int which, const ReqDesc& uni, const ReqDesc* table,
-                   int64_t n_upper, int depth, bool one_tree) {
+                   int64_t n_upper, int depth) {
     const dim3 g(grid_cap(Launch{l.st, q.trace_blocks}, n_upper, TB)), b(TB);
-    if (table && one_tree) {
-        hipLaunchKernelGGL((k_shadow<false, false, true>), g, b, 0, l.st, q, which, depth, uni, table);
-        return;
-    }
-    if (q.stats) {
-        if (table) hipLaunchKernelGGL((k_shadow<false, true>), g, b, 0, l.st, q, which, depth, uni, table);
-        else hipLaunchKernelGGL((k_shadow<true, true>), g, b, 0, l.st, q, which, depth, uni, table);
-    } else {
-        if (table) hipLaunchKernelGGL((k_shadow<false, false>), g, b, 0, l.st, q, which, depth, uni, table);
-        else hipLaunchKernelGGL((k_shadow<true, false>), g, b, 0, l.st, q, which, depth, uni, table);
-    }
+    if (table) hipLaunchKernelGGL((k_shadow<false, false>), g, b, 0, l.st, q, which, depth, uni, table);
+    else if (q.stats) hipLaunchKernelGGL((k_shadow<true, true>), g, b, 0, l.st, q, which, depth, uni, table);
+    else hipLaunchKernelGGL((k_shadow<true, false>), g, b, 0, l.st, q, which, depth, uni, table);
 }
 void launch_paths(const Launch& l, const Queues& q, const ReqDesc& r, uint32_t n, bool cam) {
     const dim3 g(grid_of(n, PATH_TB)), b(PATH_TB);

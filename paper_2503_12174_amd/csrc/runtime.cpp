@@ -808,7 +808,7 @@ void forward_wave(dpcs_context ctx, Queues& q, ReqDesc& r, uint32_t a, uint32_t 
         // (the closest-hit launch empties the next path queue and this depth's shadow queues)
         q.stats = prof_stats(ctx, DPCS_STAGE_TRACE);
         pr = prof_begin(ctx, DPCS_STAGE_TRACE);
-        launch_trace(l, q, cur, r, nullptr, n, d == 0);
+        launch_trace(l, q, cur, r, n, d == 0);
         prof_end(ctx, pr, q.cnt + cur, 0);
         if (side && d > 0) (void)hipStreamWaitEvent(ctx->stream, ctx->ev_shadow, 0);
         pr = prof_begin(ctx, DPCS_STAGE_SHADE);
@@ -882,7 +882,7 @@ void adjoint_wave(dpcs_context ctx, Queues& q, const AdjQueues& aq, ReqDesc& r, 
     for (int d = 0; d < r.max_depth; ++d) {   // (the closest-hit launch empties the next queues)
         q.stats = prof_stats(ctx, DPCS_STAGE_TRACE);
         pr = prof_begin(ctx, DPCS_STAGE_TRACE);
-        launch_trace(l, q, cur, r, nullptr, n);
+        launch_trace(l, q, cur, r, n);
         prof_end(ctx, pr, q.cnt + cur, 0);
         if (side && d > 0) (void)hipStreamWaitEvent(ctx->stream, ctx->ev_shadow, 0);
         pr = prof_begin(ctx, DPCS_STAGE_ADJ_SHADE);

@@ -416,18 +416,18 @@ void dpcs_server_s::wave(Launch& l) {
         launch_set_count(l, q.cnt, 0, (uint32_t)used, 1, 4);
     }
     for (int d = 0; d < max_depth && !small; ++d) {
-        launch_trace(l, q, cur, any, nullptr, used);   // (empties the queues shading appends to)
+        launch_trace(l, q, cur, any, used);   // (empties the queues shading appends to)
         if (side_fwd && d > 0) (void)hipStreamWaitEvent(st, ev_shadow, 0);
         launch_shade(l, q, cur, d, any, table, used);
         if (side_fwd) {
             (void)hipEventRecord(ev_shade, st);
             (void)hipStreamWaitEvent(side, ev_shade, 0);
-            launch_shadow(ls, qs, 0, any, table, used, d, true);
-            if (env) launch_shadow(ls, qs, 1, any, table, used, d, true);
+            launch_shadow(ls, qs, 0, any, table, used, d);
+            if (env) launch_shadow(ls, qs, 1, any, table, used, d);
             (void)hipEventRecord(ev_shadow, side);
         } else {
-            launch_shadow(l, q, 0, any, table, used, d, true);
-            if (env) launch_shadow(l, q, 1, any, table, used, d, true);
+            launch_shadow(l, q, 0, any, table, used, d);
+            if (env) launch_shadow(l, q, 1, any, table, used, d);
         }
         cur ^= 1;
     }
@@ -524,7 +524,7 @@ void dpcs_server_s::wave(Launch& l) {
                 if (replay) {
                     launch_adj_replay(l, q, aq, cur, d, any, table, n_adj);
                 } else {   // (adjoint shadow rays beside the next closest hit, as in the forward)
-                    launch_trace(l, q, cur, any, nullptr, n_adj);
+                    launch_trace(l, q, cur, any, n_adj);
                     if (side_adj && d > 0) (void)hipStreamWaitEvent(st, ev_shadow, 0);
                     launch_adj_shade(l, q, aq, cur, d, any, table, n_adj);
                     if (side_adj) {

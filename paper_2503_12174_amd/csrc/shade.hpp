@@ -13,18 +13,6 @@ __device__ __forceinline__ const ReqDesc& sel(const ReqDesc& uni, const ReqDesc*
     return UNI ? uni : table[slot];
 }
 
-// wave-aggregated append: one atomic per wave64, lane order preserved
-__device__ __forceinline__ uint32_t wave_append(bool pred, uint32_t* counter) {
-    const unsigned long long m = __ballot(pred);
-    if (m == 0ull) return 0u;
-    const int lane = __lane_id();
-    const int leader = __ffsll((unsigned long long)m) - 1;
-    uint32_t base = 0;
-    if (lane == leader) base = atomicAdd(counter, (uint32_t)__popcll(m));
-    base = (uint32_t)__shfl((int)base, leader);
-    return base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-}
-
 // workgroup-aggregated append to NQ queues: one atomic per queue per workgroup
 // (instead of one per wave), lane order preserved within each wave.  Every thread of
 // the workgroup (NT threads) must call it, with its predicates; idx[q] is the slot of
