@@ -372,7 +372,11 @@ DPCS_API dpcs_status dpcs_debug_brdf(dpcs_context ctx, int32_t brdf, const doubl
  * stage is bracketed by HIP events on the context's stream and its work-item count
  * (queue size) is copied to pinned host memory.  mode 2: as 1, and the traversal
  * kernels also count visited BVH nodes and tested triangles (slower; use it to measure
- * the traversal byte model, not to time).  Enabling or disabling clears the record. */
+ * the traversal byte model, not to time).  A profiled call runs its stages as launches of
+ * their own: a wave small enough that one launch otherwise runs its whole paths (up to
+ * 655,360 paths, 2^20 on a tree of a few nodes) or its whole replay (2^17 samples of up to
+ * 4 depths) has the same results here, but stage times of a slower route than the
+ * unprofiled call takes.  Enabling or disabling clears the record. */
 enum {
     DPCS_STAGE_RAYGEN = 0, DPCS_STAGE_TRACE = 1, DPCS_STAGE_SHADE = 2, DPCS_STAGE_SHADOW = 3,
     DPCS_STAGE_FINALIZE = 4, DPCS_STAGE_ADJ_PIXEL = 5, DPCS_STAGE_ADJ_SHADE = 6, DPCS_STAGE_ADJ_SHADOW = 7,

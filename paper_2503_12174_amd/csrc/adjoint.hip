@@ -207,7 +207,7 @@ __device__ __forceinline__ bool put_ep_rec(const MapBins& mb, uint32_t slot, dou
 // radiance to q.L.  Otherwise (the record replay) the pixel's cotangent alone goes to delta
 // at the pixel's first sample: the replay forms a sample's own from it and the sample's
 // radiance, so this pass reads the radiance once and writes 16 bytes per pixel (256^2 x 64
-// spp: 48 -> 16 us, bound by that read).
+// spp: 48 -> 26 us, bound by that read).
 __device__ __forceinline__ void adj_pixel_block(const Queues& q, const AdjQueues& aq, const ReqDesc& r, uint32_t block,
                                                 uint32_t p0, uint32_t p1, const float* sample_L, float4* pix_dE,
                                                 bool per_sample) {
@@ -300,12 +300,9 @@ __global__ void __launch_bounds__(BLOCK) k_adj_pixel_segs(Queues q, AdjQueues aq
                     per_sample);
 }
 
-// dst[k] += the sum over nb workgroup partials part[b * stride + k], k < nv, in a fixed
-// order (FP64), so the scalar gradients are the same on every run
-// one workgroup per value k < nv (grid nv): dst[k] += the sum of the nb partials of k, in
-// a fixed order (per thread a strided run, then a tree)
-// value blockIdx.x of nb per-block partials (stride floats apart) added to dst, in a fixed order
-// (strided FP64 sums, then trees)
+// dst[k] += the sum over nb workgroup partials part[b * stride + k], one workgroup per value
+// k < nv, in a fixed order (FP64: strided runs, then trees), so the scalar gradients are the
+// same on every run
 __global__ void __launch_bounds__(SUM_TB) k_sum_partials(const float* __restrict__ part, int nb, int stride, int nv,
                                                          float* __restrict__ dst) {
     __shared__ double red[SUM_TB / 64];
@@ -1086,7 +1083,7 @@ __device__ __forceinline__ void replay_vertex(const ReqDesc& r, int depth, uint3
 // derivative L_r / f df is settled here and every vertex leaves one map record.
 // Bound by memory traffic and FP64 issue; on the 50k-triangle corner (256^2 x 64 spp, depth
 // 4), where about a third of the vertices lie at or before a sample's last lit one, the four
-// launches take 358 us against 812 us when every vertex was replayed and the bounce
+// launches take 318 us against 812 us when every vertex was replayed and the bounce
 // derivatives waited, with 60 more bytes of state, for the next vertex.
 // TEX: the maps' cotangents are wanted; without them only projector light counts, no
 // derivative of the reflectance is formed and no remaining radiance carried.
@@ -1196,7 +1193,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4)))
 // A small wave's replay, one thread per sample over all its depths: the map records of every depth go
 // to the bins before one flush (so max_depth <= BIN_DEPTHS), and the path state stays in registers.
 // Bound by the latency of a sample's chain of loads and FP64 operations; once the chip is full, the
-// queues' launches win, which gather the samples that go on (186 registers here: 2 waves per SIMD).
+// queues' launches win, which gather the samples that go on (204 registers here: 2 waves per SIMD).
 template <bool TEX>
 __device__ __forceinline__ void replay_paths_block(const Queues& q, float4* delta, const MapBins& tb, const MapBins& eb,
                                                    uint32_t n, const float* __restrict__ sample_L, const ReqDesc& r,
@@ -1541,14 +1538,14 @@ __device__ __forceinline__ void write_scalars(const ReqDesc& r, const float* acc
         d_scalars[15 + a] += -acc[6] * r.clip_k / (wa * wa);
     }
 }
-// one 256-thread workgroup: the PRF backward's partials (nb blocks) into acc[8..20), then
-// the scalar gradients
-// (one wave per value: a workgroup that took the twelve in turn spent 12 us in its barriers)
-__global__ void __launch_bounds__(768) k_adj_scalars(ReqDesc r, float* __restrict__ acc, float* d_scalars, int nb) {
+// one workgroup: the PRF backward's partials (nb blocks) into acc[8..20), a wave per value, then
+// the scalar gradients (a workgroup that took the twelve in turn spent 12 us in its barriers)
+constexpr int PRF_SCALARS = 12;   // d gamma_p[3], d M[9]
+__global__ void __launch_bounds__(64 * PRF_SCALARS) k_adj_scalars(ReqDesc r, float* __restrict__ acc, float* d_scalars, int nb) {
     if (r.d_part) {
         const int k = threadIdx.x >> 6;
         double s = 0.0;
-        for (int b = threadIdx.x & 63; b < nb; b += 64) s += r.d_part[(size_t)b * 12 + k];
+        for (int b = threadIdx.x & 63; b < nb; b += 64) s += r.d_part[(size_t)b * PRF_SCALARS + k];
         for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
         if ((threadIdx.x & 63) == 0 && s != 0.0) acc[8 + k] += (float)s;
         __syncthreads();
@@ -1695,7 +1692,7 @@ void launch_adj_finish(const Launch& l, const ReqDesc& r, float* d_proj, float* 
     if (g + gm == 0) return;   // the camera pose alone
     hipLaunchKernelGGL(k_adj_prf, dim3(g + gm), dim3(BLOCK), 0, l.st, r, d_proj, acc, (int)g, d_albedo, d_rough,
                        d_spec, d_metal, d_nmap);
-    hipLaunchKernelGGL(k_adj_scalars, dim3(1), dim3(768), 0, l.st, r, acc, d_scalars, (int)g);
+    hipLaunchKernelGGL(k_adj_scalars, dim3(1), dim3(64 * PRF_SCALARS), 0, l.st, r, acc, d_scalars, (int)g);
 }
 void launch_adj_finish(const Launch& l, const ReqDesc* table, const FinishSeg* segs, int n) {
     for (int k = 0; k < n; k += WAVE_SEGS) {

@@ -75,9 +75,9 @@ __device__ __forceinline__ D3 mat3(const double* m, D3 a) {
 // rms in units of 2^-53, plain and these forms: reflectance 6.3 and 5.5, density 6.3 and 5.4,
 // normal derivatives 5.8 and 5.1, projector falloff 2.3 and 1.4).  The build contracts
 // nothing by itself (the FP32 triangle test relies on that), so every kernel forms the same value.
-// 50k-triangle corner, 256^2 x 64 spp: camera-vertex shading 214 -> 194 us, record replay
-// 358 -> 326 us (the deeper vertices' shading is bound by its memory traffic); camera-pose
-// terms at 16 spp 258 -> 148 us.
+// 50k-triangle corner, 256^2 x 64 spp: camera-vertex shading 214 -> 193 us, record replay
+// 358 -> 318 us (the deeper vertices' shading is bound by its memory traffic); camera-pose
+// terms at 16 spp 258 -> 152 us.
 // ---------------------------------------------------------------------------
 // Newton steps r += r (1 - x r) from the estimate
 __device__ __forceinline__ double frcp(double x) {

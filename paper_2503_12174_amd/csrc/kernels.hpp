@@ -125,7 +125,7 @@ constexpr int TRACE_TB = 128;                  // threads per workgroup of the t
 // latency-bound enough that occupancy pays more than the odd spilled register costs
 #define TRAVERSAL_OCCUPANCY __attribute__((amdgpu_waves_per_eu(8, 8)))
 // except the forward's shadow rays: with the staged tree top their any-hit loop spills a
-// few registers at 64 VGPRs; at 7 waves (71 VGPRs, no spill) they run ~3 % faster
+// few registers at 64 VGPRs; at 7 waves (72 VGPRs, 8 to 12 bytes spilled) they run ~3 % faster
 #define SHADOW_OCCUPANCY __attribute__((amdgpu_waves_per_eu(7, 7)))
 // and the re-tracing replay's shadow rays, whose gradient bookkeeping after the query
 // spilled ~150 bytes per lane at 64 VGPRs: at 4 waves (105 VGPRs) nothing spills and
@@ -135,11 +135,12 @@ constexpr int PATH_TB = 64;   // threads per workgroup of the whole-path kernel
 // Waves of up to SMALL_PATHS paths run a whole path per thread (k_paths), larger ones queues and
 // three launches per depth: those gather the paths that go on into full waves at 8 waves per
 // SIMD; k_paths has 4 and loses the lanes whose path ended, but no launch waits for the one
-// before.  Renders by queues and by k_paths: quad and cube, depth 3, 64 x 64 x 4 90 and 46 us,
-// 128 x 128 x 16 165 and 71; corner of 50k triangles, depth 4, 256 x 256 spp 4 372 and 248, spp 8
-// 444 and 400, 640 x 360 x 4 (0.92 M) 581 and 589, 256 x 256 x 16 598 and 675; of 200k, depth 6, lit
-// room, 317 x 203 x 9 (0.58 M) 1086 and 829.  A tree of a few nodes (less than TOP_NODES) has
-// little to gather: 256 x 256 x 16 of the quad and cube 312 and 192.
+// before.  Renders by queues and by k_paths, us, corner of 50k triangles at 16 k, 0.33 M and 0.66 M
+// paths: depth 1 62 and 47, 96 and 73, 117 and 101; depth 2 153 and 94, 225 and 158, 287 and 246;
+// depth 4 307 and 167, 402 and 269, 480 and 421; beyond, depth 4, 640 x 360 x 4 (0.92 M) 581 and
+// 589, 256 x 256 x 16 598 and 675; of 200k, depth 6, lit room, 317 x 203 x 9 (0.58 M) 1086 and 829.
+// A tree of a few nodes (less than TOP_NODES) has little to gather: the quad and cube at 16 k and
+// 0.98 M, depth 1 38 and 25, 92 and 62; depth 4 108 and 47, 276 and 144.
 constexpr int64_t SMALL_PATHS = 5 << 17, SMALL_PATHS_TINY = 1 << 20;
 // Traversal grids are capped at `rounds` x grid_cap x 128 threads (grid_cap x 128 threads
 // is one resident round at 8 waves per SIMD); the spill region holds SPILL ints for every
@@ -341,11 +342,12 @@ void launch_adj_shadow(const Launch& l, const Queues& q, const AdjQueues& aq, in
 // null: q.L holds it
 void launch_adj_replay(const Launch& l, const Queues& q, const AdjQueues& aq, int cur, int depth, const ReqDesc& uni,
                        const ReqDesc* table, int64_t n_upper, const float* sample_L = nullptr);
-// adds the binned records of tb / eb into r.d_tex / r.dEp and empties the bins
 // The whole replay of a small wave from its records (small_replay: where that pays, and the bins
-// hold every depth's records).  Forward and VJP by depth and whole: quad and cube, 64 x 64 x 32 150
-// and 143 us, 128 x 128 x 16 177 and 182, 256 x 256 x 16 390 and 473; corner of 50k triangles, 128 x
-// 128 x 8 482 and 476, 256 x 256 x 4 375 and 389.
+// hold every depth's records).  VJP from records by depth and whole, us, 4 k and 131 k samples:
+// corner of 50k triangles, depth 1 93 and 92, 98 and 96; depth 2 108 and 104, 116 and 112; depth 4
+// 127 and 123, 141 and 130; quad and cube, depth 1 69 and 68, 77 and 77; depth 4 98 and 90, 111 and
+// 96.  Beyond, forward and VJP: quad and cube, 256 x 256 x 16 390 and 473; corner, 256 x 256 x 4 375
+// and 389.
 constexpr int64_t SMALL_REPLAY = 1 << 17;
 bool small_replay(const AdjQueues& aq, const ReqDesc& r, int64_t n);
 // The same for up to JOINT_SEGS requests of the loop at once, each with bins of its own, and the
@@ -364,6 +366,7 @@ struct JointList {
 void launch_replay_joint(const Launch& l, const Queues& q, float4* delta, const ReqDesc* table, JointList& f);
 void launch_replay_paths(const Launch& l, const Queues& q, const AdjQueues& aq, const ReqDesc& r, uint32_t n,
                          const float* sample_L = nullptr);
+// adds the binned records of tb / eb into r.d_tex / r.dEp and empties the bins
 void launch_map_flush(const Launch& l, const AdjQueues& aq, const ReqDesc& r);
 // tile side and bin count for a W x H map (false: too many tiles, bin nothing)
 bool map_tiling(int W, int H, int& T, int& nbx, int& nby);

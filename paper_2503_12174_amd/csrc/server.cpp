@@ -4,9 +4,9 @@
 // context's device.  Requests are admitted while the device-memory estimate of all
 // admitted requests fits the budget and a descriptor slot is free.  Every launch
 // wave packs whole-pixel segments of all active requests into shared path queues:
-// raygen / finalize / adj_pixel run per segment, trace / shade / shadow (and their
-// adjoint forms) run once over the shared queues and read each path's request
-// descriptor from a device table by slot.  Compensation-step requests (forward +
+// raygen / finalize / adj_pixel run over lists of segments, trace / shade / shadow (and their
+// adjoint forms) once over the shared queues -- or whole paths, where a wave is small -- and
+// read each path's request descriptor from a device table by slot.  Compensation-step requests (forward +
 // VJP) put their segments first so their replay fills a dense queue prefix.  A
 // request completes when its last wave (and its gradient reduction) has passed on
 // the device; its latency is measured from submit to that point on the host clock.
@@ -241,8 +241,11 @@ struct dpcs_server_s {
     AdjQueues aq{};
     uint32_t* rec = nullptr;     // path records of a wave's compensation segments
     int64_t rec_cap = 0;         // words
-    char* tex_bins = nullptr;    // binning buffers (texture maps, E_p) of one-request
-    char* ep_bins = nullptr;     // compensation waves, or null: every wave scatters directly
+    // binning buffers of compensation waves (null: every wave scatters directly): one request
+    // at a time has texture records at tex_bins and E_p records at ep_bins; several together
+    // share [tex_bins, tex_bins + bins_bytes), so ep_bins has to follow tex_bins in one allocation
+    char* tex_bins = nullptr;
+    char* ep_bins = nullptr;
     int64_t tex_bins_cap = 0, ep_bins_cap = 0;
     size_t bins_bytes = 0;       // both together, from tex_bins on
     int64_t st_binned = 0;       // waves whose compensation gradients were binned
@@ -679,9 +682,9 @@ extern "C" dpcs_status dpcs_server_create(dpcs_context ctx, size_t memory_budget
         delete s;
         return fail(ctx, DPCS_E_INVALID, "memory budget smaller than the shared queues of one wave");
     }
-    // binning buffers for one-request compensation waves (records of up to BIN_DEPTHS
-    // texture and E_p entries per path between flushes), when they take at most
-    // a quarter of the budget (~1.2 GB for 2^21-path waves)
+    // binning buffers for compensation waves (records of up to BIN_DEPTHS texture and E_p
+    // entries per path between flushes), when they take at most a quarter of the budget
+    // (~1.2 GB for 2^21-path waves)
     s->tex_bins_cap = s->lat_cap * BIN_DEPTHS;
     s->ep_bins_cap = s->lat_cap * BIN_DEPTHS;
     const size_t bins_bytes = loop_bins_bytes(s->tex_bins_cap, 5, 8) + loop_bins_bytes(s->ep_bins_cap, 3, 6);
@@ -748,8 +751,8 @@ extern "C" dpcs_status dpcs_server_create(dpcs_context ctx, size_t memory_budget
     s->q.hit = (int*)take(4 * c);
     s->q.L = (float4*)take(16 * c);
     s->aq.delta = (float4*)take(16 * c);
-    s->aq.tb = MapBins{};   // several requests' compensation paths: direct scatter (a
-    s->aq.eb = MapBins{};   // wave of one request binds the binning buffers instead)
+    s->aq.tb = MapBins{};   // the replay of all requests at once scatters directly (binned waves
+    s->aq.eb = MapBins{};   // bind the buffers per request, or side by side)
     s->q.cnt = (uint32_t*)take(4 * (SHADOW_CNT + 4));
     s->q.spill = (int*)take(spill_bytes);
     s->spill2 = (int*)take(spill_bytes);

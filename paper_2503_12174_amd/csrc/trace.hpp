@@ -6,7 +6,7 @@
 //   n2 = (lo1.z, hi1.x, hi1.y, hi1.z)  n3 = (child0, child1, -, -) as int bits
 // BVH4 node (128 B, one cache line, 8 x float4): the four children's boxes as
 // structure of arrays, lo.x[4], lo.y[4], lo.z[4], hi.x[4], hi.y[4], hi.z[4], then the
-// four child references and 16 unused bytes.
+// four child references, the binary node it stands for (refits) and 12 unused bytes.
 // child >= 0: internal node index; child < 0: leaf ~child (one triangle, leaf order).
 // An unused slot of a BVH4 node holds an inverted box far from the scene, which the
 // 4-wide box test never enters, and the dummy leaf nt (one record past the mesh's
@@ -284,14 +284,13 @@ __device__ __forceinline__ void sort2(uint32_t& a, uint32_t& b) {
 // An axis along which the ray does not move (less than 2^-80 of its largest component, so for
 // directions of any length, or 0) takes the reciprocal of that least movement -- infinite for
 // directions shorter than 2^-46, whose slab values on the axis come out NaN or infinite and let
-// every box pass; every offset is widened by 2^-40 in space besides, so such a slab lets pass exactly the
-// boxes that hold the ray's coordinate, faces included.  (With 1 / 0 both slab values came
-// out NaN and the axis let every box pass: a bounce straight along the normal of an
+// every box pass.  Every offset is widened by 2^-40 in space besides, so such a slab lets pass
+// exactly the boxes that hold the ray's coordinate, faces included.  (With 1 / 0 a unit
+// direction's slab values came out NaN too: a bounce straight along the normal of an
 // axis-aligned face, one sample in 2^24, walked a whole wall of the corner, 12 ms for one
 // ray.)  The widening multiplies rather than adding a multiple of |t|, so infinite slab
-// values stay infinite instead of turning NaN,
-// and an inverted box (lo = +1e30, hi = -1e30: every near plane ahead of every far
-// plane) is always missed.
+// values stay infinite instead of turning NaN, and an inverted box (lo = +1e30, hi = -1e30:
+// every near plane ahead of every far plane) is always missed.
 struct Box4Ray {
     float ix, iy, iz;             // 1 / d, less the widening (near planes)
     float jx, jy, jz;             // 1 / d and the widening (far planes)
