@@ -131,9 +131,9 @@ __device__ __forceinline__ D3 fmadd(D3 a, double s, D3 b) { return {fma(a.x, s, 
 // in the projector's frame (xp.z > 0) and the vector tow to the projector.  One quotient: by
 // way of 1 / cos alpha its rounding counts three times.
 __device__ __forceinline__ double projector_falloff(D3 xp, D3 tow, D3& wp, double& dist) {
-    const double d2 = fdot(tow, tow), id = frsqrt(d2), d = d2 * id;
-    dist = fma(fma(-d, d, d2), 0.5 * id, d);
-    wp = tow * id;
+    const double d2 = fdot(tow, tow);
+    dist = fsqrt(d2);
+    wp = tow * frcp(dist);   // (with 1 / dist from the root's own Newton steps k_shade spilled)
     const double l2 = fdot(xp, xp);
     return div_rn(l2 * fsqrt(l2), xp.z * xp.z * xp.z * d2);
 }
